@@ -21,9 +21,18 @@ __device__ __forceinline__ uint32_t bl_f32_to_bf16(float f) {
     return u >> 16;
 }
 
-/* Correctly rounded fp32 quotient: the fp64 quotient of two fp32 values,
- * rounded to fp32, equals the directly rounded fp32 quotient (53 >= 2*24+2). */
-__device__ __forceinline__ float bl_div_rn(float a, float b) { return (float)((double)a / (double)b); }
+/* Two fp32 -> packed bf16 bit patterns (a in the low half), round to nearest even: one
+ * instruction, the bits of bl_f32_to_bf16 for every finite input (compared over all of them). */
+typedef __bf16 bl_v2bf __attribute__((ext_vector_type(2)));
+typedef float bl_v2f __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t bl_pack2_bf16(float a, float b) {
+    const bl_v2f v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bl_v2bf));
+}
+
+/* Correctly rounded fp32 quotient (IEEE division: about ten fp32 instructions; by way of an fp64
+ * quotient, the same bits, it took about three times as long). */
+__device__ __forceinline__ float bl_div_rn(float a, float b) { return a / b; }
 
 /* DPP cross-lane moves inside a row of 16 lanes (old value = 0 for disabled lanes). */
 template <int CTRL>
@@ -48,18 +57,34 @@ __device__ __forceinline__ int bl_group_sum(int v) {
     return v;
 }
 
-/* Full-wave integer sum / float max via butterflies (ds_bpermute for the
- * cross-row steps). */
+/* Sum over the 64 lanes, the same in every lane. */
 __device__ __forceinline__ int bl_wave_sum(int v) {
     v = bl_group_sum<16>(v);
-    v += __shfl_xor(v, 16);
-    v += __shfl_xor(v, 32);
-    return v;
+    return (__builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16)) +
+           (__builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48));
+}
+/* Maximum of NON-NEGATIVE floats (they order like their bit patterns: no canonicalising moves),
+ * over 16 lanes and over the 64 lanes of a wave: DPP inside the rows of 16, then four readlanes. */
+__device__ __forceinline__ float bl_max_pos(float a, float b) {
+    const uint32_t x = __float_as_uint(a), y = __float_as_uint(b);
+    return __uint_as_float(x > y ? x : y);
+}
+template <int CTRL>
+__device__ __forceinline__ float bl_dppf(float v) {
+    return __int_as_float(bl_dpp<CTRL>(__float_as_int(v)));
+}
+__device__ __forceinline__ float bl_lane_f(float v, int l) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+__device__ __forceinline__ float bl_row_max(float v) {
+    v = bl_max_pos(v, bl_dppf<BL_DPP_QUAD_XOR1>(v));
+    v = bl_max_pos(v, bl_dppf<BL_DPP_QUAD_XOR2>(v));
+    v = bl_max_pos(v, bl_dppf<BL_DPP_ROW_HALF_MIRROR>(v));
+    return bl_max_pos(v, bl_dppf<BL_DPP_ROW_MIRROR>(v));
 }
 __device__ __forceinline__ float bl_wave_max(float v) {
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) v = fmaxf(v, __shfl_xor(v, o));
-    return v;
+    v = bl_row_max(v);
+    return bl_max_pos(bl_max_pos(bl_lane_f(v, 0), bl_lane_f(v, 16)), bl_max_pos(bl_lane_f(v, 32), bl_lane_f(v, 48)));
 }
 
 /* 4x4 byte transpose of four dwords: out[s].byte[b] = in[b].byte[s]. */

@@ -136,13 +136,13 @@ __global__ __launch_bounds__(256) void bl_gemv_rows(const bl_gemv_group grp) {
                 const int u = tid + j * 256;
                 if (u < groups) {
                     if (!have_xv) bl_produce16<NORM>(P.prod, m, u, K, first_block, rn, xv[2 * j], xv[2 * j + 1]);
-                    mx = fmaxf(mx, fmaxf(bl_absmax8_bf16(xv[2 * j]), bl_absmax8_bf16(xv[2 * j + 1])));
+                    mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16(xv[2 * j]), bl_absmax8_bf16(xv[2 * j + 1])));
                 }
             }
             for (int u = tid + 512; u < groups; u += 256) {
                 uint4 lo, hi;
                 bl_produce16<NORM>(P.prod, m, u, K, false, rn, lo, hi);
-                mx = fmaxf(mx, fmaxf(bl_absmax8_bf16(lo), bl_absmax8_bf16(hi)));
+                mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16(lo), bl_absmax8_bf16(hi)));
             }
             mx = bl_wave_max(mx);
             if (lane == 0) fs[M + w] = mx;
@@ -398,7 +398,7 @@ __global__ __launch_bounds__(256) void bl_gemv_mma(const bl_gemv_group grp, cons
                 const int u = lane + j * 64;
                 if (u < groups) {
                     if (!have_xv) bl_produce16<NORM>(P.prod, m, u, K, first_block, 1.0f, xv[2 * j], xv[2 * j + 1]);
-                    mx = fmaxf(mx, fmaxf(bl_absmax8_bf16(xv[2 * j]), bl_absmax8_bf16(xv[2 * j + 1])));
+                    mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16(xv[2 * j]), bl_absmax8_bf16(xv[2 * j + 1])));
                 }
             }
             if (pre_bf16) {
@@ -416,13 +416,13 @@ __global__ __launch_bounds__(256) void bl_gemv_mma(const bl_gemv_group grp, cons
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
                         if (u0 + 64 * j < groups)
-                            mx = fmaxf(mx, fmaxf(bl_absmax8_bf16(t[2 * j]), bl_absmax8_bf16(t[2 * j + 1])));
+                            mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16(t[2 * j]), bl_absmax8_bf16(t[2 * j + 1])));
                 }
             } else {
                 for (int u = lane + 128; u < groups; u += 64) {
                     uint4 lo, hi;
                     bl_produce16<NORM>(P.prod, m, u, K, false, 1.0f, lo, hi);
-                    mx = fmaxf(mx, fmaxf(bl_absmax8_bf16(lo), bl_absmax8_bf16(hi)));
+                    mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16(lo), bl_absmax8_bf16(hi)));
                 }
             }
             const float gamma = bl_wave_max(mx);
@@ -496,13 +496,13 @@ __global__ __launch_bounds__(256) void bl_gemv_mma(const bl_gemv_group grp, cons
                 const int u = tid + j * 256;
                 if (u < groups) {
                     if (!have_xv) bl_produce16<NORM>(P.prod, m, u, K, first_block, rn, xv[2 * j], xv[2 * j + 1]);
-                    mx = fmaxf(mx, fmaxf(bl_absmax8_bf16(xv[2 * j]), bl_absmax8_bf16(xv[2 * j + 1])));
+                    mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16(xv[2 * j]), bl_absmax8_bf16(xv[2 * j + 1])));
                 }
             }
             for (int u = tid + 512; u < groups; u += 256) {
                 uint4 lo, hi;
                 bl_produce16<NORM>(P.prod, m, u, K, false, rn, lo, hi);
-                mx = fmaxf(mx, fmaxf(bl_absmax8_bf16(lo), bl_absmax8_bf16(hi)));
+                mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16(lo), bl_absmax8_bf16(hi)));
             }
             mx = bl_wave_max(mx);
             if (m > 0) __syncthreads();                 /* previous token's fs[] readers are done */

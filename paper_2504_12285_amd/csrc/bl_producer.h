@@ -18,10 +18,6 @@ struct bl_prod_dev {
     float eps;
 };
 
-__device__ __forceinline__ uint32_t bl_pack2_bf16(float a, float b) {
-    return bl_f32_to_bf16(a) | (bl_f32_to_bf16(b) << 16);
-}
-
 /* fp32 values of k = 16u .. 16u+15 of token m, before narrowing (any kind).
  * store_aux: this caller also writes the fp32 by-product (RESIDUAL: the sum). */
 __device__ __forceinline__ void bl_produce16_f32(const bl_prod_dev& pd, int m, int u, int K, bool store_aux,
@@ -169,30 +165,40 @@ __device__ __forceinline__ float bl_norm_produce2(const bl_prod_dev& pd, int m, 
     return rn;
 }
 
-/* Quantise 8 bf16 (one uint4) to two dwords of int8: q = clamp(rint(x*inv), -127, 127). */
-__device__ __forceinline__ void bl_quant8_words(const uint4 v, float inv, uint32_t& lo, uint32_t& hi) {
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-    uint32_t o[2] = {0u, 0u};
+/* Four int8 in one dword: q = rint(f * inv), ties to even.  Adding 1.5 * 2^23 leaves the rounded
+ * integer in the low bits of the sum (its unit in the last place is 1 there), so a value costs a
+ * multiply, an add and three quarters of a byte permute.  CLAMP: for an inv that does not come
+ * from the absmax of these values; with |f| <= gamma, fl(f * fl(127 / gamma)) never rounds beyond 127. */
+template <bool CLAMP>
+__device__ __forceinline__ uint32_t bl_quant4(float f0, float f1, float f2, float f3, float inv) {
+    float v[4] = {f0 * inv, f1 * inv, f2 * inv, f3 * inv};
+    uint32_t r[4];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const uint32_t hbits = (j & 1) ? (w[j >> 1] >> 16) : (w[j >> 1] & 0xFFFFu);
-        float r = rintf(bl_bf16_to_f32(hbits) * inv);
-        r = fminf(fmaxf(r, -127.0f), 127.0f);
-        o[j >> 2] |= ((uint32_t)(int)r & 0xFFu) << (8 * (j & 3));
+    for (int e = 0; e < 4; ++e) {
+        if (CLAMP) v[e] = fminf(fmaxf(v[e], -127.0f), 127.0f);
+        r[e] = __float_as_uint(v[e] + 12582912.0f);
     }
-    lo = o[0];
-    hi = o[1];
+    return __builtin_amdgcn_perm(r[1], r[0], 0x0C0C0400u) | __builtin_amdgcn_perm(r[3], r[2], 0x04000C0Cu);
 }
 
+/* Quantise 8 bf16 (one uint4) to two dwords of int8. */
+template <bool CLAMP = false>
+__device__ __forceinline__ void bl_quant8_words(const uint4 v, float inv, uint32_t& lo, uint32_t& hi) {
+    auto l = [](uint32_t w) { return __uint_as_float(w << 16); };
+    auto h = [](uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); };
+    lo = bl_quant4<CLAMP>(l(v.x), h(v.x), l(v.y), h(v.y), inv);
+    hi = bl_quant4<CLAMP>(l(v.z), h(v.z), l(v.w), h(v.w), inv);
+}
+
+/* Largest magnitude of 8 bf16: without its sign a bf16 orders like its bit pattern, so the maxima
+ * are taken two at a time on 16-bit integers. */
+typedef unsigned short bl_v2us __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ float bl_absmax8_bf16(const uint4 v) {
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-    float m = 0.0f;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        m = fmaxf(m, fabsf(bl_bf16_to_f32(w[j] & 0xFFFFu)));
-        m = fmaxf(m, fabsf(bl_bf16_to_f32(w[j] >> 16)));
-    }
-    return m;
+    auto a = [](uint32_t w) { return __builtin_bit_cast(bl_v2us, w & 0x7FFF7FFFu); };
+    const bl_v2us m = __builtin_elementwise_max(__builtin_elementwise_max(a(v.x), a(v.y)),
+                                                __builtin_elementwise_max(a(v.z), a(v.w)));
+    const uint32_t u = __builtin_bit_cast(uint32_t, m);
+    return bl_max_pos(__uint_as_float(u << 16), __uint_as_float(u & 0xFFFF0000u));
 }
 
 __device__ __forceinline__ int bl_sum16(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3) {

@@ -1,129 +1,172 @@
 /* Per-token absmax int8 activation quantisation (Section 2, "Activation
- * Quantization", of the BitNet b1.58 2B4T report).  One workgroup per token
- * row; the row is read twice (absmax, then quantise), the second pass hitting
- * cache.  HBM-bound at prefill sizes, latency-bound at decode sizes. */
+ * Quantization", of the BitNet b1.58 2B4T report).  HBM-bound at prefill sizes,
+ * latency-bound at decode sizes. */
 #include "bl_device.h"
 #include "bl_host.h"
 #include "bl_producer.h"
 
 #define QUANT_THREADS 256
+#define QUANT_WAVE_ROWS 1024
 
-/* Quantise 8 bf16 values held in a uint4 to 8 int8 in a uint2; returns their sum. */
-__device__ __forceinline__ int bl_quant8(const uint4 v, float inv, uint2* out) {
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-    uint32_t o[2] = {0u, 0u};
-    int sum = 0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const uint32_t h = (j & 1) ? (w[j >> 1] >> 16) : (w[j >> 1] & 0xFFFFu);
-        float r = rintf(bl_bf16_to_f32(h) * inv);
-        r = fminf(fmaxf(r, -127.0f), 127.0f);
-        const int qi = (int)r;
-        sum += qi;
-        o[j >> 2] |= ((uint32_t)qi & 0xFFu) << (8 * (j & 3));
-    }
-    out->x = o[0];
-    out->y = o[1];
-    return sum;
-}
-
-__device__ __forceinline__ float bl_absmax8(const uint4 v) {
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-    float m = 0.0f;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        m = fmaxf(m, fabsf(bl_bf16_to_f32(w[j] & 0xFFFFu)));
-        m = fmaxf(m, fabsf(bl_bf16_to_f32(w[j] >> 16)));
-    }
-    return m;
-}
-
-__global__ __launch_bounds__(QUANT_THREADS) void bl_quant_rows(const uint4* __restrict__ X, int K8,
-                                                                uint2* __restrict__ q, float* __restrict__ scale,
-                                                                int32_t* __restrict__ rowsum) {
-    __shared__ float smax[QUANT_THREADS / BL_WAVE];
-    __shared__ int ssum[QUANT_THREADS / BL_WAVE];
-    const int64_t m = blockIdx.x;
-    const uint4* x = X + m * K8;
-    uint2* qo = q + m * K8;
+/* The quantiser of rows that exist as bf16.  TPR threads (64 or 256) share a row and hold all of it
+ * in registers between the absmax and the rounding: NV units of eight elements each (K <= 8 * TPR *
+ * NV), so the row is read once.  TPR = 64: a row is one wave's work, no LDS and no barrier.
+ * RAGGED: K is not a multiple of 64; the row's start need not be 16-byte aligned (the 16-byte loads
+ * are then unaligned ones), its last partial unit is read element by element, and the output row of
+ * Kp = ceil(K/64)*64 bytes has zeros behind K.  KNOWN: the row maximum is given in absmax[m] (bits of
+ * max |x|), read by every thread of the row and then cleared, so that the next product's epilogue
+ * can fold its maxima into it again.
+ * Bound by HBM at prefill sizes, else by the launch and the chain load -> maximum -> round -> store.
+ * Against one workgroup per row that read the row twice (and a ragged row in 2-byte loads): quantiser +
+ * product at 777 x 2999 -> 5003 42.8 -> 38.4 us, the four of a layer at 2048 tokens 177.5 -> 174.2 us. */
+template <int TPR, int NV, bool RAGGED, bool KNOWN>
+__global__ __launch_bounds__(QUANT_THREADS) void bl_quant_rows(const uint16_t* __restrict__ X, int M, int K, int Kp,
+                                                                int* __restrict__ absmax, int8_t* __restrict__ q,
+                                                                float* __restrict__ scale, int32_t* __restrict__ rowsum) {
+    constexpr int ROWS = QUANT_THREADS / TPR, WPR = TPR / BL_WAVE;   /* rows per workgroup, waves per row */
+    __shared__ float smax[WPR];
+    __shared__ int ssum[WPR];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-
-    float mx = 0.0f;
-    for (int i = threadIdx.x; i < K8; i += QUANT_THREADS) mx = fmaxf(mx, bl_absmax8(x[i]));
-    mx = bl_wave_max(mx);
-    if (lane == 0) smax[w] = mx;
-    __syncthreads();
-    float gamma = smax[0];
+    const int t = TPR == 64 ? lane : (int)threadIdx.x;               /* thread of the row */
+    const int m = (int)blockIdx.x * ROWS + (TPR == 64 ? w : 0);
+    if (m >= M) return;                                              /* (whole waves, and no barrier when ROWS > 1) */
+    const uint16_t* x = X + (int64_t)m * K;
+    int8_t* qo = q + (int64_t)m * Kp;
+    const int full = K >> 3, units = Kp >> 3;
+    uint4 v[NV];
 #pragma unroll
-    for (int i = 1; i < QUANT_THREADS / BL_WAVE; ++i) gamma = fmaxf(gamma, smax[i]);
-
+    for (int i = 0; i < NV; ++i) {
+        const int u = t + i * TPR;
+        v[i] = make_uint4(0, 0, 0, 0);
+        if (u < full) {
+            if (RAGGED) __builtin_memcpy(&v[i], x + u * 8, 16);
+            else v[i] = *(const uint4*)(x + u * 8);
+        } else if (RAGGED && u == full) {
+            uint32_t e[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) e[j] = u * 8 + j < K ? x[u * 8 + j] : 0u;
+            v[i] = make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16);
+        }
+    }
+    float gamma;
+    if (KNOWN) {
+        gamma = __int_as_float(absmax[m]);
+    } else {
+        float mx = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) mx = bl_max_pos(mx, bl_absmax8_bf16(v[i]));
+        gamma = bl_wave_max(mx);
+        if (WPR > 1) {
+            if (lane == 0) smax[w] = gamma;
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < WPR; ++i) gamma = fmaxf(gamma, smax[i]);
+        }
+    }
     const float g = fmaxf(gamma, 1e-5f);
     const float inv = bl_div_rn(127.0f, g);
     int sum = 0;
-    for (int i = threadIdx.x; i < K8; i += QUANT_THREADS) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int u = t + i * TPR;
+        if (u >= units) continue;
         uint2 o;
-        sum += bl_quant8(x[i], inv, &o);
-        qo[i] = o;
+        bl_quant8_words<KNOWN>(v[i], inv, o.x, o.y);
+        sum = __builtin_amdgcn_sdot4((int)o.x, 0x01010101, sum, false);
+        sum = __builtin_amdgcn_sdot4((int)o.y, 0x01010101, sum, false);
+        *(uint2*)(qo + u * 8) = o;
     }
     sum = bl_wave_sum(sum);
-    if (lane == 0) ssum[w] = sum;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        scale[m] = bl_div_rn(g, 127.0f);
-        if (rowsum) {
-            int t = 0;
+    if (WPR > 1) {
+        if (lane == 0) ssum[w] = sum;
+        __syncthreads();                      /* (KNOWN: every thread has read absmax[m]) */
+        sum = 0;
 #pragma unroll
-            for (int i = 0; i < QUANT_THREADS / BL_WAVE; ++i) t += ssum[i];
-            rowsum[m] = t;
-        }
+        for (int i = 0; i < WPR; ++i) sum += ssum[i];
+    }
+    if (t == 0) {
+        if (KNOWN) absmax[m] = 0;
+        scale[m] = bl_div_rn(g, 127.0f);
+        if (rowsum) rowsum[m] = sum;
     }
 }
 
-/* The same quantiser for a ragged K (not a multiple of 64): element-wise reads of the bf16 row
- * (its start need not be 16-byte aligned), output row of Kp = ceil(K/64)*64 bytes with zeros in
- * the padding. */
-__global__ __launch_bounds__(QUANT_THREADS) void bl_quant_rows_any(const uint16_t* __restrict__ X, int K, int Kp,
-                                                                    int8_t* __restrict__ q, float* __restrict__ scale,
-                                                                    int32_t* __restrict__ rowsum) {
+/* Rows too long for the registers (K > 8192): one workgroup per row, read twice. */
+template <bool RAGGED, bool KNOWN>
+__global__ __launch_bounds__(QUANT_THREADS) void bl_quant_long(const uint16_t* __restrict__ X, int K, int Kp,
+                                                                int* __restrict__ absmax, int8_t* __restrict__ q,
+                                                                float* __restrict__ scale, int32_t* __restrict__ rowsum) {
     __shared__ float smax[QUANT_THREADS / BL_WAVE];
     __shared__ int ssum[QUANT_THREADS / BL_WAVE];
     const int64_t m = blockIdx.x;
     const uint16_t* x = X + m * K;
     int8_t* qo = q + m * Kp;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    float mx = 0.0f;
-    for (int i = threadIdx.x; i < K; i += QUANT_THREADS) mx = fmaxf(mx, fabsf(bl_bf16_to_f32(x[i])));
-    mx = bl_wave_max(mx);
-    if (lane == 0) smax[w] = mx;
-    __syncthreads();
-    float gamma = smax[0];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, full = K >> 3, units = Kp >> 3;
+    auto ld = [&](int u) {
+        uint4 v = make_uint4(0, 0, 0, 0);
+        if (u < full) {
+            if (RAGGED) __builtin_memcpy(&v, x + u * 8, 16);
+            else v = *(const uint4*)(x + u * 8);
+        } else if (RAGGED && u == full) {
+            uint32_t e[8];
 #pragma unroll
-    for (int i = 1; i < QUANT_THREADS / BL_WAVE; ++i) gamma = fmaxf(gamma, smax[i]);
+            for (int j = 0; j < 8; ++j) e[j] = u * 8 + j < K ? x[u * 8 + j] : 0u;
+            v = make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16);
+        }
+        return v;
+    };
+    float gamma;
+    if (KNOWN) {
+        gamma = __int_as_float(absmax[m]);
+    } else {
+        float mx = 0.0f;
+        for (int u = threadIdx.x; u < units; u += QUANT_THREADS) mx = bl_max_pos(mx, bl_absmax8_bf16(ld(u)));
+        mx = bl_wave_max(mx);
+        if (lane == 0) smax[w] = mx;
+        __syncthreads();
+        gamma = fmaxf(fmaxf(smax[0], smax[1]), fmaxf(smax[2], smax[3]));
+    }
     const float g = fmaxf(gamma, 1e-5f);
     const float inv = bl_div_rn(127.0f, g);
     int sum = 0;
-    for (int i = threadIdx.x; i < Kp; i += QUANT_THREADS) {
-        int qi = 0;
-        if (i < K) {
-            float r = rintf(bl_bf16_to_f32(x[i]) * inv);
-            r = fminf(fmaxf(r, -127.0f), 127.0f);
-            qi = (int)r;
-        }
-        sum += qi;
-        qo[i] = (int8_t)qi;
+    for (int u = threadIdx.x; u < units; u += QUANT_THREADS) {
+        uint2 o;
+        bl_quant8_words<KNOWN>(ld(u), inv, o.x, o.y);
+        sum = __builtin_amdgcn_sdot4((int)o.x, 0x01010101, sum, false);
+        sum = __builtin_amdgcn_sdot4((int)o.y, 0x01010101, sum, false);
+        *(uint2*)(qo + u * 8) = o;
     }
     sum = bl_wave_sum(sum);
     if (lane == 0) ssum[w] = sum;
-    __syncthreads();
+    __syncthreads();                          /* (KNOWN: every thread has read absmax[m]) */
     if (threadIdx.x == 0) {
+        if (KNOWN) absmax[m] = 0;
         scale[m] = bl_div_rn(g, 127.0f);
-        if (rowsum) {
-            int t = 0;
-#pragma unroll
-            for (int i = 0; i < QUANT_THREADS / BL_WAVE; ++i) t += ssum[i];
-            rowsum[m] = t;
-        }
+        if (rowsum) rowsum[m] = (ssum[0] + ssum[1]) + (ssum[2] + ssum[3]);
     }
+}
+
+template <bool RAGGED, bool KNOWN>
+static bl_status launch_quant(const uint16_t* X, int64_t M64, int64_t K64, int* absmax, int8_t* q, float* scale,
+                              int32_t* rowsum, hipStream_t st) {
+    const int M = (int)M64, K = (int)K64, Kp = (int)bl_kpad(K64);
+    /* A row is one wave's work when the rows alone fill the chip (256 CUs, four waves each), else four
+     * waves share it: with few rows a wave's own chain of instructions is what takes the time. */
+    const bool wave_rows = M >= QUANT_WAVE_ROWS;
+    const unsigned b4 = (unsigned)((M + 3) / 4), b1 = (unsigned)M;
+    if (Kp > 8192)
+        bl_quant_long<RAGGED, KNOWN><<<b1, QUANT_THREADS, 0, st>>>(X, K, Kp, absmax, q, scale, rowsum);
+    else if (!wave_rows && Kp <= 4096)
+        bl_quant_rows<256, 2, RAGGED, KNOWN><<<b1, QUANT_THREADS, 0, st>>>(X, M, K, Kp, absmax, q, scale, rowsum);
+    else if (!wave_rows)
+        bl_quant_rows<256, 4, RAGGED, KNOWN><<<b1, QUANT_THREADS, 0, st>>>(X, M, K, Kp, absmax, q, scale, rowsum);
+    else if (Kp <= 2048)
+        bl_quant_rows<64, 4, RAGGED, KNOWN><<<b4, QUANT_THREADS, 0, st>>>(X, M, K, Kp, absmax, q, scale, rowsum);
+    else if (Kp <= 4096)
+        bl_quant_rows<64, 8, RAGGED, KNOWN><<<b4, QUANT_THREADS, 0, st>>>(X, M, K, Kp, absmax, q, scale, rowsum);
+    else
+        bl_quant_rows<64, 16, RAGGED, KNOWN><<<b4, QUANT_THREADS, 0, st>>>(X, M, K, Kp, absmax, q, scale, rowsum);
+    return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
 }
 
 /* Producer + quantiser: the bf16 row is produced on the fly (bl_produce16) and
@@ -148,13 +191,13 @@ __global__ __launch_bounds__(QUANT_THREADS) void bl_quant_rows_ex(const bl_prod_
         const int u = tid + j * QUANT_THREADS;
         if (u < groups) {
             if (!NORM) bl_produce16<NORM>(pd, m, u, K, true, rn, xv[2 * j], xv[2 * j + 1]);
-            mx = fmaxf(mx, fmaxf(bl_absmax8_bf16(xv[2 * j]), bl_absmax8_bf16(xv[2 * j + 1])));
+            mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16(xv[2 * j]), bl_absmax8_bf16(xv[2 * j + 1])));
         }
     }
     for (int u = tid + 2 * QUANT_THREADS; u < groups; u += QUANT_THREADS) {
         uint4 lo, hi;
         bl_produce16<NORM>(pd, m, u, K, true, rn, lo, hi);
-        mx = fmaxf(mx, fmaxf(bl_absmax8_bf16(lo), bl_absmax8_bf16(hi)));
+        mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16(lo), bl_absmax8_bf16(hi)));
     }
     mx = bl_wave_max(mx);
     if (lane == 0) smax[w] = mx;
@@ -213,42 +256,7 @@ extern "C" bl_status bl_quant_act_ex(const bl_producer* prod, int64_t M, int64_t
     return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
 }
 
-/* Quantiser behind a fused producer epilogue: the bf16 row and its absmax already exist, so one
- * pass quantises.  absmax[m] holds the float bits of max_k |x|; it is read by every thread and then
- * cleared, so that the next product's epilogue can fold its maxima into it again. */
-__global__ __launch_bounds__(QUANT_THREADS) void bl_quant_rows_absmax(const uint4* __restrict__ X, int K8,
-                                                                       int* __restrict__ absmax,
-                                                                       uint2* __restrict__ q, float* __restrict__ scale,
-                                                                       int32_t* __restrict__ rowsum) {
-    __shared__ int ssum[QUANT_THREADS / BL_WAVE];
-    const int64_t m = blockIdx.x;
-    const uint4* x = X + m * K8;
-    uint2* qo = q + m * K8;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const float gamma = __int_as_float(absmax[m]);
-    const float g = fmaxf(gamma, 1e-5f);
-    const float inv = bl_div_rn(127.0f, g);
-    int sum = 0;
-    for (int i = threadIdx.x; i < K8; i += QUANT_THREADS) {
-        uint2 o;
-        sum += bl_quant8(x[i], inv, &o);
-        qo[i] = o;
-    }
-    sum = bl_wave_sum(sum);
-    if (lane == 0) ssum[w] = sum;
-    __syncthreads();                      /* every thread has read absmax[m] */
-    if (threadIdx.x == 0) {
-        absmax[m] = 0;
-        scale[m] = bl_div_rn(g, 127.0f);
-        if (rowsum) {
-            int t = 0;
-#pragma unroll
-            for (int i = 0; i < QUANT_THREADS / BL_WAVE; ++i) t += ssum[i];
-            rowsum[m] = t;
-        }
-    }
-}
-
+/* Quantiser behind a fused producer epilogue: the bf16 row and its absmax already exist. */
 extern "C" bl_status bl_quant_from_absmax(const uint16_t* X, float* absmax, int64_t M, int64_t K, int8_t* q,
                                           float* scale, int32_t* rowsum, bl_stream s) {
     if (!X || !absmax || !q || !scale) return BL_ERR_NULL;
@@ -256,9 +264,7 @@ extern "C" bl_status bl_quant_from_absmax(const uint16_t* X, float* absmax, int6
     if (!bl_aligned(X, 16) || !bl_aligned(q, 16) || !bl_aligned(scale, 4) || !bl_aligned(rowsum, 4) ||
         !bl_aligned(absmax, 4))
         return BL_ERR_ALIGN;
-    bl_quant_rows_absmax<<<(unsigned)M, QUANT_THREADS, 0, (hipStream_t)s>>>((const uint4*)X, (int)(K / 8), (int*)absmax,
-                                                                           (uint2*)q, scale, rowsum);
-    return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
+    return launch_quant<false, true>(X, M, K, (int*)absmax, q, scale, rowsum, (hipStream_t)s);
 }
 
 extern "C" bl_status bl_quant_act_int8(const uint16_t* X, int64_t M, int64_t K, int8_t* q, float* scale,
@@ -268,12 +274,9 @@ extern "C" bl_status bl_quant_act_int8(const uint16_t* X, int64_t M, int64_t K, 
     if (K % 64 != 0) {
         if (!bl_aligned(X, 2) || !bl_aligned(q, 16) || !bl_aligned(scale, 4) || !bl_aligned(rowsum, 4))
             return BL_ERR_ALIGN;
-        bl_quant_rows_any<<<(unsigned)M, QUANT_THREADS, 0, (hipStream_t)s>>>(X, (int)K, (int)bl_kpad(K), q, scale, rowsum);
-        return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
+        return launch_quant<true, false>(X, M, K, nullptr, q, scale, rowsum, (hipStream_t)s);
     }
     if (!bl_aligned(X, 16) || !bl_aligned(q, 16) || !bl_aligned(scale, 4) || !bl_aligned(rowsum, 4))
         return BL_ERR_ALIGN;
-    bl_quant_rows<<<(unsigned)M, QUANT_THREADS, 0, (hipStream_t)s>>>((const uint4*)X, (int)(K / 8), (uint2*)q,
-                                                                    scale, rowsum);
-    return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
+    return launch_quant<false, false>(X, M, K, nullptr, q, scale, rowsum, (hipStream_t)s);
 }

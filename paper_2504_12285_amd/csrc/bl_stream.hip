@@ -129,13 +129,13 @@ __global__ __launch_bounds__(256) void bl_stream_prep(const bl_stream_prep_item*
             const int u = tid + j * 256;
             if (u < groups) {
                 if (!have_xv) bl_produce16<NORM>(pd, 0, u, K, true, rn, xv[2 * j], xv[2 * j + 1]);
-                mx = fmaxf(mx, fmaxf(bl_absmax8_bf16(xv[2 * j]), bl_absmax8_bf16(xv[2 * j + 1])));
+                mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16(xv[2 * j]), bl_absmax8_bf16(xv[2 * j + 1])));
             }
         }
         for (int u = tid + 512; u < groups; u += 256) {
             uint4 lo, hi;
             bl_produce16<NORM>(pd, 0, u, K, false, rn, lo, hi);
-            mx = fmaxf(mx, fmaxf(bl_absmax8_bf16(lo), bl_absmax8_bf16(hi)));
+            mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16(lo), bl_absmax8_bf16(hi)));
         }
         mx = bl_wave_max(mx);
         if (lane == 0) fs[w] = mx;
@@ -226,7 +226,7 @@ __device__ __forceinline__ void bl_stream_stage(const bl_stream_item& P, int* __
         };
         float mx = 0.0f;
         for (int u = tid; u < groups; u += 256)
-            mx = fmaxf(mx, fmaxf(bl_absmax8_bf16(ld(2 * u)), bl_absmax8_bf16(ld(2 * u + 1))));
+            mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16(ld(2 * u)), bl_absmax8_bf16(ld(2 * u + 1))));
         mx = bl_wave_max(mx);
         if (lane == 0) fs[w] = mx;
         __syncthreads();
@@ -413,7 +413,7 @@ __device__ __forceinline__ void bl_stream_stage_t5(const bl_stream_item& P, int*
         };
         float mx = 0.0f;
         for (int u = tid; u < groups; u += 256)
-            mx = fmaxf(mx, fmaxf(bl_absmax8_bf16(ld(2 * u)), bl_absmax8_bf16(ld(2 * u + 1))));
+            mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16(ld(2 * u)), bl_absmax8_bf16(ld(2 * u + 1))));
         mx = bl_wave_max(mx);
         if (lane == 0) fs[w] = mx;
         __syncthreads();
@@ -617,7 +617,7 @@ __device__ __forceinline__ void bl_km_slice(const bl_stream_item& P, const int u
             };
             float mx = 0.0f;
             for (int u = tid; u < groups; u += 256)
-                mx = fmaxf(mx, fmaxf(bl_absmax8_bf16(ld(2 * u)), bl_absmax8_bf16(ld(2 * u + 1))));
+                mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16(ld(2 * u)), bl_absmax8_bf16(ld(2 * u + 1))));
             mx = bl_wave_max(mx);
             if (lane == 0) fs[lw] = mx;
             __syncthreads();
