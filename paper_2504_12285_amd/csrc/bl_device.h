@@ -9,7 +9,20 @@
 typedef int bl_v4i __attribute__((ext_vector_type(4)));
 typedef int bl_v16i __attribute__((ext_vector_type(16)));
 
+typedef float bl_v4f __attribute__((ext_vector_type(4)));
+typedef uint32_t bl_v2u __attribute__((ext_vector_type(2)));
+
 #define BL_WAVE 64
+
+/* A pointer that reached a kernel inside a structure is generic to the compiler once it has been
+ * pinned or read from memory: its loads become flat_* instructions, which count on both counters
+ * and are waited for all at once.  Casting it to the global address space gives global_* with
+ * exact waits. */
+#define BL_G __attribute__((address_space(1)))
+template <typename T>
+__device__ __forceinline__ T BL_G* bl_g(T* p) { return (T BL_G*)p; }
+template <typename T>
+__device__ __forceinline__ const T BL_G* bl_gc(const void* p) { return (const T BL_G*)p; }
 
 /* bf16 bit pattern -> fp32 (exact). */
 __device__ __forceinline__ float bl_bf16_to_f32(uint32_t h) { return __uint_as_float(h << 16); }

@@ -56,3 +56,6 @@ __device__ __forceinline__ bl_gemv_prob bl_fetch_prob(const bl_gemv_group& grp) 
 /* Batched decode, 17..64 tokens with int8 inputs (bl_gemv_panel.hip): lays the products of
  * the group out over workgroups and launches them. */
 bl_status bl_gemv_panel_launch(bl_gemv_group& grp, int M, hipStream_t st);
+
+/* One token and one product, K <= 8192 (bl_gemv_one.hip). */
+bl_status bl_gemv_one_launch(const bl_gemv_prob& P, hipStream_t st);

@@ -29,10 +29,7 @@
 
 /* ---- device side -------------------------------------------------------------------------- */
 
-/* Pointers read from the product table are generic to the compiler; they are cast to the
- * global address space so that their loads and stores are global_* instructions with exact
- * counter waits (a generic access forces a full wait at every use). */
-#define BL_G __attribute__((address_space(1)))
+/* (pointers read from the product table are cast to the global address space: BL_G) */
 typedef bl_v4i BL_G bl_gv4i;
 
 /* What the streaming kernel needs to know about one product (device memory). */

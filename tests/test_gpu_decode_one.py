@@ -1,0 +1,115 @@
+"""The one-token, one-product decode kernel against the general dot4 kernel (test hook path 1), bit for
+bit over every producer, normalisation with and without gains, both layouts, int8 inputs, residuals
+and the edges of its size classes; and against the CPU oracle on rows whose maximum it cannot settle
+from the sum of squares."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def bl():
+    from paper_2504_12285_amd import binding
+    binding.load()
+    return binding
+
+
+def _both(bl, make, outs):
+    """Runs the descriptor `make()` through the default kernel and the dot4 kernel; compares every output's bits."""
+    got = []
+    for path in (0, 1):
+        bl._check(bl.load().bl_debug_force_path(path), "bl_debug_force_path")
+        try:
+            for t in outs:
+                t.fill_(-1)
+            item, layout = make()
+            bl.bl_bitlinear_decode_group(bl.make_decode_descs([item]), layout, 1)
+            torch.cuda.synchronize()
+            got.append([t.cpu().numpy().view(np.uint8).copy() for t in outs])
+        finally:
+            bl.load().bl_debug_force_path(0)
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+
+
+SIZES = [(1, 64), (7, 128), (9, 960), (2048, 64), (2049, 3072), (4096, 3136), (4097, 4096), (300, 4160), (4100, 7168),
+         (600, 7232), (4200, 8192), (16385, 256), (16390, 4096), (8200, 5120)]
+
+
+@pytest.mark.parametrize("N,K", SIZES)
+@pytest.mark.parametrize("kind", ["bf16", "f32", "attn", "residual", "gate", "int8"])
+def test_against_the_dot4_kernel(bl, kind, N, K):
+    g = torch.Generator(device=DEV).manual_seed(N + 7 * K)
+    W = torch.randint(-1, 2, (N, K), generator=g, device=DEV, dtype=torch.int8)
+    x = torch.randn(1, 2 * K, generator=g, device=DEV) * 3
+    x2 = torch.randn(1, K, generator=g, device=DEV)
+    gain = 1.0 + 0.2 * torch.randn(K, generator=g, device=DEV)
+    res = torch.randn(1, N, generator=g, device=DEV)
+    acc = torch.empty((1, N), dtype=torch.int32, device=DEV)
+    y = torch.empty((1, N), device=DEV)
+    q = torch.empty((1, K), dtype=torch.int8, device=DEV)
+    sc, aux = torch.empty(1, device=DEV), torch.empty((1, K), device=DEV)
+    for layout in (0, 1):
+        packed, beta = bl.bl_pack_ternary(W, layout, beta=0.03)
+        for norm, with_gain in ((False, False), (True, False), (True, True)):
+            if kind == "int8" and norm:
+                continue
+            kw = dict(norm=norm, gain=gain if with_gain else None, eps=1e-5)
+            hd = 64 if K % 64 == 0 else 16
+            heads = K // hd
+            kv = heads // 2 if heads % 2 == 0 else heads
+            qkv = torch.cat([x, x2, x], 1)[:, :(heads + 2 * kv) * hd].contiguous()
+            prod = {"bf16": lambda: bl.make_producer(bl.BL_PROD_BF16, xb, **kw),
+                    "f32": lambda: bl.make_producer(bl.BL_PROD_F32, x, **kw),
+                    "attn": lambda: bl.make_producer(bl.BL_PROD_ATTN_V, qkv, n_q=heads, n_kv=kv, head_dim=hd, **kw),
+                    "residual": lambda: bl.make_producer(bl.BL_PROD_RESIDUAL, x, x2, aux, **kw),
+                    "gate": lambda: bl.make_producer(bl.BL_PROD_RELU2_GATE, x, **kw)}
+            xb = x[:, :K].to(torch.bfloat16).contiguous()
+            item = dict(packed=packed, beta=beta, N=N, K=K, acc=acc, y=y, residual=res if with_gain or layout else None)
+            outs = [acc, y]
+            if kind == "int8":
+                item["q"], item["scale"], item["rowsum"] = bl.bl_quant_act_int8(xb)
+            else:
+                item.update(prod=prod[kind](), q_out=q, scale_out=sc, fixed_scale=0.0 if layout else 0.5)
+                outs += [q, sc] + ([aux] if kind == "residual" else [])
+            _both(bl, lambda: (item, layout), outs)
+
+
+@pytest.mark.parametrize("case", ["midpoint", "tiny", "huge gain", "zero", "large"])
+def test_rows_whose_maximum_is_taken_directly(bl, case):
+    """Rows where r * max|t*gain| lies on a bf16 rounding boundary or outside the bound's range."""
+    K, N = 2560, 40
+    rng = np.random.default_rng(5)
+    t = rng.standard_normal(K).astype(np.float32)
+    gain = np.ones(K, np.float32)
+    if case == "midpoint":                       # many rows, so that some straddle a boundary: scale the largest value
+        rows = [t * np.float32(1) for _ in range(64)]
+        for i, r_ in enumerate(rows):
+            r_[17] = np.float32(8.0) + np.float32(i) * np.float32(2.0 ** -9)
+    elif case == "tiny":
+        rows = [(t * np.float32(1e-30)), (t * np.float32(1e-38))]
+    elif case == "huge gain":
+        gain[3] = np.float32(2.0 ** 90)
+        rows = [t]
+    elif case == "zero":
+        rows = [t * np.float32(0)]
+    else:
+        rows = [t * np.float32(1e18)]
+    W = rng.integers(-1, 2, size=(N, K)).astype(np.int8)
+    packed, beta = bl.bl_pack_ternary(torch.from_numpy(W).to(DEV), 1, beta=0.5)
+    q = torch.empty((1, K), dtype=torch.int8, device=DEV)
+    acc, sc = torch.empty((1, N), dtype=torch.int32, device=DEV), torch.empty(1, device=DEV)
+    for row in rows:
+        xd, gd = torch.from_numpy(row.reshape(1, K)).to(DEV), torch.from_numpy(gain).to(DEV)
+        item = dict(packed=packed, beta=beta, N=N, K=K, acc=acc, q_out=q, scale_out=sc,
+                    prod=bl.make_producer(bl.BL_PROD_F32, xd, norm=True, gain=gd, eps=1e-5))
+        _both(bl, lambda: (item, 1), [acc, q, sc])
+        X = oracle.rmsnorm_rows(row.reshape(1, K), gain, 1e-5)
+        q_o, s_o, _ = oracle.quant_act(X)
+        assert np.array_equal(q.cpu().numpy(), q_o)
+        assert np.array_equal(sc.cpu().numpy().view(np.uint32), s_o.view(np.uint32))
