@@ -288,13 +288,16 @@ __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : 
     float bt = (!TABLE && want_cf) ? *beta : 0.0f;
     /* what the epilogue of the tile in flight stores to (TABLE: set when that tile was set up) */
     int eN = N;
-    const float* eres = residual;
-    int32_t* eacc = acc;
-    float* ey = y;
+    /* (cast to the global address space: read from the table they would be generic, see BL_G) */
+    const float BL_G* eres = bl_gc<float>(residual);
+    int32_t BL_G* eacc = bl_g(acc);
+    float BL_G* ey = bl_g(y);
+    const int32_t BL_G* rowsum_g = bl_gc<int32_t>(rowsum);
+    const float BL_G* scale_g = bl_gc<float>(scale);
     int nN = N, nsteps = steps;
-    const float* nres = residual;
-    int32_t* nacc = acc;
-    float* ny = y;
+    const float BL_G* nres = eres;
+    int32_t BL_G* nacc = eacc;
+    float BL_G* ny = ey;
     auto load_item = [&](int vb, int& tn) {
         int lo = 0, hi = nitems - 1;
         while (lo < hi) {
@@ -305,17 +308,17 @@ __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : 
         tn = vb - tile0[lo];
         packed = it.packed;
         q = it.q;
-        rowsum = it.rowsum;
-        scale = it.scale;
+        rowsum_g = bl_gc<int32_t>(it.rowsum);
+        scale_g = bl_gc<float>(it.scale);
         N = nN = it.N;
         K = it.K;
         kb = K / 4;
         nsteps = K / G3_BK;
-        nres = it.residual;
-        nacc = it.acc;
-        ny = it.y;
+        nres = bl_gc<float>(it.residual);
+        nacc = bl_g(it.acc);
+        ny = bl_g(it.y);
         want_cf = it.y != nullptr;
-        bt = want_cf ? *it.beta : 0.0f;
+        bt = want_cf ? *bl_gc<float>(it.beta) : 0.0f;
     };
 
     /* XCD-aware tile order: workgroup L runs on XCD L%8.  The tile grid is cut
@@ -376,8 +379,8 @@ __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : 
          * would put a memory round trip between the last MFMA and the first store) */
         if (tid < G3_BM) {
             const int m = m0 + tid;
-            row_rs = m < M ? rowsum[m] : 0;
-            row_cf = (want_cf && m < M) ? bt * scale[m] : 0.0f;
+            row_rs = m < M ? rowsum_g[m] : 0;
+            row_cf = (want_cf && m < M) ? bt * scale_g[m] : 0.0f;
         }
     };
     auto issue = [&](int kk, int buf) {
@@ -463,7 +466,7 @@ __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : 
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni)
                 __builtin_nontemporal_store(__int_as_float(P[mi][ni][vq * 4 + v4]),
-                                            (float*)((char*)ey + (size_t)(bo + ((uint32_t)v4 * (uint32_t)eN + ni * 32u) * 4u)));
+                                            (float BL_G*)((char BL_G*)ey + (size_t)(bo + ((uint32_t)v4 * (uint32_t)eN + ni * 32u) * 4u)));
     };
 
     while (true) {

@@ -89,24 +89,24 @@ __global__ __launch_bounds__(256) void bl_gemv_rows(const bl_gemv_group grp) {
         for (int j = 0; j < 2; ++j) {
             const int u = tid + j * 256;
             if (u < groups) {
-                xv[2 * j] = ((const uint4*)P.prod.in0)[2 * u];
-                xv[2 * j + 1] = ((const uint4*)P.prod.in0)[2 * u + 1];
+                xv[2 * j] = __builtin_bit_cast(uint4, bl_gc<bl_v4i>(P.prod.in0)[2 * u]);
+                xv[2 * j + 1] = __builtin_bit_cast(uint4, bl_gc<bl_v4i>(P.prod.in0)[2 * u + 1]);
             }
         }
     } else if (!P.fused && tid < M * groups) {
-        qv = *(const bl_v4i*)(P.q + (int64_t)(tid / groups) * K + (int64_t)(tid % groups) * 16);
+        qv = *bl_gc<bl_v4i>(P.q + (int64_t)(tid / groups) * K + (int64_t)(tid % groups) * 16);
     }
     /* small loads go out before the weight stream and are used late */
-    const float bt = *P.beta;
+    const float bt = *bl_gc<float>(P.beta);
     float sc_in = 0.0f;
     int rs_in = 0;
     if (!P.fused && tid < M) {
-        if (P.scale) sc_in = P.scale[tid];
-        if (P.rowsum) rs_in = P.rowsum[tid];
+        if (P.scale) sc_in = bl_gc<float>(P.scale)[tid];
+        if (P.rowsum) rs_in = bl_gc<int32_t>(P.rowsum)[tid];
     }
 
     bl_v4i p[L];
-    const bl_v4i* wrow = P.packed + (int64_t)(row_ok ? n : 0) * nchunks;
+    const bl_v4i BL_G* wrow = bl_gc<bl_v4i>(P.packed) + (int64_t)(row_ok ? n : 0) * nchunks;
 #pragma unroll
     for (int i = 0; i < L; ++i) {
         const int chunk = (i * ksplit + kp) * G + g;
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(256) void bl_gemv_rows(const bl_gemv_group grp) {
                     bl_quant8_words(xv[2 * j], inv, a0, a1);
                     bl_quant8_words(xv[2 * j + 1], inv, a2, a3);
                     part += bl_sum16(a0, a1, a2, a3);
-                    if (emit) *(uint4*)(P.q_out + (int64_t)m * K + u * 16) = make_uint4(a0, a1, a2, a3);
+                    if (emit) *(bl_v4i BL_G*)(P.q_out + (int64_t)m * K + u * 16) = bl_v4i{(int)a0, (int)a1, (int)a2, (int)a3};
                     bl_put16(Q + m * (K / 4), u, P.layout, a0, a1, a2, a3);
                 }
             }
@@ -171,7 +171,7 @@ __global__ __launch_bounds__(256) void bl_gemv_rows(const bl_gemv_group grp) {
                 bl_quant8_words(lo, inv, a0, a1);
                 bl_quant8_words(hi, inv, a2, a3);
                 part += bl_sum16(a0, a1, a2, a3);
-                if (emit) *(uint4*)(P.q_out + (int64_t)m * K + u * 16) = make_uint4(a0, a1, a2, a3);
+                if (emit) *(bl_v4i BL_G*)(P.q_out + (int64_t)m * K + u * 16) = bl_v4i{(int)a0, (int)a1, (int)a2, (int)a3};
                 bl_put16(Q + m * (K / 4), u, P.layout, a0, a1, a2, a3);
             }
             part = bl_wave_sum(part);
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(256) void bl_gemv_rows(const bl_gemv_group grp) {
             if (tid == 0) {
                 const float sc = bl_div_rn(gg, 127.0f);
                 fs[m] = P.fixed_scale > 0.0f ? P.fixed_scale : sc;
-                if (P.scale_out && first_block) P.scale_out[m] = sc;
+                if (P.scale_out && first_block) bl_g(P.scale_out)[m] = sc;
             }
             __syncthreads();                       /* Q, sq[m], fs[m] complete; fs[M..] reusable */
         }
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(256) void bl_gemv_rows(const bl_gemv_group grp) {
         for (int u = tid; u < M * groups; u += 256) {
             const int m = u / groups, c16 = u - m * groups;
             bl_v4i v = qv;
-            if (u >= 256) v = *(const bl_v4i*)(P.q + (int64_t)m * K + (int64_t)c16 * 16);
+            if (u >= 256) v = *bl_gc<bl_v4i>(P.q + (int64_t)m * K + (int64_t)c16 * 16);
             if (need_sum) atomicAdd(&sq[m], bl_sum16((uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]));
             bl_put16(Q + m * (K / 4), c16, P.layout, (uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]);
         }
@@ -241,10 +241,10 @@ __global__ __launch_bounds__(256) void bl_gemv_rows(const bl_gemv_group grp) {
 #pragma unroll
         for (int m = 0; m < M; ++m) {
             const int val = o[m] - sq[m];
-            if (P.acc) P.acc[(int64_t)m * N + n_out] = val;
+            if (P.acc) bl_g(P.acc)[(int64_t)m * N + n_out] = val;
             if (P.y) {
                 const float t = (float)val * (bt * fs[m]);
-                P.y[(int64_t)m * N + n_out] = P.residual ? P.residual[(int64_t)m * N + n_out] + t : t;
+                bl_g(P.y)[(int64_t)m * N + n_out] = P.residual ? bl_gc<float>(P.residual)[(int64_t)m * N + n_out] + t : t;
             }
         }
     }
@@ -339,23 +339,23 @@ __global__ __launch_bounds__(256) void bl_gemv_mma(const bl_gemv_group grp, cons
     /* without normalisation every wave quantises tokens w, w+4, .. on its own: lane l holds
      * groups l and l+64 of the wave's first token */
     if (pre_bf16 && w < M) {
-        const uint4* xr = (const uint4*)((const uint16_t*)P.prod.in0 + (int64_t)w * K);
+        const bl_v4i BL_G* xr = bl_gc<bl_v4i>((const uint16_t*)P.prod.in0 + (int64_t)w * K);
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int u = lane + j * 64;
             if (u < groups) {
-                xv[2 * j] = xr[2 * u];
-                xv[2 * j + 1] = xr[2 * u + 1];
+                xv[2 * j] = __builtin_bit_cast(uint4, xr[2 * u]);
+                xv[2 * j + 1] = __builtin_bit_cast(uint4, xr[2 * u + 1]);
             }
         }
     }
     /* small loads go out now and are used late: nothing below waits for them alone */
-    const float bt = *P.beta;
+    const float bt = *bl_gc<float>(P.beta);
     float sc_in = 0.0f;
     int rs_in = 0;
     if (!fused && tid < M) {
-        if (P.scale) sc_in = P.scale[tid];
-        if (P.rowsum) rs_in = P.rowsum[tid];
+        if (P.scale) sc_in = bl_gc<float>(P.scale)[tid];
+        if (P.rowsum) rs_in = bl_gc<int32_t>(P.rowsum)[tid];
     }
 
     /* 2. every weight load of this wave.  The matrix core wants lane 16*kg+c to hold chunk kg
@@ -366,7 +366,7 @@ __global__ __launch_bounds__(256) void bl_gemv_mma(const bl_gemv_group grp, cons
         const int lrow = lane >> 2, lkg = lane & 3;
         const int ln = n - c + lrow;                      /* the row this lane fetches */
         const bool lok = ln < N;
-        const bl_v4i* wrow = P.packed + (int64_t)(lok ? ln : 0) * nchunks;
+        const bl_v4i BL_G* wrow = bl_gc<bl_v4i>(P.packed) + (int64_t)(lok ? ln : 0) * nchunks;
 #pragma unroll
         for (int i = 0; i < L; ++i) {
             const int chunk = (i * ksplit + kp) * 4 + lkg;
@@ -404,14 +404,14 @@ __global__ __launch_bounds__(256) void bl_gemv_mma(const bl_gemv_group grp, cons
             if (pre_bf16) {
                 /* plain bf16 rows: the lane's other groups four at a time, so that their loads
                  * are in flight together (one round trip instead of four) */
-                const uint4* xr = (const uint4*)((const uint16_t*)P.prod.in0 + (int64_t)m * K);
+                const bl_v4i BL_G* xr = bl_gc<bl_v4i>((const uint16_t*)P.prod.in0 + (int64_t)m * K);
                 for (int u0 = lane + 128; u0 < groups; u0 += 256) {
                     uint4 t[8];
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
                         if (u0 + 64 * j < groups) {
-                            t[2 * j] = xr[2 * (u0 + 64 * j)];
-                            t[2 * j + 1] = xr[2 * (u0 + 64 * j) + 1];
+                            t[2 * j] = __builtin_bit_cast(uint4, xr[2 * (u0 + 64 * j)]);
+                            t[2 * j + 1] = __builtin_bit_cast(uint4, xr[2 * (u0 + 64 * j) + 1]);
                         }
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
@@ -437,19 +437,19 @@ __global__ __launch_bounds__(256) void bl_gemv_mma(const bl_gemv_group grp, cons
                     uint32_t a0, a1, a2, a3;
                     bl_quant8_words(xv[2 * j], inv, a0, a1);
                     bl_quant8_words(xv[2 * j + 1], inv, a2, a3);
-                    if (emit) *(uint4*)(P.q_out + (int64_t)m * K + u * 16) = make_uint4(a0, a1, a2, a3);
+                    if (emit) *(bl_v4i BL_G*)(P.q_out + (int64_t)m * K + u * 16) = bl_v4i{(int)a0, (int)a1, (int)a2, (int)a3};
                     *(uint4*)(Qm + u * 16) = make_uint4(a0, a1, a2, a3);
                 }
             }
             if (pre_bf16) {
-                const uint4* xr = (const uint4*)((const uint16_t*)P.prod.in0 + (int64_t)m * K);
+                const bl_v4i BL_G* xr = bl_gc<bl_v4i>((const uint16_t*)P.prod.in0 + (int64_t)m * K);
                 for (int u0 = lane + 128; u0 < groups; u0 += 256) {
                     uint4 t[8];
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
                         if (u0 + 64 * j < groups) {
-                            t[2 * j] = xr[2 * (u0 + 64 * j)];
-                            t[2 * j + 1] = xr[2 * (u0 + 64 * j) + 1];
+                            t[2 * j] = __builtin_bit_cast(uint4, xr[2 * (u0 + 64 * j)]);
+                            t[2 * j + 1] = __builtin_bit_cast(uint4, xr[2 * (u0 + 64 * j) + 1]);
                         }
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
@@ -458,7 +458,7 @@ __global__ __launch_bounds__(256) void bl_gemv_mma(const bl_gemv_group grp, cons
                             uint32_t a0, a1, a2, a3;
                             bl_quant8_words(t[2 * j], inv, a0, a1);
                             bl_quant8_words(t[2 * j + 1], inv, a2, a3);
-                            if (emit) *(uint4*)(P.q_out + (int64_t)m * K + u * 16) = make_uint4(a0, a1, a2, a3);
+                            if (emit) *(bl_v4i BL_G*)(P.q_out + (int64_t)m * K + u * 16) = bl_v4i{(int)a0, (int)a1, (int)a2, (int)a3};
                             *(uint4*)(Qm + u * 16) = make_uint4(a0, a1, a2, a3);
                         }
                     }
@@ -470,14 +470,14 @@ __global__ __launch_bounds__(256) void bl_gemv_mma(const bl_gemv_group grp, cons
                     bl_produce16<NORM>(P.prod, m, u, K, first_block, 1.0f, lo, hi);
                     bl_quant8_words(lo, inv, a0, a1);
                     bl_quant8_words(hi, inv, a2, a3);
-                    if (emit) *(uint4*)(P.q_out + (int64_t)m * K + u * 16) = make_uint4(a0, a1, a2, a3);
+                    if (emit) *(bl_v4i BL_G*)(P.q_out + (int64_t)m * K + u * 16) = bl_v4i{(int)a0, (int)a1, (int)a2, (int)a3};
                     *(uint4*)(Qm + u * 16) = make_uint4(a0, a1, a2, a3);
                 }
             }
             if (lane == 0) {
                 const float sc = bl_div_rn(gg, 127.0f);
                 fscale[m] = P.fixed_scale > 0.0f ? P.fixed_scale : sc;
-                if (P.scale_out && first_block) P.scale_out[m] = sc;
+                if (P.scale_out && first_block) bl_g(P.scale_out)[m] = sc;
             }
         }
         __syncthreads();
@@ -520,7 +520,7 @@ __global__ __launch_bounds__(256) void bl_gemv_mma(const bl_gemv_group grp, cons
                     uint32_t a0, a1, a2, a3;
                     bl_quant8_words(xv[2 * j], inv, a0, a1);
                     bl_quant8_words(xv[2 * j + 1], inv, a2, a3);
-                    if (emit) *(uint4*)(P.q_out + (int64_t)m * K + u * 16) = make_uint4(a0, a1, a2, a3);
+                    if (emit) *(bl_v4i BL_G*)(P.q_out + (int64_t)m * K + u * 16) = bl_v4i{(int)a0, (int)a1, (int)a2, (int)a3};
                     *(uint4*)(Qm + u * 16) = make_uint4(a0, a1, a2, a3);
                 }
             }
@@ -530,13 +530,13 @@ __global__ __launch_bounds__(256) void bl_gemv_mma(const bl_gemv_group grp, cons
                 bl_produce16<NORM>(P.prod, m, u, K, first_block, rn, lo, hi);
                 bl_quant8_words(lo, inv, a0, a1);
                 bl_quant8_words(hi, inv, a2, a3);
-                if (emit) *(uint4*)(P.q_out + (int64_t)m * K + u * 16) = make_uint4(a0, a1, a2, a3);
+                if (emit) *(bl_v4i BL_G*)(P.q_out + (int64_t)m * K + u * 16) = bl_v4i{(int)a0, (int)a1, (int)a2, (int)a3};
                 *(uint4*)(Qm + u * 16) = make_uint4(a0, a1, a2, a3);
             }
             if (tid == 0) {
                 const float sc = bl_div_rn(gg, 127.0f);
                 fscale[m] = P.fixed_scale > 0.0f ? P.fixed_scale : sc;
-                if (P.scale_out && first_block) P.scale_out[m] = sc;
+                if (P.scale_out && first_block) bl_g(P.scale_out)[m] = sc;
             }
         }
         __syncthreads();
@@ -659,10 +659,10 @@ __global__ __launch_bounds__(256) void bl_gemv_mma(const bl_gemv_group grp, cons
                 const int tok = t * 16 + kg * 4 + v;
                 if (tok < M) {
                     const int val = D[t][v] - (need_sum ? 0 : rs4[v]);
-                    if (P.acc) P.acc[(int64_t)tok * N + n] = val;
+                    if (P.acc) bl_g(P.acc)[(int64_t)tok * N + n] = val;
                     if (P.y) {
                         const float r = (float)val * (bt * scv[v]);
-                        P.y[(int64_t)tok * N + n] = P.residual ? P.residual[(int64_t)tok * N + n] + r : r;
+                        bl_g(P.y)[(int64_t)tok * N + n] = P.residual ? bl_gc<float>(P.residual)[(int64_t)tok * N + n] + r : r;
                     }
                 }
             }

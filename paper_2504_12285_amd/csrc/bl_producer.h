@@ -23,9 +23,10 @@ struct bl_prod_dev {
 __device__ __forceinline__ void bl_produce16_f32(const bl_prod_dev& pd, int m, int u, int K, bool store_aux,
                                                  float v[16]) {
     if (pd.kind == BL_PROD_BF16) {
-        const uint4* xr = (const uint4*)((const uint16_t*)pd.in0 + (int64_t)m * K);
-        const uint4 lo = xr[2 * u], hi = xr[2 * u + 1];
-        const uint32_t w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+        const bl_v4i BL_G* xr = bl_gc<bl_v4i>((const uint16_t*)pd.in0 + (int64_t)m * K);
+        const bl_v4i lo = xr[2 * u], hi = xr[2 * u + 1];
+        const uint32_t w[8] = {(uint32_t)lo[0], (uint32_t)lo[1], (uint32_t)lo[2], (uint32_t)lo[3],
+                               (uint32_t)hi[0], (uint32_t)hi[1], (uint32_t)hi[2], (uint32_t)hi[3]};
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             v[2 * j] = bl_bf16_to_f32(w[j] & 0xFFFFu);
@@ -34,11 +35,11 @@ __device__ __forceinline__ void bl_produce16_f32(const bl_prod_dev& pd, int m, i
         return;
     }
     if (pd.kind == BL_PROD_RELU2_GATE) {
-        const float4* g4 = (const float4*)((const float*)pd.in0 + (int64_t)m * 2 * K + (int64_t)u * 16);
-        const float4* u4 = (const float4*)((const float*)pd.in0 + (int64_t)m * 2 * K + K + (int64_t)u * 16);
+        const bl_v4f BL_G* g4 = bl_gc<bl_v4f>((const float*)pd.in0 + (int64_t)m * 2 * K + (int64_t)u * 16);
+        const bl_v4f BL_G* u4 = bl_gc<bl_v4f>((const float*)pd.in0 + (int64_t)m * 2 * K + K + (int64_t)u * 16);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const float4 g = g4[j], up = u4[j];
+            const bl_v4f g = g4[j], up = u4[j];
             const float gg[4] = {g.x, g.y, g.z, g.w}, uu[4] = {up.x, up.y, up.z, up.w};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -56,23 +57,23 @@ __device__ __forceinline__ void bl_produce16_f32(const bl_prod_dev& pd, int m, i
     } else {
         off = (int64_t)m * K + (int64_t)u * 16;
     }
-    const float4* a4 = (const float4*)((const float*)pd.in0 + off);
+    const bl_v4f BL_G* a4 = bl_gc<bl_v4f>((const float*)pd.in0 + off);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const float4 a = a4[j];
+        const bl_v4f a = a4[j];
         v[4 * j] = a.x; v[4 * j + 1] = a.y; v[4 * j + 2] = a.z; v[4 * j + 3] = a.w;
     }
     if (pd.kind == BL_PROD_RESIDUAL) {
-        const float4* b4 = (const float4*)(pd.in1 + off);
+        const bl_v4f BL_G* b4 = bl_gc<bl_v4f>(pd.in1 + off);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const float4 b = b4[j];
+            const bl_v4f b = b4[j];
             v[4 * j] += b.x; v[4 * j + 1] += b.y; v[4 * j + 2] += b.z; v[4 * j + 3] += b.w;
         }
         if (store_aux && pd.aux_out) {
-            float4* o4 = (float4*)(pd.aux_out + off);
+            bl_v4f BL_G* o4 = (bl_v4f BL_G*)(pd.aux_out + off);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) o4[j] = make_float4(v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]);
+            for (int j = 0; j < 4; ++j) o4[j] = bl_v4f{v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]};
         }
     }
 }
@@ -84,9 +85,9 @@ template <bool NORM>
 __device__ __forceinline__ void bl_produce16(const bl_prod_dev& pd, int m, int u, int K, bool store_aux, float rn,
                                              uint4& lo, uint4& hi) {
     if (pd.kind == BL_PROD_BF16 && !(NORM && pd.norm)) {
-        const uint4* xr = (const uint4*)((const uint16_t*)pd.in0 + (int64_t)m * K);
-        lo = xr[2 * u];
-        hi = xr[2 * u + 1];
+        const bl_v4i BL_G* xr = bl_gc<bl_v4i>((const uint16_t*)pd.in0 + (int64_t)m * K);
+        lo = __builtin_bit_cast(uint4, xr[2 * u]);
+        hi = __builtin_bit_cast(uint4, xr[2 * u + 1]);
         return;
     }
     float v[16];
@@ -95,10 +96,10 @@ __device__ __forceinline__ void bl_produce16(const bl_prod_dev& pd, int m, int u
 #pragma unroll
         for (int e = 0; e < 16; ++e) v[e] = v[e] * rn;
         if (pd.gain) {
-            const float4* g4 = (const float4*)(pd.gain + (int64_t)u * 16);
+            const bl_v4f BL_G* g4 = bl_gc<bl_v4f>(pd.gain + (int64_t)u * 16);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const float4 g = g4[j];
+                const bl_v4f g = g4[j];
                 v[4 * j] *= g.x; v[4 * j + 1] *= g.y; v[4 * j + 2] *= g.z; v[4 * j + 3] *= g.w;
             }
         }
@@ -149,10 +150,10 @@ __device__ __forceinline__ float bl_norm_produce2(const bl_prod_dev& pd, int m, 
 #pragma unroll
             for (int e = 0; e < 16; ++e) v[e] = v[e] * rn;
             if (pd.gain) {
-                const float4* g4 = (const float4*)(pd.gain + (int64_t)u * 16);
+                const bl_v4f BL_G* g4 = bl_gc<bl_v4f>(pd.gain + (int64_t)u * 16);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const float4 g = g4[q];
+                    const bl_v4f g = g4[q];
                     v[4 * q] *= g.x; v[4 * q + 1] *= g.y; v[4 * q + 2] *= g.z; v[4 * q + 3] *= g.w;
                 }
             }

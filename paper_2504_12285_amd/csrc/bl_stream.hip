@@ -148,8 +148,8 @@ __global__ __launch_bounds__(256) void bl_stream_prep(const bl_stream_prep_item*
                 bl_quant8_words(xv[2 * j], inv, a0, a1);
                 bl_quant8_words(xv[2 * j + 1], inv, a2, a3);
                 part += bl_sum16(a0, a1, a2, a3);
-                if (it.q_out) *(uint4*)(it.q_out + u * 16) = make_uint4(a0, a1, a2, a3);
-                *(uint4*)(it.q_ws + u * 16) = make_uint4(a0, a1, a2, a3);
+                if (it.q_out) *(bl_v4i BL_G*)(it.q_out + u * 16) = bl_v4i{(int)a0, (int)a1, (int)a2, (int)a3};
+                *(bl_v4i BL_G*)(it.q_ws + u * 16) = bl_v4i{(int)a0, (int)a1, (int)a2, (int)a3};
             }
         }
         for (int u = tid + 512; u < groups; u += 256) {
@@ -159,8 +159,8 @@ __global__ __launch_bounds__(256) void bl_stream_prep(const bl_stream_prep_item*
             bl_quant8_words(lo, inv, a0, a1);
             bl_quant8_words(hi, inv, a2, a3);
             part += bl_sum16(a0, a1, a2, a3);
-            if (it.q_out) *(uint4*)(it.q_out + u * 16) = make_uint4(a0, a1, a2, a3);
-            *(uint4*)(it.q_ws + u * 16) = make_uint4(a0, a1, a2, a3);
+            if (it.q_out) *(bl_v4i BL_G*)(it.q_out + u * 16) = bl_v4i{(int)a0, (int)a1, (int)a2, (int)a3};
+            *(bl_v4i BL_G*)(it.q_ws + u * 16) = bl_v4i{(int)a0, (int)a1, (int)a2, (int)a3};
         }
         if (tid == 0) {
             const float sc = bl_div_rn(gg, 127.0f);
@@ -1019,7 +1019,7 @@ __global__ __launch_bounds__(256) void bl_mb_finish(const bl_mb_fin_item* __rest
     const int64_t total = (int64_t)F.M * F.N;
     const int64_t base = (int64_t)blockIdx.x * 1024 + threadIdx.x;
     if (base >= total) return;
-    const float bt = F.y ? *F.beta : 0.0f;
+    const float bt = F.y ? *bl_gc<float>(F.beta) : 0.0f;
     /* four elements per thread, every load of a step issued before the first use */
     int part[4], rs[4];
     float cf[4], res[4];
@@ -1028,21 +1028,21 @@ __global__ __launch_bounds__(256) void bl_mb_finish(const bl_mb_fin_item* __rest
         const int64_t e = base + j * 256;
         const bool ok = e < total;
         const int t = ok ? (int)(e / F.N) : 0;
-        part[j] = ok ? F.ws[e] : 0;
-        rs[j] = F.rowsum[t];
-        cf[j] = F.y ? F.scale[t] : 0.0f;
-        res[j] = (ok && F.residual) ? F.residual[e] : 0.0f;
+        part[j] = ok ? bl_g(F.ws)[e] : 0;
+        rs[j] = bl_gc<int32_t>(F.rowsum)[t];
+        cf[j] = F.y ? bl_gc<float>(F.scale)[t] : 0.0f;
+        res[j] = (ok && F.residual) ? bl_gc<float>(F.residual)[e] : 0.0f;
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int64_t e = base + j * 256;
         if (e < total) {
             const int val = part[j] - rs[j];
-            F.ws[e] = 0;
-            if (F.acc) F.acc[e] = val;
+            bl_g(F.ws)[e] = 0;
+            if (F.acc) bl_g(F.acc)[e] = val;
             if (F.y) {
                 const float o = (float)val * (bt * cf[j]);
-                F.y[e] = F.residual ? res[j] + o : o;
+                bl_g(F.y)[e] = F.residual ? res[j] + o : o;
             }
         }
     }
