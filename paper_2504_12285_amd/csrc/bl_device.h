@@ -146,6 +146,15 @@ __device__ __forceinline__ bl_v4i bl_unpack16(uint32_t p) {
     return b;
 }
 
+/* A packed word of layout 0 (weight i at bits 2i) in layout-1 order (at bits 8(i%4) + 2(i/4)): the
+ * transpose of a 4 x 4 matrix of bit pairs, two delta swaps of six cheap instructions each. */
+__device__ __forceinline__ uint32_t bl_word_to_k16(uint32_t p) {
+    uint32_t t = ((p >> 12) ^ p) & 0x0000F0F0u;
+    p = p ^ t ^ (t << 12);
+    t = ((p >> 6) ^ p) & 0x00CC00CCu;
+    return p ^ t ^ (t << 6);
+}
+
 /* Wait for in-flight matrix-core results before ordinary vector instructions
  * read an accumulator.  The hardware has no interlock for that read, and the
  * compiler's wait-state count for the gfx950 16x16x64 int8 MFMA proved too

@@ -11,194 +11,6 @@
 
 #include <atomic>
 
-#define GEMM_THREADS 256
-
-#define GEMM_PAD 16   /* bytes of padding per activation row in LDS (bank spread) */
-
-/* Block tile BM x BN, k step BK (64 or 128), four waves arranged WGM x WGN.
- * LDS is double buffered: while the matrix cores work on buffer b, the next
- * k step travels global -> registers -> buffer 1-b; one barrier per k step.
- *   A buffer: BM rows x (BK + pad) int8 activations.
- *   W buffer: BN rows x (BK/16 + 1) packed words (16 weights each).
- * Operand mapping of v_mfma_i32_32x32x32_i8: lane l supplies 16 consecutive k
- * (offset 16*(l/32)) of row l%32 for both operands; a packed word expands to
- * exactly those 16 int8 (layout 1), so one ds_read_b32 feeds one B operand. */
-template <int BM, int BN, int BK, int WGM, int LAYOUT>
-__global__ __launch_bounds__(GEMM_THREADS) void bl_gemm_mfma(const uint8_t* __restrict__ packed,
-                                                              const int8_t* __restrict__ q,
-                                                              const int32_t* __restrict__ rowsum,
-                                                              const float* __restrict__ beta,
-                                                              const float* __restrict__ scale, int M, int N, int K,
-                                                              const float* __restrict__ residual,
-                                                              int32_t* __restrict__ acc, float* __restrict__ y) {
-    constexpr int WGN = 4 / WGM;
-    constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NI = WN / 32;
-    constexpr int KS = BK / 32;                       /* MFMA k sub-steps per k step  */
-    constexpr int A_STRIDE = BK + GEMM_PAD;           /* bytes                        */
-    constexpr int W_WORDS = BK / 16;                  /* packed words per row, k step */
-    constexpr int W_STRIDE = W_WORDS + 1;             /* dwords                       */
-    constexpr int A_UPR = BK / 16;                    /* 16-byte units per A row      */
-    constexpr int A_UNITS = BM * A_UPR / GEMM_THREADS;
-    constexpr int W_UPR = BK / 64;                    /* 16-byte units per W row      */
-    constexpr int W_UNITS = (BN * W_UPR + GEMM_THREADS - 1) / GEMM_THREADS;
-    static_assert(BM * A_UPR % GEMM_THREADS == 0, "A tile must split evenly");
-    static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile must be a multiple of 32");
-
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    constexpr int A_BYTES = BM * A_STRIDE;
-    constexpr int W_BYTES = BN * W_STRIDE * 4;
-    auto As = [&](int b) { return smem + b * A_BYTES; };
-    auto Ws = [&](int b) { return (uint32_t*)(smem + 2 * A_BYTES + b * W_BYTES); };
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;
-    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-    const int l32 = lane & 31, h = lane >> 5;
-    const int kb = K / 4;
-
-    bl_v16i C[MI][NI];
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) C[mi][ni][v] = 0;
-
-    uint4 areg[A_UNITS];
-    uint4 wreg[W_UNITS];
-    const uint8_t* aptr[A_UNITS];
-    const uint8_t* wptr[W_UNITS];
-#pragma unroll
-    for (int i = 0; i < A_UNITS; ++i) {
-        const int u = tid + i * GEMM_THREADS, row = u / A_UPR, c = u % A_UPR;
-        int m = m0 + row;
-        if (m >= M) m = M - 1;
-        aptr[i] = (const uint8_t*)q + (int64_t)m * K + c * 16;
-    }
-#pragma unroll
-    for (int i = 0; i < W_UNITS; ++i) {
-        const int u = tid + i * GEMM_THREADS, row = u / W_UPR, c = u % W_UPR;
-        int n = n0 + row;
-        if (n >= N) n = N - 1;
-        wptr[i] = packed + (int64_t)n * kb + c * 16;
-    }
-
-    auto load_tiles = [&](int kk) {
-#pragma unroll
-        for (int i = 0; i < A_UNITS; ++i) areg[i] = *(const uint4*)(aptr[i] + (int64_t)kk * BK);
-#pragma unroll
-        for (int i = 0; i < W_UNITS; ++i)
-            if (tid + i * GEMM_THREADS < BN * W_UPR) wreg[i] = *(const uint4*)(wptr[i] + (int64_t)kk * (BK / 4));
-    };
-    auto store_tiles = [&](int b) {
-#pragma unroll
-        for (int i = 0; i < A_UNITS; ++i) {
-            const int u = tid + i * GEMM_THREADS, row = u / A_UPR, c = u % A_UPR;
-            uint32_t a0 = areg[i].x, a1 = areg[i].y, a2 = areg[i].z, a3 = areg[i].w;
-            if (LAYOUT == 0) bl_transpose4x4(a0, a1, a2, a3);
-            *(uint4*)(As(b) + row * A_STRIDE + c * 16) = make_uint4(a0, a1, a2, a3);
-        }
-#pragma unroll
-        for (int i = 0; i < W_UNITS; ++i) {
-            const int u = tid + i * GEMM_THREADS, row = u / W_UPR, c = u % W_UPR;
-            if (u < BN * W_UPR) {
-                uint32_t* d = Ws(b) + row * W_STRIDE + c * 4;
-                d[0] = wreg[i].x; d[1] = wreg[i].y; d[2] = wreg[i].z; d[3] = wreg[i].w;
-            }
-        }
-    };
-
-    const int steps = K / BK;
-    load_tiles(0);
-    store_tiles(0);
-    __syncthreads();
-    for (int kk = 0; kk < steps; ++kk) {
-        const int b = kk & 1;
-        if (kk + 1 < steps) load_tiles(kk + 1);
-        const uint8_t* Ab = As(b) + (wm0 + l32) * A_STRIDE + h * 16;
-        const uint32_t* Wb = Ws(b) + (wn0 + l32) * W_STRIDE + h;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            bl_v4i a[MI];
-#pragma unroll
-            for (int mi = 0; mi < MI; ++mi) a[mi] = *(const bl_v4i*)(Ab + mi * 32 * A_STRIDE + ks * 32);
-#pragma unroll
-            for (int ni = 0; ni < NI; ++ni) {
-                const uint32_t p = Wb[ni * 32 * W_STRIDE + ks * 2];
-                bl_v4i bop;
-                bop[0] = (int)(p & 0x03030303u);
-                bop[1] = (int)((p >> 2) & 0x03030303u);
-                bop[2] = (int)((p >> 4) & 0x03030303u);
-                bop[3] = (int)((p >> 6) & 0x03030303u);
-#pragma unroll
-                for (int mi = 0; mi < MI; ++mi)
-                    C[mi][ni] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[mi], bop, C[mi][ni], 0, 0, 0);
-            }
-        }
-        if (kk + 1 < steps) store_tiles(b ^ 1);
-        __syncthreads();
-    }
-
-    /* Epilogue: per-row terms through LDS once (see bl_gemm_tile256). */
-    bl_mfma_fence();
-    __syncthreads();
-    int* rs_s = (int*)smem;
-    float* cf_s = (float*)(smem + BM * 4);
-    for (int i = tid; i < BM; i += GEMM_THREADS) {
-        const int m = m0 + i;
-        rs_s[i] = m < M ? rowsum[m] : 0;
-        cf_s[i] = (y && m < M) ? *beta * scale[m] : 0.0f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int ml = wm0 + mi * 32 + (v >> 2) * 8 + h * 4 + (v & 3);
-            const int m = m0 + ml;
-            if (m < M) {
-                const int rs = rs_s[ml];
-                const float c = cf_s[ml];
-#pragma unroll
-                for (int ni = 0; ni < NI; ++ni) {
-                    const int n = n0 + wn0 + ni * 32 + l32;
-                    if (n < N) {
-                        const int val = C[mi][ni][v] - rs;
-                        if (acc) acc[(int64_t)m * N + n] = val;
-                        if (y) {
-                            const float t = (float)val * c;
-                            y[(int64_t)m * N + n] = residual ? residual[(int64_t)m * N + n] + t : t;
-                        }
-                    }
-                }
-            }
-        }
-}
-
-template <int BM, int BN, int BK, int WGM>
-static bl_status launch_gemm(const uint8_t* packed, const float* beta, int layout, const int8_t* q,
-                             const float* scale, const int32_t* rowsum, int M, int N, int K,
-                             const float* residual, int32_t* acc, float* y, hipStream_t st) {
-    constexpr size_t lds = 2 * (size_t)(BM * (BK + GEMM_PAD) + BN * (BK / 16 + 1) * 4);
-    dim3 grid((unsigned)((N + BN - 1) / BN), (unsigned)((M + BM - 1) / BM));
-    auto k0 = bl_gemm_mfma<BM, BN, BK, WGM, 0>;
-    auto k1 = bl_gemm_mfma<BM, BN, BK, WGM, 1>;
-    auto kern = layout == 0 ? k0 : k1;
-    if (lds > 64 * 1024) {
-        /* (two threads may both set the attribute: the call is idempotent) */
-        static std::atomic<bool> set[2];
-        std::atomic<bool>& done = set[layout == 0 ? 0 : 1];
-        if (!done.load(std::memory_order_acquire)) {
-            if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
-                hipSuccess)
-                return BL_ERR_HIP;
-            done.store(true, std::memory_order_release);
-        }
-    }
-    kern<<<grid, GEMM_THREADS, lds, st>>>(packed, q, rowsum, beta, scale, M, N, K, residual, acc, y);
-    return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
-}
-
 /* ---- large-tile pipelined kernel -------------------------------------------
  * 256 x 256 output tile per workgroup, k step 128, three LDS stages filled by
  * direct global->LDS loads (no register staging) two k steps ahead of the
@@ -245,7 +57,12 @@ static bl_status launch_gemm(const uint8_t* packed, const float* beta, int layou
  * the following step leaves exactly those stores in flight.  Interior tiles
  * with a following tile only; edge tiles and a workgroup's last tile store at once.  fp32 output
  * alone (no int32 output, no residual). */
-template <int BM, int BN, int STAGES, int WM, int WN, int EPI, bool TABLE = false, bool DEFER = false>
+/* HALF: K is an odd multiple of 64, so the last k step has only its first 64 columns: lane half 1 (the
+ * second unit of a weight row) multiplies nothing there, its weights are set to zero and its loads go to
+ * the step's first half (inside the row): 777 x 2999 -> 5003 with its quantiser 28.8 us against 38.4 on a
+ * register-staged kernel of 128 x 128 tiles, one workgroup per compute unit.  LAYOUT 0: a packed word is turned into layout-1 order in the
+ * register before it is opened (bl_word_to_k16): 1000 x 2560 -> 3840 24.0 us against 29.2. */
+template <int BM, int BN, int STAGES, int WM, int WN, int EPI, bool TABLE = false, bool DEFER = false, bool HALF = false, int LAYOUT = 1>
 __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : BM * BN >= 128 * 128 ? 3 : 4)) void bl_gemm_tile256(const uint8_t* __restrict__ packed,
                                                                 const int8_t* __restrict__ q,
                                                                 const int32_t* __restrict__ rowsum,
@@ -261,6 +78,7 @@ __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : 
                                                                 const int* __restrict__ wg_start,
                                                                 const int* __restrict__ tile_list) {
     static_assert(!TABLE || EPI == 0, "the table walk has the plain epilogue only");
+    static_assert(!(HALF || LAYOUT == 0) || (EPI == 0 && !TABLE), "ragged K and layout 0: plain products");
     static_assert(!DEFER || (EPI == 0 && !TABLE && STAGES == 2), "deferred stores: plain epilogue, two stages");
     static_assert(EPI != 2 || (BN == 128 && WN == 2 && BN / WN / 32 == 2), "the gate epilogue pairs ni = 0 with ni = 1");
     constexpr int NW = WM * WN, THREADS = NW * 64;
@@ -283,7 +101,7 @@ __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : 
     const int wm0 = (wave / WN) * (MI * 32), wn0 = (wave % WN) * (NI * 32);
     /* fixed for the launch, or (TABLE) those of the product whose tile is set up next */
     int kb = K / 4;
-    int steps = K / G3_BK;
+    int steps = HALF ? (K + G3_BK - 1) / G3_BK : K / G3_BK;
     bool want_cf = EPI != 0 || y != nullptr;            /* the fused epilogues always rescale */
     float bt = (!TABLE && want_cf) ? *beta : 0.0f;
     /* what the epilogue of the tile in flight stores to (TABLE: set when that tile was set up) */
@@ -385,13 +203,19 @@ __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : 
     };
     auto issue = [&](int kk, int buf) {
         uint8_t* st = smem + buf * G3_STAGE_BYTES;
+        /* HALF, last step: units of the second half are fetched from the first (bit 2 of a lane's unit
+         * is that of lane ^ wave: the swizzle's row bits above it are the piece's number) */
+        static_assert(NW % 2 == 0, "the parity of a piece is that of its wave");
+        const bool last = HALF && kk == steps - 1;
+        const int aback = last ? (((lane >> 2) ^ wave) & 1) * 64 : 0;
+        const int wback = last ? ((lane ^ (lane >> 4)) & 1) * 16 : 0;
 #pragma unroll
         for (int j = 0; j < A_LOADS; ++j)
-            __builtin_amdgcn_global_load_lds((bl_gptr)(asrc[j] + (int64_t)kk * G3_BK),
+            __builtin_amdgcn_global_load_lds((bl_gptr)(asrc[j] + ((int64_t)kk * G3_BK - aback)),
                                              (bl_lptr)(st + (j * NW + wave) * 1024), 16, 0, 0);
 #pragma unroll
         for (int j = 0; j < W_LOADS; ++j)
-            __builtin_amdgcn_global_load_lds((bl_gptr)(wsrc[j] + (int64_t)kk * (G3_BK / 4)),
+            __builtin_amdgcn_global_load_lds((bl_gptr)(wsrc[j] + ((int64_t)kk * (G3_BK / 4) - wback)),
                                              (bl_lptr)(st + G3_A_BYTES + (j * NW + wave) * 1024), 16, 0, 0);
     };
 
@@ -503,6 +327,10 @@ __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : 
             bl_v4i wq[NI], a[2][MI];
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni) wq[ni] = *(const bl_v4i*)(st + w_off + ni * 32 * 32);
+            if (HALF && kk == steps - 1 && h == 1) {
+#pragma unroll
+                for (int ni = 0; ni < NI; ++ni) wq[ni] = bl_v4i{0, 0, 0, 0};
+            }
 #pragma unroll
             for (int mi = 0; mi < MI; ++mi)
                 a[0][mi] = *(const bl_v4i*)(st + a_row_off + mi * 32 * G3_BK + (((4 * h) ^ a_swz) * 16));
@@ -516,7 +344,7 @@ __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : 
                 }
 #pragma unroll
                 for (int ni = 0; ni < NI; ++ni) {
-                    const bl_v4i bop = bl_unpack16((uint32_t)wq[ni][ks]);
+                    const bl_v4i bop = bl_unpack16(LAYOUT == 0 ? bl_word_to_k16((uint32_t)wq[ni][ks]) : (uint32_t)wq[ni][ks]);
 #pragma unroll
                     for (int mi = 0; mi < MI; ++mi)
                         C[mi][ni] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[ks & 1][mi], bop, C[mi][ni], 0, 0, 0);
@@ -732,13 +560,13 @@ struct bl_epi_args {
     int* absmax;
 };
 
-template <int BM, int BN, int STAGES, int WM, int WN, int EPI = 0, bool DEFER = false>
+template <int BM, int BN, int STAGES, int WM, int WN, int EPI = 0, bool DEFER = false, bool HALF = false, int LAYOUT = 1>
 static bl_status launch_tile256_t(const uint8_t* packed, const float* beta, const int8_t* q, const float* scale,
                                   const int32_t* rowsum, int M, int N, int K, const float* residual,
                                   int32_t* acc, float* y, hipStream_t st, bl_epi_args ep = bl_epi_args{nullptr, nullptr}) {
     constexpr int G3_BM = BM;
     constexpr int lds = STAGES * (BM * G3_BK + BN * G3_BK / 4) + BM * 8 * (DEFER ? 2 : 1);
-    auto kern = bl_gemm_tile256<BM, BN, STAGES, WM, WN, EPI, false, DEFER>;
+    auto kern = bl_gemm_tile256<BM, BN, STAGES, WM, WN, EPI, false, DEFER, HALF, LAYOUT>;
     static std::atomic<bool> attr_set;
     if (!attr_set.load(std::memory_order_acquire)) {
         if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
@@ -828,6 +656,29 @@ __global__ __launch_bounds__(256) void bl_rowsum_kernel(const int8_t* __restrict
     if (lane == 0) rowsum[m] = s;
 }
 
+/* Tile choice of a plain product.  Measured on MI355X at M = 2048 on the four 2B-layer shapes: 128x128
+ * tiles, k step 128, two LDS stages filled by direct global->LDS loads, XCD-aware tile order, three
+ * workgroups per CU: about 1450 TOPS over the layer against 1310 for a register-staged 128x128 kernel.
+ * Also measured and dropped (no longer in the library): 256x256 tiles with 2x2 / 2x4 / 4x2 waves and
+ * 256x128 (0.9 - 1.1 POP/s), a three-stage 128x128 and 4- or 6-stage pipelines (what hides the load
+ * latency is the number of workgroups per CU, not the depth), 64x256 (equal within noise).  When the
+ * problem has at most ~1.5 tiles of 128x128 per CU, 64x128 tiles balance better: +17..21 % on the
+ * N = 2560 shapes at M = 2048, +22..27 % on every small shape at M = 1024, equal at 480 tiles and slower
+ * on the wide shape.
+ * fp32 output alone: the stores of a tile travel during the workgroup's next tile (measured at M = 2048 /
+ * 8192: the 13824-wide shape 77 - 80 us against 86 - 90, 297 - 308 against 317 - 327; the 64 x 128 kernel
+ * with deferred stores loses: it has under one tile per workgroup on the shapes it serves). */
+template <bool HALF, int LAYOUT>
+static bl_status launch_plain(const uint8_t* packed, const float* beta, const int8_t* q, const float* scale,
+                              const int32_t* rowsum, int m, int n, int k, const float* residual, int32_t* acc, float* y,
+                              hipStream_t st) {
+    if ((int64_t)((m + 127) / 128) * ((n + 127) / 128) <= 400)
+        return launch_tile256_t<64, 128, 2, 1, 4, 0, false, HALF, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
+    if (!acc && !residual && (int64_t)m * n < ((int64_t)1 << 30))
+        return launch_tile256_t<128, 128, 2, 2, 2, 0, true, HALF, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
+    return launch_tile256_t<128, 128, 2, 2, 2, 0, false, HALF, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
+}
+
 /* Arguments already validated by the public entry points. */
 bl_status bl_gemm_dispatch(const uint8_t* packed, const float* beta, int layout, const int8_t* q,
                            const float* scale, const int32_t* rowsum, int64_t M, int64_t N, int64_t K,
@@ -839,32 +690,12 @@ bl_status bl_gemm_dispatch(const uint8_t* packed, const float* beta, int layout,
         bl_rowsum_kernel<<<(unsigned)((M + 3) / 4), 256, 0, st>>>(q, (int)M, (int)K, rs);
         rowsum = rs;
     }
-    /* Tile choice.  Measured on MI355X at M = 2048 on the four 2B-layer shapes: 128x128 tiles,
-     * k step 128, two LDS stages filled by direct global->LDS loads, XCD-aware tile order, three
-     * workgroups per CU: about 1450 TOPS over the layer against 1310 for the register-staged
-     * 128x128 kernel.  Also measured and dropped (no longer in the library): 256x256 tiles with
-     * 2x2 / 2x4 / 4x2 waves and 256x128 (0.9 - 1.1 POP/s), a three-stage 128x128 and 4- or 6-stage
-     * pipelines (what hides the load latency is the number of workgroups per CU, not the depth),
-     * 64x256 (equal within noise).  When the problem has at most ~1.5 tiles of 128x128 per CU,
-     * 64x128 tiles balance better: +17..21 % on the N = 2560 shapes at M = 2048, +22..27 % on every
-     * small shape at M = 1024, equal at 480 tiles and slower on the wide shape.  Both need layout 1
-     * and K % 128 == 0; other inputs use the register-staged kernel, which permutes the activation
-     * bytes for layout 0. */
-    const int m = (int)M, n = (int)N, k = (int)K;
-    if (layout == 1 && k % G3_BK == 0) {
-        if ((int64_t)((m + 127) / 128) * ((n + 127) / 128) <= 400)
-            return launch_tile256_t<64, 128, 2, 1, 4>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
-        /* fp32 output alone: the stores of a tile travel during the workgroup's next tile (measured at
-         * M = 2048 / 8192: the 13824-wide shape 77 - 80 us against 86 - 90, 297 - 308 against 317 - 327;
-         * the 64 x 128 kernel with deferred stores loses: it has under one tile per workgroup on the
-         * shapes it serves) */
-        if (!acc && !residual && (int64_t)m * n < ((int64_t)1 << 30))
-            return launch_tile256_t<128, 128, 2, 2, 2, 0, true>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
-        return launch_tile256_t<128, 128, 2, 2, 2>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
-    }
-    if (k % 128 == 0)
-        return launch_gemm<128, 128, 128, 2>(packed, beta, layout, q, scale, rowsum, m, n, k, residual, acc, y, st);
-    return launch_gemm<128, 128, 64, 2>(packed, beta, layout, q, scale, rowsum, m, n, k, residual, acc, y, st);
+    const int m = (int)M, n = (int)N, k = (int)K;              /* k: a multiple of 64 */
+    if (layout == 1 && k % G3_BK == 0)
+        return launch_plain<false, 1>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
+    if (layout == 1) return launch_plain<true, 1>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
+    if (k % G3_BK == 0) return launch_plain<false, 0>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
+    return launch_plain<true, 0>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
 }
 
 extern "C" bl_status bl_gemm_w158a8_res(const uint8_t* packed, const float* beta, int layout, const int8_t* q,
