@@ -361,13 +361,14 @@ __device__ __forceinline__ void bl_stream_slice(const bl_stream_item& P, const i
 
 /* ---- five weights per byte (BL_LAYOUT_TRIT5) ---------------------------------------------------
  * A byte b = ceil(v * 256 / 243) holds v = sum_i c_i * 3^(4-i), five offset codes c_i in {0,1,2}.
- * Multiplying by 3 moves the leading base-3 digit into bits 8..9 and leaves the rest of the
- * number in the low byte: five multiply-and-mask steps give the five digits, no table and no
- * division.  The four bytes of a word are handled as two pairs in 16-bit lanes (a byte times 3
- * fits 10 bits), and a byte permute gathers the four digits of step i into one register whose
- * bytes pair with k = 20*word + 4*i + 0..3: an operand of v_dot4_i32_i8 against the activations
- * in their natural order.  Per 16-byte load: 80 weights, 20 dot products, ~100 more vector
- * instructions: three times the work per weight of the 2-bit form. */
+ * Multiplying by 9 moves the two leading base-3 digits, as one number 0..8, into bits 8..11 and leaves
+ * the rest in the low byte.  The four bytes of a word are handled as two pairs in 16-bit lanes (a byte
+ * times 9 fits 12 bits); a byte permute gathers the four numbers, and two more use them as selectors into
+ * eight-byte tables: the first and the second digit of four weights each, an operand of v_dot4_i32_i8
+ * against k = 20*word + 4*i + 0..3.  A selector of 8 replicates the sign of table byte 1, so the tables
+ * hold c - 3 (entry 8 is then -1 and byte 1 negative, as it has to be); sum_k (c - 3) q = sum_k c q - 3 sum_k q.
+ * Per 16-byte load: 80 weights, 20 dot products and ~80 more instructions (digit by digit: ~100, of
+ * which the three-operand ones take twice the time of the plain ones). */
 #define BL_T5_QSTRIDE 24      /* dwords per 80-weight chunk in LDS: 20 + 4 of padding */
 
 __device__ __forceinline__ int bl_t5_dot(const bl_v4i p, const bl_v4i* a, int A) {
@@ -375,17 +376,20 @@ __device__ __forceinline__ int bl_t5_dot(const bl_v4i p, const bl_v4i* a, int A)
     for (int d = 0; d < 4; ++d) {
         const uint32_t w = (uint32_t)p[d];
         uint32_t e = w & 0x00FF00FFu, o = (w >> 8) & 0x00FF00FFu;
+        auto dot = [&](uint32_t dg, int i) { A = __builtin_amdgcn_sdot4((int)dg, a[(5 * d + i) >> 2][(5 * d + i) & 3], A, false); };
 #pragma unroll
-        for (int i = 0; i < 5; ++i) {
-            e = (e << 1) + e;
-            o = (o << 1) + o;
-            const uint32_t dg = __builtin_amdgcn_perm(o, e, 0x07030501u);   /* bits 8..15 of the four lanes */
-            A = __builtin_amdgcn_sdot4((int)dg, a[(5 * d + i) >> 2][(5 * d + i) & 3], A, false);
-            if (i < 4) {
-                e &= 0x00FF00FFu;
-                o &= 0x00FF00FFu;
-            }
+        for (int i = 0; i < 4; i += 2) {
+            e = (e << 3) + e;
+            o = (o << 3) + o;
+            const uint32_t t = __builtin_amdgcn_perm(o, e, 0x07030501u);    /* bits 8..15 of the four lanes */
+            dot(__builtin_amdgcn_perm(0xFFFFFEFEu, 0xFEFDFDFDu, t), i);     /* t / 3 - 3 */
+            dot(__builtin_amdgcn_perm(0xFEFDFFFEu, 0xFDFFFEFDu, t), i + 1); /* t % 3 - 3 */
+            e &= 0x00FF00FFu;
+            o &= 0x00FF00FFu;
         }
+        e = (e << 1) + e;
+        o = (o << 1) + o;
+        dot(__builtin_amdgcn_perm(o, e, 0x07030501u) + 0xFDFDFDFDu, 4);
     }
     return A;
 }
@@ -503,7 +507,7 @@ __device__ __forceinline__ void bl_stream_slice_t5(const bl_stream_item& P, cons
         const int rg = ub + unit;
         const int n = rg * R + r;
         if (g == 0 && n < N) {
-            const int val = v - rs;
+            const int val = v + 2 * rs;                  /* sum (c - 3) q + 3 sum q - sum q */
             if (acc_g) acc_g[n] = val;
             if (y_g) {
                 const float t = (float)val * cf;
