@@ -129,9 +129,32 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
-def _stream():
-    import torch
-    return torch.cuda.current_stream().cuda_stream
+_torch = None
+
+
+def _get_torch():
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    return _torch
+
+
+def _first_stream():
+    """Resolves how the current stream is read (once), and reads it.  The two raw getters are what
+    torch.cuda.current_stream() ends in; the Stream object around them costs 2.8 us a call against 0.2."""
+    global _stream
+    torch = _get_torch()
+    handle = torch.cuda.current_stream().cuda_stream        # initialises the device, raises without one
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is None or device is None:
+        _stream = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
+    else:
+        _stream = lambda: raw(device())  # noqa: E731
+    return handle
+
+
+_stream = _first_stream
 
 
 def bl_version():
@@ -143,7 +166,8 @@ def bl_packed_bytes(N, K, layout=BL_LAYOUT_K16):
 
 
 def bl_padded_k(K):
-    return load().bl_padded_k(K)
+    """Mirror of bl_padded_k: the same arithmetic without a foreign call (it sits in front of every launch)."""
+    return (K + 63) // 64 * 64 if 1 <= K <= 1 << 24 else 0
 
 
 def bl_workspace_bytes(op, M, N, K):
@@ -151,14 +175,14 @@ def bl_workspace_bytes(op, M, N, K):
 
 
 def _workspace(nbytes, device):
-    import torch
+    torch = _get_torch()
     return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
 
 
 def bl_pack_ternary(W, layout=BL_LAYOUT_K16, beta=None):
     """W: cuda fp32 [N][K] latent weights, or cuda int8 ternary with `beta` given.
     Returns (packed uint8 [N*K/4], beta fp32 [1])."""
-    import torch
+    torch = _get_torch()
     N, K = W.shape
     assert W.is_cuda and W.is_contiguous()
     nbytes = bl_packed_bytes(N, K, layout)
@@ -182,7 +206,7 @@ def bl_pack_ternary(W, layout=BL_LAYOUT_K16, beta=None):
 
 def bl_unpack_ternary(packed, N, K, layout=BL_LAYOUT_K16):
     """Returns (Wt int8 [N][K], bad int32 [1])."""
-    import torch
+    torch = _get_torch()
     Wt = torch.empty((N, K), dtype=torch.int8, device=packed.device)
     bad = torch.empty(1, dtype=torch.int32, device=packed.device)
     _check(load().bl_unpack_ternary(_ptr(packed), N, K, layout, _ptr(Wt), _ptr(bad), _stream()),
@@ -193,7 +217,7 @@ def bl_unpack_ternary(packed, N, K, layout=BL_LAYOUT_K16):
 def bl_quant_act_int8(X, want_rowsum=True):
     """X: cuda bfloat16 [M][K].  Returns (q int8 [M][Kp] with Kp = bl_padded_k(K) and zeros in the padding,
     scale fp32 [M], rowsum int32 [M] or None)."""
-    import torch
+    torch = _get_torch()
     assert X.is_cuda and X.is_contiguous() and X.dtype == torch.bfloat16
     M, K = X.shape
     q = torch.empty((M, bl_padded_k(K)), dtype=torch.int8, device=X.device)
@@ -205,7 +229,7 @@ def bl_quant_act_int8(X, want_rowsum=True):
 
 
 def _matmul(fn_name, op, packed, beta, layout, q, scale, rowsum, N, want_acc, want_y, acc, y, workspace, K=None):
-    import torch
+    torch = _get_torch()
     M = q.shape[0]
     K = q.shape[1] if K is None else K          # q is [M][Kp]: pass the true K of a ragged matrix explicitly
     assert q.shape[1] == bl_padded_k(K)
@@ -238,7 +262,7 @@ def bl_gemm_w158a8(packed, beta, layout, q, scale, rowsum, N, want_acc=True, wan
 
 def bl_bitlinear_decode(packed, beta, layout, X, N, want_acc=False, want_y=True, want_q=False, acc=None, y=None):
     """Fused decode BitLinear, M <= 4: bf16 X [M][K] -> (acc, y, q, scale)."""
-    import torch
+    torch = _get_torch()
     assert X.is_cuda and X.is_contiguous() and X.dtype == torch.bfloat16
     M, K = X.shape
     if want_acc and acc is None:
@@ -275,7 +299,7 @@ def bl_bitlinear_decode_group(descs, layout, M):
 def bl_quant_act_ex(prod, M, K, device, want_rowsum=True, q=None, scale=None, rowsum=None):
     """Producer + quantiser (prefill side).  prod: Producer from make_producer.
     Returns (q int8 [M][K], scale fp32 [M], rowsum int32 [M] or None)."""
-    import torch
+    torch = _get_torch()
     if q is None:
         q = torch.empty((M, K), dtype=torch.int8, device=device)
     if scale is None:
@@ -290,7 +314,7 @@ def bl_quant_act_ex(prod, M, K, device, want_rowsum=True, q=None, scale=None, ro
 def bl_gemm_w158a8_res(packed, beta, layout, q, scale, rowsum, N, residual, want_acc=False, want_y=True,
                        acc=None, y=None, workspace=None):
     """Prefill product with a residual added in the epilogue.  Returns (acc, y)."""
-    import torch
+    torch = _get_torch()
     M, K = q.shape
     if want_acc and acc is None:
         acc = torch.empty((M, N), dtype=torch.int32, device=q.device)
@@ -318,7 +342,7 @@ class Stack:
     bl_stack_run per step.  Holds the device table and keeps the descriptors' tensors alive."""
 
     def __init__(self, items, layout, M, device):
-        import torch
+        torch = _get_torch()
         self.items = items                      # keeps every tensor of the table alive
         self.descs = make_decode_descs(items)
         nbytes = load().bl_stack_table_bytes(self.descs, len(items)) if M == 1 else \
@@ -347,7 +371,7 @@ def bl_gemm_w158a8_fused(packed, beta, layout, q, scale, rowsum, N, kind, x_bf16
 
 def bl_quant_from_absmax(X, absmax, q=None, scale=None, rowsum=None):
     """One-pass quantiser of bf16 rows X [M][K] with known row maxima (cleared by the call)."""
-    import torch
+    torch = _get_torch()
     M, K = X.shape
     if q is None:
         q = torch.empty((M, K), dtype=torch.int8, device=X.device)
