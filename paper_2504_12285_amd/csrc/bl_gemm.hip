@@ -32,9 +32,7 @@
  * therefore needs exactly unit h of a weight row: one ds_read_b128 per 32 rows
  * and k step, and one per (32 rows, sub-step) for the activations.
  *
- * Workgroups are numbered so that the 32 that share an XCD (and its L2) at a
- * time form an 8 x 4 patch of tiles: 8 activation row tiles x 4 weight tiles.
- * Requires layout 1, K % 128 == 0. */
+ * K a multiple of 64 (HALF: an odd one); layout 1, or 0 through bl_word_to_k16. */
 #define G3_BK 128
 
 
@@ -68,7 +66,7 @@ __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : 
                                                                 const int32_t* __restrict__ rowsum,
                                                                 const float* __restrict__ beta,
                                                                 const float* __restrict__ scale, int M, int N,
-                                                                int K, int tiles_m, int tiles_n, int gm,
+                                                                int K, int tiles_m, int tiles_n, int band,
                                                                 int vgrid, const float* __restrict__ residual,
                                                                 int32_t* __restrict__ acc, float* __restrict__ y,
                                                                 uint16_t* __restrict__ xb, int* __restrict__ absmax,
@@ -139,19 +137,22 @@ __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : 
         bt = want_cf ? *bl_gc<float>(it.beta) : 0.0f;
     };
 
-    /* XCD-aware tile order: workgroup L runs on XCD L%8.  The tile grid is cut
-     * into gm x gn = 8 rectangular regions, one per XCD, narrow enough in M that
-     * a region's activation panel stays in that XCD's 4 MB L2 while its weight
-     * tiles stream through; inside a region the row tiles vary fastest.  The grid is
-     * persistent: a workgroup takes virtual blocks vb = blockIdx.x, + gridDim.x, .. (gridDim.x
-     * is a multiple of 8, so a workgroup stays on its XCD's region). */
-    const int gn = 8 / gm;
-    const int rm = (tiles_m + gm - 1) / gm, rn = (tiles_n + gn - 1) / gn;
+    /* XCD-aware tile order: workgroup L runs on XCD L%8.  The row tiles are cut into bands so narrow that
+     * a band's activation panel stays in an XCD's 4 MB L2 while its weight tiles stream through; the tiles
+     * are numbered band by band, row tiles fastest, and each XCD takes one eighth of the sequence, so that
+     * the XCDs are even whatever the tile counts (a rectangular region each leaves a quarter of them idle
+     * at 17 row tiles: 2140 x 3840 -> 13458 148 us, here 122; 1100 x 2560 -> 7000 36 against 27.5).  The grid is persistent: a workgroup takes
+     * virtual blocks vb = blockIdx.x, + gridDim.x, .. (gridDim.x is a multiple of 8, so it stays on its
+     * XCD's share). */
+    const int tiles = tiles_m * tiles_n, share = (tiles + 7) >> 3, band_tiles = band * tiles_n;
     auto tile_of = [&](int vb, int& tm, int& tn) {
-        const int xcd = vb & 7, idx = vb >> 3;
-        tm = (xcd / gn) * rm + idx % rm;
-        tn = (xcd % gn) * rn + idx / rm;
-        return tm < tiles_m && tn < tiles_n;
+        const int idx = vb >> 3, at = (vb & 7) * share + idx;
+        if (idx >= share || at >= tiles) return false;
+        const int b = at / band_tiles, in = at - b * band_tiles;
+        const int rows = min(band, tiles_m - b * band);
+        tn = in / rows;
+        tm = b * band + (in - tn * rows);
+        return true;
     };
     int vend = vgrid;
     if constexpr (TABLE) vend = wg_start[blockIdx.x + 1];
@@ -586,13 +587,13 @@ static bl_status launch_tile256_t(const uint8_t* packed, const float* beta, cons
     }
     /* the gate epilogue's tile holds 64 gate rows and the 64 matching up rows: N/2 / 64 column tiles */
     const int tiles_m = (M + G3_BM - 1) / G3_BM, tiles_n = EPI == 2 ? (N / 2 + BN / 2 - 1) / (BN / 2) : (N + BN - 1) / BN;
-    /* rows of activations per XCD region: at most ~1.5 MB of int8 (measured, medians of six
-     * interleaved rounds at M = 2048: +7 % on the 13824-wide shape against whole-M regions,
-     * equal on the others) */
-    int gm = 1;
-    while (gm < 8 && (int64_t)((tiles_m + gm - 1) / gm) * BM * K > (3 << 19)) gm *= 2;
-    const int gn = 8 / gm;
-    const int vgrid = 8 * ((tiles_m + gm - 1) / gm) * ((tiles_n + gn - 1) / gn);
+    /* rows of activations per band: at most ~1.5 MB of int8 (measured, medians of six interleaved rounds at
+     * M = 2048: +7 % on the 13824-wide shape against bands of all rows, equal on the others) */
+    int64_t most = (3 << 19) / ((int64_t)BM * K);
+    if (most < 1) most = 1;
+    const int bands = (int)((tiles_m + most - 1) / most), band = (tiles_m + bands - 1) / bands;
+    if ((int64_t)tiles_m * tiles_n > ((int64_t)1 << 30)) return BL_ERR_SHAPE;   /* (outputs beyond 2^43 values) */
+    const int vgrid = 8 * ((tiles_m * tiles_n + 7) / 8);
     /* persistent grid: what is resident at once (a multiple of 8 keeps a workgroup on its XCD's region) */
     static std::atomic<int> resident{0};
     int blocks = resident.load(std::memory_order_acquire);
@@ -608,7 +609,7 @@ static bl_status launch_tile256_t(const uint8_t* packed, const float* beta, cons
         resident.store(blocks, std::memory_order_release);
     }
     if (blocks > vgrid) blocks = vgrid;
-    kern<<<blocks, WM * WN * 64, lds, st>>>(packed, q, rowsum, beta, scale, M, N, K, tiles_m, tiles_n, gm, vgrid,
+    kern<<<blocks, WM * WN * 64, lds, st>>>(packed, q, rowsum, beta, scale, M, N, K, tiles_m, tiles_n, band, vgrid,
                                             residual, acc, y, ep.xb, ep.absmax, (long long*)bl_clock_stamps(), nullptr, nullptr, 0, nullptr, nullptr);
     return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
 }
