@@ -649,6 +649,154 @@ bl_status bl_gemm_table_launch(const bl_tile_item* items, const int* tile0, int 
     return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
 }
 
+/* ---- few tiles: the k loop split over the waves of a workgroup -------------------------------
+ * With few tokens (65 .. a few hundred) a product has fewer 64 x 128 tiles than the chip has compute
+ * units, and its time is one tile's serial chain of k steps (about 720 clocks each, of which the matrix
+ * cores work 256).  Here a workgroup owns a 64 x 32 tile and each of its four waves takes every fourth
+ * k step of it alone: four times the workgroups, a quarter of the chain, and no barrier inside the loop (a
+ * wave's stages in LDS are its own; it waits for its own loads).  The four partial tiles meet in LDS and
+ * each wave finishes a quarter of the rows.  The weights cost the same bytes as before, the activations
+ * are fetched by four times as many workgroups, from the L2.
+ * Same LDS layout, swizzles, half last step and layout-0 words as bl_gemm_tile256 (one wave: pieces of
+ * eight activation rows and one of 32 weight rows).
+ * Used up to KS_MAX_TILES tiles of 64 x 128; measured (us, 64 x 128 tiles / this kernel): 40 tiles
+ * 128 x 6912 -> 2560 22.2 / 10.7, 80 tiles 256 x 2560 -> 2560 12.4 / 7.9, 128 tiles 1000 x 4096 -> 1000
+ * 16.3 / 11.6, 140 tiles 400 x 6912 -> 2560 27.8 / 21.2, 160 tiles 512 x 2560 -> 2560 12.3 / 11.8, 216 tiles
+ * 128 x 2560 -> 13824 12.9 / 14.3, 240 tiles 512 x 2560 -> 3840 12.7 / 13.9: there the tiles fill the chip. */
+#define KS_MAX_TILES 160
+#define KS_STAGE (64 * G3_BK + 32 * G3_BK / 4)
+
+template <int LAYOUT>
+__global__ __launch_bounds__(256, 2) void bl_gemm_ksplit(const uint8_t* __restrict__ packed, const int8_t* __restrict__ q,
+                                                         const int32_t* __restrict__ rowsum, const float* __restrict__ beta,
+                                                         const float* __restrict__ scale, int M, int N, int K, int tiles_m,
+                                                         int tiles, const float* __restrict__ residual,
+                                                         int32_t* __restrict__ acc, float* __restrict__ y) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];      /* [wave][stage] */
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int l32 = lane & 31, h = lane >> 5;
+    /* workgroup L runs on XCD L % 8: each XCD takes one eighth of the tiles, row tiles fastest */
+    const int share = (tiles + 7) >> 3, at = ((int)blockIdx.x & 7) * share + ((int)blockIdx.x >> 3);
+    if (((int)blockIdx.x >> 3) >= share || at >= tiles) return;         /* the whole workgroup */
+    const int tn = at / tiles_m, tm = at - tn * tiles_m, m0 = tm * 64, n0 = tn * 32;
+    const int steps = (K + G3_BK - 1) / G3_BK;
+    const bool half = (K & 64) != 0;
+
+    /* what the rows this wave finishes need: rows (w >> 1) * 32 + (v >> 2) * 8 + h * 4 + (v & 3), v = 8 (w & 1) .. + 7 */
+    int rs[8];
+    float sc[8], rr[8];
+    const int n = n0 + l32;
+    const float bt = y ? *beta : 0.0f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int v = (w & 1) * 8 + i;
+        int m = m0 + (w >> 1) * 32 + (v >> 2) * 8 + h * 4 + (v & 3);
+        m = m < M ? m : M - 1;
+        rs[i] = rowsum[m];
+        sc[i] = y ? scale[m] : 0.0f;
+        rr[i] = y && residual ? residual[(int64_t)m * N + (n < N ? n : N - 1)] : 0.0f;
+    }
+
+    const uint8_t* asrc[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int row = j * 8 + (lane >> 3), u = (lane & 7) ^ ((row >> 1) & 7);
+        const int m = m0 + row < M ? m0 + row : M - 1;
+        asrc[j] = (const uint8_t*)q + (int64_t)m * K + u * 16;
+    }
+    const int wrow = n0 + (lane >> 1) < N ? n0 + (lane >> 1) : N - 1, wu = (lane & 1) ^ ((lane >> 4) & 1);
+    const uint8_t* const wsrc = packed + (int64_t)wrow * (K / 4) + wu * 16;
+    uint8_t* const base = smem + w * 2 * KS_STAGE;
+    auto issue = [&](int kk, int buf) {
+        uint8_t* st = base + buf * KS_STAGE;
+        const bool last = half && kk == steps - 1;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int back = last ? (((lane >> 2) ^ j) & 1) * 64 : 0;   /* units of the second half: from the first */
+            __builtin_amdgcn_global_load_lds((bl_gptr)(asrc[j] + ((int64_t)kk * G3_BK - back)), (bl_lptr)(st + j * 1024), 16, 0, 0);
+        }
+        __builtin_amdgcn_global_load_lds((bl_gptr)(wsrc + ((int64_t)kk * (G3_BK / 4) - (last ? wu * 16 : 0))),
+                                         (bl_lptr)(st + 64 * G3_BK), 16, 0, 0);
+    };
+    const int a_off = l32 * G3_BK, a_swz = (l32 >> 1) & 7;
+    const int w_off = 64 * G3_BK + (l32 * 2 + (h ^ ((l32 >> 3) & 1))) * 16;
+
+    bl_v16i C[2];
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) C[mi][v] = 0;
+    int buf = 0;
+    if (w < steps) issue(w, 0);
+    for (int kk = w; kk < steps; kk += 4) {
+        /* the other buffer's reads (the step before) have been performed before loads overwrite it */
+        BL_WAIT_LGKM0();
+        asm volatile("" ::: "memory");
+        if (kk + 4 < steps) {
+            issue(kk + 4, buf ^ 1);
+            BL_WAIT_VM(9);                                              /* all but the nine just issued */
+        } else {
+            BL_WAIT_VM(0);
+        }
+        asm volatile("" ::: "memory");
+        const uint8_t* st = base + buf * KS_STAGE;
+        bl_v4i wq = *(const bl_v4i*)(st + w_off), a[4][2];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+            for (int mi = 0; mi < 2; ++mi) a[ks][mi] = *(const bl_v4i*)(st + a_off + mi * 32 * G3_BK + (((4 * h + ks) ^ a_swz) * 16));
+        __builtin_amdgcn_sched_barrier(0);                              /* one wait for the step, not one per read */
+        if (half && kk == steps - 1 && h == 1) wq = bl_v4i{0, 0, 0, 0};
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const bl_v4i bop = bl_unpack16(LAYOUT == 0 ? bl_word_to_k16((uint32_t)wq[ks]) : (uint32_t)wq[ks]);
+#pragma unroll
+            for (int mi = 0; mi < 2; ++mi) C[mi] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[ks][mi], bop, C[mi], 0, 0, 0);
+        }
+        buf ^= 1;
+    }
+    bl_mfma_fence();
+    /* the partial tiles meet (a wave's part lies in its own stages, which it has read) */
+    BL_WAIT_LGKM0();
+    asm volatile("" ::: "memory");
+    int* const part = (int*)base;
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) part[(mi * 16 + v) * 64 + lane] = C[mi][v];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int v = (w & 1) * 8 + i, m = m0 + (w >> 1) * 32 + (v >> 2) * 8 + h * 4 + (v & 3);
+        int sum = -rs[i];
+#pragma unroll
+        for (int ww = 0; ww < 4; ++ww) sum += ((const int*)(smem + ww * 2 * KS_STAGE))[((w >> 1) * 16 + v) * 64 + lane];
+        if (m < M && n < N) {
+            if (acc) acc[(int64_t)m * N + n] = sum;
+            if (y) {
+                const float t = (float)sum * (bt * sc[i]);
+                y[(int64_t)m * N + n] = residual ? rr[i] + t : t;
+            }
+        }
+    }
+}
+
+template <int LAYOUT>
+static bl_status launch_ksplit(const uint8_t* packed, const float* beta, const int8_t* q, const float* scale,
+                               const int32_t* rowsum, int m, int n, int k, const float* residual, int32_t* acc, float* y,
+                               hipStream_t st) {
+    constexpr int lds = 8 * KS_STAGE;
+    auto kern = bl_gemm_ksplit<LAYOUT>;
+    static std::atomic<bool> attr_set;
+    if (!attr_set.load(std::memory_order_acquire)) {
+        if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) return BL_ERR_HIP;
+        attr_set.store(true, std::memory_order_release);
+    }
+    const int tiles_m = (m + 63) / 64, tiles = tiles_m * ((n + 31) / 32);
+    kern<<<(tiles + 7) / 8 * 8, 256, lds, st>>>(packed, q, rowsum, beta, scale, m, n, k, tiles_m, tiles, residual, acc, y);
+    return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
+}
+
 /* rowsum[m] = sum_k q[m][k]; one wave per row. */
 __global__ __launch_bounds__(256) void bl_rowsum_kernel(const int8_t* __restrict__ q, int M, int K,
                                                          int32_t* __restrict__ rowsum) {
@@ -684,6 +832,8 @@ template <bool HALF, int LAYOUT>
 static bl_status launch_plain(const uint8_t* packed, const float* beta, const int8_t* q, const float* scale,
                               const int32_t* rowsum, int m, int n, int k, const float* residual, int32_t* acc, float* y,
                               hipStream_t st) {
+    if ((int64_t)((m + 63) / 64) * ((n + 127) / 128) <= KS_MAX_TILES)
+        return launch_ksplit<LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
     if ((int64_t)((m + 127) / 128) * ((n + 127) / 128) <= 400)
         return launch_tile256_t<64, 128, 2, 1, 4, 0, false, HALF, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
     if (!acc && !residual && (int64_t)m * n < ((int64_t)1 << 30))
