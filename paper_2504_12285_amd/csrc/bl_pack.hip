@@ -299,21 +299,21 @@ __global__ __launch_bounds__(PACK_THREADS) void bl_unpack_t5(const uint32_t* __r
 }
 
 /* ---- k-major form (BL_LAYOUT_KMAJOR, see bitlinear.h): the transposed matrix, one row per k ------
- * A workgroup takes 64 k x 256 n: lane = k, so that a wave reads 64 consecutive weights of a row of W
- * at a time; each thread packs four words (16 rows n each), which go through LDS so that the 64 bytes
+ * A workgroup takes 64 k x 64 J n (J = 4, or 1 where that would leave compute units without work): lane = k, so that a wave reads 64 consecutive weights of a row of W
+ * at a time; each thread packs J words (16 rows n each), which go through LDS so that the 16 J bytes
  * of a k leave together.  2560 x 6912: 31 us (before, a thread per word with the lanes 16 rows apart: 125). */
-template <int IN>
+template <int IN, int J>
 __global__ __launch_bounds__(PACK_THREADS) void bl_pack_km(const void* __restrict__ Wv, const bl_pack_scale sc, int64_t N,
                                                             int64_t K, int64_t wpr, uint32_t* __restrict__ packed) {
     __shared__ double red[PACK_THREADS];
-    __shared__ uint32_t tile[64][17];
+    __shared__ uint32_t tile[64][4 * J + 1];
     const float T = IN == 0 ? bl_pack_threshold(sc, red) : 0.0f;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t kt = (K + 63) / 64, nt = (wpr + 15) / 16;
+    const int64_t kt = (K + 63) / 64, nt = (wpr + 4 * J - 1) / (4 * J);
     for (int64_t t = blockIdx.x; t < kt * nt; t += gridDim.x) {
-        const int64_t tn = t / kt, k = (t - tn * kt) * 64 + lane, nw0 = tn * 16 + w * 4;
+        const int64_t tn = t / kt, k = (t - tn * kt) * 64 + lane, nw0 = (tn * 4 + w) * J;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < J; ++j) {
             uint32_t word = 0;
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
@@ -322,14 +322,14 @@ __global__ __launch_bounds__(PACK_THREADS) void bl_pack_km(const void* __restric
                 if (n < N && k < K) c = IN == 0 ? bl_code(((const float*)Wv)[n * K + k], T) : bl_code_i8(((const int8_t*)Wv)[n * K + k]);
                 word |= c << (2 * i);
             }
-            tile[lane][w * 4 + j] = word;
+            tile[lane][w * J + j] = word;
         }
         __syncthreads();
         const int64_t ko = (t - tn * kt) * 64 + (threadIdx.x >> 2);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t nw = tn * 16 + (threadIdx.x & 3) * 4 + j;
-            if (ko < K && nw < wpr) packed[ko * wpr + nw] = tile[threadIdx.x >> 2][(threadIdx.x & 3) * 4 + j];
+        for (int j = 0; j < J; ++j) {
+            const int64_t nw = (tn * 4 + (threadIdx.x & 3)) * J + j;
+            if (ko < K && nw < wpr) packed[ko * wpr + nw] = tile[threadIdx.x >> 2][(threadIdx.x & 3) * J + j];
         }
         __syncthreads();
     }
@@ -383,9 +383,16 @@ extern "C" bl_status bl_pack_ternary(const void* W, int in_kind, int64_t N, int6
     /* grids of what is resident at once (eight workgroups per compute unit): each adds the partial sums up once */
     const auto grid = [](int64_t blocks) { return (unsigned)(blocks < 8 * 256 ? blocks : 8 * 256); };
     if (layout == BL_LAYOUT_KMAJOR) {
-        const int64_t wpr = (N + 63) / 64 * 4, tiles = ((K + 63) / 64) * ((wpr + 15) / 16);
-        if (latent) bl_pack_km<0><<<grid(tiles), PACK_THREADS, 0, st>>>(W, sc, N, K, wpr, out);
-        else bl_pack_km<1><<<grid(tiles), PACK_THREADS, 0, st>>>(W, sc, N, K, wpr, out);
+        const int64_t wpr = (N + 63) / 64 * 4, kt = (K + 63) / 64, tiles = kt * ((wpr + 15) / 16), tiles1 = kt * (wpr / 4);
+        /* (896 x 704 from int8: with 154 workgroups of one word per thread 5.4 us; 44 of four words made the
+         * call 1.7 us longer) */
+        if (tiles >= 1024) {
+            if (latent) bl_pack_km<0, 4><<<grid(tiles), PACK_THREADS, 0, st>>>(W, sc, N, K, wpr, out);
+            else bl_pack_km<1, 4><<<grid(tiles), PACK_THREADS, 0, st>>>(W, sc, N, K, wpr, out);
+        } else {
+            if (latent) bl_pack_km<0, 1><<<grid(tiles1), PACK_THREADS, 0, st>>>(W, sc, N, K, wpr, out);
+            else bl_pack_km<1, 1><<<grid(tiles1), PACK_THREADS, 0, st>>>(W, sc, N, K, wpr, out);
+        }
     } else if (layout == BL_LAYOUT_TRIT5) {
         const int64_t wpr = bl_kpad5(K) / 20, words = bl_npad(N) * wpr;
         const unsigned g = grid((words + PACK_THREADS - 1) / PACK_THREADS);
