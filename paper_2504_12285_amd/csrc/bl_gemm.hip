@@ -66,7 +66,7 @@ __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : 
                                                                 const int32_t* __restrict__ rowsum,
                                                                 const float* __restrict__ beta,
                                                                 const float* __restrict__ scale, int M, int N,
-                                                                int K, int tiles_m, int tiles_n, int band,
+                                                                int K, int tiles_m, int tiles_n, int gm, int band,
                                                                 int vgrid, const float* __restrict__ residual,
                                                                 int32_t* __restrict__ acc, float* __restrict__ y,
                                                                 uint16_t* __restrict__ xb, int* __restrict__ absmax,
@@ -138,15 +138,21 @@ __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : 
     };
 
     /* XCD-aware tile order: workgroup L runs on XCD L%8.  The row tiles are cut into bands so narrow that
-     * a band's activation panel stays in an XCD's 4 MB L2 while its weight tiles stream through; the tiles
-     * are numbered band by band, row tiles fastest, and each XCD takes one eighth of the sequence, so that
-     * the XCDs are even whatever the tile counts (a rectangular region each leaves a quarter of them idle
-     * at 17 row tiles: 2140 x 3840 -> 13458 148 us, here 122; 1100 x 2560 -> 7000 36 against 27.5).  The grid is persistent: a workgroup takes
-     * virtual blocks vb = blockIdx.x, + gridDim.x, .. (gridDim.x is a multiple of 8, so it stays on its
-     * XCD's share). */
+     * a band's activation panel stays in an XCD's 4 MB L2 while its weight tiles stream through, row tiles
+     * fastest.  Either a rectangle per XCD (gm bands x 8 / gm column blocks), or (gm = 0) the tiles are
+     * numbered band by band and each XCD takes one eighth of the sequence, so that the XCDs are even whatever
+     * the tile counts; the host chooses.  The grid is persistent: a workgroup takes virtual blocks
+     * vb = blockIdx.x, + gridDim.x, .. (gridDim.x is a multiple of 8, so it stays on its XCD's share). */
     const int tiles = tiles_m * tiles_n, share = (tiles + 7) >> 3, band_tiles = band * tiles_n;
+    const int gn = gm ? 8 / gm : 1, cols = (tiles_n + gn - 1) / gn;
     auto tile_of = [&](int vb, int& tm, int& tn) {
-        const int idx = vb >> 3, at = (vb & 7) * share + idx;
+        const int xcd = vb & 7, idx = vb >> 3;
+        if (gm) {
+            tm = (xcd / gn) * band + idx % band;
+            tn = (xcd % gn) * cols + idx / band;
+            return idx < band * cols && tm < tiles_m && tn < tiles_n;
+        }
+        const int at = xcd * share + idx;
         if (idx >= share || at >= tiles) return false;
         const int b = at / band_tiles, in = at - b * band_tiles;
         const int rows = min(band, tiles_m - b * band);
@@ -587,13 +593,26 @@ static bl_status launch_tile256_t(const uint8_t* packed, const float* beta, cons
     }
     /* the gate epilogue's tile holds 64 gate rows and the 64 matching up rows: N/2 / 64 column tiles */
     const int tiles_m = (M + G3_BM - 1) / G3_BM, tiles_n = EPI == 2 ? (N / 2 + BN / 2 - 1) / (BN / 2) : (N + BN - 1) / BN;
-    /* rows of activations per band: at most ~1.5 MB of int8 (measured, medians of six interleaved rounds at
-     * M = 2048: +7 % on the 13824-wide shape against bands of all rows, equal on the others) */
-    int64_t most = (3 << 19) / ((int64_t)BM * K);
-    if (most < 1) most = 1;
-    const int bands = (int)((tiles_m + most - 1) / most), band = (tiles_m + bands - 1) / bands;
     if ((int64_t)tiles_m * tiles_n > ((int64_t)1 << 30)) return BL_ERR_SHAPE;   /* (outputs beyond 2^43 values) */
-    const int vgrid = 8 * ((tiles_m * tiles_n + 7) / 8);
+    /* rows of activations per band: at most ~1.5 MB of int8 (measured, medians of six interleaved rounds at
+     * M = 2048: +7 % on the 13824-wide shape against bands of all rows, equal on the others).  A rectangle
+     * per XCD unless its size means more tiles for the busiest of an XCD's 32 compute units than an even share
+     * does: 2140 x 3840 -> 13458 (17 row tiles, bands of 3: two XCDs idle) 148 / 122 us, 1100 x 2560 -> 7000 (70
+     * tiles against 62) 36 / 27.5; 777 x 2999 -> 5003 with its quantiser (70 and 60 tiles against 65: three on
+     * the busiest unit either way) 28.1 / 30.6. */
+    int gm = 1;
+    while (gm < 8 && (int64_t)((tiles_m + gm - 1) / gm) * BM * K > (3 << 19)) gm *= 2;
+    int band = (tiles_m + gm - 1) / gm;
+    const int rect = band * ((tiles_n + 8 / gm - 1) / (8 / gm)), share = (tiles_m * tiles_n + 7) / 8;
+    int vgrid = 8 * rect;
+    if ((rect + 31) / 32 > (share + 31) / 32) {
+        int64_t most = (3 << 19) / ((int64_t)BM * K);
+        if (most < 1) most = 1;
+        const int bands = (int)((tiles_m + most - 1) / most);
+        band = (tiles_m + bands - 1) / bands;
+        gm = 0;
+        vgrid = 8 * share;
+    }
     /* persistent grid: what is resident at once (a multiple of 8 keeps a workgroup on its XCD's region) */
     static std::atomic<int> resident{0};
     int blocks = resident.load(std::memory_order_acquire);
@@ -609,7 +628,7 @@ static bl_status launch_tile256_t(const uint8_t* packed, const float* beta, cons
         resident.store(blocks, std::memory_order_release);
     }
     if (blocks > vgrid) blocks = vgrid;
-    kern<<<blocks, WM * WN * 64, lds, st>>>(packed, q, rowsum, beta, scale, M, N, K, tiles_m, tiles_n, band, vgrid,
+    kern<<<blocks, WM * WN * 64, lds, st>>>(packed, q, rowsum, beta, scale, M, N, K, tiles_m, tiles_n, gm, band, vgrid,
                                             residual, acc, y, ep.xb, ep.absmax, (long long*)bl_clock_stamps(), nullptr, nullptr, 0, nullptr, nullptr);
     return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
 }
@@ -644,7 +663,7 @@ bl_status bl_gemm_table_launch(const bl_tile_item* items, const int* tile0, int 
     hipStream_t st = (hipStream_t)s;
     if (g_table_blocks.load(std::memory_order_acquire) == 0) return BL_ERR_VALUE;   /* no table was built in this process */
     bl_gemm_tile256<64, 128, 2, 1, 4, 0, true><<<blocks, 256, TABLE_LDS, st>>>(
-        nullptr, nullptr, nullptr, nullptr, nullptr, M, 0, G3_BK, 1, 0, 1, total_tiles, nullptr, nullptr, nullptr, nullptr,
+        nullptr, nullptr, nullptr, nullptr, nullptr, M, 0, G3_BK, 1, 0, 1, 1, total_tiles, nullptr, nullptr, nullptr, nullptr,
         nullptr, nullptr, items, tile0, nitems, wg_start, tile_list);
     return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
 }
