@@ -11,13 +11,10 @@
 
 #include <atomic>
 
-/* ---- large-tile pipelined kernel -------------------------------------------
- * 256 x 256 output tile per workgroup, k step 128, three LDS stages filled by
- * direct global->LDS loads (no register staging) two k steps ahead of the
- * matrix cores; one barrier per k step.  WM x WN waves (4 or 8 in total): with
- * eight waves every SIMD holds two, so one wave's unpack and LDS traffic hide
- * behind the other's MFMAs (a single wave reaches only ~60 % of the MFMA rate
- * once the unpack instructions share its issue slot).
+/* ---- tile kernel ------------------------------------------------------------
+ * BM x BN output tile per workgroup, k step 128, STAGES LDS stages filled by direct
+ * global->LDS loads (no register staging) ahead of the matrix cores; one barrier per
+ * k step.  WM x WN waves.
  *
  * LDS stage = A part (BM rows x 128 int8, 16-byte units XOR-swizzled by
  * (row/2)%8) + W part (BN rows x 32 packed bytes = two units, swapped by row/8%2): with these
