@@ -843,7 +843,11 @@ __global__ __launch_bounds__(256) void bl_rowsum_kernel(const int8_t* __restrict
  * on the wide shape.
  * fp32 output alone: the stores of a tile travel during the workgroup's next tile (measured at M = 2048 /
  * 8192: the 13824-wide shape 77 - 80 us against 86 - 90, 297 - 308 against 317 - 327; the 64 x 128 kernel
- * with deferred stores loses: it has under one tile per workgroup on the shapes it serves). */
+ * with deferred stores loses: it has under one tile per workgroup on the shapes it serves).
+ * Deferred stores mean two workgroups per CU instead of three: between 512 and 768 tiles that is a second
+ * round, which long rows do not win back (4096 x 6912 -> 2560 83.3 us against 78.6 in one round, 4096 x 6976
+ * 93.4 / 83.6, 3000 x 4096 -> 3200 51.8 / 49.9) and short ones do (4096 x 2560 -> 2560 37.4 / 37.4, 3500 x 2048 ->
+ * 3400 34.6 / 39.7, 2816 x 1024 -> 3840 19.4 / 21.9). */
 template <bool HALF, int LAYOUT>
 static bl_status launch_plain(const uint8_t* packed, const float* beta, const int8_t* q, const float* scale,
                               const int32_t* rowsum, int m, int n, int k, const float* residual, int32_t* acc, float* y,
@@ -852,7 +856,9 @@ static bl_status launch_plain(const uint8_t* packed, const float* beta, const in
         return launch_ksplit<LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
     if ((int64_t)((m + 127) / 128) * ((n + 127) / 128) <= 400)
         return launch_tile256_t<64, 128, 2, 1, 4, 0, false, HALF, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
-    if (!acc && !residual && (int64_t)m * n < ((int64_t)1 << 30))
+    const int64_t tiles = (int64_t)((m + 127) / 128) * ((n + 127) / 128);
+    const bool one_round = tiles > 512 && tiles <= 768 && k >= 4096;
+    if (!one_round && !acc && !residual && (int64_t)m * n < ((int64_t)1 << 30))
         return launch_tile256_t<128, 128, 2, 2, 2, 0, true, HALF, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
     return launch_tile256_t<128, 128, 2, 2, 2, 0, false, HALF, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
 }

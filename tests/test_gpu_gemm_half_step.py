@@ -1,6 +1,6 @@
 """The prefill tile kernel on rows whose last k step is half (K padded to an odd multiple of 64) and on the
 plain bit order, for every tile choice: the k loop split over waves (up to 160 tiles of 64 x 128), 64 x 128, 128 x 128 with deferred stores (fp32 output
-alone) and without (int32 output, residual).  Bit for bit against an exact integer product, with the last
+alone) and without (int32 output, residual, 513 to 768 tiles of long rows).  Bit for bit against an exact integer product, with the last
 row and column ends that the loads of the half step must stay inside."""
 import numpy as np
 import pytest
@@ -19,7 +19,7 @@ def bl():
 
 @pytest.mark.parametrize("layout", [0, 1])
 @pytest.mark.parametrize("M,N,K", [(65, 130, 64), (129, 257, 192), (300, 515, 2999), (70, 128, 128), (64, 1, 1), (700, 2000, 192), (1000, 1500, 256),
-                                   (200, 96, 448), (640, 2048, 576),
+                                   (200, 96, 448), (640, 2048, 576), (2600, 3300, 4160), (2600, 3300, 4096),
                                    (2600, 2700, 320), (2700, 2600, 64), (2561, 2689, 256), (2570, 2700, 1100)])
 def test_half_steps_and_layouts(bl, layout, M, N, K):
     g = torch.Generator(device=DEV).manual_seed(M + N + K)
