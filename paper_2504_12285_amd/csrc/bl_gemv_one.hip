@@ -73,6 +73,18 @@ __device__ __forceinline__ double bl_rsqrt64(double v) {
     return r;
 }
 
+/* The factor r = fp32(1 / sqrt(ss / K + eps)) of the normalisation, the bits of those fp64 operations rounded
+ * one by one.  The fast form is off by less than 2^-50 (the estimate's last step, inv_k for a division),
+ * they by less than 2^-51: where both ends of a 2^-48 interval round to the same finite fp32, that is r.
+ * About one row in 2^23, and rows whose sum is zero, infinite or NaN, take the operations themselves;
+ * every thread of the workgroup decides on the same sum. */
+__device__ __forceinline__ float bl_norm_factor(double ss, double inv_k, int K, float eps) {
+    const double e = bl_rsqrt64(ss * inv_k + (double)eps);
+    const float lo = (float)(e * (1.0 - 0x1p-48)), hi = (float)(e * (1.0 + 0x1p-48));
+    if (lo == hi && lo > 0.0f && hi < __builtin_inff()) return lo;
+    return (float)(1.0 / sqrt(ss / (double)K + (double)eps));
+}
+
 /* What the kernel needs to know, fetched from the arguments in one go. */
 struct bl_one_args {
     const void* packed;
@@ -261,7 +273,7 @@ __global__ __launch_bounds__(BL_ONE_WAVES * 64) void bl_gemv_one(const bl_one_ar
             __syncthreads();
             const double ss = bl_few_sum<NW>(sd[lw]);
             const float U = bl_few_max<NW>(fs[lw]);
-            const float rn = (float)bl_rsqrt64(ss * P.inv_k + (double)P.eps);
+            const float rn = bl_norm_factor(ss, P.inv_k, K, P.eps);
             narrow(rn);
             /* The maximum of |bf16((t*r)*gain)| without a second meeting of the waves: it lies within a
              * relative 2^-22 of r * max|t*gain| (three roundings), and narrowing is monotonic, so where both
