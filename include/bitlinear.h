@@ -64,7 +64,9 @@
  * BL_ERR_SHAPE / BL_ERR_ALIGN.  Entry points that read bf16 or fp32 activations inside a
  * product kernel (fused producers, epilogues, bl_stack_* with X) need K % 64 == 0 and say so;
  * a ragged K goes through bl_quant_act_int8 and the int8 inputs of the products.
- * Non-finite activations or weights: undefined.
+ * Non-finite inputs have no defined result, but what they spoil is bounded: an activation row and
+ * its outputs (a NaN is passed over by gamma and quantises to -127, the other values of the row as
+ * without it; an infinity makes the scale infinite), or the packed matrix (its beta).
  * There is no bias argument (the report removes all biases, Section 2).
  */
 #ifndef BITLINEAR_H

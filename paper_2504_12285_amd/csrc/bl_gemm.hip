@@ -487,6 +487,7 @@ __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : 
              * the 32 lanes of a half wave (DPP), then one atomic max per row on the float bits
              * (non-negative floats order like integers, so the result does not depend on the order) */
             const int NOUT = EPI == 2 ? N / 2 : N;
+            constexpr int MAG0 = 0x007F0000;          /* added to a magnitude's bits: infinity is the largest int, a NaN negative */
 #pragma unroll
             for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
@@ -497,7 +498,7 @@ __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : 
                         const int v = vq * 4 + v4;
                         const int ml = wm0 + mi * 32 + vq * 8 + h * 4 + v4;
                         const int m = m0 + ml;
-                        float mx = 0.0f;
+                        int mx = MAG0;
                         if (m < M) {
                             const int rs = rs_s[ml];
                             const float c = cf_s[ml];
@@ -513,7 +514,7 @@ __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : 
                                         if (y) __builtin_nontemporal_store(o, y + (int64_t)m * N + n);
                                         const uint32_t bits = bl_pack2_bf16(o, o);
                                         xb[(int64_t)m * NOUT + n] = (uint16_t)bits;
-                                        mx = bl_max_pos(mx, __uint_as_float((bits << 16) & 0x7FFF0000u));
+                                        mx = max(mx, (int)(((bits << 16) & 0x7FFF0000u) + (uint32_t)MAG0));
                                     }
                                 }
                             } else {
@@ -531,11 +532,11 @@ __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : 
                                     if (y) __builtin_nontemporal_store(o, y + (int64_t)m * NOUT + j);
                                     const uint32_t bits = bl_pack2_bf16(o, o);
                                     xb[(int64_t)m * NOUT + j] = (uint16_t)bits;
-                                    mx = bl_max_pos(mx, __uint_as_float((bits << 16) & 0x7FFF0000u));
+                                    mx = max(mx, (int)(((bits << 16) & 0x7FFF0000u) + (uint32_t)MAG0));
                                 }
                             }
                         }
-                        rowmax[v4] = mx;
+                        rowmax[v4] = __int_as_float(mx - MAG0);
                     }
                     if constexpr (EPI == 1) {
                         if (mi + 1 < MI) fetch_res(mi + 1, vq);

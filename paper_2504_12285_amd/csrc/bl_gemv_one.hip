@@ -15,6 +15,8 @@
  * 2560 x 2560 4.0, 13824 x 2560 5.1, 2560 x 6912 6.0, against 5.8 / 5.8 / 8.0 / 8.6 on bl_gemv_rows.
  * What is left: 1.3 - 1.6 us launch boundary, about 1 us until the row has come from beyond the L2,
  * two exchanges through LDS, and the vector instructions of a whole row on every compute unit. */
+#include <type_traits>
+
 #include "bl_device.h"
 #include "bl_gemv_common.h"
 #include "bl_host.h"
@@ -75,14 +77,16 @@ __device__ __forceinline__ double bl_rsqrt64(double v) {
 
 /* The factor r = fp32(1 / sqrt(ss / K + eps)) of the normalisation, the bits of those fp64 operations rounded
  * one by one.  The fast form is off by less than 2^-50 (the estimate's last step, inv_k for a division),
- * they by less than 2^-51: where both ends of a 2^-48 interval round to the same finite fp32, that is r.
- * About one row in 2^23, and rows whose sum is zero, infinite or NaN, take the operations themselves;
- * every thread of the workgroup decides on the same sum. */
+ * they by less than 2^-51, so it rounds like them unless it lies within 2^-47 of the midpoint of two fp32,
+ * which the 29 bits that the rounding drops tell.  About one row in 2^22, and rows whose sum is zero,
+ * infinite or NaN, take the operations themselves; every thread of the workgroup decides on the same sum. */
 __device__ __forceinline__ float bl_norm_factor(double ss, double inv_k, int K, float eps) {
     const double e = bl_rsqrt64(ss * inv_k + (double)eps);
-    const float lo = (float)(e * (1.0 - 0x1p-48)), hi = (float)(e * (1.0 + 0x1p-48));
-    if (lo == hi && lo > 0.0f && hi < __builtin_inff()) return lo;
-    return (float)(1.0 / sqrt(ss / (double)K + (double)eps));
+    float r = (float)e;
+    const uint32_t off = (__double2loint(e) & 0x1FFFFFFFu) - (0x10000000u - 32u);
+    if (__builtin_expect(!(off > 64u && r > 0x1p-126f && r < __builtin_inff()), 0))
+        r = (float)(1.0 / sqrt(ss / (double)K + (double)eps));
+    return r;
 }
 
 /* What the kernel needs to know, fetched from the arguments in one go. */
@@ -229,7 +233,7 @@ __global__ __launch_bounds__(BL_ONE_WAVES * 64) void bl_gemv_one(const bl_one_ar
                         /* (an fp32 value squared is exact in fp64, so the fused form rounds as the separate one) */
                         part = __builtin_fma((double)v[j][e], (double)v[j][e], part);
                         um = fmaxf(um, fabsf(has_gain ? v[j][e] * gn[e] : v[j][e]));
-                        if (has_gain) gm = fmaxf(gm, fabsf(gn[e]));
+                        if (has_gain) gm += fabsf(gn[e]);              /* (at least the maximum, and NaN if one is) */
                     }
                 }
             }
@@ -248,20 +252,21 @@ __global__ __launch_bounds__(BL_ONE_WAVES * 64) void bl_gemv_one(const bl_one_ar
                 xb[j] = bl_v2u{bl_pack2_bf16(v[j][0], v[j][1]), bl_pack2_bf16(v[j][2], v[j][3])};
             }
         };
-        auto row_absmax = [&]() {                              /* over the whole row; contains one barrier */
-            bl_v2us m2 = {0, 0};
+        auto row_absmax = [&](auto skip_nan) {                 /* over the whole row; contains one barrier */
+            bl_mag2<decltype(skip_nan)::value> m2;
 #pragma unroll
             for (int j = 0; j < UN; ++j) {                     /* (a thread beyond the row holds its last unit again) */
-                m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(bl_v2us, xb[j].x & 0x7FFF7FFFu));
-                m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(bl_v2us, xb[j].y & 0x7FFF7FFFu));
+                m2.take(xb[j].x);
+                m2.take(xb[j].y);
             }
-            const uint32_t mu = __builtin_bit_cast(uint32_t, m2);
-            const float mx = bl_wave_max(bl_max_pos(__uint_as_float(mu << 16), __uint_as_float(mu & 0xFFFF0000u)));
+            const float mx = bl_wave_max(m2.get());
             if (lane == 0) fs[w] = mx;
             __syncthreads();
             return bl_few_max<NW>(fs[lw]);
         };
-        float gamma;
+        /* the rows that may hold a NaN take their maximum and their quantiser with it in mind */
+        bool special = false;
+        float gamma = 0.0f;
         if (norm) {
             part = bl_row_sum(part);
             part = (bl_lane_d(part, 0) + bl_lane_d(part, 16)) + (bl_lane_d(part, 32) + bl_lane_d(part, 48));
@@ -279,32 +284,42 @@ __global__ __launch_bounds__(BL_ONE_WAVES * 64) void bl_gemv_one(const bl_one_ar
              * relative 2^-22 of r * max|t*gain| (three roundings), and narrowing is monotonic, so where both
              * ends of a slightly wider interval narrow to the same bf16, that is it.  About one row in 2^12
              * straddles a boundary (and rows where subnormal or infinite products could break the bound are
-             * sent the same way): those take the maximum itself.  Every thread decides on the same values. */
+             * sent the same way, as are sums and gains that are not finite): those take the maximum itself.  Every
+             * thread decides on the same values. */
             const float c = rn * U;
             const uint32_t ends = bl_pack2_bf16(c * (1.0f - 0x1p-20f), c * (1.0f + 0x1p-20f));
             if ((ends & 0xFFFFu) == (ends >> 16) && c >= 0x1p-60f && c <= 0x1p120f && rn <= 0x1p40f && U <= 0x1p120f) {
                 gamma = __uint_as_float(ends & 0xFFFF0000u);
             } else {
-                __syncthreads();                               /* every wave has read fs */
-                gamma = row_absmax();
+                special = true;
             }
         } else {
             if (SRC != BL_ONE_BF16) narrow(1.0f);
-            gamma = row_absmax();
+            gamma = row_absmax(std::false_type{});
+            special = !(gamma < __builtin_inff());
+        }
+        if (__builtin_expect(special, 0)) {
+            __syncthreads();                                   /* every wave has read fs */
+            gamma = row_absmax(std::true_type{});
         }
         const float gg = fmaxf(gamma, 1e-5f);
         const float inv = bl_div_rn(127.0f, gg);
         int part_q = 0;
+        auto quantise = [&](auto mode) {
 #pragma unroll
-        for (int j = 0; j < UN; ++j) {
-            const int u = tid + j * nthreads;
-            if (u >= units) continue;
-            const uint32_t o = bl_quant4<false>(__uint_as_float(xb[j].x << 16), __uint_as_float(xb[j].x & 0xFFFF0000u),
-                                                __uint_as_float(xb[j].y << 16), __uint_as_float(xb[j].y & 0xFFFF0000u), inv);
-            *(uint32_t*)(Qs + (u >> 4) * BL_ONE_QSTRIDE + (u & 15) * 4) = o;
-            part_q = __builtin_amdgcn_sdot4((int)o, 0x01010101, part_q, false);
-            if (first_block && P.q_out) *(uint32_t BL_G*)(P.q_out + u * 4) = o;
-        }
+            for (int j = 0; j < UN; ++j) {
+                const int u = tid + j * nthreads;
+                if (u >= units) continue;
+                const uint32_t o = bl_quant4<decltype(mode)::value>(
+                    __uint_as_float(xb[j].x << 16), __uint_as_float(xb[j].x & 0xFFFF0000u),
+                    __uint_as_float(xb[j].y << 16), __uint_as_float(xb[j].y & 0xFFFF0000u), inv);
+                *(uint32_t*)(Qs + (u >> 4) * BL_ONE_QSTRIDE + (u & 15) * 4) = o;
+                part_q = __builtin_amdgcn_sdot4((int)o, 0x01010101, part_q, false);
+                if (first_block && P.q_out) *(uint32_t BL_G*)(P.q_out + u * 4) = o;
+            }
+        };
+        if (__builtin_expect(special, 0)) quantise(bl_mode<BL_Q_ROW>{});
+        else quantise(bl_mode<BL_Q_FINITE>{});
         if (tid < 16) *(uint32_t*)(Qs + nchunks * BL_ONE_QSTRIDE + tid * 4) = 0;
         part_q = bl_wave_sum(part_q);
         if (lane == 0) qsum[w] = part_q;

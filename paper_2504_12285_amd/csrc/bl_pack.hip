@@ -48,9 +48,14 @@ struct bl_pack_scale {
 /* The threshold of the ternariser: rint(W / d) is non-zero exactly where |W| > T.  The fp32 quotient
  * rounds above 0.5 (ties to even: 0.5 itself gives 0) exactly where the real quotient is greater than
  * 0.5 + 2^-25, the midpoint between 0.5 and its successor, i.e. where |W| > d * (0.5 + 2^-25); that
- * product is exact in fp64, and T is the largest fp32 not above it.  Every thread of the workgroup
- * calls this; red: PACK_THREADS doubles of LDS. */
-__device__ __forceinline__ float bl_pack_threshold(const bl_pack_scale& sc, double* red) {
+ * product is exact in fp64, and T is the largest fp32 not above it.  A quotient that is NaN clamps to -1,
+ * code 0: every weight where beta is NaN, the infinite ones where it is infinite (`above` is then 0).  Every
+ * thread of the workgroup calls this; red: PACK_THREADS doubles of LDS. */
+struct bl_ternary {
+    float T;
+    uint32_t above;           /* code of w > T */
+};
+__device__ __forceinline__ bl_ternary bl_pack_threshold(const bl_pack_scale& sc, double* red) {
     double s = 0.0;
     for (int i = threadIdx.x; i < sc.np; i += PACK_THREADS) s += sc.partial[i];
     red[threadIdx.x] = s;
@@ -64,18 +69,19 @@ __device__ __forceinline__ float bl_pack_threshold(const bl_pack_scale& sc, doub
     const double td = (double)(beta + 1e-5f) * (0.5 + 0x1p-25);
     float T = (float)td;
     if ((double)T > td) T = __uint_as_float(__float_as_uint(T) - 1);
-    return T;
+    const bool inf = T == __builtin_inff();
+    return {inf ? 0x1.fffffep127f : T, inf ? 0u : 2u};
 }
-__device__ __forceinline__ uint32_t bl_code(float w, float T) {
-    uint32_t c = w > T ? 2u : 1u;
-    return w < -T ? 0u : c;
+__device__ __forceinline__ uint32_t bl_code(float w, bl_ternary t) {
+    const uint32_t c = w > t.T ? t.above : 1u;
+    return w >= -t.T ? c : 0u;
 }
 __device__ __forceinline__ uint32_t bl_code_i8(int b) { return (uint32_t)((b < -1 ? -1 : (b > 1 ? 1 : b)) + 1); }
 
 /* The codes of four consecutive weights, one per byte; nv < 4: the row ends behind nv of them, the
  * others are weight 0 (code 1).  The address need not be aligned beyond the element. */
 template <int IN>
-__device__ __forceinline__ uint32_t bl_codes4(const void* __restrict__ Wv, int64_t at, int nv, float T) {
+__device__ __forceinline__ uint32_t bl_codes4(const void* __restrict__ Wv, int64_t at, int nv, bl_ternary T) {
     if (IN == 0) {
         const float* p = (const float*)Wv + at;
         bl_v4f f = {0, 0, 0, 0};
@@ -86,7 +92,9 @@ __device__ __forceinline__ uint32_t bl_codes4(const void* __restrict__ Wv, int64
             for (int e = 0; e < 4; ++e)
                 if (e < nv) f[e] = p[e];
         }
-        return bl_code(f[0], T) | bl_code(f[1], T) << 8 | bl_code(f[2], T) << 16 | bl_code(f[3], T) << 24;
+        uint32_t c = bl_code(f[0], T) | bl_code(f[1], T) << 8 | bl_code(f[2], T) << 16 | bl_code(f[3], T) << 24;
+        if (nv < 4) c = (c & ~(~0u << (8 * nv))) | (0x01010101u & (~0u << (8 * nv)));
+        return c;
     }
     const int8_t* p = (const int8_t*)Wv + at;
     uint32_t w = 0;
@@ -143,7 +151,7 @@ __global__ __launch_bounds__(PACK_THREADS) void bl_pack_flat(const bl_v4f* __res
         for (int j = 0; j < 4; ++j) f[j] = W[(c + j < chunks ? c + j : chunks - 1) * 64 + lane];
     };
     load(c0);
-    const float T = bl_pack_threshold(sc, red);
+    const bl_ternary T = bl_pack_threshold(sc, red);
     while (c0 < chunks) {
         uint32_t c[4];
 #pragma unroll
@@ -163,7 +171,7 @@ template <int LAYOUT, int IN>
 __global__ __launch_bounds__(PACK_THREADS) void bl_pack_words(const void* __restrict__ Wv, const bl_pack_scale sc, int64_t N,
                                                                int64_t K, int64_t wpr, uint32_t* __restrict__ packed) {
     __shared__ double red[PACK_THREADS];
-    const float T = IN == 0 ? bl_pack_threshold(sc, red) : 0.0f;
+    const bl_ternary T = IN == 0 ? bl_pack_threshold(sc, red) : bl_ternary{};
     const int lane = threadIdx.x & 63;
     const int64_t cpr = (wpr + 15) / 16, chunks = (N + 3) / 4 * 4 * cpr;
     const int64_t waves = (int64_t)gridDim.x * (PACK_THREADS / 64);
@@ -250,7 +258,7 @@ __global__ __launch_bounds__(PACK_THREADS) void bl_pack_t5(const void* __restric
                                                             int64_t K, int64_t wpr, int64_t words,
                                                             uint32_t* __restrict__ packed) {
     __shared__ double red[PACK_THREADS];
-    const float T = IN == 0 ? bl_pack_threshold(sc, red) : 0.0f;
+    const bl_ternary T = IN == 0 ? bl_pack_threshold(sc, red) : bl_ternary{};
     for (int64_t g = (int64_t)blockIdx.x * PACK_THREADS + threadIdx.x; g < words; g += (int64_t)gridDim.x * PACK_THREADS) {
         const int64_t n = g / wpr, k0 = (g - n * wpr) * 20;
         uint32_t c[5], v = 0;
@@ -307,7 +315,7 @@ __global__ __launch_bounds__(PACK_THREADS) void bl_pack_km(const void* __restric
                                                             int64_t K, int64_t wpr, uint32_t* __restrict__ packed) {
     __shared__ double red[PACK_THREADS];
     __shared__ uint32_t tile[64][4 * J + 1];
-    const float T = IN == 0 ? bl_pack_threshold(sc, red) : 0.0f;
+    const bl_ternary T = IN == 0 ? bl_pack_threshold(sc, red) : bl_ternary{};
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t kt = (K + 63) / 64, nt = (wpr + 4 * J - 1) / (4 * J);
     for (int64_t t = blockIdx.x; t < kt * nt; t += gridDim.x) {

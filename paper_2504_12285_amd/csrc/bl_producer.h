@@ -168,38 +168,64 @@ __device__ __forceinline__ float bl_norm_produce2(const bl_prod_dev& pd, int m, 
 
 /* Four int8 in one dword: q = rint(f * inv), ties to even.  Adding 1.5 * 2^23 leaves the rounded
  * integer in the low bits of the sum (its unit in the last place is 1 there), so a value costs a
- * multiply, an add and three quarters of a byte permute.  CLAMP: for an inv that does not come
- * from the absmax of these values; with |f| <= gamma, fl(f * fl(127 / gamma)) never rounds beyond 127. */
-template <bool CLAMP>
+ * multiply, an add and three quarters of a byte permute.  With |f| <= gamma, fl(f * fl(127 / gamma)) never
+ * rounds beyond 127, so what is clamped is a choice: BL_Q_ROW where f may be NaN (it becomes -127 and no other
+ * value of the row changes), BL_Q_ANY for an inv that does not come from the absmax of these values,
+ * BL_Q_FINITE where the row is known to be finite. */
+enum { BL_Q_FINITE, BL_Q_ROW, BL_Q_ANY };
+template <int MODE>
+struct bl_mode {
+    static constexpr int value = MODE;
+};
+template <int MODE>
 __device__ __forceinline__ uint32_t bl_quant4(float f0, float f1, float f2, float f3, float inv) {
     float v[4] = {f0 * inv, f1 * inv, f2 * inv, f3 * inv};
     uint32_t r[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        if (CLAMP) v[e] = fminf(fmaxf(v[e], -127.0f), 127.0f);
+        if (MODE != BL_Q_FINITE) v[e] = fmaxf(v[e], -127.0f);
+        if (MODE == BL_Q_ANY) v[e] = fminf(v[e], 127.0f);
         r[e] = __float_as_uint(v[e] + 12582912.0f);
     }
     return __builtin_amdgcn_perm(r[1], r[0], 0x0C0C0400u) | __builtin_amdgcn_perm(r[3], r[2], 0x04000C0Cu);
 }
 
 /* Quantise 8 bf16 (one uint4) to two dwords of int8. */
-template <bool CLAMP = false>
+template <int MODE = BL_Q_ROW>
 __device__ __forceinline__ void bl_quant8_words(const uint4 v, float inv, uint32_t& lo, uint32_t& hi) {
     auto l = [](uint32_t w) { return __uint_as_float(w << 16); };
     auto h = [](uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); };
-    lo = bl_quant4<CLAMP>(l(v.x), h(v.x), l(v.y), h(v.y), inv);
-    hi = bl_quant4<CLAMP>(l(v.z), h(v.z), l(v.w), h(v.w), inv);
+    lo = bl_quant4<MODE>(l(v.x), h(v.x), l(v.y), h(v.y), inv);
+    hi = bl_quant4<MODE>(l(v.z), h(v.z), l(v.w), h(v.w), inv);
 }
 
-/* Largest magnitude of 8 bf16: without its sign a bf16 orders like its bit pattern, so the maxima
- * are taken two at a time on 16-bit integers. */
+/* Largest magnitude of 8 bf16: without its sign a bf16 orders like its bit pattern, so the maxima are
+ * taken two at a time on 16-bit integers.  SKIP: NaN are passed over; with 0x7F added infinity is 0x7FFF
+ * and a NaN, whose pattern lies above infinity's, negative.  Otherwise a NaN is the largest. */
+typedef short bl_v2s __attribute__((ext_vector_type(2)));
 typedef unsigned short bl_v2us __attribute__((ext_vector_type(2)));
+template <bool SKIP>
+struct bl_mag2 {
+    static constexpr uint32_t BIAS = SKIP ? 0x007F007Fu : 0u;
+    uint32_t m = BIAS;
+    __device__ __forceinline__ void take(uint32_t w) {
+        w = (w & 0x7FFF7FFFu) + BIAS;
+        if (SKIP) m = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(bl_v2s, m), __builtin_bit_cast(bl_v2s, w)));
+        else m = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(bl_v2us, m), __builtin_bit_cast(bl_v2us, w)));
+    }
+    __device__ __forceinline__ float get() const {
+        const uint32_t u = m - BIAS;
+        return bl_max_pos(__uint_as_float(u << 16), __uint_as_float(u & 0xFFFF0000u));
+    }
+};
+template <bool SKIP = true>
 __device__ __forceinline__ float bl_absmax8_bf16(const uint4 v) {
-    auto a = [](uint32_t w) { return __builtin_bit_cast(bl_v2us, w & 0x7FFF7FFFu); };
-    const bl_v2us m = __builtin_elementwise_max(__builtin_elementwise_max(a(v.x), a(v.y)),
-                                                __builtin_elementwise_max(a(v.z), a(v.w)));
-    const uint32_t u = __builtin_bit_cast(uint32_t, m);
-    return bl_max_pos(__uint_as_float(u << 16), __uint_as_float(u & 0xFFFF0000u));
+    bl_mag2<SKIP> m;
+    m.take(v.x);
+    m.take(v.y);
+    m.take(v.z);
+    m.take(v.w);
+    return m.get();
 }
 
 __device__ __forceinline__ int bl_sum16(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3) {

@@ -1,12 +1,39 @@
 /* Per-token absmax int8 activation quantisation (Section 2, "Activation
  * Quantization", of the BitNet b1.58 2B4T report).  HBM-bound at prefill sizes,
  * latency-bound at decode sizes. */
+#include <type_traits>
+
 #include "bl_device.h"
 #include "bl_host.h"
 #include "bl_producer.h"
 
 #define QUANT_THREADS 256
 #define QUANT_WAVE_ROWS 1024
+
+/* Unit u (eight elements) of a bf16 row: zeros behind K (RAGGED: inside the unit too). */
+template <bool RAGGED>
+__device__ __forceinline__ uint4 bl_row_unit(const uint16_t* x, int u, int K) {
+    const int full = K >> 3;
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (u < full) {
+        if (RAGGED) __builtin_memcpy(&v, x + u * 8, 16);
+        else v = *(const uint4*)(x + u * 8);
+    } else if (RAGGED && u == full) {
+        uint32_t e[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) e[j] = u * 8 + j < K ? x[u * 8 + j] : 0u;
+        v = make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16);
+    }
+    return v;
+}
+template <int MODE>
+__device__ __forceinline__ int bl_quant_unit(const uint4 v, float inv, int8_t* q, int sum) {
+    uint2 o;
+    bl_quant8_words<MODE>(v, inv, o.x, o.y);
+    *(uint2*)q = o;
+    sum = __builtin_amdgcn_sdot4((int)o.x, 0x01010101, sum, false);
+    return __builtin_amdgcn_sdot4((int)o.y, 0x01010101, sum, false);
+}
 
 /* The quantiser of rows that exist as bf16.  TPR threads (64 or 256) share a row and hold all of it
  * in registers between the absmax and the rounding: NV units of eight elements each (K <= 8 * TPR *
@@ -17,6 +44,8 @@
  * max |x|), read by every thread of the row and then cleared, so that the next product's epilogue
  * can fold its maxima into it again.
  * Bound by HBM at prefill sizes, else by the launch and the chain load -> maximum -> round -> store.
+ * A row whose maximum is infinite or NaN (without looking, a NaN is the largest) is read again with NaN passed
+ * over: looking in every row cost up to a tenth (2048 x 2560 3.8 -> 4.2 us).
  * Against one workgroup per row that read the row twice (and a ragged row in 2-byte loads): quantiser +
  * product at 777 x 2999 -> 5003 42.8 -> 38.4 us, the four of a layer at 2048 tokens 177.5 -> 174.2 us. */
 template <int TPR, int NV, bool RAGGED, bool KNOWN>
@@ -32,49 +61,46 @@ __global__ __launch_bounds__(QUANT_THREADS) void bl_quant_rows(const uint16_t* _
     if (m >= M) return;                                              /* (whole waves, and no barrier when ROWS > 1) */
     const uint16_t* x = X + (int64_t)m * K;
     int8_t* qo = q + (int64_t)m * Kp;
-    const int full = K >> 3, units = Kp >> 3;
+    const int units = Kp >> 3;
     uint4 v[NV];
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        const int u = t + i * TPR;
-        v[i] = make_uint4(0, 0, 0, 0);
-        if (u < full) {
-            if (RAGGED) __builtin_memcpy(&v[i], x + u * 8, 16);
-            else v[i] = *(const uint4*)(x + u * 8);
-        } else if (RAGGED && u == full) {
-            uint32_t e[8];
+    for (int i = 0; i < NV; ++i) v[i] = bl_row_unit<RAGGED>(x, t + i * TPR, K);
+    auto row_max = [&](float mx) {                                   /* one barrier where several waves share the row */
+        mx = bl_wave_max(mx);
+        if (WPR > 1) {
+            if (lane == 0) smax[w] = mx;
+            __syncthreads();
 #pragma unroll
-            for (int j = 0; j < 8; ++j) e[j] = u * 8 + j < K ? x[u * 8 + j] : 0u;
-            v[i] = make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16);
+            for (int i = 0; i < WPR; ++i) mx = bl_max_pos(mx, smax[i]);
         }
-    }
+        return mx;
+    };
     float gamma;
     if (KNOWN) {
         gamma = __int_as_float(absmax[m]);
     } else {
         float mx = 0.0f;
 #pragma unroll
-        for (int i = 0; i < NV; ++i) mx = bl_max_pos(mx, bl_absmax8_bf16(v[i]));
-        gamma = bl_wave_max(mx);
-        if (WPR > 1) {
-            if (lane == 0) smax[w] = gamma;
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < WPR; ++i) gamma = fmaxf(gamma, smax[i]);
-        }
+        for (int i = 0; i < NV; ++i) mx = bl_max_pos(mx, bl_absmax8_bf16<false>(v[i]));
+        gamma = row_max(mx);
     }
-    const float g = fmaxf(gamma, 1e-5f);
-    const float inv = bl_div_rn(127.0f, g);
+    float g, inv;
     int sum = 0;
+    if (__builtin_expect(KNOWN || gamma < __builtin_inff(), 1)) {    /* (the same in every thread of the row) */
+        g = fmaxf(gamma, 1e-5f);
+        inv = bl_div_rn(127.0f, g);
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        const int u = t + i * TPR;
-        if (u >= units) continue;
-        uint2 o;
-        bl_quant8_words<KNOWN>(v[i], inv, o.x, o.y);
-        sum = __builtin_amdgcn_sdot4((int)o.x, 0x01010101, sum, false);
-        sum = __builtin_amdgcn_sdot4((int)o.y, 0x01010101, sum, false);
-        *(uint2*)(qo + u * 8) = o;
+        for (int i = 0; i < NV; ++i)
+            if (t + i * TPR < units) sum = bl_quant_unit<KNOWN ? BL_Q_ANY : BL_Q_FINITE>(v[i], inv, qo + (t + i * TPR) * 8, sum);
+    } else {
+        float mx = 0.0f;
+#pragma unroll 1
+        for (int u = t; u < units; u += TPR) mx = bl_max_pos(mx, bl_absmax8_bf16(bl_row_unit<RAGGED>(x, u, K)));
+        if (WPR > 1) __syncthreads();                                /* smax has been read */
+        g = fmaxf(row_max(mx), 1e-5f);
+        inv = bl_div_rn(127.0f, g);
+#pragma unroll 1
+        for (int u = t; u < units; u += TPR) sum = bl_quant_unit<BL_Q_ROW>(bl_row_unit<RAGGED>(x, u, K), inv, qo + u * 8, sum);
     }
     sum = bl_wave_sum(sum);
     if (WPR > 1) {
@@ -101,40 +127,34 @@ __global__ __launch_bounds__(QUANT_THREADS) void bl_quant_long(const uint16_t* _
     const int64_t m = blockIdx.x;
     const uint16_t* x = X + m * K;
     int8_t* qo = q + m * Kp;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, full = K >> 3, units = Kp >> 3;
-    auto ld = [&](int u) {
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (u < full) {
-            if (RAGGED) __builtin_memcpy(&v, x + u * 8, 16);
-            else v = *(const uint4*)(x + u * 8);
-        } else if (RAGGED && u == full) {
-            uint32_t e[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) e[j] = u * 8 + j < K ? x[u * 8 + j] : 0u;
-            v = make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16);
-        }
-        return v;
-    };
-    float gamma;
-    if (KNOWN) {
-        gamma = __int_as_float(absmax[m]);
-    } else {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, units = Kp >> 3;
+    auto row_absmax = [&](auto skip_nan) {
         float mx = 0.0f;
-        for (int u = threadIdx.x; u < units; u += QUANT_THREADS) mx = bl_max_pos(mx, bl_absmax8_bf16(ld(u)));
+        for (int u = threadIdx.x; u < units; u += QUANT_THREADS)
+            mx = bl_max_pos(mx, bl_absmax8_bf16<decltype(skip_nan)::value>(bl_row_unit<RAGGED>(x, u, K)));
         mx = bl_wave_max(mx);
         if (lane == 0) smax[w] = mx;
         __syncthreads();
-        gamma = fmaxf(fmaxf(smax[0], smax[1]), fmaxf(smax[2], smax[3]));
-    }
-    const float g = fmaxf(gamma, 1e-5f);
-    const float inv = bl_div_rn(127.0f, g);
+        return bl_max_pos(bl_max_pos(smax[0], smax[1]), bl_max_pos(smax[2], smax[3]));
+    };
+    float g, inv;
     int sum = 0;
-    for (int u = threadIdx.x; u < units; u += QUANT_THREADS) {
-        uint2 o;
-        bl_quant8_words<KNOWN>(ld(u), inv, o.x, o.y);
-        sum = __builtin_amdgcn_sdot4((int)o.x, 0x01010101, sum, false);
-        sum = __builtin_amdgcn_sdot4((int)o.y, 0x01010101, sum, false);
-        *(uint2*)(qo + u * 8) = o;
+    auto quantise = [&](float gamma, auto mode) {
+        g = fmaxf(gamma, 1e-5f);
+        inv = bl_div_rn(127.0f, g);
+        for (int u = threadIdx.x; u < units; u += QUANT_THREADS)
+            sum = bl_quant_unit<decltype(mode)::value>(bl_row_unit<RAGGED>(x, u, K), inv, qo + u * 8, sum);
+    };
+    if (KNOWN) {
+        quantise(__int_as_float(absmax[m]), bl_mode<BL_Q_ANY>{});
+    } else {
+        const float gamma = row_absmax(std::false_type{});
+        if (__builtin_expect(gamma < __builtin_inff(), 1)) {
+            quantise(gamma, bl_mode<BL_Q_FINITE>{});
+        } else {
+            __syncthreads();                  /* smax has been read */
+            quantise(row_absmax(std::true_type{}), bl_mode<BL_Q_ROW>{});
+        }
     }
     sum = bl_wave_sum(sum);
     if (lane == 0) ssum[w] = sum;
@@ -185,49 +205,64 @@ __global__ __launch_bounds__(QUANT_THREADS) void bl_quant_rows_ex(const bl_prod_
     uint4 xv[4];
     float rn = 1.0f;
     if (NORM) rn = bl_norm_produce2(pd, m, K, true, snorm, xv);
+    auto row_max = [&](float mx) {
+        mx = bl_wave_max(mx);
+        if (lane == 0) smax[w] = mx;
+        __syncthreads();
+        return bl_max_pos(bl_max_pos(smax[0], smax[1]), bl_max_pos(smax[2], smax[3]));
+    };
+    int8_t* qo = q + (int64_t)m * K;
+    float g, inv;
+    int sum = 0;
+    auto put = [&](int u, const uint4 lo, const uint4 hi, auto mode) {
+        uint32_t a0, a1, a2, a3;
+        bl_quant8_words<decltype(mode)::value>(lo, inv, a0, a1);
+        bl_quant8_words<decltype(mode)::value>(hi, inv, a2, a3);
+        sum += bl_sum16(a0, a1, a2, a3);
+        *(uint4*)(qo + u * 16) = make_uint4(a0, a1, a2, a3);
+    };
     float mx = 0.0f;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         const int u = tid + j * QUANT_THREADS;
         if (u < groups) {
             if (!NORM) bl_produce16<NORM>(pd, m, u, K, true, rn, xv[2 * j], xv[2 * j + 1]);
-            mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16(xv[2 * j]), bl_absmax8_bf16(xv[2 * j + 1])));
+            mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16<false>(xv[2 * j]), bl_absmax8_bf16<false>(xv[2 * j + 1])));
         }
     }
+    uint4 lo, hi;
     for (int u = tid + 2 * QUANT_THREADS; u < groups; u += QUANT_THREADS) {
-        uint4 lo, hi;
         bl_produce16<NORM>(pd, m, u, K, true, rn, lo, hi);
-        mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16(lo), bl_absmax8_bf16(hi)));
+        mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16<false>(lo), bl_absmax8_bf16<false>(hi)));
     }
-    mx = bl_wave_max(mx);
-    if (lane == 0) smax[w] = mx;
-    __syncthreads();
-    float gamma = smax[0];
+    const float gamma = row_max(mx);
+    if (__builtin_expect(gamma < __builtin_inff(), 1)) {
+        g = fmaxf(gamma, 1e-5f);
+        inv = bl_div_rn(127.0f, g);
 #pragma unroll
-    for (int i = 1; i < QUANT_THREADS / BL_WAVE; ++i) gamma = fmaxf(gamma, smax[i]);
-    const float g = fmaxf(gamma, 1e-5f);
-    const float inv = bl_div_rn(127.0f, g);
-    int8_t* qo = q + (int64_t)m * K;
-    int sum = 0;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int u = tid + j * QUANT_THREADS;
-        if (u < groups) {
-            uint32_t a0, a1, a2, a3;
-            bl_quant8_words(xv[2 * j], inv, a0, a1);
-            bl_quant8_words(xv[2 * j + 1], inv, a2, a3);
-            sum += bl_sum16(a0, a1, a2, a3);
-            *(uint4*)(qo + u * 16) = make_uint4(a0, a1, a2, a3);
+        for (int j = 0; j < 2; ++j) {
+            const int u = tid + j * QUANT_THREADS;
+            if (u < groups) put(u, xv[2 * j], xv[2 * j + 1], bl_mode<BL_Q_FINITE>{});
         }
-    }
-    for (int u = tid + 2 * QUANT_THREADS; u < groups; u += QUANT_THREADS) {
-        uint4 lo, hi;
-        uint32_t a0, a1, a2, a3;
-        bl_produce16<NORM>(pd, m, u, K, false, rn, lo, hi);
-        bl_quant8_words(lo, inv, a0, a1);
-        bl_quant8_words(hi, inv, a2, a3);
-        sum += bl_sum16(a0, a1, a2, a3);
-        *(uint4*)(qo + u * 16) = make_uint4(a0, a1, a2, a3);
+        for (int u = tid + 2 * QUANT_THREADS; u < groups; u += QUANT_THREADS) {
+            bl_produce16<NORM>(pd, m, u, K, false, rn, lo, hi);
+            put(u, lo, hi, bl_mode<BL_Q_FINITE>{});
+        }
+    } else {                                  /* infinite or NaN somewhere: the row once more, with NaN passed over */
+        mx = 0.0f;
+#pragma unroll 1
+        for (int u = tid; u < groups; u += QUANT_THREADS) {
+            bl_produce16<NORM>(pd, m, u, K, false, rn, lo, hi);
+            mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16(lo), bl_absmax8_bf16(hi)));
+        }
+        __syncthreads();                      /* smax has been read */
+        g = fmaxf(row_max(mx), 1e-5f);
+        inv = bl_div_rn(127.0f, g);
+#pragma unroll 1
+        for (int u = tid; u < groups; u += QUANT_THREADS) {
+            bl_produce16<NORM>(pd, m, u, K, false, rn, lo, hi);
+            put(u, lo, hi, bl_mode<BL_Q_ROW>{});
+        }
     }
     sum = bl_wave_sum(sum);
     if (lane == 0) ssum[w] = sum;
