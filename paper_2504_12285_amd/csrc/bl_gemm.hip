@@ -688,13 +688,20 @@ __global__ __launch_bounds__(256, 2) void bl_gemm_ksplit(const uint8_t* __restri
                                                          const int32_t* __restrict__ rowsum, const float* __restrict__ beta,
                                                          const float* __restrict__ scale, int M, int N, int K, int tiles_m,
                                                          int tiles, const float* __restrict__ residual,
-                                                         int32_t* __restrict__ acc, float* __restrict__ y) {
+                                                         int32_t* __restrict__ acc, float* __restrict__ y,
+                                                         long long* __restrict__ stamps) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];      /* [wave][stage] */
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int l32 = lane & 31, h = lane >> 5;
     /* workgroup L runs on XCD L % 8: each XCD takes one eighth of the tiles, row tiles fastest */
     const int share = (tiles + 7) >> 3, at = ((int)blockIdx.x & 7) * share + ((int)blockIdx.x >> 3);
-    if (((int)blockIdx.x >> 3) >= share || at >= tiles) return;         /* the whole workgroup */
+    if (((int)blockIdx.x >> 3) >= share || at >= tiles) return;         /* the whole workgroup (never workgroup 0) */
+    const bool stamp = stamps != nullptr && blockIdx.x == 0;            /* measurement hook, as in bl_gemm_tile256 */
+    long long c_start = 0, w_start = 0;
+    if (stamp) {
+        c_start = clock64();
+        w_start = wall_clock64();
+    }
     const int tn = at / tiles_m, tm = at - tn * tiles_m, m0 = tm * 64, n0 = tn * 32;
     const int steps = (K + G3_BK - 1) / G3_BK;
     const bool half = (K & 64) != 0;
@@ -796,6 +803,10 @@ __global__ __launch_bounds__(256, 2) void bl_gemm_ksplit(const uint8_t* __restri
             }
         }
     }
+    if (stamp && threadIdx.x == 0) {
+        stamps[0] = clock64() - c_start;
+        stamps[1] = wall_clock64() - w_start;
+    }
 }
 
 template <int LAYOUT>
@@ -810,7 +821,8 @@ static bl_status launch_ksplit(const uint8_t* packed, const float* beta, const i
         attr_set.store(true, std::memory_order_release);
     }
     const int tiles_m = (m + 63) / 64, tiles = tiles_m * ((n + 31) / 32);
-    kern<<<(tiles + 7) / 8 * 8, 256, lds, st>>>(packed, q, rowsum, beta, scale, m, n, k, tiles_m, tiles, residual, acc, y);
+    kern<<<(tiles + 7) / 8 * 8, 256, lds, st>>>(packed, q, rowsum, beta, scale, m, n, k, tiles_m, tiles, residual, acc, y,
+                                                 (long long*)bl_clock_stamps());
     return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
 }
 
