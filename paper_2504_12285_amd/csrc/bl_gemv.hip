@@ -744,7 +744,8 @@ static bl_status launch_mma_l(int L, const bl_gemv_group& grp, int M, int blocks
  * scheme (the caller then uses the prefill kernel). */
 bl_status bl_gemv_launch_group(bl_gemv_group& grp, int M, hipStream_t st) {
     const int forced = bl_forced_decode_path();   /* 0 default, 1 dot4, 2 row-resident, 3 panel */
-    if (!forced && M == 1 && grp.count == 1) return bl_gemv_one_launch(grp.p[0], st);
+    bl_status one;
+    if (!forced && M == 1 && grp.count == 1 && bl_gemv_one_launch(grp.p[0], st, &one)) return one;
     bool any_norm = false, any_fused = false;
     for (int i = 0; i < grp.count; ++i) {
         any_norm = any_norm || (grp.p[i].fused && grp.p[i].prod.norm);

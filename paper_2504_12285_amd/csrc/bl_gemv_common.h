@@ -57,5 +57,6 @@ __device__ __forceinline__ bl_gemv_prob bl_fetch_prob(const bl_gemv_group& grp) 
  * the group out over workgroups and launches them. */
 bl_status bl_gemv_panel_launch(bl_gemv_group& grp, int M, hipStream_t st);
 
-/* One token and one product, K <= 8192 (bl_gemv_one.hip). */
-bl_status bl_gemv_one_launch(const bl_gemv_prob& P, hipStream_t st);
+/* One token and one product, K <= 8192 (bl_gemv_one.hip): launches it, or returns false for the sizes
+ * that the general kernels do better. */
+bool bl_gemv_one_launch(const bl_gemv_prob& P, hipStream_t st, bl_status* status);

@@ -406,13 +406,33 @@ static void launch_one(const bl_one_args& A, int src, bool norm, hipStream_t st)
     }
 }
 
+/* Which single products of one token this kernel takes; the others go to bl_gemv_rows.  Ratios: time here over
+ * time there, both layouts, bf16 and int8 inputs / normalised rows, 22 widths x 16 lengths.
+ *   N <= 4096 (one or two row groups to a wave): 0.73 - 1.01 / 0.64 - 0.80: all.
+ *   N = 4097 .. 4351 and 8193 .. 8447 (a 17th row to a workgroup, a 257th workgroup): 0.93 - 1.16 / 0.71 - 0.89.
+ *   K > 4096 (32 lanes to a row), other N: 0.67 - 1.04 / 0.59 - 0.91: all.
+ *   K <= 4096, N = 16385 .. 24576 (257 .. 384 workgroups of 64 rows): 0.88 - 1.45 / 0.60 - 1.09, from K = 1025 on 0.60 - 1.05.
+ *   K <= 4096, other N: 0.43 - 0.92 normalised: all; bf16 and int8 up to K = 2048 0.77 - 1.44: none; K = 2049 .. 3072
+ *   0.75 - 1.03 (below N = 8193 from K = 2305 on; 1.0 - 1.06 before); K = 3073 .. 4096 0.78 - 1.07 beyond N = 8192,
+ *   0.94 - 1.16 below. */
+static bool one_token_kernel(int N, int K, bool norm) {
+    if (N <= 4096) return true;
+    if (!norm && N < 8448 && N % 4096 > 0 && N % 4096 < 256) return false;
+    if (K > 4096) return true;
+    if (N > 16384 && N <= 24576) return norm && K > 1024;
+    if (norm) return true;
+    if (N <= 8192) return K > 2304 && K <= 3072;
+    return K > 2048;
+}
+
 /* One token, one product, K <= 8192: one workgroup per compute unit (256) while the rows last.  Four
  * waves, one per SIMD: what every wave does for itself (reductions, the factor of the normalisation, the
  * reciprocal) is a third of the instructions, and with eight or sixteen waves the SIMDs do it two and
  * four times.  Sixteen lanes to a weight row (K <= 4096) or 32: at K = 2560 a row is 40 loads of 16 bytes, 40 of
  * 48 slots. */
-bl_status bl_gemv_one_launch(const bl_gemv_prob& P, hipStream_t st) {
+bool bl_gemv_one_launch(const bl_gemv_prob& P, hipStream_t st, bl_status* status) {
     const bl_prod_dev& d = P.prod;
+    if (!one_token_kernel(P.N, P.K, P.fused && d.norm)) return false;
     bl_one_args A = {};
     A.packed = P.packed; A.beta = P.beta; A.residual = P.residual; A.acc = P.acc; A.y = P.y;
     A.N = P.N; A.K = P.K; A.layout = P.layout;
@@ -451,5 +471,6 @@ bl_status bl_gemv_one_launch(const bl_gemv_prob& P, hipStream_t st) {
         else if (P.K <= 7168) launch_one<32, 4, 4, 7>(A, src, norm, st);
         else launch_one<32, 4, 4, 8>(A, src, norm, st);
     }
-    return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
+    *status = hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
+    return true;
 }

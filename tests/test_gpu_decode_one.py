@@ -38,7 +38,10 @@ def _both(bl, make, outs):
 
 
 SIZES = [(1, 64), (7, 128), (9, 960), (2048, 64), (2049, 3072), (4096, 3136), (4097, 4096), (300, 4160), (4100, 7168),
-         (600, 7232), (4200, 8192), (16385, 256), (16390, 4096), (8200, 5120)]
+         (600, 7232), (4200, 8192), (16385, 256), (16390, 4096), (8200, 5120),
+         # the edges of the ranges that go to this kernel
+         (4097, 2368), (4352, 2304), (4352, 2368), (8192, 3072), (8192, 3136), (8448, 2112), (8448, 3136), (8449, 4160), (16384, 4096),
+         (16385, 3072), (24576, 1024), (24577, 3136)]
 
 
 @pytest.mark.parametrize("N,K", SIZES)
