@@ -826,6 +826,221 @@ static bl_status launch_ksplit(const uint8_t* packed, const float* beta, const i
     return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
 }
 
+#define GEMM_THREADS 256
+#define GEMM_PAD 16   /* bytes of padding per activation row in LDS (bank spread) */
+
+/* ---- register-staged kernel: launches bound by their output --------------------------------
+ * One workgroup per tile and plain stores: where the k loop is short against the output, or rows of the
+ * output do not start on whole cache lines, it writes faster than the tile kernels above (which are
+ * faster everywhere else; the rule is staged_is_faster below).
+ * Block tile BM x BN, k step BK (64 or 128), four waves arranged WGM x WGN.
+ * LDS is double buffered: while the matrix cores work on buffer b, the next
+ * k step travels global -> registers -> buffer 1-b; one barrier per k step.
+ *   A buffer: BM rows x (BK + pad) int8 activations.
+ *   W buffer: BN rows x (BK/16 + 1) packed words (16 weights each).
+ * Operand mapping of v_mfma_i32_32x32x32_i8: lane l supplies 16 consecutive k
+ * (offset 16*(l/32)) of row l%32 for both operands; a packed word expands to
+ * exactly those 16 int8 (layout 1), so one ds_read_b32 feeds one B operand. */
+template <int BM, int BN, int BK, int WGM, int LAYOUT>
+__global__ __launch_bounds__(GEMM_THREADS) void bl_gemm_mfma(const uint8_t* __restrict__ packed,
+                                                              const int8_t* __restrict__ q,
+                                                              const int32_t* __restrict__ rowsum,
+                                                              const float* __restrict__ beta,
+                                                              const float* __restrict__ scale, int M, int N, int K,
+                                                              int32_t* __restrict__ acc, float* __restrict__ y,
+                                                              long long* __restrict__ stamps) {
+    constexpr int WGN = 4 / WGM;
+    constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NI = WN / 32;
+    constexpr int KS = BK / 32;                       /* MFMA k sub-steps per k step  */
+    constexpr int A_STRIDE = BK + GEMM_PAD;           /* bytes                        */
+    constexpr int W_WORDS = BK / 16;                  /* packed words per row, k step */
+    constexpr int W_STRIDE = W_WORDS + 1;             /* dwords                       */
+    constexpr int A_UPR = BK / 16;                    /* 16-byte units per A row      */
+    constexpr int A_UNITS = BM * A_UPR / GEMM_THREADS;
+    constexpr int W_UPR = BK / 64;                    /* 16-byte units per W row      */
+    constexpr int W_UNITS = (BN * W_UPR + GEMM_THREADS - 1) / GEMM_THREADS;
+    static_assert(BM * A_UPR % GEMM_THREADS == 0, "A tile must split evenly");
+    static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile must be a multiple of 32");
+
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    constexpr int A_BYTES = BM * A_STRIDE;
+    constexpr int W_BYTES = BN * W_STRIDE * 4;
+    auto As = [&](int b) { return smem + b * A_BYTES; };
+    auto Ws = [&](int b) { return (uint32_t*)(smem + 2 * A_BYTES + b * W_BYTES); };
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;
+    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
+    const int l32 = lane & 31, h = lane >> 5;
+    const int kb = K / 4;
+    const bool stamp = stamps != nullptr && blockIdx.x == 0 && blockIdx.y == 0;   /* measurement hook, as in bl_gemm_tile256 */
+    long long c_start = 0, w_start = 0;
+    if (stamp) {
+        c_start = clock64();
+        w_start = wall_clock64();
+    }
+
+    bl_v16i C[MI][NI];
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) C[mi][ni][v] = 0;
+
+    uint4 areg[A_UNITS];
+    uint4 wreg[W_UNITS];
+    const uint8_t* aptr[A_UNITS];
+    const uint8_t* wptr[W_UNITS];
+#pragma unroll
+    for (int i = 0; i < A_UNITS; ++i) {
+        const int u = tid + i * GEMM_THREADS, row = u / A_UPR, c = u % A_UPR;
+        int m = m0 + row;
+        if (m >= M) m = M - 1;
+        aptr[i] = (const uint8_t*)q + (int64_t)m * K + c * 16;
+    }
+#pragma unroll
+    for (int i = 0; i < W_UNITS; ++i) {
+        const int u = tid + i * GEMM_THREADS, row = u / W_UPR, c = u % W_UPR;
+        int n = n0 + row;
+        if (n >= N) n = N - 1;
+        wptr[i] = packed + (int64_t)n * kb + c * 16;
+    }
+
+    auto load_tiles = [&](int kk) {
+#pragma unroll
+        for (int i = 0; i < A_UNITS; ++i) areg[i] = *(const uint4*)(aptr[i] + (int64_t)kk * BK);
+#pragma unroll
+        for (int i = 0; i < W_UNITS; ++i)
+            if (tid + i * GEMM_THREADS < BN * W_UPR) wreg[i] = *(const uint4*)(wptr[i] + (int64_t)kk * (BK / 4));
+    };
+    auto store_tiles = [&](int b) {
+#pragma unroll
+        for (int i = 0; i < A_UNITS; ++i) {
+            const int u = tid + i * GEMM_THREADS, row = u / A_UPR, c = u % A_UPR;
+            uint32_t a0 = areg[i].x, a1 = areg[i].y, a2 = areg[i].z, a3 = areg[i].w;
+            if (LAYOUT == 0) bl_transpose4x4(a0, a1, a2, a3);
+            *(uint4*)(As(b) + row * A_STRIDE + c * 16) = make_uint4(a0, a1, a2, a3);
+        }
+#pragma unroll
+        for (int i = 0; i < W_UNITS; ++i) {
+            const int u = tid + i * GEMM_THREADS, row = u / W_UPR, c = u % W_UPR;
+            if (u < BN * W_UPR) {
+                uint32_t* d = Ws(b) + row * W_STRIDE + c * 4;
+                d[0] = wreg[i].x; d[1] = wreg[i].y; d[2] = wreg[i].z; d[3] = wreg[i].w;
+            }
+        }
+    };
+
+    const int steps = K / BK;
+    load_tiles(0);
+    store_tiles(0);
+    __syncthreads();
+    for (int kk = 0; kk < steps; ++kk) {
+        const int b = kk & 1;
+        if (kk + 1 < steps) load_tiles(kk + 1);
+        const uint8_t* Ab = As(b) + (wm0 + l32) * A_STRIDE + h * 16;
+        const uint32_t* Wb = Ws(b) + (wn0 + l32) * W_STRIDE + h;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            bl_v4i a[MI];
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi) a[mi] = *(const bl_v4i*)(Ab + mi * 32 * A_STRIDE + ks * 32);
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) {
+                const uint32_t p = Wb[ni * 32 * W_STRIDE + ks * 2];
+                bl_v4i bop;
+                bop[0] = (int)(p & 0x03030303u);
+                bop[1] = (int)((p >> 2) & 0x03030303u);
+                bop[2] = (int)((p >> 4) & 0x03030303u);
+                bop[3] = (int)((p >> 6) & 0x03030303u);
+#pragma unroll
+                for (int mi = 0; mi < MI; ++mi)
+                    C[mi][ni] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[mi], bop, C[mi][ni], 0, 0, 0);
+            }
+        }
+        if (kk + 1 < steps) store_tiles(b ^ 1);
+        __syncthreads();
+    }
+
+    /* Epilogue: per-row terms through LDS once (see bl_gemm_tile256). */
+    bl_mfma_fence();
+    __syncthreads();
+    int* rs_s = (int*)smem;
+    float* cf_s = (float*)(smem + BM * 4);
+    for (int i = tid; i < BM; i += GEMM_THREADS) {
+        const int m = m0 + i;
+        rs_s[i] = m < M ? rowsum[m] : 0;
+        cf_s[i] = (y && m < M) ? *beta * scale[m] : 0.0f;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int ml = wm0 + mi * 32 + (v >> 2) * 8 + h * 4 + (v & 3);
+            const int m = m0 + ml;
+            if (m < M) {
+                const int rs = rs_s[ml];
+                const float c = cf_s[ml];
+#pragma unroll
+                for (int ni = 0; ni < NI; ++ni) {
+                    const int n = n0 + wn0 + ni * 32 + l32;
+                    if (n < N) {
+                        const int val = C[mi][ni][v] - rs;
+                        if (acc) acc[(int64_t)m * N + n] = val;
+                        if (y) {
+                            const float t = (float)val * c;
+                            y[(int64_t)m * N + n] = t;
+                        }
+                    }
+                }
+            }
+        }
+    if (stamp && tid == 0) {
+        stamps[0] = clock64() - c_start;
+        stamps[1] = wall_clock64() - w_start;
+    }
+}
+
+template <int BK, int LAYOUT>
+static bl_status launch_staged(const uint8_t* packed, const float* beta, const int8_t* q, const float* scale,
+                               const int32_t* rowsum, int M, int N, int K, int32_t* acc, float* y, hipStream_t st) {
+    constexpr size_t lds = 2 * (size_t)(128 * (BK + GEMM_PAD) + 128 * (BK / 16 + 1) * 4);
+    static_assert(lds <= 64 * 1024, "no attribute needed");
+    const dim3 grid((unsigned)((N + 127) / 128), (unsigned)((M + 127) / 128));
+    bl_gemm_mfma<128, 128, BK, 2, LAYOUT><<<grid, GEMM_THREADS, lds, st>>>(packed, q, rowsum, beta, scale, M, N, K, acc, y,
+                                                                           (long long*)bl_clock_stamps());
+    return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
+}
+
+/* Whether a product in layout 0, or with a half last k step (layout 1 with K % 128 == 0 was never measured
+ * here), is faster on the register-staged kernel.  Measured over 32 shapes x 20 lengths, both layouts; time of the
+ * tile kernels over its time, in the ranges that it takes / just outside:
+ *   residual given: 0.16 - 0.93, never.  At most 160 tiles of 64 x 128 (split k loop): 0.18 - 0.6, never.
+ *   int32 and fp32 outputs, up to 400 tiles of 128 x 128: K <= 256 0.98 - 1.12 / 0.93 - 1.04;  to 768 tiles: half
+ *   steps to K = 3072 0.93 - 1.39 / 0.9 - 1.05, whole ones at every K 1.02 - 1.36;  beyond: half steps to K = 1024
+ *   (1152 where N % 16 != 0) 0.84 - 1.46 / 0.8 - 1.09, whole ones to 3072 0.92 - 1.4 / 0.94 - 1.06.
+ *   int32 output alone, 401 .. 768 tiles: K <= 512 (640 where N % 16 != 0) 1.0 - 1.19 / 0.95 - 1.08.
+ *   fp32 output alone, more than 400 tiles: K <= 64 (128 beyond 768 tiles) 0.83 - 1.11 / 0.9 - 1.08; where the
+ *   output's rows do not start on 64 bytes (N % 16 != 0) the non-temporal stores of the tile kernels write lines in
+ *   parts: K <= 640 (1152 where N % 4 != 0) 0.79 - 1.66, and for 513 .. 768 tiles, a second round of the deferred
+ *   stores, K <= 3072 0.96 - 1.37 / 0.98 - 1.05; rows on 64 but not on 128 bytes, beyond 768 tiles: K <= 256 1.0 - 1.12. */
+static bool staged_is_faster(int m, int n, int k, bool acc, bool y, bool residual) {
+    if (residual || m > 65535 * 128 || (int64_t)((m + 63) / 64) * ((n + 127) / 128) <= KS_MAX_TILES) return false;
+    const int64_t tiles = (int64_t)((m + 127) / 128) * ((n + 127) / 128);
+    const bool half = k % G3_BK != 0, many = tiles > 768, parts = n % 16 != 0;
+    if (acc && y) {
+        if (tiles <= 400) return k <= 256;
+        if (many) return k <= (!half ? 3072 : parts ? 1152 : 1024);
+        return !half || k <= 3072;
+    }
+    if (tiles <= 400) return false;
+    if (acc) return !many && k <= (parts ? 640 : 512);
+    if (parts) return k <= (tiles > 512 && !many ? 3072 : n % 4 != 0 ? 1152 : 640);
+    return k <= (!many ? 64 : n % 32 != 0 ? 256 : 128);
+}
+
 /* rowsum[m] = sum_k q[m][k]; one wave per row. */
 __global__ __launch_bounds__(256) void bl_rowsum_kernel(const int8_t* __restrict__ q, int M, int K,
                                                          int32_t* __restrict__ rowsum) {
@@ -860,18 +1075,26 @@ __global__ __launch_bounds__(256) void bl_rowsum_kernel(const int8_t* __restrict
  * Deferred stores mean two workgroups per CU instead of three: between 512 and 768 tiles that is a second
  * round, which long rows do not win back (4096 x 6912 -> 2560 83.3 us against 78.6 in one round, 4096 x 6976
  * 93.4 / 83.6, 3000 x 4096 -> 3200 51.8 / 49.9) and short ones do (4096 x 2560 -> 2560 37.4 / 37.4, 3500 x 2048 ->
- * 3400 34.6 / 39.7, 2816 x 1024 -> 3840 19.4 / 21.9). */
+ * 3400 34.6 / 39.7, 2816 x 1024 -> 3840 19.4 / 21.9); over eight shapes of 546 to 756 tiles, one round against two:
+ * K = 2048 0.96 - 1.14 times the time, 2560 0.93 - 1.12, 3072 0.92 - 1.09, 3584 0.91 - 1.04, 4096 0.91 - 1.02, 4608 0.90 - 1.01.
+ * Layout 0, whose words are turned in the k loop, loses
+ * with two workgroups for every long row: 4096 x 6912 -> 13824 422 us deferred, 390 at once, 4096 x 4096 ->
+ * 13824 263 / 245, 2048 x 4096 -> 7000 equal. */
 template <bool HALF, int LAYOUT>
 static bl_status launch_plain(const uint8_t* packed, const float* beta, const int8_t* q, const float* scale,
                               const int32_t* rowsum, int m, int n, int k, const float* residual, int32_t* acc, float* y,
                               hipStream_t st) {
+    if constexpr (HALF || LAYOUT == 0) {
+        if (staged_is_faster(m, n, k, acc != nullptr, y != nullptr, residual != nullptr))
+            return launch_staged<HALF ? 64 : 128, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, acc, y, st);
+    }
     if ((int64_t)((m + 63) / 64) * ((n + 127) / 128) <= KS_MAX_TILES)
         return launch_ksplit<LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
     if ((int64_t)((m + 127) / 128) * ((n + 127) / 128) <= 400)
         return launch_tile256_t<64, 128, 2, 1, 4, 0, false, HALF, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
     const int64_t tiles = (int64_t)((m + 127) / 128) * ((n + 127) / 128);
     const bool one_round = tiles > 512 && tiles <= 768 && k >= 4096;
-    if (!one_round && !acc && !residual && (int64_t)m * n < ((int64_t)1 << 30))
+    if (!one_round && !(LAYOUT == 0 && k >= 4096) && !acc && !residual && (int64_t)m * n < ((int64_t)1 << 30))
         return launch_tile256_t<128, 128, 2, 2, 2, 0, true, HALF, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
     return launch_tile256_t<128, 128, 2, 2, 2, 0, false, HALF, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
 }
