@@ -270,7 +270,9 @@ __global__ __launch_bounds__(256) void bl_gemv_rows(const bl_gemv_group grp) {
  * next phase are in flight during the products of the current one.  Fused
  * inputs: produced, quantised and staged whole, one token at a time.
  * Dynamic LDS: BL_MMA_HEAD ints, then max(M*(row+16), MT*4096) bytes. */
-template <int L, int MT, bool NEED_SUM, bool NORM>
+/* FUSED: some product of the group has a fused input.  Without one the kernel is half as long; carrying the
+ * fused path along cost int8 calls 2 - 13 % (2560 x 2560, 16 tokens: 5.72 us with it, 5.24 without; 8 tokens 5.08 / 4.45). */
+template <int L, int MT, bool NEED_SUM, bool NORM, bool FUSED>
 __global__ __launch_bounds__(256) void bl_gemv_mma(const bl_gemv_group grp, const int M, const int LF, const int budget) {
     extern __shared__ int lds[];
     const bl_gemv_prob P = bl_fetch_prob(grp);
@@ -282,7 +284,7 @@ __global__ __launch_bounds__(256) void bl_gemv_mma(const bl_gemv_group grp, cons
     const int n = ((int)blockIdx.x - P.block0) * rows_per_block + rg * 16 + c;
     const bool row_ok = n < N;
     const int groups = K / 16;
-    const bool fused = P.fused != 0;
+    const bool fused = FUSED && P.fused != 0;
     /* int8 inputs: everything at once when M rows of K fit the LDS budget, else two
      * buffers of PK = 1024 << LF columns (the launcher sized LF so that a phase is 64
      * (token, 1024-column) pieces: 16 loads per wave) */
@@ -697,27 +699,33 @@ static bl_status launch_mma(const bl_gemv_group& grp, int M, int blocks, hipStre
     int LF = 0;
     while ((M << (LF + 1)) <= 64 && 2 * (size_t)M * ((1024 << (LF + 1)) + BL_MMA_PAD) <= (size_t)budget) ++LF;
     bool have_sums = true;   /* every product brings its own row sums */
+    bool any_fused = false;
     size_t rows = (size_t)MT * 4096;
     for (int i = 0; i < grp.count; ++i) {
         const bl_gemv_prob& P = grp.p[i];
         if (P.fused || !P.rowsum) have_sums = false;
+        any_fused = any_fused || P.fused;
         size_t need = (size_t)M * (P.K + BL_MMA_PAD);
         if (!P.fused && need > (size_t)budget) need = 2 * (size_t)M * ((1024 << LF) + BL_MMA_PAD);
         if (need > rows) rows = need;
     }
     const size_t lds = rows + BL_MMA_HEAD * 4;
-    /* normalising producers are fused inputs: those never bring row sums */
-    auto kern = NORM ? bl_gemv_mma<L, MT, true, NORM>
-                     : (have_sums ? bl_gemv_mma<L, MT, false, false> : bl_gemv_mma<L, MT, true, false>);
+    /* fused inputs never bring row sums and have at most 16 tokens (MT = 1) */
+    if (any_fused && MT > 1) return BL_ERR_SHAPE;
+    auto kern = have_sums ? bl_gemv_mma<L, MT, false, false, false> : bl_gemv_mma<L, MT, true, false, false>;
+    if constexpr (MT == 1) {
+        if (NORM || any_fused) kern = bl_gemv_mma<L, MT, true, NORM, true>;
+    }
     if (lds > 160 * 1024) return BL_ERR_SHAPE;
     if (lds > 64 * 1024) {
         /* (two threads may both set the attribute: the call is idempotent) */
-        static std::atomic<bool> done[2];
-        if (!done[have_sums].load(std::memory_order_acquire)) {
+        static std::atomic<bool> done[3];
+        const int variant = any_fused ? 2 : have_sums;
+        if (!done[variant].load(std::memory_order_acquire)) {
             if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) !=
                 hipSuccess)
                 return BL_ERR_HIP;
-            done[have_sums].store(true, std::memory_order_release);
+            done[variant].store(true, std::memory_order_release);
         }
     }
     kern<<<blocks, 256, lds, st>>>(grp, M, LF, budget);
