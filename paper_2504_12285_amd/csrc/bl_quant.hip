@@ -8,7 +8,6 @@
 #include "bl_producer.h"
 
 #define QUANT_THREADS 256
-#define QUANT_WAVE_ROWS 1024
 
 /* Unit u (eight elements) of a bf16 row: zeros behind K (RAGGED: inside the unit too). */
 template <bool RAGGED>
@@ -170,9 +169,11 @@ template <bool RAGGED, bool KNOWN>
 static bl_status launch_quant(const uint16_t* X, int64_t M64, int64_t K64, int* absmax, int8_t* q, float* scale,
                               int32_t* rowsum, hipStream_t st) {
     const int M = (int)M64, K = (int)K64, Kp = (int)bl_kpad(K64);
-    /* A row is one wave's work when the rows alone fill the chip (256 CUs, four waves each), else four
-     * waves share it: with few rows a wave's own chain of instructions is what takes the time. */
-    const bool wave_rows = M >= QUANT_WAVE_ROWS;
+    /* A row is one wave's work when the rows alone fill the chip, else four waves share it: with few rows, or
+     * long ones, a wave's own chain of instructions is what takes the time.  One wave against four, 18 heights: K <= 1024
+     * from 1024 rows on 0.51 - 0.97, K = 2048 0.85 - 1.0; K = 2560 .. 4096 below 2048 rows 0.95 - 1.25, from 2048 on
+     * 0.86 - 1.06; K = 4160 .. 8192 0.94 - 1.46: never. */
+    const bool wave_rows = Kp <= 2048 ? M >= 1024 : Kp <= 4096 && M >= 2048;
     const unsigned b4 = (unsigned)((M + 3) / 4), b1 = (unsigned)M;
     if (Kp > 8192)
         bl_quant_long<RAGGED, KNOWN><<<b1, QUANT_THREADS, 0, st>>>(X, K, Kp, absmax, q, scale, rowsum);
@@ -182,10 +183,8 @@ static bl_status launch_quant(const uint16_t* X, int64_t M64, int64_t K64, int* 
         bl_quant_rows<256, 4, RAGGED, KNOWN><<<b1, QUANT_THREADS, 0, st>>>(X, M, K, Kp, absmax, q, scale, rowsum);
     else if (Kp <= 2048)
         bl_quant_rows<64, 4, RAGGED, KNOWN><<<b4, QUANT_THREADS, 0, st>>>(X, M, K, Kp, absmax, q, scale, rowsum);
-    else if (Kp <= 4096)
-        bl_quant_rows<64, 8, RAGGED, KNOWN><<<b4, QUANT_THREADS, 0, st>>>(X, M, K, Kp, absmax, q, scale, rowsum);
     else
-        bl_quant_rows<64, 16, RAGGED, KNOWN><<<b4, QUANT_THREADS, 0, st>>>(X, M, K, Kp, absmax, q, scale, rowsum);
+        bl_quant_rows<64, 8, RAGGED, KNOWN><<<b4, QUANT_THREADS, 0, st>>>(X, M, K, Kp, absmax, q, scale, rowsum);
     return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
 }
 

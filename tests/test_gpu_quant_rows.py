@@ -21,7 +21,8 @@ def bl():
 
 
 @pytest.mark.parametrize("M,K", [(1023, 64), (1024, 64), (1025, 7), (1024, 2048), (1024, 2049), (1027, 4096), (1024, 4104),
-                                 (1024, 8191), (1024, 8192), (7, 4096), (7, 4097), (7, 8192), (3, 8256), (1030, 8200)])
+                                 (1024, 8191), (1024, 8192), (7, 4096), (7, 4097), (7, 8192), (3, 8256), (1030, 8200),
+                                 (2047, 2049), (2048, 2049), (2049, 4096), (2050, 4040), (2048, 4097)])
 def test_quant_rows_at_the_edges_of_the_split(bl, M, K):
     X = synth.activations_bf16(31 + K, M, K)
     q_o, s_o, r_o = oracle.quant_act(X)
@@ -31,7 +32,7 @@ def test_quant_rows_at_the_edges_of_the_split(bl, M, K):
     assert np.array_equal(r.cpu().numpy(), r_o)
 
 
-@pytest.mark.parametrize("M,K", [(5, 2560), (1026, 2560), (1024, 6912), (3, 8256)])
+@pytest.mark.parametrize("M,K", [(5, 2560), (1026, 2560), (1024, 6912), (3, 8256), (2050, 2112)])
 def test_quant_with_given_row_maxima(bl, M, K):
     X = synth.activations_bf16(77 + K, M, K)
     Xd = to_dev(X)
