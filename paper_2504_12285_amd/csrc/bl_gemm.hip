@@ -576,19 +576,38 @@ struct bl_epi_args {
     int* absmax;
 };
 
+/* Workgroups of a kernel that are resident at once (a multiple of 8 keeps a workgroup on its XCD's region), 0 on
+ * error; asked once, together with the attribute that its LDS needs. */
+template <int BM, int BN, int STAGES, int WM, int WN, int EPI, bool DEFER, bool HALF, int LAYOUT>
+struct bl_tile256_launch {
+    static constexpr int lds = STAGES * (BM * G3_BK + BN * G3_BK / 4) + BM * 8 * (DEFER ? 2 : 1);
+    static int resident() {
+        static std::atomic<int> cached{0};
+        int blocks = cached.load(std::memory_order_acquire);
+        if (blocks > 0) return blocks;
+        const auto kern = bl_gemm_tile256<BM, BN, STAGES, WM, WN, EPI, false, DEFER, HALF, LAYOUT>;
+        int dev = 0, cus = 0, per_cu = 0;
+        if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess ||
+            hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kern, WM * WN * 64, lds) != hipSuccess ||
+            cus < 1 || per_cu < 1)
+            return 0;
+        blocks = cus * per_cu / 8 * 8;
+        if (blocks < 8) blocks = 8;
+        cached.store(blocks, std::memory_order_release);
+        return blocks;
+    }
+};
+
 template <int BM, int BN, int STAGES, int WM, int WN, int EPI = 0, bool DEFER = false, bool HALF = false, int LAYOUT = 1>
 static bl_status launch_tile256_t(const uint8_t* packed, const float* beta, const int8_t* q, const float* scale,
                                   const int32_t* rowsum, int M, int N, int K, const float* residual,
                                   int32_t* acc, float* y, hipStream_t st, bl_epi_args ep = bl_epi_args{nullptr, nullptr}) {
     constexpr int G3_BM = BM;
-    constexpr int lds = STAGES * (BM * G3_BK + BN * G3_BK / 4) + BM * 8 * (DEFER ? 2 : 1);
-    auto kern = bl_gemm_tile256<BM, BN, STAGES, WM, WN, EPI, false, DEFER, HALF, LAYOUT>;
-    static std::atomic<bool> attr_set;
-    if (!attr_set.load(std::memory_order_acquire)) {
-        if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
-            return BL_ERR_HIP;
-        attr_set.store(true, std::memory_order_release);
-    }
+    using L = bl_tile256_launch<BM, BN, STAGES, WM, WN, EPI, DEFER, HALF, LAYOUT>;
+    int blocks = L::resident();                          /* a persistent grid */
+    if (blocks == 0) return BL_ERR_HIP;
     /* the gate epilogue's tile holds 64 gate rows and the 64 matching up rows: N/2 / 64 column tiles */
     const int tiles_m = (M + G3_BM - 1) / G3_BM, tiles_n = EPI == 2 ? (N / 2 + BN / 2 - 1) / (BN / 2) : (N + BN - 1) / BN;
     if ((int64_t)tiles_m * tiles_n > ((int64_t)1 << 30)) return BL_ERR_SHAPE;   /* (outputs beyond 2^43 values) */
@@ -611,23 +630,9 @@ static bl_status launch_tile256_t(const uint8_t* packed, const float* beta, cons
         gm = 0;
         vgrid = 8 * share;
     }
-    /* persistent grid: what is resident at once (a multiple of 8 keeps a workgroup on its XCD's region) */
-    static std::atomic<int> resident{0};
-    int blocks = resident.load(std::memory_order_acquire);
-    if (blocks == 0) {
-        int dev = 0, cus = 0, per_cu = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kern, WM * WN * 64, lds) != hipSuccess ||
-            cus < 1 || per_cu < 1)
-            return BL_ERR_HIP;
-        blocks = cus * per_cu / 8 * 8;
-        if (blocks < 8) blocks = 8;
-        resident.store(blocks, std::memory_order_release);
-    }
     if (blocks > vgrid) blocks = vgrid;
-    kern<<<blocks, WM * WN * 64, lds, st>>>(packed, q, rowsum, beta, scale, M, N, K, tiles_m, tiles_n, gm, band, vgrid,
-                                            residual, acc, y, ep.xb, ep.absmax, (long long*)bl_clock_stamps(), nullptr, nullptr, 0, nullptr, nullptr);
+    bl_gemm_tile256<BM, BN, STAGES, WM, WN, EPI, false, DEFER, HALF, LAYOUT><<<blocks, WM * WN * 64, L::lds, st>>>(
+        packed, q, rowsum, beta, scale, M, N, K, tiles_m, tiles_n, gm, band, vgrid, residual, acc, y, ep.xb, ep.absmax, (long long*)bl_clock_stamps(), nullptr, nullptr, 0, nullptr, nullptr);
     return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
 }
 
@@ -1072,7 +1077,7 @@ __global__ __launch_bounds__(256) void bl_rowsum_kernel(const int8_t* __restrict
  * fp32 output alone: the stores of a tile travel during the workgroup's next tile (measured at M = 2048 /
  * 8192: the 13824-wide shape 77 - 80 us against 86 - 90, 297 - 308 against 317 - 327; the 64 x 128 kernel
  * with deferred stores loses: it has under one tile per workgroup on the shapes it serves).
- * Deferred stores mean two workgroups per CU instead of three: between 512 and 768 tiles that is a second
+ * Deferred stores mean two workgroups per CU instead of three: between 512 and 768 tiles (what is resident) that is a second
  * round, which long rows do not win back (4096 x 6912 -> 2560 83.3 us against 78.6 in one round, 4096 x 6976
  * 93.4 / 83.6, 3000 x 4096 -> 3200 51.8 / 49.9) and short ones do (4096 x 2560 -> 2560 37.4 / 37.4, 3500 x 2048 ->
  * 3400 34.6 / 39.7, 2816 x 1024 -> 3840 19.4 / 21.9); over eight shapes of 546 to 756 tiles, one round against two:
@@ -1093,7 +1098,10 @@ static bl_status launch_plain(const uint8_t* packed, const float* beta, const in
     if ((int64_t)((m + 127) / 128) * ((n + 127) / 128) <= 400)
         return launch_tile256_t<64, 128, 2, 1, 4, 0, false, HALF, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
     const int64_t tiles = (int64_t)((m + 127) / 128) * ((n + 127) / 128);
-    const bool one_round = tiles > 512 && tiles <= 768 && k >= 4096;
+    const int two_rounds = bl_tile256_launch<128, 128, 2, 2, 2, 0, true, HALF, LAYOUT>::resident();
+    const int one = bl_tile256_launch<128, 128, 2, 2, 2, 0, false, HALF, LAYOUT>::resident();
+    if (two_rounds == 0 || one == 0) return BL_ERR_HIP;
+    const bool one_round = tiles > two_rounds && tiles <= one && k >= 4096;
     if (!one_round && !(LAYOUT == 0 && k >= 4096) && !acc && !residual && (int64_t)m * n < ((int64_t)1 << 30))
         return launch_tile256_t<128, 128, 2, 2, 2, 0, true, HALF, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
     return launch_tile256_t<128, 128, 2, 2, 2, 0, false, HALF, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
