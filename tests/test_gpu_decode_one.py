@@ -116,3 +116,68 @@ def test_rows_whose_maximum_is_taken_directly(bl, case):
         q_o, s_o, _ = oracle.quant_act(X)
         assert np.array_equal(q.cpu().numpy(), q_o)
         assert np.array_equal(sc.cpu().numpy().view(np.uint32), s_o.view(np.uint32))
+
+
+def _settled(c):
+    """Whether the kernel settles the row maximum from c = fl(r * max|t*gain|): both ends of the interval narrow to the same bf16."""
+    f = np.float32
+    ends = np.array([f(c * f(1.0 - 2.0 ** -20)), f(c * f(1.0 + 2.0 ** -20))], np.float32)
+    lo, hi = oracle.f32_to_bf16(ends)
+    return lo == hi and 2.0 ** -60 <= c <= 2.0 ** 120
+
+
+def _rows_around_a_boundary(K, g):
+    """Rows whose largest value is walked, one fp32 at a time, over the place where its normalised value lies in the
+    middle of two bf16.  g: its gain.  Yields (row, settled)."""
+    f = np.float32
+    t = np.random.default_rng(5).standard_normal(K).astype(np.float32)
+    t[17] = 0.0
+    S = float((t.astype(np.float64) ** 2).sum())
+    for mid in (4.015625, 4.046875, 7.984375, 8.03125 + 2.0 ** -5):     # odd multiples of half a bf16 step
+        p = mid * np.sqrt((S / K + 1e-5) / (float(g) ** 2 - mid * mid / K))
+        for step in range(-24, 25):
+            row = t.copy()
+            row[17] = (np.array([p], np.float32).view(np.int32) + step).view(np.float32)[0]
+            r = f(1.0 / np.sqrt((row.astype(np.float64) ** 2).sum() / K + float(f(1e-5))))
+            yield row, _settled(f(r * abs(f(row[17] * g))))
+
+
+@pytest.mark.parametrize("g", [1.0, 1.3749, -0.8])
+def test_maxima_on_both_sides_of_a_rounding_boundary(bl, g):
+    K, N = 2560, 40
+    gain = np.full(K, 0.125, np.float32)
+    gain[17] = g
+    W = np.random.default_rng(6).integers(-1, 2, size=(N, K)).astype(np.int8)
+    packed, beta = bl.bl_pack_ternary(torch.from_numpy(W).to(DEV), 1, beta=0.5)
+    q = torch.empty((1, K), dtype=torch.int8, device=DEV)
+    acc, sc = torch.empty((1, N), dtype=torch.int32, device=DEV), torch.empty(1, device=DEV)
+    gd = torch.from_numpy(gain).to(DEV)
+    direct, largest = 0, set()
+    for row, settled in _rows_around_a_boundary(K, np.float32(g)):
+        direct += not settled
+        xd = torch.from_numpy(row.reshape(1, K)).to(DEV)
+        item = dict(packed=packed, beta=beta, N=N, K=K, acc=acc, q_out=q, scale_out=sc,
+                    prod=bl.make_producer(bl.BL_PROD_F32, xd, norm=True, gain=gd, eps=1e-5))
+        bl.bl_bitlinear_decode_group(bl.make_decode_descs([item]), 1, 1)
+        q_o, s_o, _ = oracle.quant_act(oracle.rmsnorm_rows(row.reshape(1, K), gain, 1e-5))
+        assert np.array_equal(q.cpu().numpy(), q_o)
+        assert np.array_equal(sc.cpu().numpy().view(np.uint32), s_o.view(np.uint32))
+        largest.add(float(s_o[0]))
+    assert 16 <= direct <= 4 * 49 - 16 and len(largest) >= 6           # (conditions of the rows: both ways are taken, both sides met)
+
+
+def test_largest_values_beyond_the_range_of_the_shortcut(bl):
+    """max|t*gain| > 2^120: the row maximum is taken itself."""
+    K, N = 2560, 40
+    row = (np.random.default_rng(8).standard_normal((1, K)) * 3e36).astype(np.float32)
+    assert np.abs(row).max() > 2.0 ** 120
+    W = np.random.default_rng(6).integers(-1, 2, size=(N, K)).astype(np.int8)
+    packed, beta = bl.bl_pack_ternary(torch.from_numpy(W).to(DEV), 1, beta=0.5)
+    q, sc = torch.empty((1, K), dtype=torch.int8, device=DEV), torch.empty(1, device=DEV)
+    acc = torch.empty((1, N), dtype=torch.int32, device=DEV)
+    xd = torch.from_numpy(row).to(DEV)
+    item = dict(packed=packed, beta=beta, N=N, K=K, acc=acc, q_out=q, scale_out=sc,
+                prod=bl.make_producer(bl.BL_PROD_F32, xd, norm=True, eps=1e-5))
+    bl.bl_bitlinear_decode_group(bl.make_decode_descs([item]), 1, 1)
+    q_o, s_o, _ = oracle.quant_act(oracle.rmsnorm_rows(row, None, 1e-5))
+    assert np.array_equal(q.cpu().numpy(), q_o) and np.array_equal(sc.cpu().numpy().view(np.uint32), s_o.view(np.uint32))
