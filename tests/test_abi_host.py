@@ -55,6 +55,12 @@ def test_sizes(lib):
     assert b"BL_ERR_SHAPE" in lib.bl_status_str(2)
 
 
+def test_padded_k_of_the_binding_is_the_library_s(lib):
+    """The binding computes it itself (no foreign call in front of every launch)."""
+    for K in list(range(-70, 700)) + [6912, 6913, (1 << 24) - 1, 1 << 24, (1 << 24) + 1, 1 << 40]:
+        assert bl.bl_padded_k(K) == lib.bl_padded_k(K)
+
+
 def test_argument_errors_need_no_gpu(lib):
     buf = (ctypes.c_char * 4096)()
     p = (ctypes.addressof(buf) + 255) & ~255  # an aligned host address: never dereferenced on error paths
