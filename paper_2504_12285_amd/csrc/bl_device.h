@@ -27,15 +27,8 @@ __device__ __forceinline__ const T BL_G* bl_gc(const void* p) { return (const T 
 /* bf16 bit pattern -> fp32 (exact). */
 __device__ __forceinline__ float bl_bf16_to_f32(uint32_t h) { return __uint_as_float(h << 16); }
 
-/* fp32 -> bf16 bit pattern, round to nearest even (finite inputs). */
-__device__ __forceinline__ uint32_t bl_f32_to_bf16(float f) {
-    uint32_t u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return u >> 16;
-}
-
 /* Two fp32 -> packed bf16 bit patterns (a in the low half), round to nearest even: one
- * instruction, the bits of bl_f32_to_bf16 for every finite input (compared over all of them). */
+ * instruction, the bits of that definition for every finite input (tests/test_gpu_rounding.py goes through all). */
 typedef __bf16 bl_v2bf __attribute__((ext_vector_type(2)));
 typedef float bl_v2f __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t bl_pack2_bf16(float a, float b) {
