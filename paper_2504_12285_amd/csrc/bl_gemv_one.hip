@@ -23,7 +23,7 @@
 #include "bl_producer.h"
 
 #define BL_ONE_GAIN_MAX 0x1p40f   /* normalisation gains beyond it take the maximum of the row itself */
-#define BL_ONE_WAVES 4
+#define BL_ONE_WAVES 4            /* (bl_few_sum and bl_few_max join four) */
 #define BL_ONE_QSTRIDE 80     /* bytes of LDS per 64-wide k chunk: 16 lanes reading 16 bytes each meet 64 banks */
 
 template <int CTRL>
@@ -36,25 +36,19 @@ __device__ __forceinline__ double bl_row_sum(double v) {
     v += bl_dppd<BL_DPP_ROW_HALF_MIRROR>(v);
     return v + bl_dppd<BL_DPP_ROW_MIRROR>(v);
 }
-/* Over aligned groups of 4 or 8 lanes. */
-template <int W>
+/* Over aligned groups of four lanes (one value per wave). */
 __device__ __forceinline__ double bl_few_sum(double v) {
     v += bl_dppd<BL_DPP_QUAD_XOR1>(v);
-    v += bl_dppd<BL_DPP_QUAD_XOR2>(v);
-    if (W > 4) v += bl_dppd<BL_DPP_ROW_HALF_MIRROR>(v);
-    return v;
+    return v + bl_dppd<BL_DPP_QUAD_XOR2>(v);
 }
-template <int W>
 __device__ __forceinline__ float bl_few_max(float v) {
     v = bl_max_pos(v, bl_dppf<BL_DPP_QUAD_XOR1>(v));
-    v = bl_max_pos(v, bl_dppf<BL_DPP_QUAD_XOR2>(v));
-    if (W > 4) v = bl_max_pos(v, bl_dppf<BL_DPP_ROW_HALF_MIRROR>(v));
-    return v;
+    return bl_max_pos(v, bl_dppf<BL_DPP_QUAD_XOR2>(v));
 }
-/* Sum over the G lanes of a weight row, in every one of them. */
+/* Sum over the G = 16 or 32 lanes of a weight row, in every one of them. */
 template <int G>
 __device__ __forceinline__ int bl_lanes_sum(int v) {
-    if (G == 64) return bl_wave_sum(v);
+    static_assert(G == 16 || G == 32, "");
     v = bl_group_sum<16>(v);
     if (G == 32) {
         const auto t = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
@@ -262,7 +256,7 @@ __global__ __launch_bounds__(BL_ONE_WAVES * 64) void bl_gemv_one(const bl_one_ar
             const float mx = bl_wave_max(m2.get());
             if (lane == 0) fs[w] = mx;
             __syncthreads();
-            return bl_few_max<NW>(fs[lw]);
+            return bl_few_max(fs[lw]);
         };
         /* the rows that may hold a NaN take their maximum and their quantiser with it in mind */
         bool special = false;
@@ -276,8 +270,8 @@ __global__ __launch_bounds__(BL_ONE_WAVES * 64) void bl_gemv_one(const bl_one_ar
                 fs[w] = um;
             }
             __syncthreads();
-            const double ss = bl_few_sum<NW>(sd[lw]);
-            const float U = bl_few_max<NW>(fs[lw]);
+            const double ss = bl_few_sum(sd[lw]);
+            const float U = bl_few_max(fs[lw]);
             const float rn = bl_norm_factor(ss, P.inv_k, K, P.eps);
             narrow(rn);
             /* The maximum of |bf16((t*r)*gain)| without a second meeting of the waves: it lies within a
