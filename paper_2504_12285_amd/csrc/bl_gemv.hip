@@ -147,8 +147,8 @@ __global__ __launch_bounds__(256) void bl_gemv_rows(const bl_gemv_group grp) {
             mx = bl_wave_max(mx);
             if (lane == 0) fs[M + w] = mx;
             __syncthreads();
-            const float gamma = fmaxf(fmaxf(fs[M], fs[M + 1]), fmaxf(fs[M + 2], fs[M + 3]));
-            const float gg = fmaxf(gamma, 1e-5f);
+            const float gamma = bl_max_pos(bl_max_pos(fs[M], fs[M + 1]), bl_max_pos(fs[M + 2], fs[M + 3]));   /* (NaN is the largest) */
+            float gg = fmaxf(gamma, 1e-5f);
             const float inv = bl_div_rn(127.0f, gg);
             const bool emit = P.q_out && first_block;
             int part = 0;
@@ -173,6 +173,23 @@ __global__ __launch_bounds__(256) void bl_gemv_rows(const bl_gemv_group grp) {
                 part += bl_sum16(a0, a1, a2, a3);
                 if (emit) *(bl_v4i BL_G*)(P.q_out + (int64_t)m * K + u * 16) = bl_v4i{(int)a0, (int)a1, (int)a2, (int)a3};
                 bl_put16(Q + m * (K / 4), u, P.layout, a0, a1, a2, a3);
+            }
+            if (bl_not_finite(gamma)) {
+                part = 0;
+                gg = bl_quant_row_again(
+                    groups, tid, 256, [&](int u, uint4& lo, uint4& hi) { bl_produce16<NORM>(P.prod, m, u, K, false, rn, lo, hi); },
+                    [&](float v) {
+                        v = bl_wave_max(v);
+                        __syncthreads();                   /* fs[M..] has been read */
+                        if (lane == 0) fs[M + w] = v;
+                        __syncthreads();
+                        return bl_max_pos(bl_max_pos(fs[M], fs[M + 1]), bl_max_pos(fs[M + 2], fs[M + 3]));
+                    },
+                    [&](int u, uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3) {
+                        part += bl_sum16(a0, a1, a2, a3);
+                        if (emit) *(bl_v4i BL_G*)(P.q_out + (int64_t)m * K + u * 16) = bl_v4i{(int)a0, (int)a1, (int)a2, (int)a3};
+                        bl_put16(Q + m * (K / 4), u, P.layout, a0, a1, a2, a3);
+                    });
             }
             part = bl_wave_sum(part);
             if (lane == 0) atomicAdd(&sq[m], part);   /* four LDS atomics per token */
@@ -428,7 +445,7 @@ __global__ __launch_bounds__(256) void bl_gemv_mma(const bl_gemv_group grp, cons
                 }
             }
             const float gamma = bl_wave_max(mx);
-            const float gg = fmaxf(gamma, 1e-5f);
+            float gg = fmaxf(gamma, 1e-5f);
             const float inv = bl_div_rn(127.0f, gg);
             const bool emit = P.q_out && first_block;
             uint8_t* Qm = Q + m * qstride;
@@ -476,6 +493,14 @@ __global__ __launch_bounds__(256) void bl_gemv_mma(const bl_gemv_group grp, cons
                     *(uint4*)(Qm + u * 16) = make_uint4(a0, a1, a2, a3);
                 }
             }
+            if (bl_not_finite(gamma))
+                gg = bl_quant_row_again(
+                    groups, lane, 64, [&](int u, uint4& lo, uint4& hi) { bl_produce16<NORM>(P.prod, m, u, K, false, 1.0f, lo, hi); },
+                    [](float v) { return bl_wave_max(v); },
+                    [&](int u, uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3) {
+                        if (emit) *(bl_v4i BL_G*)(P.q_out + (int64_t)m * K + u * 16) = bl_v4i{(int)a0, (int)a1, (int)a2, (int)a3};
+                        *(uint4*)(Qm + u * 16) = make_uint4(a0, a1, a2, a3);
+                    });
             if (lane == 0) {
                 const float sc = bl_div_rn(gg, 127.0f);
                 fscale[m] = P.fixed_scale > 0.0f ? P.fixed_scale : sc;
@@ -484,6 +509,8 @@ __global__ __launch_bounds__(256) void bl_gemv_mma(const bl_gemv_group grp, cons
         }
         __syncthreads();
     } else if (fused) {
+        /* (every row with NaN in mind: a chain of eight normalised tokens 1.4 - 3.1 % longer than without, 4.3 % with a
+         * second look apart) */
 #pragma unroll 1
         for (int m = 0; m < M; ++m) {
             float rn = 1.0f;
@@ -498,19 +525,19 @@ __global__ __launch_bounds__(256) void bl_gemv_mma(const bl_gemv_group grp, cons
                 const int u = tid + j * 256;
                 if (u < groups) {
                     if (!have_xv) bl_produce16<NORM>(P.prod, m, u, K, first_block, rn, xv[2 * j], xv[2 * j + 1]);
-                    mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16(xv[2 * j]), bl_absmax8_bf16(xv[2 * j + 1])));
+                    mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16<true>(xv[2 * j]), bl_absmax8_bf16<true>(xv[2 * j + 1])));
                 }
             }
             for (int u = tid + 512; u < groups; u += 256) {
                 uint4 lo, hi;
                 bl_produce16<NORM>(P.prod, m, u, K, false, rn, lo, hi);
-                mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16(lo), bl_absmax8_bf16(hi)));
+                mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16<true>(lo), bl_absmax8_bf16<true>(hi)));
             }
             mx = bl_wave_max(mx);
             if (m > 0) __syncthreads();                 /* previous token's fs[] readers are done */
             if (lane == 0) fs[w] = mx;
             __syncthreads();
-            const float gamma = fmaxf(fmaxf(fs[0], fs[1]), fmaxf(fs[2], fs[3]));
+            const float gamma = bl_max_pos(bl_max_pos(fs[0], fs[1]), bl_max_pos(fs[2], fs[3]));
             const float gg = fmaxf(gamma, 1e-5f);
             const float inv = bl_div_rn(127.0f, gg);
             const bool emit = P.q_out && first_block;
@@ -520,8 +547,8 @@ __global__ __launch_bounds__(256) void bl_gemv_mma(const bl_gemv_group grp, cons
                 const int u = tid + j * 256;
                 if (u < groups) {
                     uint32_t a0, a1, a2, a3;
-                    bl_quant8_words(xv[2 * j], inv, a0, a1);
-                    bl_quant8_words(xv[2 * j + 1], inv, a2, a3);
+                    bl_quant8_words<BL_Q_ROW>(xv[2 * j], inv, a0, a1);
+                    bl_quant8_words<BL_Q_ROW>(xv[2 * j + 1], inv, a2, a3);
                     if (emit) *(bl_v4i BL_G*)(P.q_out + (int64_t)m * K + u * 16) = bl_v4i{(int)a0, (int)a1, (int)a2, (int)a3};
                     *(uint4*)(Qm + u * 16) = make_uint4(a0, a1, a2, a3);
                 }
@@ -530,8 +557,8 @@ __global__ __launch_bounds__(256) void bl_gemv_mma(const bl_gemv_group grp, cons
                 uint32_t a0, a1, a2, a3;
                 uint4 lo, hi;
                 bl_produce16<NORM>(P.prod, m, u, K, first_block, rn, lo, hi);
-                bl_quant8_words(lo, inv, a0, a1);
-                bl_quant8_words(hi, inv, a2, a3);
+                bl_quant8_words<BL_Q_ROW>(lo, inv, a0, a1);
+                bl_quant8_words<BL_Q_ROW>(hi, inv, a2, a3);
                 if (emit) *(bl_v4i BL_G*)(P.q_out + (int64_t)m * K + u * 16) = bl_v4i{(int)a0, (int)a1, (int)a2, (int)a3};
                 *(uint4*)(Qm + u * 16) = make_uint4(a0, a1, a2, a3);
             }

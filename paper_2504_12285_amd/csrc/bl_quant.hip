@@ -94,7 +94,7 @@ __global__ __launch_bounds__(QUANT_THREADS) void bl_quant_rows(const uint16_t* _
     } else {
         float mx = 0.0f;
 #pragma unroll 1
-        for (int u = t; u < units; u += TPR) mx = bl_max_pos(mx, bl_absmax8_bf16(bl_row_unit<RAGGED>(x, u, K)));
+        for (int u = t; u < units; u += TPR) mx = bl_max_pos(mx, bl_absmax8_bf16<true>(bl_row_unit<RAGGED>(x, u, K)));
         if (WPR > 1) __syncthreads();                                /* smax has been read */
         g = fmaxf(row_max(mx), 1e-5f);
         inv = bl_div_rn(127.0f, g);
@@ -213,10 +213,10 @@ __global__ __launch_bounds__(QUANT_THREADS) void bl_quant_rows_ex(const bl_prod_
     int8_t* qo = q + (int64_t)m * K;
     float g, inv;
     int sum = 0;
-    auto put = [&](int u, const uint4 lo, const uint4 hi, auto mode) {
+    auto put = [&](int u, const uint4 lo, const uint4 hi) {
         uint32_t a0, a1, a2, a3;
-        bl_quant8_words<decltype(mode)::value>(lo, inv, a0, a1);
-        bl_quant8_words<decltype(mode)::value>(hi, inv, a2, a3);
+        bl_quant8_words(lo, inv, a0, a1);
+        bl_quant8_words(hi, inv, a2, a3);
         sum += bl_sum16(a0, a1, a2, a3);
         *(uint4*)(qo + u * 16) = make_uint4(a0, a1, a2, a3);
     };
@@ -235,33 +235,29 @@ __global__ __launch_bounds__(QUANT_THREADS) void bl_quant_rows_ex(const bl_prod_
         mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16<false>(lo), bl_absmax8_bf16<false>(hi)));
     }
     const float gamma = row_max(mx);
-    if (__builtin_expect(gamma < __builtin_inff(), 1)) {
+    if (!bl_not_finite(gamma)) {
         g = fmaxf(gamma, 1e-5f);
         inv = bl_div_rn(127.0f, g);
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int u = tid + j * QUANT_THREADS;
-            if (u < groups) put(u, xv[2 * j], xv[2 * j + 1], bl_mode<BL_Q_FINITE>{});
+            if (u < groups) put(u, xv[2 * j], xv[2 * j + 1]);
         }
         for (int u = tid + 2 * QUANT_THREADS; u < groups; u += QUANT_THREADS) {
             bl_produce16<NORM>(pd, m, u, K, false, rn, lo, hi);
-            put(u, lo, hi, bl_mode<BL_Q_FINITE>{});
+            put(u, lo, hi);
         }
-    } else {                                  /* infinite or NaN somewhere: the row once more, with NaN passed over */
-        mx = 0.0f;
-#pragma unroll 1
-        for (int u = tid; u < groups; u += QUANT_THREADS) {
-            bl_produce16<NORM>(pd, m, u, K, false, rn, lo, hi);
-            mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16(lo), bl_absmax8_bf16(hi)));
-        }
-        __syncthreads();                      /* smax has been read */
-        g = fmaxf(row_max(mx), 1e-5f);
-        inv = bl_div_rn(127.0f, g);
-#pragma unroll 1
-        for (int u = tid; u < groups; u += QUANT_THREADS) {
-            bl_produce16<NORM>(pd, m, u, K, false, rn, lo, hi);
-            put(u, lo, hi, bl_mode<BL_Q_ROW>{});
-        }
+    } else {
+        g = bl_quant_row_again(
+            groups, tid, QUANT_THREADS, [&](int u, uint4& l, uint4& h) { bl_produce16<NORM>(pd, m, u, K, false, rn, l, h); },
+            [&](float v) {
+                __syncthreads();              /* smax has been read */
+                return row_max(v);
+            },
+            [&](int u, uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3) {
+                sum += bl_sum16(a0, a1, a2, a3);
+                *(uint4*)(qo + u * 16) = make_uint4(a0, a1, a2, a3);
+            });
     }
     sum = bl_wave_sum(sum);
     if (lane == 0) ssum[w] = sum;

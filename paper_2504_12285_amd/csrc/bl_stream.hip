@@ -137,8 +137,8 @@ __global__ __launch_bounds__(256) void bl_stream_prep(const bl_stream_prep_item*
         mx = bl_wave_max(mx);
         if (lane == 0) fs[w] = mx;
         __syncthreads();
-        const float gamma = fmaxf(fmaxf(fs[0], fs[1]), fmaxf(fs[2], fs[3]));
-        const float gg = fmaxf(gamma, 1e-5f);
+        const float gamma = bl_max_pos(bl_max_pos(fs[0], fs[1]), bl_max_pos(fs[2], fs[3]));   /* (NaN is the largest) */
+        float gg = fmaxf(gamma, 1e-5f);
         const float inv = bl_div_rn(127.0f, gg);
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
@@ -161,6 +161,23 @@ __global__ __launch_bounds__(256) void bl_stream_prep(const bl_stream_prep_item*
             part += bl_sum16(a0, a1, a2, a3);
             if (it.q_out) *(bl_v4i BL_G*)(it.q_out + u * 16) = bl_v4i{(int)a0, (int)a1, (int)a2, (int)a3};
             *(bl_v4i BL_G*)(it.q_ws + u * 16) = bl_v4i{(int)a0, (int)a1, (int)a2, (int)a3};
+        }
+        if (bl_not_finite(gamma)) {
+            part = 0;
+            gg = bl_quant_row_again(
+                groups, tid, 256, [&](int u, uint4& lo, uint4& hi) { bl_produce16<NORM>(pd, 0, u, K, false, rn, lo, hi); },
+                [&](float v) {
+                    v = bl_wave_max(v);
+                    __syncthreads();                       /* fs has been read */
+                    if (lane == 0) fs[w] = v;
+                    __syncthreads();
+                    return bl_max_pos(bl_max_pos(fs[0], fs[1]), bl_max_pos(fs[2], fs[3]));
+                },
+                [&](int u, uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3) {
+                    part += bl_sum16(a0, a1, a2, a3);
+                    if (it.q_out) *(bl_v4i BL_G*)(it.q_out + u * 16) = bl_v4i{(int)a0, (int)a1, (int)a2, (int)a3};
+                    *(bl_v4i BL_G*)(it.q_ws + u * 16) = bl_v4i{(int)a0, (int)a1, (int)a2, (int)a3};
+                });
         }
         if (tid == 0) {
             const float sc = bl_div_rn(gg, 127.0f);
@@ -227,8 +244,8 @@ __device__ __forceinline__ void bl_stream_stage(const bl_stream_item& P, int* __
         mx = bl_wave_max(mx);
         if (lane == 0) fs[w] = mx;
         __syncthreads();
-        const float gamma = fmaxf(fmaxf(fs[0], fs[1]), fmaxf(fs[2], fs[3]));
-        const float gg = fmaxf(gamma, 1e-5f);
+        const float gamma = bl_max_pos(bl_max_pos(fs[0], fs[1]), bl_max_pos(fs[2], fs[3]));   /* (NaN is the largest) */
+        float gg = fmaxf(gamma, 1e-5f);
         const float inv = bl_div_rn(127.0f, gg);
         for (int u = tid; u < groups; u += 256) {
             uint32_t a0, a1, a2, a3;
@@ -238,6 +255,26 @@ __device__ __forceinline__ void bl_stream_stage(const bl_stream_item& P, int* __
             const bl_v4i qv = {(int)a0, (int)a1, (int)a2, (int)a3};
             if (owner && P.q_out) *(bl_gv4i*)(P.q_out + u * 16) = qv;
             bl_lds_put16(Qs, u, P.layout, a0, a1, a2, a3);
+        }
+        if (bl_not_finite(gamma)) {
+            part = 0;
+            gg = bl_quant_row_again(
+                groups, tid, 256, [&](int u, uint4& lo, uint4& hi) {
+                    lo = ld(2 * u);
+                    hi = ld(2 * u + 1);
+                },
+                [&](float v) {
+                    v = bl_wave_max(v);
+                    __syncthreads();                       /* fs has been read */
+                    if (lane == 0) fs[w] = v;
+                    __syncthreads();
+                    return bl_max_pos(bl_max_pos(fs[0], fs[1]), bl_max_pos(fs[2], fs[3]));
+                },
+                [&](int u, uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3) {
+                    part += bl_sum16(a0, a1, a2, a3);
+                    if (owner && P.q_out) *(bl_gv4i*)(P.q_out + u * 16) = bl_v4i{(int)a0, (int)a1, (int)a2, (int)a3};
+                    bl_lds_put16(Qs, u, P.layout, a0, a1, a2, a3);
+                });
         }
         if (tid == 0) {
             const float sc = bl_div_rn(gg, 127.0f);
@@ -418,8 +455,8 @@ __device__ __forceinline__ void bl_stream_stage_t5(const bl_stream_item& P, int*
         mx = bl_wave_max(mx);
         if (lane == 0) fs[w] = mx;
         __syncthreads();
-        const float gamma = fmaxf(fmaxf(fs[0], fs[1]), fmaxf(fs[2], fs[3]));
-        const float gg = fmaxf(gamma, 1e-5f);
+        const float gamma = bl_max_pos(bl_max_pos(fs[0], fs[1]), bl_max_pos(fs[2], fs[3]));   /* (NaN is the largest) */
+        float gg = fmaxf(gamma, 1e-5f);
         const float inv = bl_div_rn(127.0f, gg);
         for (int u = tid; u < groups; u += 256) {
             uint32_t a0, a1, a2, a3;
@@ -429,6 +466,27 @@ __device__ __forceinline__ void bl_stream_stage_t5(const bl_stream_item& P, int*
             const bl_v4i qv = {(int)a0, (int)a1, (int)a2, (int)a3};
             if (owner && P.q_out) *(bl_gv4i*)(P.q_out + u * 16) = qv;
             put(u, qv);
+        }
+        if (bl_not_finite(gamma)) {
+            part = 0;
+            gg = bl_quant_row_again(
+                groups, tid, 256, [&](int u, uint4& lo, uint4& hi) {
+                    lo = ld(2 * u);
+                    hi = ld(2 * u + 1);
+                },
+                [&](float v) {
+                    v = bl_wave_max(v);
+                    __syncthreads();                       /* fs has been read */
+                    if (lane == 0) fs[w] = v;
+                    __syncthreads();
+                    return bl_max_pos(bl_max_pos(fs[0], fs[1]), bl_max_pos(fs[2], fs[3]));
+                },
+                [&](int u, uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3) {
+                    part += bl_sum16(a0, a1, a2, a3);
+                    const bl_v4i qv = {(int)a0, (int)a1, (int)a2, (int)a3};
+                    if (owner && P.q_out) *(bl_gv4i*)(P.q_out + u * 16) = qv;
+                    put(u, qv);
+                });
         }
         if (tid == 0) {
             const float sc = bl_div_rn(gg, 127.0f);
@@ -622,8 +680,8 @@ __device__ __forceinline__ void bl_km_slice(const bl_stream_item& P, const int u
             mx = bl_wave_max(mx);
             if (lane == 0) fs[lw] = mx;
             __syncthreads();
-            const float gamma = fmaxf(fmaxf(fs[0], fs[1]), fmaxf(fs[2], fs[3]));
-            const float gg = fmaxf(gamma, 1e-5f);
+            const float gamma = bl_max_pos(bl_max_pos(fs[0], fs[1]), bl_max_pos(fs[2], fs[3]));   /* (NaN is the largest) */
+            float gg = fmaxf(gamma, 1e-5f);
             const float inv = bl_div_rn(127.0f, gg);
             int part = 0;
             for (int u = tid; u < groups; u += 256) {
@@ -634,6 +692,27 @@ __device__ __forceinline__ void bl_km_slice(const bl_stream_item& P, const int u
                 const bl_v4i qv = {(int)a0, (int)a1, (int)a2, (int)a3};
                 if (ub == 0 && P.q_out) *(bl_gv4i*)(P.q_out + u * 16) = qv;
                 Q4[u] = qv;
+            }
+            if (bl_not_finite(gamma)) {
+                part = 0;
+                gg = bl_quant_row_again(
+                    groups, tid, 256, [&](int u, uint4& lo, uint4& hi) {
+                        lo = ld(2 * u);
+                        hi = ld(2 * u + 1);
+                    },
+                    [&](float v) {
+                        v = bl_wave_max(v);
+                        __syncthreads();                       /* fs has been read */
+                        if (lane == 0) fs[lw] = v;
+                        __syncthreads();
+                        return bl_max_pos(bl_max_pos(fs[0], fs[1]), bl_max_pos(fs[2], fs[3]));
+                    },
+                    [&](int u, uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3) {
+                        part += bl_sum16(a0, a1, a2, a3);
+                        const bl_v4i qv = {(int)a0, (int)a1, (int)a2, (int)a3};
+                        if (ub == 0 && P.q_out) *(bl_gv4i*)(P.q_out + u * 16) = qv;
+                        Q4[u] = qv;
+                    });
             }
             part = bl_wave_sum(part);
             if (lane == 0) ssum[lw] = part;

@@ -124,3 +124,43 @@ def test_packing(bl, layout, N, K, bad):
     assert np.isnan(b) if np.isnan(bad) else b == np.inf
     want = oracle.pack_kmajor(Wt) if layout == 3 else oracle.pack_trit5(Wt) if layout == 2 else oracle.pack_padded(Wt, layout)
     assert np.array_equal(packed.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("norm", [False, True])
+@pytest.mark.parametrize("M", [1, 2, 3, 4, 8, 16])
+def test_produced_rows(bl, M, norm):
+    """Rows that a producer makes in front of the product, for K with and without a second pass: a normalised row with
+    a NaN is NaN throughout, one with an infinity is zeros and a NaN; the other rows do not change."""
+    for K in (2560, 5952):
+        N = 24
+        u, x = _rows(max(M, 6), K, 11 + K)
+        u, x = u[:M], x[:M].copy()
+        if M == 1 and norm:
+            x[0, 7] = np.inf
+        t = x
+        if norm:
+            with np.errstate(invalid="ignore", divide="ignore", over="ignore"):
+                r = (1.0 / np.sqrt((x.astype(np.float64) ** 2).sum(1) / K + float(np.float32(1e-5)))).astype(np.float32)
+                t = x * r[:, None]
+            t = (oracle.f32_to_bf16(np.where(np.isnan(t), np.float32(0), t)).astype(np.uint32) << 16).view(np.float32) + np.where(np.isnan(t), np.float32("nan"), np.float32(0))
+        want = _quantised(t)
+        W = np.random.default_rng(K).integers(-1, 2, size=(N, K)).astype(np.int8)
+        packed, beta = bl.bl_pack_ternary(to_dev(W), 1, beta=0.5)
+        prod = lambda: bl.make_producer(bl.BL_PROD_F32, xd, norm=norm, eps=1e-5)
+        xd = to_dev(x)
+        q, s = torch.empty((M, K), dtype=torch.int8, device=DEV), torch.empty(M, device=DEV)
+        acc = torch.empty((M, N), dtype=torch.int32, device=DEV)
+        acc_want = want[0].astype(np.int32) @ W.T.astype(np.int32)
+        if M * (K + 16) <= 96 * 1024:
+            item = dict(packed=packed, beta=beta, N=N, K=K, acc=acc, q_out=q, scale_out=s, prod=prod())
+            bl.bl_bitlinear_decode_group(bl.make_decode_descs([item]), 1, M)
+            _check(q, s, want)
+            assert np.array_equal(acc.cpu().numpy(), acc_want)
+        q, s, _ = bl.bl_quant_act_ex(prod(), M, K, torch.device(DEV))
+        _check(q, s, want)
+        if M == 1:
+            item = dict(packed=packed, beta=beta, N=N, K=K, acc=acc.fill_(7), q_out=torch.empty((1, K), dtype=torch.int8, device=DEV),
+                        scale_out=torch.empty(1, device=DEV), prod=prod())
+            bl.Stack([item], 1, 1, torch.device(DEV)).run()
+            _check(item["q_out"], item["scale_out"], want)
+            assert np.array_equal(acc.cpu().numpy(), acc_want)
