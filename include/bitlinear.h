@@ -400,10 +400,9 @@ bl_status bl_debug_force_path(int path);
  *                         the constant-rate wall clock (bl_probe_wall_clock_khz), so
  *                         stamps[0] / stamps[1] x that rate is the clock the kernel ran at.
  *   bl_probe_wall_clock_khz  rate of that wall clock in kHz (0 on error).  Host-only query.
- *   bl_debug_clock_stamps  measurement hook for the prefill tile kernel: while a device buffer
- *                         of 2 x int64 is registered, every launch of that kernel (bl_gemm_w158a8
- *                         and its variants on the direct-to-LDS path) leaves the same two counts
- *                         of its workgroup 0 there; NULL (the default) switches it off.
+ *   bl_debug_clock_stamps  measurement hook for the prefill kernels: while a device buffer
+ *                         of 2 x int64 is registered, every product launch of bl_gemm_w158a8 and
+ *                         its variants leaves the same two counts of its workgroup 0 there; NULL (the default) switches it off.
  *                         Process-wide and atomic; results never depend on it.
  * sink: device, 64 int32, never written in practice (it keeps the work observable). */
 bl_status bl_probe_stream_read(const void* buf, size_t bytes, int workgroups_per_cu, int32_t* sink,

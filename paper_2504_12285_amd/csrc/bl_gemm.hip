@@ -55,7 +55,8 @@
 /* HALF: K is an odd multiple of 64, so the last k step has only its first 64 columns: lane half 1 (the
  * second unit of a weight row) multiplies nothing there, its weights are set to zero and its loads go to
  * the step's first half (inside the row): 777 x 2999 -> 5003 with its quantiser 28.8 us against 38.4 on a
- * register-staged kernel of 128 x 128 tiles, one workgroup per compute unit.  LAYOUT 0: a packed word is turned into layout-1 order in the
+ * register-staged kernel of 128 x 128 tiles, one workgroup per compute unit.  (With deferred stores it spills nine
+ * registers, and is the fastest form all the same: 4096 x 2112 -> 7040 76 us, 83 with stores at once.)  LAYOUT 0: a packed word is turned into layout-1 order in the
  * register before it is opened (bl_word_to_k16): 1000 x 2560 -> 3840 24.0 us against 29.2. */
 template <int BM, int BN, int STAGES, int WM, int WN, int EPI, bool TABLE = false, bool DEFER = false, bool HALF = false, int LAYOUT = 1>
 __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : BM * BN >= 128 * 128 ? 3 : 4)) void bl_gemm_tile256(const uint8_t* __restrict__ packed,
@@ -381,7 +382,7 @@ __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : 
         /* EPI 1: the residual values of four row groups (32 rows) are requested ahead, a group's successor
          * when it has been stored; clamped and unconditional.  The first ones travel while the row terms are
          * handed over.  (Fetched in front of their own stores they cost eight round trips to memory per
-         * tile; all at once they spill.  With the row maxima by DPP instead of shuffles, at M = 4096: residual
+         * tile; all at once they spill 63 registers, this form three.  With the row maxima by DPP instead of shuffles, at M = 4096: residual
          * epilogue 82 -> 75.5 us, gate epilogue 180 -> 168 us, means of two layers.) */
         float rres[EPI == 1 ? 4 : 1][4][NI];
         auto fetch_res = [&](const int mi, const int vq) __attribute__((always_inline)) {

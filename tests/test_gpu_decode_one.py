@@ -85,12 +85,13 @@ def test_against_the_dot4_kernel(bl, kind, N, K):
 
 @pytest.mark.parametrize("case", ["midpoint", "tiny", "huge gain", "zero", "large"])
 def test_rows_whose_maximum_is_taken_directly(bl, case):
-    """Rows where r * max|t*gain| lies on a bf16 rounding boundary or outside the bound's range."""
+    """Rows outside the bound's range (tiny, huge gain, zero), and ordinary ones with large values; the rows on a bf16
+    rounding boundary are those of test_maxima_on_both_sides_of_a_rounding_boundary."""
     K, N = 2560, 40
     rng = np.random.default_rng(5)
     t = rng.standard_normal(K).astype(np.float32)
     gain = np.ones(K, np.float32)
-    if case == "midpoint":                       # many rows, so that some straddle a boundary: scale the largest value
+    if case == "midpoint":                       # many rows, their largest values 2^-12 apart
         rows = [t * np.float32(1) for _ in range(64)]
         for i, r_ in enumerate(rows):
             r_[17] = np.float32(8.0) + np.float32(i) * np.float32(2.0 ** -9)
