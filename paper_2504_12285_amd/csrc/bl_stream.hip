@@ -5,13 +5,8 @@
  * A table of products lives in device memory.  The grid is as many workgroups as stay
  * resident; each owns one contiguous slice of the table's weight bytes, cut at row-group
  * boundaries, so a workgroup meets one or two products and quantises / stages the activation
- * row of a product once, into LDS.  Inside a product the four waves of a workgroup take row
- * groups round-robin and double-buffer the 128-bit weight loads: the loads of row group i+1
- * are issued before the dot products of row group i.
- *
- * Arithmetic as in bl_gemv.hip: offset codes c = Wt + 1, bit-pair levels isolated by masks,
- * v_dot4_i32_i8 into four accumulators carrying 1, 4, 16, 16, DPP sums over the G lanes of
- * a row, rowsum subtracted once per output.  One token per product (M = 1).
+ * row of a product once, into LDS.  Inside a product the 128-bit weight loads are double-buffered:
+ * the next loads are issued before the products of the ones that have landed.
  */
 #include <string.h>
 
@@ -46,7 +41,9 @@ struct bl_stream_item {
     int8_t* q_out;            /* xbf16 only: the caller's optional copies of q and absmax/127 */
     float* scale_out;
     float fixed_scale;        /* xbf16 only: > 0 replaces absmax/127 in the rescale */
-    int N, nchunks, lgG, lp, layout, units;
+    int N, nchunks, lp, layout, units;
+    int shift;                /* one token: chunks that the loads of odd rows start in front of their row (0 or 4) */
+    int parts;                /* one token: the row is read in this many parts of wave-wide loads (128 bytes of a row each) */
     int qgroups;              /* 16-byte groups of the quantised row (its padded length / 16) */
     int m;                    /* tokens of the entry (batched form; 1 otherwise) */
     int row_chunks, c0;       /* batched form: 16-byte chunks of a whole packed row; first chunk of the entry's k part */
@@ -72,32 +69,6 @@ struct bl_stream_prep_item {
     float fixed_scale;
     int K;
 };
-
-/* Sum over aligned groups of 1 << lgG lanes (8, 16, 32 or 64), result in every lane. */
-__device__ __forceinline__ int bl_group_sum_rt(int v, int lgG) {
-    v = bl_group_sum<8>(v);
-    if (lgG >= 4) v += bl_dpp<BL_DPP_ROW_MIRROR>(v);
-    if (lgG >= 5) v += __shfl_xor(v, 16);
-    if (lgG >= 6) v += __shfl_xor(v, 32);
-    return v;
-}
-
-/* The four bit-pair levels of four packed words against the sixteen activation dwords
- * a[s][d] of one chunk. */
-__device__ __forceinline__ void bl_stream_dot(const bl_v4i p, const bl_v4i* a, int* A) {
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            const uint32_t w = (uint32_t)p[d];
-            const uint32_t lv = s == 0 ? (w & 0x03030303u)
-                              : s == 1 ? (w & 0x0C0C0C0Cu)
-                              : s == 2 ? (w & 0x30303030u)
-                                       : ((w >> 2) & 0x30303030u);
-            A[s] = __builtin_amdgcn_sdot4((int)lv, a[s][d], A[s], false);
-        }
-    }
-}
 
 /* Preparation: one workgroup per table entry that needs it.  Fused entries: producer, RMS
  * normalisation (NORM), per-token absmax, int8 quantisation (Section 2) into the workspace,
@@ -197,84 +168,272 @@ __global__ __launch_bounds__(256) void bl_stream_prep(const bl_stream_prep_item*
 }
 
 /* ---- the stream kernel ----------------------------------------------------------------------
+ * One token, so a weight meets one activation; the products run on the matrix cores all the same,
+ * because the vector unit was what a wave waited for (~60 vector instructions per 16-byte load and
+ * lane: masks and four-wide dot products; five weights per byte: ~100).
+ *
+ * v_mfma_f32_32x32x64_f8f6f4 with a 4-bit B operand takes 32 weights of a lane as they lie: a
+ * packed word masked with 0x33333333 is eight nibbles 00cc, the e2m1 number c / 2, so a word costs
+ * two masks and a shift.  The activation q = 16 a + b, -8 <= a <= 7, 0 <= b <= 15, is two 6-bit numbers:
+ * e2m3 holds +-n / 8 exactly for n <= 16, with the code n itself.  Both pieces ride in one
+ * instruction as two rows of A.  Every product is a multiple of 1/16 and every sum below 2^24 of
+ * them (K <= 20480), so the fp32 accumulators hold the exact integers whatever the order.
+ *
+ * Loads keep the pattern that streams: eight consecutive lanes fetch 128 consecutive bytes of a
+ * row, a wave-wide load covers eight rows (read alone 6.6 TB/s; 16 rows x 64 bytes, the order the
+ * matrix core would like, 5.6, and 32 x 32 bytes 3.0).  Lane 8 r + u, which holds 16-byte chunk u
+ * of the r-th row, is column 8 (r % 4) + u of B in k group r / 4.  Different columns need different
+ * activations (chunk u's) and the two k groups hold different rows, so A has a row for each u
+ * (8), k group (2) and piece (2), 32 together, zero in the other k group; of the 32 x 32 results
+ * the one with the column's own u counts, and a row's eight chunks are added at the end.  The matrix
+ * core computes 32 times what is wanted and is busy a fifth of the time.
+ * Thirty layers of 2560 / 6912 in one launch: 88.9 -> 85.4 us in the 2-bit form (six tenths of it the order of the
+ * loads, below), 107.4 -> 89.4 in the form of five per byte; sixty of 640 / 1280 20.7 -> 15.4 and 39.0 -> 17.5.
+ * (One layer of 2560 / 6912, five per byte: 8.7 -> 9.7; its rows of 6912 are three dependent parts.)
+ *
  * A product's quantised activation row lives in LDS for the workgroup (staged once per product
- * and workgroup: quantised from bf16 right there, or copied from the int8 row) and is read with
- * ds_read_b128 right before each group of sixteen dot products.  Holding the row in registers
- * instead (80 per lane) was measured: 2 waves per SIMD, 5.7 - 5.9 TB/s against 5.85 - 6.2 here
- * with 4; the loop issues ~300 vector instructions per 5 KiB of weights, so the vector unit,
- * not the memory, sets the pace (a plain read with the same access pattern gets 7.0 TB/s).
+ * and workgroup: quantised from bf16 right there, or taken from the int8 row), as the 6-bit pieces
+ * in operand order, and is read right before use.
  * Every workgroup that meets a bf16 product quantises the row for itself: nothing crosses
  * workgroups inside the launch.  (A hand-over through ready flags was measured and dropped:
  * fresh data needs either an L2 write-back + invalidate per wave, +40 us per launch, or
  * uncached loads of the row by every wave, +26 us; a separate preparation launch costs 5.5 us.)
- * LDS image: per 64-wide k chunk 20 dwords (16 + 4 of padding so that the eight chunks a wave
- * reads together fall on different banks), dword s*4+d = the bytes that pair with bit-pair
- * level s of packed word d; one all-zero chunk behind the last for lanes whose load is clamped. */
-#define BL_QSTRIDE 20
+ * LDS image: per 16-byte chunk of a weight row and per piece the A operands of the instructions that
+ * multiply it, 24 bytes (32 codes) each: 96 bytes a chunk (2-bit form: even and odd bit pairs of the
+ * four words) or 160 (five per byte: digits 0/1, 2/3, 4; 16 unused).  Both strides put the eight
+ * chunks that a wave reads together on different banks.  Zeros from the row's end to the end of the
+ * last part, and one zero chunk behind for the lanes of the other k group. */
+#define BL_FORM_BIT2 0
+#define BL_FORM_TRIT5 1
+#define BL_B2_CHUNK 96
+#define BL_T5_CHUNK 160
+#define BL_T5_SET 24          /* bytes between the operands of a chunk and piece */
 
-__device__ __forceinline__ void bl_lds_put16(int* __restrict__ Qs, int c16, int layout, uint32_t a0, uint32_t a1,
-                                             uint32_t a2, uint32_t a3) {
-    if (layout == 0) bl_transpose4x4(a0, a1, a2, a3);
-    int* dst = Qs + (c16 >> 2) * BL_QSTRIDE + (c16 & 3);
-    dst[0] = (int)a0;
-    dst[4] = (int)a1;
-    dst[8] = (int)a2;
-    dst[12] = (int)a3;
+typedef int bl_v2i __attribute__((ext_vector_type(2)));
+typedef int bl_v8i __attribute__((ext_vector_type(8)));
+typedef float bl_v16f __attribute__((ext_vector_type(16)));
+
+typedef uint32_t bl_u32a2 __attribute__((aligned(2)));
+/* Eight activations (two dwords, in nibble order) -> 6 bytes of the operand at dst (low piece, q % 16) and
+ * dst + piece_bytes (high piece, q >> 4).  A code is sign and magnitude in six bits: the low piece is its own
+ * code, the high piece -8 .. 7 is h or, where negative, 32 | (16 - h).  Two codes are joined by a dot product
+ * with 1 and 64.  NEG: of -q. */
+template <bool NEG = false>
+__device__ __forceinline__ void bl_lds_put8(uint8_t* dst, int piece_bytes, uint32_t x, uint32_t y) {
+    auto put = [](uint8_t* p, uint32_t c0, uint32_t c1) {
+        if (NEG) {
+            c0 ^= 0x20202020u;
+            c1 ^= 0x20202020u;
+        }
+        auto two = [](uint32_t c, uint32_t w, uint32_t add) { return __builtin_amdgcn_udot4(c, w, add, false); };
+        const uint32_t z0 = two(c0, 0x00004001u, two(c0, 0x40010000u, 0u) << 12);
+        const uint32_t z1 = two(c1, 0x00004001u, two(c1, 0x40010000u, 0u) << 12);
+        *(bl_u32a2*)p = z0 | (z1 << 24);
+        *(uint16_t*)(p + 4) = (uint16_t)(z1 >> 8);
+    };
+    auto high = [](uint32_t q) {
+        const uint32_t s = (q >> 7) & 0x01010101u;
+        const uint32_t h = ((q >> 4) & 0x0F0F0F0Fu) ^ ((s << 4) - s);
+        return h + ((s << 5) + s);
+    };
+    put(dst, x & 0x0F0F0F0Fu, y & 0x0F0F0F0Fu);
+    put(dst + piece_bytes, high(x), high(y));
+}
+/* 2-bit form: the sixteen activations k = 16 c16 .. + 15 (word c16 % 4 of chunk c16 / 4).  Nibble j of
+ * the word masked at bit pair parity f is bit pair 2 j + f: weight 2 j + f in layout 0, weight
+ * 4 (pair % 4) + pair / 4 in layout 1. */
+__device__ __forceinline__ void bl_lds_put16(uint8_t* Qs, int c16, int layout, uint32_t a0, uint32_t a1, uint32_t a2,
+                                             uint32_t a3) {
+    uint8_t* const dst = Qs + (c16 >> 2) * BL_B2_CHUNK + (c16 & 3) * 6;
+    if (layout == 0) {
+        bl_lds_put8(dst, 48, __builtin_amdgcn_perm(a1, a0, 0x06040200u), __builtin_amdgcn_perm(a3, a2, 0x06040200u));
+        bl_lds_put8(dst + 24, 48, __builtin_amdgcn_perm(a1, a0, 0x07050301u), __builtin_amdgcn_perm(a3, a2, 0x07050301u));
+    } else {
+        bl_lds_put8(dst, 48, __builtin_amdgcn_perm(a2, a0, 0x05010400u), __builtin_amdgcn_perm(a2, a0, 0x07030602u));
+        bl_lds_put8(dst + 24, 48, __builtin_amdgcn_perm(a3, a1, 0x05010400u), __builtin_amdgcn_perm(a3, a1, 0x07030602u));
+    }
+}
+/* Five per byte: the twenty activations of word wd, x[i] = those that meet digit i of its four bytes
+ * (k = 20 wd + 4 i + 0..3).  A byte's two nibbles hold digits 0 and 1, or 2 and 3, or 4 and nothing; digit 4
+ * comes with the other sign (bl_t5_digits). */
+__device__ __forceinline__ void bl_lds_put20(uint8_t* Qs, int wd, const uint32_t* x) {
+    constexpr int PIECE = BL_T5_CHUNK / 2;
+    uint8_t* const dst = Qs + (wd >> 2) * BL_T5_CHUNK + (wd & 3) * 6;
+    bl_lds_put8(dst, PIECE, __builtin_amdgcn_perm(x[1], x[0], 0x05010400u), __builtin_amdgcn_perm(x[1], x[0], 0x07030602u));
+    bl_lds_put8(dst + BL_T5_SET, PIECE, __builtin_amdgcn_perm(x[3], x[2], 0x05010400u),
+                __builtin_amdgcn_perm(x[3], x[2], 0x07030602u));
+    bl_lds_put8<true>(dst + 2 * BL_T5_SET, PIECE, __builtin_amdgcn_perm(0u, x[4], 0x05010400u),
+                      __builtin_amdgcn_perm(0u, x[4], 0x07030602u));
 }
 
-/* Stages the activation row of P: Qs = the image above, misc[0] = sum_k q, misc[1] = token part
- * of the rescale factor (float bits).  Ends with a barrier. */
-__device__ __forceinline__ void bl_stream_stage(const bl_stream_item& P, int* __restrict__ Qs,
-                                                    int* __restrict__ misc, bool owner) {
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int groups = P.nchunks * 4;
+/* A barrier behind which the LDS writes in front of it are seen; loads stay in flight (__syncthreads waits for them). */
+__device__ __forceinline__ void bl_lds_barrier() {
+    asm volatile("" ::: "memory");
+    BL_WAIT_LGKM0();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+/* The activations that meet one packed word, as they were loaded (nothing waits for them here): UD pairs of bf16
+ * words, or, of an int8 row, UD dwords in x[.][0] (five per byte) or in the first sixteen bytes.  A row may end
+ * inside a word of five: the values behind `valid` dwords are zeros. */
+template <int FORM>
+struct bl_unit {
+    static constexpr int UD = FORM == BL_FORM_TRIT5 ? 5 : 4;
+    bl_v2i x[UD];
+    int valid;
+    __device__ __forceinline__ void load(const uint16_t* xbf16, int wd, int dwords) {
+        valid = dwords - wd * UD;
+        if constexpr (FORM == BL_FORM_TRIT5) {
+            const bl_v2i BL_G* p = bl_gc<bl_v2i>(xbf16) + wd * UD;
+#pragma unroll
+            for (int i = 0; i < UD; ++i) x[i] = p[i < valid ? i : 0];
+        } else {
+            const bl_gv4i* p = (const bl_gv4i*)xbf16 + wd * 2;
+            const bl_v4i a = p[0], b = p[1];
+            x[0] = bl_v2i{a[0], a[1]};
+            x[1] = bl_v2i{a[2], a[3]};
+            x[2] = bl_v2i{b[0], b[1]};
+            x[3] = bl_v2i{b[2], b[3]};
+        }
+    }
+    __device__ __forceinline__ void load_q(const int8_t* q, int wd, int dwords) {
+        valid = dwords - wd * UD;
+        if constexpr (FORM == BL_FORM_TRIT5) {
+            const int BL_G* p = bl_gc<int>(q) + wd * UD;
+#pragma unroll
+            for (int i = 0; i < UD; ++i) x[i] = bl_v2i{p[i < valid ? i : 0], 0};
+        } else {
+            const bl_v4i a = ((const bl_gv4i*)q)[wd];
+            x[0] = bl_v2i{a[0], a[1]};
+            x[1] = bl_v2i{a[2], a[3]};
+            x[2] = x[3] = bl_v2i{0, 0};
+        }
+    }
+    __device__ __forceinline__ uint32_t get(int i, int e) const {
+        return FORM == BL_FORM_BIT2 || i < valid ? (uint32_t)x[i][e] : 0u;
+    }
+    __device__ __forceinline__ uint32_t get_q(int i) const {
+        return FORM == BL_FORM_BIT2 ? (uint32_t)x[i >> 1][i & 1] : get(i, 0);
+    }
+    template <bool SKIP>
+    __device__ __forceinline__ float absmax() const {
+        bl_mag2<SKIP> m;
+#pragma unroll
+        for (int i = 0; i < UD; ++i) {
+            m.take(get(i, 0));
+            m.take(get(i, 1));
+        }
+        return m.get();
+    }
+    template <int MODE>
+    __device__ __forceinline__ void quant(float inv, uint32_t* a) const {
+        auto l = [](uint32_t w) { return __uint_as_float(w << 16); };
+        auto h = [](uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); };
+#pragma unroll
+        for (int i = 0; i < UD; ++i)
+            a[i] = bl_quant4<MODE>(l(get(i, 0)), h(get(i, 0)), l(get(i, 1)), h(get(i, 1)), inv);
+    }
+};
+
+/* What a workgroup reads of a product besides its weights, requested in front of the first of them: loads arrive in
+ * order, and the weights take longer. */
+template <int FORM>
+struct bl_row {
+    bl_unit<FORM> x[2];       /* this thread's first two words' activations (all of them up to K = 8192) */
+    int rowsum;
+    float scale, beta;
+};
+
+/* Stages the activation row of P: Qs = the image above, misc[0] = what the sum of a row's products is
+ * taken from (2-bit form: sum_k q, subtracted; five per byte: sum_k q with digit 4's terms negative, the
+ * products are subtracted), misc[1] = token part of the rescale factor (float bits).  The waves meet at barriers that
+ * wait for LDS alone: the first weights stay in flight.  Ends with a barrier. */
+template <int FORM, int LP>
+__device__ __forceinline__ void bl_stream_stage(const bl_stream_item& P, const bl_row<FORM>& row,
+                                                    uint8_t* __restrict__ Qs, int* __restrict__ misc, bool owner) {
+    constexpr int CHUNK = FORM == BL_FORM_TRIT5 ? BL_T5_CHUNK : BL_B2_CHUNK, UD = bl_unit<FORM>::UD;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));          /* nothing of this is worth a register outside (the compiler would hoist it and spill) */
+    const int lane = tid & 63, w = tid >> 6;
+    const int words = P.nchunks * 4, dwords = P.qgroups * 4;
     float* fs = (float*)(misc + 2);
     int* ssum = misc + 6;
-    if (tid < BL_QSTRIDE) Qs[P.nchunks * BL_QSTRIDE + tid] = 0;
+    /* zeros in front of and behind the row, see bl_stream_slice */
+    {
+        const int lead = P.shift * CHUNK / 16, tail = (P.shift + P.nchunks) * CHUNK / 16,
+                  all = (P.shift + P.parts * LP * 8 + 1) * CHUNK / 16;
+#pragma unroll 1
+        for (int i = tid; i < lead + all - tail; i += 256)
+            ((bl_v4i*)Qs)[i < lead ? i : i - lead + tail] = bl_v4i{0, 0, 0, 0};
+    }
+    uint8_t* const img = Qs + P.shift * CHUNK;
     int part = 0;
+    auto place = [&](int wd, const uint32_t* a) __attribute__((always_inline)) {
+        if constexpr (FORM == BL_FORM_TRIT5) bl_lds_put20(img, wd, a);
+        else bl_lds_put16(img, wd, P.layout, a[0], a[1], a[2], a[3]);
+    };
     if (P.xbf16) {
-        const bl_gv4i* x = (const bl_gv4i*)P.xbf16;
-        auto ld = [&](int i) {
-            const bl_v4i v = x[i];
-            return make_uint4((uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]);
+        auto all_max = [&](float v) {
+            v = bl_wave_max(v);
+            if (lane == 0) fs[w] = v;
+            bl_lds_barrier();
+            return bl_max_pos(bl_max_pos(fs[0], fs[1]), bl_max_pos(fs[2], fs[3]));
         };
-        float mx = 0.0f;
-        for (int u = tid; u < groups; u += 256)
-            mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16(ld(2 * u)), bl_absmax8_bf16(ld(2 * u + 1))));
-        mx = bl_wave_max(mx);
-        if (lane == 0) fs[w] = mx;
-        __syncthreads();
-        const float gamma = bl_max_pos(bl_max_pos(fs[0], fs[1]), bl_max_pos(fs[2], fs[3]));   /* (NaN is the largest) */
-        float gg = fmaxf(gamma, 1e-5f);
-        const float inv = bl_div_rn(127.0f, gg);
-        for (int u = tid; u < groups; u += 256) {
-            uint32_t a0, a1, a2, a3;
-            bl_quant8_words(ld(2 * u), inv, a0, a1);
-            bl_quant8_words(ld(2 * u + 1), inv, a2, a3);
-            part += bl_sum16(a0, a1, a2, a3);
-            const bl_v4i qv = {(int)a0, (int)a1, (int)a2, (int)a3};
-            if (owner && P.q_out) *(bl_gv4i*)(P.q_out + u * 16) = qv;
-            bl_lds_put16(Qs, u, P.layout, a0, a1, a2, a3);
+        float inv = 0.0f;
+        auto put = [&](const bl_unit<FORM>& x, int wd, auto mode) __attribute__((always_inline)) {
+            uint32_t a[UD];
+            x.template quant<decltype(mode)::value>(inv, a);
+#pragma unroll
+            for (int i = 0; i < UD; ++i) part = __builtin_amdgcn_sdot4((int)a[i], i < 4 ? 0x01010101 : -1, part, false);
+            if (owner && P.q_out) {
+                if constexpr (FORM == BL_FORM_TRIT5) {
+#pragma unroll
+                    for (int i = 0; i < UD; ++i)
+                        if (wd * UD + i < dwords) bl_g((uint32_t*)P.q_out)[wd * UD + i] = a[i];
+                } else {
+                    ((bl_gv4i*)P.q_out)[wd] = bl_v4i{(int)a[0], (int)a[1], (int)a[2], (int)a[3]};
+                }
+            }
+            place(wd, a);
+        };
+        float mx = bl_max_pos(row.x[0].template absmax<false>(), row.x[1].template absmax<false>());
+#pragma unroll 1
+        for (int wd = tid + 512; wd < words; wd += 256) {
+            bl_unit<FORM> y;
+            y.load(P.xbf16, wd, dwords);
+            mx = bl_max_pos(mx, y.template absmax<false>());
         }
-        if (bl_not_finite(gamma)) {
-            part = 0;
-            gg = bl_quant_row_again(
-                groups, tid, 256, [&](int u, uint4& lo, uint4& hi) {
-                    lo = ld(2 * u);
-                    hi = ld(2 * u + 1);
-                },
-                [&](float v) {
-                    v = bl_wave_max(v);
-                    __syncthreads();                       /* fs has been read */
-                    if (lane == 0) fs[w] = v;
-                    __syncthreads();
-                    return bl_max_pos(bl_max_pos(fs[0], fs[1]), bl_max_pos(fs[2], fs[3]));
-                },
-                [&](int u, uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3) {
-                    part += bl_sum16(a0, a1, a2, a3);
-                    if (owner && P.q_out) *(bl_gv4i*)(P.q_out + u * 16) = bl_v4i{(int)a0, (int)a1, (int)a2, (int)a3};
-                    bl_lds_put16(Qs, u, P.layout, a0, a1, a2, a3);
-                });
+        const float gamma = all_max(mx);                       /* (NaN is the largest) */
+        float gg = fmaxf(gamma, 1e-5f);
+        if (!bl_not_finite(gamma)) {
+            inv = bl_div_rn(127.0f, gg);
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                if (tid + j * 256 < words) put(row.x[j], tid + j * 256, bl_mode<BL_Q_FINITE>{});
+#pragma unroll 1
+            for (int wd = tid + 512; wd < words; wd += 256) {
+                bl_unit<FORM> y;
+                y.load(P.xbf16, wd, dwords);
+                put(y, wd, bl_mode<BL_Q_FINITE>{});
+            }
+        } else {                                               /* once more, with NaN passed over */
+            mx = 0.0f;
+#pragma unroll 1
+            for (int wd = tid; wd < words; wd += 256) {
+                bl_unit<FORM> y;
+                y.load(P.xbf16, wd, dwords);
+                mx = bl_max_pos(mx, y.template absmax<true>());
+            }
+            bl_lds_barrier();                                   /* fs has been read */
+            gg = fmaxf(all_max(mx), 1e-5f);
+            inv = bl_div_rn(127.0f, gg);
+#pragma unroll 1
+            for (int wd = tid; wd < words; wd += 256) {
+                bl_unit<FORM> y;
+                y.load(P.xbf16, wd, dwords);
+                put(y, wd, bl_mode<BL_Q_ROW>{});
+            }
         }
         if (tid == 0) {
             const float sc = bl_div_rn(gg, 127.0f);
@@ -283,317 +442,273 @@ __device__ __forceinline__ void bl_stream_stage(const bl_stream_item& P, int* __
         }
         part = bl_wave_sum(part);
         if (lane == 0) ssum[w] = part;
-        __syncthreads();
+        bl_lds_barrier();
         if (tid == 0) misc[0] = (ssum[0] + ssum[1]) + (ssum[2] + ssum[3]);
     } else {
-        const bl_gv4i* qg = (const bl_gv4i*)P.q;
-        for (int u = tid; u < groups; u += 256) {
-            const bl_v4i v = qg[u];
-            bl_lds_put16(Qs, u, P.layout, (uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]);
+        auto take = [&](const bl_unit<FORM>& y, int wd) __attribute__((always_inline)) {
+            uint32_t a[UD];
+#pragma unroll
+            for (int i = 0; i < UD; ++i) a[i] = y.get_q(i);
+            if constexpr (FORM == BL_FORM_TRIT5) part = __builtin_amdgcn_sdot4((int)a[4], 0x01010101, part, false);
+            place(wd, a);
+        };
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            if (tid + j * 256 < words) take(row.x[j], tid + j * 256);
+#pragma unroll 1
+        for (int wd = tid + 512; wd < words; wd += 256) {
+            bl_unit<FORM> y;
+            y.load_q(P.q, wd, dwords);
+            take(y, wd);
+        }
+        if constexpr (FORM == BL_FORM_TRIT5) {
+            part = bl_wave_sum(part);
+            if (lane == 0) ssum[w] = part;
+            bl_lds_barrier();
         }
         if (tid == 0) {
-            misc[0] = *(const int32_t BL_G*)P.rowsum;
-            misc[1] = P.scale ? __float_as_int(*(const float BL_G*)P.scale) : 0;
+            misc[0] = FORM == BL_FORM_TRIT5 ? row.rowsum - 2 * ((ssum[0] + ssum[1]) + (ssum[2] + ssum[3])) : row.rowsum;
+            misc[1] = __float_as_int(row.scale);
         }
     }
-    __syncthreads();
-}
-
-/* One product slice [ub, ue) of row groups, for a product whose lanes hold LP 16-byte weight
- * loads per row (k chunks g, g+G, .. of the row; G = 1 << lgG lanes per row, R = 64 / G rows
- * per wave-wide load).  A "unit" is S consecutive row groups: S*LP loads per lane per register
- * set.  The four waves of the workgroup take units round-robin.  Every load of the steady loop
- * is unconditional (out-of-range lanes read a clamped, valid address and meet the all-zero
- * chunk, or are never stored), so the hardware counter waits are exact and the loads of unit
- * i+1 stay in flight during the dot products of unit i.  The residual value of a row travels
- * with the row's weights: a load issued later, in the epilogue, could only be waited for
- * together with every weight load issued before it (with no residual every lane reads beta
- * instead, a valid address, and the value is not used). */
-template <int LP, int S>
-__device__ __forceinline__ void bl_stream_slice(const bl_stream_item& P, const int ub, const int ue,
-                                                    int* __restrict__ Qs, int* __restrict__ misc,
-                                                    const bool restage) {
-    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int N = P.N, nchunks = P.nchunks, lgG = P.lgG;
-    const int R = 64 >> lgG;
-    const int r = lane >> lgG, g = lane & ((1 << lgG) - 1);
-    const int nunits = (ue - ub + S - 1) / S;            /* the last unit may be partial */
-    const bl_gv4i* const wbase = (const bl_gv4i*)P.packed;
-    int32_t BL_G* const acc_g = (int32_t BL_G*)P.acc;
-    float BL_G* const y_g = (float BL_G*)P.y;
-    const float BL_G* const res_g = (const float BL_G*)P.residual;
-    const float BL_G* const res_base = res_g ? res_g : (const float BL_G*)P.beta;
-    int coff[LP], qoff[LP];                              /* clamped k chunk of each load; its LDS image */
-#pragma unroll
-    for (int i = 0; i < LP; ++i) {
-        const int chunk = g + (i << lgG);
-        coff[i] = chunk < nchunks ? chunk : nchunks - 1;
-        qoff[i] = (chunk < nchunks ? chunk : nchunks) * BL_QSTRIDE;   /* clamped lanes meet the zero chunk */
-    }
-    auto issue = [&](bl_v4i* p, float* rv, int unit) {
-#pragma unroll
-        for (int j = 0; j < S; ++j) {
-            int n = (ub + unit * S + j) * R + r;
-            n = n < N ? n : N - 1;
-            const bl_gv4i* wrow = wbase + (int64_t)n * nchunks;
-#pragma unroll
-            for (int i = 0; i < LP; ++i) p[j * LP + i] = __builtin_nontemporal_load(wrow + coff[i]);
-            rv[j] = res_base[res_g ? n : 0];
-        }
-    };
-    bl_v4i pa[S * LP], pb[S * LP];
-    float ra[S], rb[S];
-    int u = w;                                           /* this wave's unit */
-    if (u < nunits) issue(pa, ra, u);                    /* in flight during the staging */
-    if (restage) __syncthreads();                        /* every wave is done with the previous image */
-    bl_stream_stage(P, Qs, misc, ub == 0);
-    if (u >= nunits) return;
-    const int rs = misc[0];
-    float cf = 0.0f;
-    if (y_g) cf = *(const float BL_G*)P.beta * __int_as_float(misc[1]);
-
-    auto finish = [&](const bl_v4i* p, const float* rv, int unit) {
-#pragma unroll
-        for (int j = 0; j < S; ++j) {
-            int A[4] = {0, 0, 0, 0};
-            /* The image does not change inside the loop, so the compiler would hoist these reads
-             * out of it and hold them in 16 * LP registers again: the address is hidden from it. */
-            bl_v4i a[1][4];
-            auto rd = [&](int i, bl_v4i* dst) {
-                int qo = qoff[i];
-                asm volatile("" : "+v"(qo));
-#pragma unroll
-                for (int s = 0; s < 4; ++s) dst[s] = *(const bl_v4i*)(Qs + qo + s * 4);
-            };
-#pragma unroll
-            for (int i = 0; i < LP; ++i) {
-                rd(i, a[0]);
-                bl_stream_dot(p[j * LP + i], a[0], A);
-            }
-            int v = A[0] + (A[1] >> 2) + ((A[2] + A[3]) >> 4);
-            v = bl_group_sum_rt(v, lgG);
-            const int rg = ub + unit * S + j;
-            const int n = rg * R + r;
-            if (g == 0 && rg < ue && n < N) {
-                const int val = v - rs;
-                if (acc_g) acc_g[n] = val;
-                if (y_g) {
-                    const float t = (float)val * cf;
-                    y_g[n] = res_g ? rv[j] + t : t;
-                }
-            }
-        }
-    };
-    for (;;) {
-        if (u + 4 >= nunits) { finish(pa, ra, u); break; }
-        issue(pb, rb, u + 4);
-        finish(pa, ra, u);
-        u += 4;
-        if (u + 4 >= nunits) { finish(pb, rb, u); break; }
-        issue(pa, ra, u + 4);
-        finish(pb, rb, u);
-        u += 4;
-    }
+    bl_lds_barrier();
 }
 
 /* ---- five weights per byte (BL_LAYOUT_TRIT5) ---------------------------------------------------
  * A byte b = ceil(v * 256 / 243) holds v = sum_i c_i * 3^(4-i), five offset codes c_i in {0,1,2}.
  * Multiplying by 9 moves the two leading base-3 digits, as one number 0..8, into bits 8..11 and leaves
  * the rest in the low byte.  The four bytes of a word are handled as two pairs in 16-bit lanes (a byte
- * times 9 fits 12 bits); a byte permute gathers the four numbers, and two more use them as selectors into
- * eight-byte tables: the first and the second digit of four weights each, an operand of v_dot4_i32_i8
- * against k = 20*word + 4*i + 0..3.  A selector of 8 replicates the sign of table byte 1, so the tables
- * hold c - 3 (entry 8 is then -1 and byte 1 negative, as it has to be); sum_k (c - 3) q = sum_k c q - 3 sum_k q.
- * Per 16-byte load: 80 weights, 20 dot products and ~80 more instructions (digit by digit: ~100, of
- * which the three-operand ones take twice the time of the plain ones). */
-#define BL_T5_QSTRIDE 24      /* dwords per 80-weight chunk in LDS: 20 + 4 of padding */
-
-__device__ __forceinline__ int bl_t5_dot(const bl_v4i p, const bl_v4i* a, int A) {
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        const uint32_t w = (uint32_t)p[d];
-        uint32_t e = w & 0x00FF00FFu, o = (w >> 8) & 0x00FF00FFu;
-        auto dot = [&](uint32_t dg, int i) { A = __builtin_amdgcn_sdot4((int)dg, a[(5 * d + i) >> 2][(5 * d + i) & 3], A, false); };
-#pragma unroll
-        for (int i = 0; i < 4; i += 2) {
-            e = (e << 3) + e;
-            o = (o << 3) + o;
-            const uint32_t t = __builtin_amdgcn_perm(o, e, 0x07030501u);    /* bits 8..15 of the four lanes */
-            dot(__builtin_amdgcn_perm(0xFFFFFEFEu, 0xFEFDFDFDu, t), i);     /* t / 3 - 3 */
-            dot(__builtin_amdgcn_perm(0xFEFDFFFEu, 0xFDFFFEFDu, t), i + 1); /* t % 3 - 3 */
-            e &= 0x00FF00FFu;
-            o &= 0x00FF00FFu;
-        }
-        e = (e << 1) + e;
-        o = (o << 1) + o;
-        dot(__builtin_amdgcn_perm(o, e, 0x07030501u) + 0xFDFDFDFDu, 4);
-    }
-    return A;
+ * times 9 fits 12 bits); a byte permute gathers the four numbers, and another uses them as selectors
+ * into an eight-byte table of both digits as two 4-bit numbers: the B operand.  Selector 8 replicates
+ * the sign of table byte 1; the table holds 2 - c, so that entry 8 is zero and no sign is set.  The
+ * last digit c is an operand as it is, against -q: sum_k W q = sum q (its own digit positions negative) -
+ * sum (2 - c) q + sum c q.  17 vector instructions per 20 weights, each four clocks of a wave; they are what the
+ * kernel waits for (without them the 30-layer table takes 74 us). */
+__device__ __forceinline__ void bl_t5_digits(const uint32_t w, int& d01, int& d23, int& d4) {
+    uint32_t mask = 0x00FF00FFu, nine = 9, three = 3;
+    asm("" : "+s"(mask), "+s"(nine), "+s"(three));          /* (in scalar registers; or the multiplications become shift-and-add) */
+    uint32_t e = w & mask, o = __builtin_amdgcn_perm(0u, w, 0x0C030C01u);
+    auto two = [&]() {
+        e = __umul24(e, nine);
+        o = __umul24(o, nine);
+        const uint32_t t = __builtin_amdgcn_perm(o, e, 0x07030501u);        /* bits 8..15 of the four lanes */
+        e &= mask;
+        o &= mask;
+        return (int)__builtin_amdgcn_perm(0x10200111u, 0x21021222u, t);     /* (2 - t / 3) | (2 - t % 3) << 4 */
+    };
+    d01 = two();
+    d23 = two();
+    e = __umul24(e, three);
+    o = __umul24(o, three);
+    d4 = (int)__builtin_amdgcn_perm(o, e, 0x07030501u);
 }
 
-/* Stages the activation row for the five-per-byte form: the int8 row in its natural order, 80
- * bytes per chunk, zeros from the end of the row to the end of the last chunk and one all-zero
- * chunk behind it.  misc as in bl_stream_stage.  Ends with a barrier. */
-__device__ __forceinline__ void bl_stream_stage_t5(const bl_stream_item& P, int* __restrict__ Qs,
-                                                       int* __restrict__ misc, bool owner) {
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int groups = P.qgroups;
-    float* fs = (float*)(misc + 2);
-    int* ssum = misc + 6;
-    auto put = [&](int u, bl_v4i v) { *(bl_v4i*)(Qs + (u / 5) * BL_T5_QSTRIDE + (u % 5) * 4) = v; };
-    for (int u = groups + tid; u < (P.nchunks + 1) * 5; u += 256) put(u, bl_v4i{0, 0, 0, 0});
-    int part = 0;
-    if (P.xbf16) {
-        const bl_gv4i* x = (const bl_gv4i*)P.xbf16;
-        auto ld = [&](int i) {
-            const bl_v4i v = x[i];
-            return make_uint4((uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]);
-        };
-        float mx = 0.0f;
-        for (int u = tid; u < groups; u += 256)
-            mx = bl_max_pos(mx, bl_max_pos(bl_absmax8_bf16(ld(2 * u)), bl_absmax8_bf16(ld(2 * u + 1))));
-        mx = bl_wave_max(mx);
-        if (lane == 0) fs[w] = mx;
-        __syncthreads();
-        const float gamma = bl_max_pos(bl_max_pos(fs[0], fs[1]), bl_max_pos(fs[2], fs[3]));   /* (NaN is the largest) */
-        float gg = fmaxf(gamma, 1e-5f);
-        const float inv = bl_div_rn(127.0f, gg);
-        for (int u = tid; u < groups; u += 256) {
-            uint32_t a0, a1, a2, a3;
-            bl_quant8_words(ld(2 * u), inv, a0, a1);
-            bl_quant8_words(ld(2 * u + 1), inv, a2, a3);
-            part += bl_sum16(a0, a1, a2, a3);
-            const bl_v4i qv = {(int)a0, (int)a1, (int)a2, (int)a3};
-            if (owner && P.q_out) *(bl_gv4i*)(P.q_out + u * 16) = qv;
-            put(u, qv);
-        }
-        if (bl_not_finite(gamma)) {
-            part = 0;
-            gg = bl_quant_row_again(
-                groups, tid, 256, [&](int u, uint4& lo, uint4& hi) {
-                    lo = ld(2 * u);
-                    hi = ld(2 * u + 1);
-                },
-                [&](float v) {
-                    v = bl_wave_max(v);
-                    __syncthreads();                       /* fs has been read */
-                    if (lane == 0) fs[w] = v;
-                    __syncthreads();
-                    return bl_max_pos(bl_max_pos(fs[0], fs[1]), bl_max_pos(fs[2], fs[3]));
-                },
-                [&](int u, uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3) {
-                    part += bl_sum16(a0, a1, a2, a3);
-                    const bl_v4i qv = {(int)a0, (int)a1, (int)a2, (int)a3};
-                    if (owner && P.q_out) *(bl_gv4i*)(P.q_out + u * 16) = qv;
-                    put(u, qv);
-                });
-        }
-        if (tid == 0) {
-            const float sc = bl_div_rn(gg, 127.0f);
-            misc[1] = __float_as_int(P.fixed_scale > 0.0f ? P.fixed_scale : sc);
-            if (owner && P.scale_out) *(float BL_G*)P.scale_out = sc;
-        }
-        part = bl_wave_sum(part);
-        if (lane == 0) ssum[w] = part;
-        __syncthreads();
-        if (tid == 0) misc[0] = (ssum[0] + ssum[1]) + (ssum[2] + ssum[3]);
-    } else {
-        const bl_gv4i* qg = (const bl_gv4i*)P.q;
-        for (int u = tid; u < groups; u += 256) put(u, qg[u]);
-        if (tid == 0) {
-            misc[0] = *(const int32_t BL_G*)P.rowsum;
-            misc[1] = P.scale ? __float_as_int(*(const float BL_G*)P.scale) : 0;
-        }
-    }
-    __syncthreads();
-}
-
-/* bl_stream_slice for the five-per-byte form: the same double-buffered, unconditional loads; a
- * load is 80 weights against 20 activation dwords read from LDS right before its dot products. */
-template <int LP>
-__device__ __forceinline__ void bl_stream_slice_t5(const bl_stream_item& P, const int ub, const int ue,
-                                                       int* __restrict__ Qs, int* __restrict__ misc,
-                                                       const bool restage) {
+/* One product slice [ub, ue) of row groups of eight weight rows.  A row group is read in P.parts
+ * parts of LP wave-wide loads; each of the four waves of the workgroup takes a contiguous quarter of the
+ * row groups (round-robin, the workgroups read in step at one stride, which may be that of few
+ * memory channels: sixty products of 13824 x 2560 100 us against 86) and
+ * keeps one part in flight while another is multiplied.  Every load of the steady loop
+ * is unconditional (out-of-range lanes read a clamped, valid address and meet zero activations,
+ * or are never stored), so the hardware counter waits are exact and the loads of the next part
+ * stay in flight during the products of this one.  The residual value of a row travels
+ * with the row's weights: a load issued later, in the epilogue, could only be waited for
+ * together with every weight load issued before it (with no residual every lane reads beta
+ * instead, a valid address, and the value is not used). */
+template <int FORM, int LP>
+__device__ __forceinline__ void bl_stream_slice(const bl_stream_item& P, const int ub, const int ue,
+                                                    uint8_t* __restrict__ Qs, int* __restrict__ misc,
+                                                    const bool restage) {
+    constexpr int CHUNK = FORM == BL_FORM_TRIT5 ? BL_T5_CHUNK : BL_B2_CHUNK;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int N = P.N, nchunks = P.nchunks, lgG = P.lgG;
-    const int R = 64 >> lgG;
-    const int r = lane >> lgG, g = lane & ((1 << lgG) - 1);
-    const int nunits = ue - ub;
-    const bl_gv4i* const wbase = (const bl_gv4i*)P.packed;
+    const int N = P.N, parts = P.parts;
+    /* lanes 0..31 take the even rows of a row group, 32..63 the odd ones.  Where rows are an odd multiple of 64 bytes
+     * long (K = 6912) an odd row starts in the middle of a 128-byte line: its loads, and its k group of A, are
+     * P.shift = 4 chunks back, so that every load of a row is one line (P.shift zero chunks in front of the image). */
+    const int r = ((lane >> 2) & 6) | (lane >> 5), u = lane & 7, h = lane >> 5;
+    const int row_bytes = P.nchunks * 16;
+    const int u16 = u * 16 - (h ? P.shift * 16 : 0);
+    const char BL_G* const wbase = (const char BL_G*)P.packed;
     int32_t BL_G* const acc_g = (int32_t BL_G*)P.acc;
     float BL_G* const y_g = (float BL_G*)P.y;
     const float BL_G* const res_g = (const float BL_G*)P.residual;
-    const float BL_G* const res_base = res_g ? res_g : (const float BL_G*)P.beta;
-    int coff[LP], qoff[LP];
+    const int each = (ue - ub) >> 2, extra = (ue - ub) & 3;
+    const int mine = each + (w < extra ? 1 : 0);         /* row groups of this wave (may be 0) */
+    const int first = ub + w * each + (w < extra ? w : extra);
+    int irg = first, ipart = 0;                          /* issue cursor */
+    /* Lanes behind their row's end read its last chunk again, which meets zero activations (the next row's chunks would
+     * do as well, but are fetched twice then: 60 layers of 640 / 1280 16.4 us against 15.4); a
+     * shifted load in front of an odd row reads the end of the even one.  Rows behind N are held inside the matrix
+     * and not stored.  Behind the wave's last row group every lane reads the first bytes of that row group once more: one
+     * line, and the loop needs no second copy of itself without loads. */
+    const int row_end = r * row_bytes + row_bytes - 16;
+    const char BL_G* rg_at = wbase + (int64_t)irg * 8 * row_bytes;
+    const float BL_G* rv_at = res_g ? res_g + (int64_t)irg * 8 : (const float BL_G*)P.beta;
+    int lane_off[LP];
 #pragma unroll
-    for (int i = 0; i < LP; ++i) {
-        const int chunk = g + (i << lgG);
-        coff[i] = chunk < nchunks ? chunk : nchunks - 1;
-        qoff[i] = (chunk < nchunks ? chunk : nchunks) * BL_T5_QSTRIDE;
-    }
-    auto issue = [&](bl_v4i* p, float& rv, int unit) {
-        int n = (ub + unit) * R + r;
-        n = n < N ? n : N - 1;
-        const bl_gv4i* wrow = wbase + (int64_t)n * nchunks;
+    for (int i = 0; i < LP; ++i) lane_off[i] = r * row_bytes + u16 + i * 128;
+    auto issue = [&](bl_v4i* p, float& rv) {
+        const bool over = irg == first + mine;
+        const int rows = N - irg * 8;                    /* rows from this row group on */
+        int off = ipart * (LP * 128);
+        const int end = max(row_end - off, 0);
+        int limit = rows >= 8 ? 0x7FFFFFFF : rows * row_bytes - 16 - off;
+        off = over ? -8 * row_bytes : limit < 0 ? 0 : off;
+        limit = over || limit < 0 ? 0 : limit;
+        asm("" : "+s"(limit));                           /* (one scalar, not a select per lane and load) */
+        const char BL_G* const base = rg_at + off;
 #pragma unroll
-        for (int i = 0; i < LP; ++i) p[i] = __builtin_nontemporal_load(wrow + coff[i]);
-        rv = res_base[res_g ? n : 0];
+        for (int i = 0; i < LP; ++i)
+            p[i] = __builtin_nontemporal_load(
+                (const bl_gv4i*)(base + (uint32_t)min(min(lane_off[i], end), limit)));
+        const int rlim = res_g ? (over ? -1 : rows - 1) : 0;
+        rv = rv_at[min(r, rlim)];
+        const bool next = !over && ++ipart == parts;
+        ipart = next ? 0 : ipart;
+        irg += next ? 1 : 0;
+        rg_at += next ? 8 * row_bytes : 0;
+        rv_at += next && res_g ? 8 : 0;
     };
     bl_v4i pa[LP], pb[LP];
     float ra = 0.0f, rb = 0.0f;
-    int u = w;
-    if (u < nunits) issue(pa, ra, u);
-    if (restage) __syncthreads();
-    bl_stream_stage_t5(P, Qs, misc, ub == 0);
-    if (u >= nunits) return;
+    bl_row<FORM> row;
+    row.rowsum = 0;
+    row.scale = 0.0f;
+    auto word = [&](int j) {                             /* (word 0 again does not change the maximum) */
+        const int wd = (int)threadIdx.x + j * 256;
+        return wd < P.nchunks * 4 ? wd : 0;
+    };
+    if (P.xbf16) {
+        row.x[0].load(P.xbf16, word(0), P.qgroups * 4);
+        row.x[1].load(P.xbf16, word(1), P.qgroups * 4);
+    } else {
+        row.x[0].load_q(P.q, word(0), P.qgroups * 4);
+        row.x[1].load_q(P.q, word(1), P.qgroups * 4);
+        row.rowsum = *bl_gc<int32_t>(P.rowsum);
+        row.scale = *bl_gc<float>(P.scale ? P.scale : P.beta);
+    }
+    row.beta = *bl_gc<float>(P.beta);
+    asm volatile("" ::: "memory");
+    issue(pa, ra);                                       /* in flight during the staging */
+    if (restage) bl_lds_barrier();                       /* every wave is done with the previous image */
+    bl_stream_stage<FORM, LP>(P, row, Qs, misc, ub == 0);
+    if (mine == 0) return;
     const int rs = misc[0];
     float cf = 0.0f;
-    if (y_g) cf = *(const float BL_G*)P.beta * __int_as_float(misc[1]);
+    if (y_g) cf = row.beta * __int_as_float(misc[1]);
 
-    auto finish = [&](const bl_v4i* p, const float rv, int unit) {
-        int A = 0;
+    /* this lane of A: chunk u, k group (lane / 8) % 2, piece (lane / 16) % 2; zeros in the other k group */
+    const bool live = ((lane >> 3) & 1) == h;
+    const int a_first = live ? (u + (h ? 0 : P.shift)) * CHUNK + ((lane >> 4) & 1) * (CHUNK / 2) : (P.shift + parts * LP * 8) * CHUNK;
+    const int a_step = live ? 8 * CHUNK : 0;
+    const int live_loads = (P.nchunks + P.shift + 7) / 8 - (parts - 1) * LP;
+    int at = a_first, ppart = 0, prg = first;            /* process cursor */
+    const int store_row = u == 0 ? r : 1 << 30;          /* one lane of eight stores */
+    bl_v16f D = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    auto step = [&](const bl_v4i* p, const float rv) {
+        /* The image does not change inside the loop, so the compiler could hoist these reads
+         * out of it and hold them in registers: the address is hidden from it. */
+        asm volatile("" : "+v"(at));
 #pragma unroll
         for (int i = 0; i < LP; ++i) {
-            int qo = qoff[i];
-            asm volatile("" : "+v"(qo));          /* keeps the reads inside the loop (see bl_stream_slice) */
-            bl_v4i a[5];
+            if (i > 0 && i >= live_loads && ppart == parts - 1) break;   /* idle slots of the last part */
+            /* (one load's operands at a time: with all of them in flight the loop spills) */
+            __builtin_amdgcn_sched_barrier(0);
+            const uint8_t* const q = Qs + at;
+            at += a_step;
+            auto operand = [&](int o) {                      /* 24 bytes, at a multiple of 16 or 8 behind one */
+                asm volatile("" ::: "memory");               /* (eight bytes of two operands in one read cost four moves) */
+                const bool first8 = o % 16 != 0;
+                const bl_v4i x = *(const bl_v4i*)(q + o + (first8 ? 8 : 0));
+                const bl_v2i y = *(const bl_v2i*)(q + o + (first8 ? 0 : 16));
+                return first8 ? bl_v8i{y[0], y[1], x[0], x[1], x[2], x[3], 0, 0} : bl_v8i{x[0], x[1], x[2], x[3], y[0], y[1], 0, 0};
+            };
+            /* (the first product of a row group starts from zero) */
+            auto first_mul = [&](const bl_v8i& a, const bl_v8i& b) {
+                if (i == 0 && ppart == 0) {
+                    bl_v16f z = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+                    D = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, z, 2, 4, 0, 0, 0, 0);
+                } else {
+                    D = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, D, 2, 4, 0, 0, 0, 0);
+                }
+            };
+            if constexpr (FORM == BL_FORM_BIT2) {
+                bl_v8i b0 = {0, 0, 0, 0, 0, 0, 0, 0}, b1 = b0;
 #pragma unroll
-            for (int t = 0; t < 5; ++t) a[t] = *(const bl_v4i*)(Qs + qo + t * 4);
-            A = bl_t5_dot(p[i], a, A);
-        }
-        const int v = bl_group_sum_rt(A, lgG);
-        const int rg = ub + unit;
-        const int n = rg * R + r;
-        if (g == 0 && n < N) {
-            const int val = v + 2 * rs;                  /* sum (c - 3) q + 3 sum q - sum q */
-            if (acc_g) acc_g[n] = val;
-            if (y_g) {
-                const float t = (float)val * cf;
-                y_g[n] = res_g ? rv + t : t;
+                for (int d = 0; d < 4; ++d) {
+                    const uint32_t wd = (uint32_t)p[i][d];
+                    b0[d] = (int)(wd & 0x33333333u);
+                    b1[d] = (int)((wd >> 2) & 0x33333333u);
+                }
+                first_mul(operand(0), b0);
+                D = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(operand(24), b1, D, 2, 4, 0, 0, 0, 0);
+            } else {
+                bl_v8i b0 = {0, 0, 0, 0, 0, 0, 0, 0}, b1 = b0, b2 = b0;
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    int d01, d23, d4;
+                    bl_t5_digits((uint32_t)p[i][d], d01, d23, d4);
+                    b0[d] = d01;
+                    b1[d] = d23;
+                    b2[d] = d4;
+                }
+                first_mul(operand(0), b0);
+                D = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(operand(BL_T5_SET), b1, D, 2, 4, 0, 0, 0, 0);
+                D = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(operand(2 * BL_T5_SET), b2, D, 2, 4, 0, 0, 0, 0);
             }
         }
+        /* (pinned: otherwise the last product goes to other registers than the accumulators that the next one starts from) */
+        asm volatile("" : "+v"(D));
+        if (++ppart < parts) return;
+        /* element v of lane l: A row (v % 4) + 8 (v / 4) + 4 (l / 32), i.e. chunk u = v % 4 + 4 (l / 32),
+         * k group v / 4 % 2, piece v / 8, against column l % 32.  A lane's own chunk is element u % 4 where
+         * u / 4 is its half. */
+        bl_mfma_fence();
+        float S[2];
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            float e[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) e[j] = __builtin_fmaf(D[8 + 4 * g + j], 16.0f, D[4 * g + j]);
+            S[g] = (u & 2) ? ((u & 1) ? e[3] : e[2]) : ((u & 1) ? e[1] : e[0]);
+        }
+        /* lower lanes: the even rows of the group, upper lanes: the odd ones */
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(S[0]), __float_as_uint(S[1]), false, false);
+        float t = __uint_as_float(u < 4 ? sw[0] : sw[1]);
+        t += bl_dppf<BL_DPP_QUAD_XOR1>(t);
+        t += bl_dppf<BL_DPP_QUAD_XOR2>(t);
+        t += bl_dppf<BL_DPP_ROW_HALF_MIRROR>(t);
+        const int v = (int)(t * 16.0f);
+        if (store_row < N - prg * 8) {
+            const int val = FORM == BL_FORM_TRIT5 ? rs - v : v - rs;
+            if (acc_g) acc_g[(int64_t)prg * 8 + (uint32_t)store_row] = val;
+            if (y_g) {
+                const float o = (float)val * cf;
+                y_g[(int64_t)prg * 8 + (uint32_t)store_row] = res_g ? rv + o : o;
+            }
+        }
+        ppart = 0;
+        at = a_first;
+        ++prg;
     };
-    for (;;) {
-        if (u + 4 >= nunits) { finish(pa, ra, u); break; }
-        issue(pb, rb, u + 4);
-        finish(pa, ra, u);
-        u += 4;
-        if (u + 4 >= nunits) { finish(pb, rb, u); break; }
-        issue(pa, ra, u + 4);
-        finish(pb, rb, u);
-        u += 4;
+    for (int left = mine * parts;;) {
+        issue(pb, rb);
+        step(pa, ra);
+        if (--left == 0) break;
+        issue(pa, ra);
+        step(pb, rb);
+        if (--left == 0) break;
     }
 }
 
 /* Persistent grid: workgroup b walks the table slice wgstart[b] .. wgstart[b+1], each entry
- * (product, row group).  Two loop shapes cover every product: five loads per lane and row, and
- * up to four (a product with fewer leaves slots idle: clamped loads that hit the cache, the
- * all-zero chunk).  Four waves per SIMD, no scratch memory: a version that spilled lost a third
- * of the stream rate. */
+ * (product, row group).  One part length per table: the host takes the one that leaves the fewest
+ * load slots idle (a row whose loads do not divide by it re-reads its last chunk, a cache hit).
+ * Four waves per SIMD, no scratch memory: a version that spilled lost a third of the stream rate. */
+template <int FORM, int LP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void bl_stream_m1(const bl_stream_item* __restrict__ items, const int2* __restrict__ wgstart, const int q_ints) {
-    extern __shared__ int lds[];                         /* q_ints ints of image + 16 */
-    int* Qs = lds;
+    extern __shared__ __attribute__((aligned(16))) int lds[];   /* q_ints ints of image + 16 */
+    uint8_t* Qs = (uint8_t*)lds;
     int* misc = lds + q_ints;
     const int2 s0 = wgstart[blockIdx.x], s1 = wgstart[blockIdx.x + 1];
     const int p_first = __builtin_amdgcn_readfirstlane(s0.x), u_first = __builtin_amdgcn_readfirstlane(s0.y);
@@ -605,30 +720,7 @@ void bl_stream_m1(const bl_stream_item* __restrict__ items, const int2* __restri
         const int ub = pi == p_first ? u_first : 0;
         const int ue = pi == p_last ? u_last : P.units;
         if (ub >= ue) continue;
-        if (P.lp == 5) bl_stream_slice<5, 1>(P, ub, ue, Qs, misc, staged);
-        else bl_stream_slice<4, 1>(P, ub, ue, Qs, misc, staged);
-        staged = true;
-    }
-}
-
-/* The same walk for a table in the five-per-byte form. */
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void bl_stream_m1_t5(const bl_stream_item* __restrict__ items, const int2* __restrict__ wgstart, const int q_ints) {
-    extern __shared__ int lds[];
-    int* Qs = lds;
-    int* misc = lds + q_ints;
-    const int2 s0 = wgstart[blockIdx.x], s1 = wgstart[blockIdx.x + 1];
-    const int p_first = __builtin_amdgcn_readfirstlane(s0.x), u_first = __builtin_amdgcn_readfirstlane(s0.y);
-    const int p_last = __builtin_amdgcn_readfirstlane(s1.x), u_last = __builtin_amdgcn_readfirstlane(s1.y);
-    bool staged = false;
-    for (int pi = p_first; pi <= p_last; ++pi) {
-        if (pi == p_last && u_last == 0) break;
-        const bl_stream_item P = items[pi];
-        const int ub = pi == p_first ? u_first : 0;
-        const int ue = pi == p_last ? u_last : P.units;
-        if (ub >= ue) continue;
-        if (P.lp == 5) bl_stream_slice_t5<5>(P, ub, ue, Qs, misc, staged);
-        else bl_stream_slice_t5<4>(P, ub, ue, Qs, misc, staged);
+        bl_stream_slice<FORM, LP>(P, ub, ue, Qs, misc, staged);
         staged = true;
     }
 }
@@ -820,7 +912,7 @@ __device__ __forceinline__ void bl_km_slice(const bl_stream_item& P, const int u
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void bl_stream_m1_km(const bl_stream_item* __restrict__ items, const int2* __restrict__ wgstart, const int q_ints,
                      const int red_ints) {
-    extern __shared__ int lds[];
+    extern __shared__ __attribute__((aligned(16))) int lds[];
     int* Qs = lds;
     int* red = lds + q_ints;
     int* misc = red + red_ints;
@@ -1133,11 +1225,12 @@ __global__ __launch_bounds__(256) void bl_mb_finish(const bl_mb_fin_item* __rest
 
 /* ---- host side ---------------------------------------------------------------------------- */
 
+#define BL_STREAM_LMIN 3
 #define BL_STREAM_LMAX 5
 #define BL_STREAM_MAX_BLOCKS 4096
 #define BL_STREAM_LDS_BYTES                                                                          \
     (layout == BL_LAYOUT_KMAJOR ? max_units * 64 + max_cols * 64 + 64                                \
-                                : (max_chunks + 1) * (layout == BL_LAYOUT_TRIT5 ? BL_T5_QSTRIDE : BL_QSTRIDE) * 4 + 64)
+                                : (max_slots + 1) * (layout == BL_LAYOUT_TRIT5 ? BL_T5_CHUNK : BL_B2_CHUNK) + 64)
 #define BL_KM_MAX_N 3072      /* k-major form: at most three dword columns of 64 lanes per weight row (48 sums per lane) */
 
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -1560,6 +1653,42 @@ extern "C" size_t bl_stack_table_bytes(const bl_decode_desc* descs, int count) {
     return stream_layout(count, q_bytes, acc_bytes).total;
 }
 
+/* 16-byte chunks of a packed weight row (not the k-major form). */
+static int64_t row_chunks(int64_t K, int layout) {
+    return layout == BL_LAYOUT_TRIT5 ? bl_kpad5(K) / 80 : bl_kpad(K) / 64;
+}
+/* Chunks that the loads of odd rows start early so that they cover whole 128-byte lines, and the wave-wide
+ * loads of a row group. */
+static int row_shift(int64_t chunks) { return chunks % 8 == 4 ? 4 : 0; }
+static int row_loads(int64_t chunks) { return (int)((chunks + row_shift(chunks) + 7) / 8); }
+/* Wave-wide loads of a part (3, 4 or 5) for a table of one-token products: the least cost over the table,
+ * in quarters of a load that is multiplied; an idle slot of a row's last part is loaded (a cache hit) but not
+ * multiplied, and a part costs about half a load besides. */
+static int part_loads(const bl_decode_desc* descs, int count, int layout) {
+    int best = BL_STREAM_LMAX;
+    int64_t least = INT64_MAX;
+    for (int lp = BL_STREAM_LMAX; lp >= BL_STREAM_LMIN; --lp) {
+        int64_t cost = 0;
+        for (int i = 0; i < count; ++i) {
+            const int64_t loads = row_loads(row_chunks(descs[i].K, layout)), parts = (loads + lp - 1) / lp;
+            cost += (descs[i].N + 7) / 8 * (3 * loads + parts * lp + 2 * parts);
+        }
+        if (cost < least) {
+            least = cost;
+            best = lp;
+        }
+    }
+    return best;
+}
+static const void* stream_kernel(int layout, int lp) {
+    if (layout == BL_LAYOUT_KMAJOR) return (const void*)bl_stream_m1_km;
+    if (layout == BL_LAYOUT_TRIT5)
+        return lp == 5 ? (const void*)bl_stream_m1<BL_FORM_TRIT5, 5>
+             : lp == 4 ? (const void*)bl_stream_m1<BL_FORM_TRIT5, 4> : (const void*)bl_stream_m1<BL_FORM_TRIT5, 3>;
+    return lp == 5 ? (const void*)bl_stream_m1<BL_FORM_BIT2, 5>
+         : lp == 4 ? (const void*)bl_stream_m1<BL_FORM_BIT2, 4> : (const void*)bl_stream_m1<BL_FORM_BIT2, 3>;
+}
+
 extern "C" bl_status bl_stack_build(const bl_decode_desc* descs, int count, int layout, int64_t M, void* table,
                                     bl_stack_plan* plan, bl_stream s) {
     if (!descs || !table || !plan) return BL_ERR_NULL;
@@ -1575,9 +1704,10 @@ extern "C" bl_status bl_stack_build(const bl_decode_desc* descs, int count, int 
     }
     const bl_stream_layout L = stream_layout(count, q_bytes, acc_bytes);
     uint8_t* const dev_base = (uint8_t*)table;
+    const int lp = layout == BL_LAYOUT_KMAJOR ? 0 : part_loads(descs, count, layout);
     std::vector<bl_stream_item> items((size_t)count);
     std::vector<bl_stream_prep_item> preps;
-    int inline_count = 0, max_chunks = 0, max_units = 0, max_cols = 0;
+    int inline_count = 0, max_slots = 0, max_units = 0, max_cols = 0;
     size_t acc_used = 0;
     std::vector<int64_t> unit_bytes((size_t)count);
     bool any_norm = false;
@@ -1596,19 +1726,17 @@ extern "C" bl_status bl_stack_build(const bl_decode_desc* descs, int count, int 
         it.y = d.y;
         it.N = (int)d.N;
         /* 16-byte loads per weight row: 64 weights each, or 80 in the five-per-byte form */
-        const int64_t row_bytes = layout == BL_LAYOUT_TRIT5    ? bl_kpad5(d.K) / 5
-                                  : layout == BL_LAYOUT_KMAJOR ? (d.N + 63) / 64 * 16
-                                                               : Kp / 4;
+        const int64_t row_bytes = (layout == BL_LAYOUT_KMAJOR ? (d.N + 63) / 64 : row_chunks(d.K, layout)) * 16;
         it.nchunks = (int)(row_bytes / 16);
         it.qgroups = (int)(Kp / 16);
-        if (it.nchunks > max_chunks) max_chunks = it.nchunks;
         it.layout = layout;
-        int lgG = 3;
-        while (((it.nchunks + (1 << lgG) - 1) >> lgG) > BL_STREAM_LMAX) ++lgG;   /* K bound checked: lgG <= 6 */
-        int R = 64 >> lgG;
-        it.lgG = lgG;
-        it.lp = (it.nchunks + (1 << lgG) - 1) >> lgG;
-        it.units = (it.N + R - 1) / R;
+        int R = 8;                                           /* weight rows of a unit */
+        if (layout != BL_LAYOUT_KMAJOR) {
+            it.shift = row_shift(it.nchunks);
+            it.parts = (row_loads(it.nchunks) + lp - 1) / lp;
+            it.units = (it.N + R - 1) / R;
+            if (it.parts * lp * 8 + it.shift > max_slots) max_slots = it.parts * lp * 8 + it.shift;
+        }
         if (layout == BL_LAYOUT_KMAJOR) {
             /* one row per k: dword columns of 16 output features; a unit is 64 consecutive k */
             const int ncols = (int)((d.N + 63) / 64 * 4);
@@ -1677,29 +1805,25 @@ extern "C" bl_status bl_stack_build(const bl_decode_desc* descs, int count, int 
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per_cu,
-            layout == BL_LAYOUT_TRIT5    ? (const void*)bl_stream_m1_t5
-            : layout == BL_LAYOUT_KMAJOR ? (const void*)bl_stream_m1_km
-                                         : (const void*)bl_stream_m1,
-            256,
-            (size_t)BL_STREAM_LDS_BYTES) != hipSuccess ||
+            &per_cu, stream_kernel(layout, lp), 256, (size_t)BL_STREAM_LDS_BYTES) != hipSuccess ||
         cus < 1 || per_cu < 1)
         return BL_ERR_HIP;
+    /* (four workgroups per compute unit also where a fifth would fit: 72 products of 13824 x 2048 84 us against 88) */
+    if (layout != BL_LAYOUT_KMAJOR && per_cu > 4) per_cu = 4;
     int64_t blocks64 = (int64_t)cus * per_cu;
     if (blocks64 > (total_units + 3) / 4) blocks64 = (total_units + 3) / 4;
     if (blocks64 > BL_STREAM_MAX_BLOCKS) blocks64 = BL_STREAM_MAX_BLOCKS;
     if (blocks64 < 1) blocks64 = 1;
     const int blocks = (int)blocks64;
 
-    /* Slice boundaries: a workgroup's time is its bytes, weighted by the measured rate of the
-     * product's register shape, plus a fixed cost each time it enters a product (activation
-     * row, pipeline refill; larger when it quantises the row itself), expressed in bytes at a
-     * workgroup's share of the stream rate. */
+    /* Slice boundaries: a workgroup's time is its bytes, plus a fixed cost each time it enters a
+     * product (activation row, pipeline refill; larger when it quantises the row itself), expressed
+     * in bytes at a workgroup's share of the stream rate. */
     std::vector<int> units_v((size_t)count);
     std::vector<int64_t> ucost_v((size_t)count), ecost_v((size_t)count);
     for (int i = 0; i < count; ++i) {
         units_v[(size_t)i] = items[(size_t)i].units;
-        ucost_v[(size_t)i] = items[(size_t)i].lp == 5 ? unit_bytes[(size_t)i] : unit_bytes[(size_t)i] * 26 / 25;
+        ucost_v[(size_t)i] = unit_bytes[(size_t)i];
         ecost_v[(size_t)i] = items[(size_t)i].xbf16 ? (int64_t)36 << 10 : (int64_t)12 << 10;
     }
     const std::vector<int2> wg = cut_slices(units_v, ucost_v, ecost_v, blocks);
@@ -1722,7 +1846,7 @@ extern "C" bl_status bl_stack_build(const bl_decode_desc* descs, int count, int 
     plan->norm = any_norm ? 1 : 0;
     plan->lds_bytes = BL_STREAM_LDS_BYTES;
     plan->layout = layout;
-    plan->red_ints = layout == BL_LAYOUT_KMAJOR ? max_cols * 16 : 0;
+    plan->red_ints = layout == BL_LAYOUT_KMAJOR ? max_cols * 16 : lp;
     plan->wg_offset = (int64_t)L.wg_off;
     plan->prep_offset = (int64_t)L.prep_off;
     plan->packed_bytes = packed_bytes;
@@ -1777,9 +1901,10 @@ extern "C" bl_status bl_stack_run(void* table, const bl_stack_plan* plan, bl_str
     if (plan->count < 1 || plan->count > BL_STACK_MAX_COUNT || plan->blocks < 1 ||
         plan->blocks > BL_STREAM_MAX_BLOCKS || plan->prep_count < 0 || plan->inline_count < 0 ||
         plan->prep_count + plan->inline_count > plan->count || plan->lds_bytes < 64 ||
-        plan->lds_bytes > 48 * 1024 || plan->lds_bytes % 16 ||
+        plan->lds_bytes > 64 * 1024 || plan->lds_bytes % 16 ||
         plan->layout < 0 || plan->layout > BL_LAYOUT_KMAJOR || plan->red_ints < 0 || plan->red_ints > BL_KM_MAX_N ||
-        (plan->layout == BL_LAYOUT_KMAJOR && (plan->red_ints < 64 || plan->lds_bytes < 64 + 64 + plan->red_ints * 4)))
+        (plan->layout == BL_LAYOUT_KMAJOR ? plan->red_ints < 64 || plan->lds_bytes < 64 + 64 + plan->red_ints * 4
+                                          : plan->red_ints < BL_STREAM_LMIN || plan->red_ints > BL_STREAM_LMAX))
         return BL_ERR_VALUE;
     const bl_stream_layout L = stream_layout(plan->count, 0);
     if (plan->wg_offset != (int64_t)L.wg_off || plan->prep_offset != (int64_t)L.prep_off) return BL_ERR_VALUE;
@@ -1799,11 +1924,14 @@ extern "C" bl_status bl_stack_run(void* table, const bl_stack_plan* plan, bl_str
         if (hipGetLastError() != hipSuccess) return BL_ERR_HIP;
         bl_km_finish<<<dim3((unsigned)((plan->red_ints + 255) / 256), (unsigned)plan->count), 256, 0, st>>>(
             (const bl_stream_item*)base);
-    } else if (plan->layout == BL_LAYOUT_TRIT5)
-        bl_stream_m1_t5<<<plan->blocks, 256, (size_t)plan->lds_bytes, st>>>(
-            (const bl_stream_item*)base, (const int2*)(base + L.wg_off), (plan->lds_bytes - 64) / 4);
-    else
-        bl_stream_m1<<<plan->blocks, 256, (size_t)plan->lds_bytes, st>>>(
-            (const bl_stream_item*)base, (const int2*)(base + L.wg_off), (plan->lds_bytes - 64) / 4);
+    } else {
+        const bl_stream_item* items = (const bl_stream_item*)base;
+        const int2* wg = (const int2*)(base + L.wg_off);
+        int q_ints = (plan->lds_bytes - 64) / 4;
+        void* args[] = {&items, &wg, &q_ints};
+        if (hipLaunchKernel(stream_kernel(plan->layout, plan->red_ints), dim3((unsigned)plan->blocks), dim3(256), args,
+                            (size_t)plan->lds_bytes, st) != hipSuccess)
+            return BL_ERR_HIP;
+    }
     return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
 }
