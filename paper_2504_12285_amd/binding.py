@@ -1,4 +1,5 @@
-"""ctypes binding of the BitLinear C-ABI (include/bitlinear.h).
+"""ctypes binding of the BitLinear C-ABI (include/bitlinear.h); the small calls of a decode loop go through
+the native form of the same marshalling (csrc/bl_torch.cpp) first.
 
 Argument marshalling only: every step of the path runs in the HIP kernels of
 libbitlinear_hip.so.  PyTorch supplies device memory and the current stream.
@@ -157,6 +158,32 @@ def _first_stream():
 _stream = _first_stream
 
 
+_native = None
+
+
+def _first_native():
+    """The small calls in native code (csrc/bl_torch.cpp), bound to the loaded library.  Like the library, it has
+    to be built; a call that it hands back (NotImplemented) is done in Python below."""
+    global _native
+    lib = load()
+    _get_torch()
+    try:
+        from . import _bl_torch
+    except ImportError as e:
+        raise RuntimeError("_bl_torch.so is not built for this interpreter and torch "
+                           "(run __graft_entry__.build()): %s" % e) from e
+    _bl_torch.bind(*(ctypes.cast(fn, _vp).value for fn in (lib.bl_quant_act_int8, lib.bl_gemv_w158a8,
+                                                            lib.bl_gemm_w158a8, lib.bl_bitlinear_decode, lib.bl_stack_run)))
+    _native = _bl_torch
+    return _native
+
+
+def _result(out, where):
+    if type(out) is int:
+        raise BitLinearError(out, where)
+    return out
+
+
 def bl_version():
     return load().bl_version()
 
@@ -217,6 +244,9 @@ def bl_unpack_ternary(packed, N, K, layout=BL_LAYOUT_K16):
 def bl_quant_act_int8(X, want_rowsum=True):
     """X: cuda bfloat16 [M][K].  Returns (q int8 [M][Kp] with Kp = bl_padded_k(K) and zeros in the padding,
     scale fp32 [M], rowsum int32 [M] or None)."""
+    out = (_native or _first_native()).quant(X, want_rowsum)
+    if out is not NotImplemented:
+        return _result(out, "bl_quant_act_int8")
     torch = _get_torch()
     assert X.is_cuda and X.is_contiguous() and X.dtype == torch.bfloat16
     M, K = X.shape
@@ -229,6 +259,10 @@ def bl_quant_act_int8(X, want_rowsum=True):
 
 
 def _matmul(fn_name, op, packed, beta, layout, q, scale, rowsum, N, want_acc, want_y, acc, y, workspace, K=None):
+    out = (_native or _first_native()).product(0 if op == BL_OP_GEMV else 1, packed, beta, layout, q, scale, rowsum, N,
+                                               want_acc, want_y, acc, y, workspace, K)
+    if out is not NotImplemented:
+        return _result(out, fn_name)
     torch = _get_torch()
     M = q.shape[0]
     K = q.shape[1] if K is None else K          # q is [M][Kp]: pass the true K of a ragged matrix explicitly
@@ -262,6 +296,9 @@ def bl_gemm_w158a8(packed, beta, layout, q, scale, rowsum, N, want_acc=True, wan
 
 def bl_bitlinear_decode(packed, beta, layout, X, N, want_acc=False, want_y=True, want_q=False, acc=None, y=None):
     """Fused decode BitLinear, M <= 4: bf16 X [M][K] -> (acc, y, q, scale)."""
+    out = (_native or _first_native()).decode(packed, beta, layout, X, N, want_acc, want_y, want_q, acc, y)
+    if out is not NotImplemented:
+        return _result(out, "bl_bitlinear_decode")
     torch = _get_torch()
     assert X.is_cuda and X.is_contiguous() and X.dtype == torch.bfloat16
     M, K = X.shape
@@ -355,6 +392,9 @@ class Stack:
                                      _stream()), "bl_stack_build")
 
     def run(self):
+        out = (_native or _first_native()).run(self.table, ctypes.addressof(self.plan))
+        if out is not NotImplemented:
+            return _result(out, "bl_stack_run")
         _check(load().bl_stack_run(_ptr(self.table), ctypes.byref(self.plan), _stream()), "bl_stack_run")
 
 
