@@ -92,7 +92,10 @@ __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : 
     int* const rs_base = (int*)(smem + STAGES * G3_STAGE_BYTES);
     int* rs_s = rs_base;
     float* cf_s = (float*)(rs_base + G3_BM);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    /* (one product in 64 x 128 tiles: the wave's number as a scalar, so that where the direct loads write is scalar
+     * arithmetic, 1 - 2 %; the table of products loses 2 % by it, the 128 x 128 kernels nothing to 2 %) */
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = BM < 128 && !TABLE ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
     const int l32 = lane & 31, h = lane >> 5;
     const int wm0 = (wave / WN) * (MI * 32), wn0 = (wave % WN) * (NI * 32);
     /* fixed for the launch, or (TABLE) those of the product whose tile is set up next */
@@ -1075,6 +1078,11 @@ __global__ __launch_bounds__(256) void bl_rowsum_kernel(const int8_t* __restrict
  * problem has at most ~1.5 tiles of 128x128 per CU, 64x128 tiles balance better: +17..21 % on the
  * N = 2560 shapes at M = 2048, +22..27 % on every small shape at M = 1024, equal at 480 tiles and slower
  * on the wide shape.
+ * At most 256 tiles of 64x128 (one workgroup to a compute unit) and long rows: four LDS stages, three k steps of loads in
+ * flight.  A lone workgroup's k step waits for its loads (0.47 us, with four stages 0.32; the matrix cores work 0.12 of it):
+ * 512 x 2560 -> 3840 15.9 / 13.5 us, 1024 x 4096 -> 2048 21.0 / 17.4, 1000 x 6912 -> 2000 30.2 / 24.3, 512 x 2304 -> 3840
+ * 14.3 / 12.9, 256 x 2304 -> 8000 13.5 / 12.8, but 256 x 2176 -> 8000 12.4 / 12.5, 256 x 2048 -> 8000 11.6 / 12.1 and 400 x 1000 ->
+ * 4000 9.3 / 9.6.  From two workgroups per unit on they cover each other: 777 x 2999 -> 5003 24.8 / 26.9.
  * fp32 output alone: the stores of a tile travel during the workgroup's next tile (measured at M = 2048 /
  * 8192: the 13824-wide shape 77 - 80 us against 86 - 90, 297 - 308 against 317 - 327; the 64 x 128 kernel
  * with deferred stores loses: it has under one tile per workgroup on the shapes it serves).
@@ -1096,6 +1104,8 @@ static bl_status launch_plain(const uint8_t* packed, const float* beta, const in
     }
     if ((int64_t)((m + 63) / 64) * ((n + 127) / 128) <= KS_MAX_TILES)
         return launch_ksplit<LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
+    if (k >= 2304 && (int64_t)((m + 63) / 64) * ((n + 127) / 128) <= 256)
+        return launch_tile256_t<64, 128, 4, 1, 4, 0, false, HALF, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
     if ((int64_t)((m + 127) / 128) * ((n + 127) / 128) <= 400)
         return launch_tile256_t<64, 128, 2, 1, 4, 0, false, HALF, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
     const int64_t tiles = (int64_t)((m + 127) / 128) * ((n + 127) / 128);
