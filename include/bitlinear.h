@@ -123,7 +123,9 @@ size_t bl_workspace_bytes(int op, int64_t M, int64_t N, int64_t K);
  *   beta     device, 1 float.
  *   workspace device, bl_workspace_bytes(BL_OP_PACK, 0, N, K) bytes.
  * Enqueues two kernels (partial |W| sums in fp64; their fixed-order sum inside
- * ternarize+pack).  The fp64 sum order is fixed, so beta is reproducible. */
+ * ternarize+pack), or three where W is large (an estimate of beta from a sample; the sums and
+ * every code that does not depend on the rest; the other codes).  The fp64 sum order is fixed for
+ * a shape and layout, so beta is reproducible. */
 bl_status bl_pack_ternary(const void* W, int in_kind, int64_t N, int64_t K, int layout,
                           uint8_t* packed, float* beta, void* workspace, bl_stream s);
 

@@ -50,11 +50,18 @@ struct bl_pack_scale {
  * 0.5 + 2^-25, the midpoint between 0.5 and its successor, i.e. where |W| > d * (0.5 + 2^-25); that
  * product is exact in fp64, and T is the largest fp32 not above it.  A quotient that is NaN clamps to -1,
  * code 0: every weight where beta is NaN, the infinite ones where it is infinite (`above` is then 0).  Every
- * thread of the workgroup calls this; red: PACK_THREADS doubles of LDS. */
+ * thread of the workgroup calls bl_pack_threshold; red: PACK_THREADS doubles of LDS. */
 struct bl_ternary {
     float T;
     uint32_t above;           /* code of w > T */
 };
+__device__ __forceinline__ bl_ternary bl_ternary_of(float beta) {
+    const double td = (double)(beta + 1e-5f) * (0.5 + 0x1p-25);
+    float T = (float)td;
+    if ((double)T > td) T = __uint_as_float(__float_as_uint(T) - 1);
+    const bool inf = T == __builtin_inff();
+    return {inf ? 0x1.fffffep127f : T, inf ? 0u : 2u};
+}
 __device__ __forceinline__ bl_ternary bl_pack_threshold(const bl_pack_scale& sc, double* red) {
     double s = 0.0;
     for (int i = threadIdx.x; i < sc.np; i += PACK_THREADS) s += sc.partial[i];
@@ -66,11 +73,7 @@ __device__ __forceinline__ bl_ternary bl_pack_threshold(const bl_pack_scale& sc,
     }
     const float beta = (float)(red[0] / sc.count);
     if (blockIdx.x == 0 && threadIdx.x == 0) *sc.beta = beta;
-    const double td = (double)(beta + 1e-5f) * (0.5 + 0x1p-25);
-    float T = (float)td;
-    if ((double)T > td) T = __uint_as_float(__float_as_uint(T) - 1);
-    const bool inf = T == __builtin_inff();
-    return {inf ? 0x1.fffffep127f : T, inf ? 0u : 2u};
+    return bl_ternary_of(beta);
 }
 __device__ __forceinline__ uint32_t bl_code(float w, bl_ternary t) {
     const uint32_t c = w > t.T ? t.above : 1u;
@@ -134,14 +137,22 @@ __device__ __forceinline__ uint32_t bl_quad_words(const uint32_t c[4]) {
     return j == 0 ? w[0] : j == 1 ? w[1] : j == 2 ? w[2] : w[3];
 }
 
+/* The codes of four chunks of W that a wave has read, packed. */
+template <int LAYOUT>
+__device__ __forceinline__ uint32_t bl_pack_group(const bl_v4f f[4], bl_ternary T) {
+    uint32_t c[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        c[j] = bl_code(f[j][0], T) | bl_code(f[j][1], T) << 8 | bl_code(f[j][2], T) << 16 | bl_code(f[j][3], T) << 24;
+    return bl_quad_words<LAYOUT>(c);
+}
+
 /* fp32 weights of a matrix without padding (N % 4 == 0 and K % 64 == 0): one run of chunks.  Bound by the
  * read of W: the first loads go out before the threshold is known, the next ones before a group is
  * packed.  One comparison per sign where a division and a rint stood; 35 M weights: 24.0 us, and the 4.6 us
  * launch that added up the partial sums is gone (before: 21.9 - 23.3 us). */
-template <int LAYOUT>
-__global__ __launch_bounds__(PACK_THREADS) void bl_pack_flat(const bl_v4f* __restrict__ W, const bl_pack_scale sc, int64_t chunks,
-                                                              uint32_t* __restrict__ packed) {
-    __shared__ double red[PACK_THREADS];
+template <int LAYOUT, class SCALE>
+__device__ __forceinline__ void bl_pack_run(const bl_v4f* __restrict__ W, int64_t chunks, uint32_t* __restrict__ packed, const SCALE& scale) {
     const int lane = threadIdx.x & 63;
     const int64_t step = (int64_t)gridDim.x * PACK_THREADS / 16;         /* chunks of all waves together */
     int64_t c0 = ((int64_t)blockIdx.x * (PACK_THREADS / 64) + (threadIdx.x >> 6)) * 4;
@@ -151,17 +162,210 @@ __global__ __launch_bounds__(PACK_THREADS) void bl_pack_flat(const bl_v4f* __res
         for (int j = 0; j < 4; ++j) f[j] = W[(c + j < chunks ? c + j : chunks - 1) * 64 + lane];
     };
     load(c0);
-    const bl_ternary T = bl_pack_threshold(sc, red);
+    const bl_ternary T = scale();
+    while (c0 < chunks) {
+        bl_v4f g[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) g[j] = f[j];
+        const int64_t at = c0;
+        c0 += step;
+        load(c0);
+        const uint32_t mine = bl_pack_group<LAYOUT>(g, T);
+        if (at + (lane & 3) < chunks) packed[(at + (lane & 3)) * 16 + (lane >> 2)] = mine;
+    }
+}
+template <int LAYOUT>
+__global__ __launch_bounds__(PACK_THREADS) void bl_pack_flat(const bl_v4f* __restrict__ W, const bl_pack_scale sc, int64_t chunks,
+                                                              uint32_t* __restrict__ packed) {
+    __shared__ double red[PACK_THREADS];
+    bl_pack_run<LAYOUT>(W, chunks, packed, [&] { return bl_pack_threshold(sc, red); });
+}
+
+/* The same matrix, large: one read of W instead of two.  beta, which every code needs, is known only when all of W has been
+ * read; but a sample of W (2^20 weights in pieces of 16, spread evenly) puts it between two ends, and a weight whose code is
+ * the same at both ends is settled.  bl_pack_guess writes those codes, writes the unused code 3 for the others (0.2 % of
+ * normally distributed weights) and adds up |W| on its way; bl_pack_settle, with beta, takes up the words that hold a 3, from
+ * W.  Where beta is not between the ends (also NaN, infinite) it packs the whole matrix again.  Exact for every
+ * input: the sample decides the time alone.  Bound by the one read of W, beside the write of the codes: 13824 x 2560 53.9 ->
+ * 38.0 us (sample 3, guess 25, settle 7 with their launches), 28672 x 8192 352 -> 218; with |W| heavy-tailed (0.1 % of it
+ * fiftyfold) 54.0 -> 41.1, every weight undecided 53.7 -> 61, beta NaN 52.8 -> 59. */
+typedef uint32_t bl_v4w __attribute__((ext_vector_type(4)));
+#define PACK_SAMPLE_BLOCKS 256
+#define PACK_SAMPLE_PIECES 65536                /* of 16 weights: a lane of every quad reads four */
+#define PACK_GUESS_BLOCKS (BL_PACK_PARTIALS - PACK_SAMPLE_BLOCKS)
+struct bl_pack_sample {                         /* in the place of one partial sum */
+    float sum, squares;
+};
+__global__ __launch_bounds__(PACK_THREADS) void bl_abs_sum_sample(const bl_v4f* __restrict__ W, int64_t pieces, bl_pack_sample* __restrict__ out) {
+    __shared__ bl_pack_sample red[PACK_THREADS / 64];
+    bl_v4f f[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        f[j] = W[((int64_t)(j * 64 * PACK_SAMPLE_BLOCKS + blockIdx.x * 64 + (threadIdx.x >> 2)) * pieces / PACK_SAMPLE_PIECES) * 4 + (threadIdx.x & 3)];
+    bl_pack_sample s = {0, 0};
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            s.sum += fabsf(f[j][i]);
+            s.squares += f[j][i] * f[j][i];
+        }
+    for (int o = 32; o > 0; o >>= 1) {
+        s.sum += __shfl_xor(s.sum, o);
+        s.squares += __shfl_xor(s.squares, o);
+    }
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        s.sum = (red[0].sum + red[1].sum) + (red[2].sum + red[3].sum);
+        s.squares = (red[0].squares + red[1].squares) + (red[2].squares + red[3].squares);
+        out[blockIdx.x] = s;
+    }
+}
+
+/* The ends: five standard deviations of the sample's mean to each side (normally distributed weights: 0.4 %), 2^-11 to 2^-5 of it. */
+struct bl_pack_ends {
+    float lo, hi;                               /* of beta */
+};
+__device__ __forceinline__ bl_pack_ends bl_guess_ends(const bl_pack_sample* __restrict__ sample, float* red) {
+    static_assert(PACK_SAMPLE_BLOCKS == PACK_THREADS && PACK_THREADS == 256, "four waves, one sum per lane");
+    bl_pack_sample s = sample[threadIdx.x];
+    for (int o = 32; o > 0; o >>= 1) {
+        s.sum += __shfl_xor(s.sum, o);
+        s.squares += __shfl_xor(s.squares, o);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        red[threadIdx.x >> 6] = s.sum;
+        red[4 + (threadIdx.x >> 6)] = s.squares;
+    }
+    __syncthreads();
+    const float n = 16.0f * PACK_SAMPLE_PIECES;
+    const float mean = ((red[0] + red[1]) + (red[2] + red[3])) / n, square = ((red[4] + red[5]) + (red[6] + red[7])) / n;
+    const float far = 5.0f * __builtin_sqrtf(square / (mean * mean) / n);
+    const float d = far > 0x1p-5f ? 0x1p-5f : far > 0x1p-11f ? far : 0x1p-11f;
+    return {mean * (1.0f - d), mean * (1.0f + d)};
+}
+
+/* The sum over a workgroup, by lanes, then by waves. */
+__device__ __forceinline__ double bl_sum_waves(double s, double* red) {
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    return (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+template <int LAYOUT, bool NT>
+__global__ __launch_bounds__(PACK_THREADS) void bl_pack_guess(const bl_v4f* __restrict__ W, const bl_pack_sample* __restrict__ sample, int64_t chunks,
+                                                               uint32_t* __restrict__ packed, double* __restrict__ partial) {
+    __shared__ double red[PACK_THREADS / 64];
+    __shared__ float ends[8];
+    const int lane = threadIdx.x & 63;
+    const int64_t step = (int64_t)gridDim.x * PACK_THREADS / 16;         /* chunks of all waves together */
+    int64_t c0 = ((int64_t)blockIdx.x * (PACK_THREADS / 64) + (threadIdx.x >> 6)) * 4;
+    bl_v4f f[4];
+    auto load = [&](int64_t c) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const bl_v4f* p = W + (c + j < chunks ? c + j : chunks - 1) * 64 + lane;
+            f[j] = NT ? __builtin_nontemporal_load(p) : *p;
+        }
+    };
+    load(c0);
+    const bl_pack_ends e = bl_guess_ends(sample, ends);
+    const float T0 = bl_ternary_of(e.lo).T, T1 = bl_ternary_of(e.hi).T;
+    double s = 0.0;
     while (c0 < chunks) {
         uint32_t c[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            c[j] = bl_code(f[j][0], T) | bl_code(f[j][1], T) << 8 | bl_code(f[j][2], T) << 16 | bl_code(f[j][3], T) << 24;
+        for (int j = 0; j < 4; ++j) {
+            c[j] = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float w = f[j][i];
+                const uint32_t sure = w > T1 ? 2u : w >= -T1 ? 3u : 0u;
+                c[j] |= (fabsf(w) <= T0 ? 1u : sure) << (8 * i);
+            }
+            if (c0 + j < chunks)
+                s += ((double)fabsf(f[j][0]) + (double)fabsf(f[j][1])) + ((double)fabsf(f[j][2]) + (double)fabsf(f[j][3]));
+        }
         const int64_t at = c0;
         c0 += step;
         load(c0);
         const uint32_t mine = bl_quad_words<LAYOUT>(c);
         if (at + (lane & 3) < chunks) packed[(at + (lane & 3)) * 16 + (lane >> 2)] = mine;
+    }
+    s = bl_sum_waves(s, red);
+    if (threadIdx.x == 0) partial[blockIdx.x] = s;
+}
+
+/* The words that hold a 3 are gathered by the wave, a quad of lanes takes one each. */
+template <int LAYOUT>
+__global__ __launch_bounds__(PACK_THREADS) void bl_pack_settle(const bl_v4f* __restrict__ W, const bl_pack_sample* __restrict__ sample,
+                                                                const bl_pack_scale sc, int64_t quads, uint32_t* __restrict__ packed) {
+    __shared__ double red[PACK_THREADS / 64];
+    __shared__ float ends[8];
+    __shared__ uint8_t list[PACK_THREADS / 64][256];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t step = (int64_t)gridDim.x * PACK_THREADS;
+    int64_t g0 = (int64_t)blockIdx.x * PACK_THREADS + wave * 64;
+    const bl_v4w* p4 = (const bl_v4w*)packed;
+    bl_v4w next = p4[g0 + lane < quads ? g0 + lane : quads - 1];
+    double sum = 0.0;
+    for (int i = threadIdx.x; i < sc.np; i += PACK_THREADS) sum += sc.partial[i];
+    const bl_pack_ends e = bl_guess_ends(sample, ends);
+    const float beta = (float)(bl_sum_waves(sum, red) / sc.count);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *sc.beta = beta;
+    const bl_ternary T = bl_ternary_of(beta);
+    if (!(beta >= e.lo && beta <= e.hi && e.hi < __builtin_inff())) {
+        bl_pack_run<LAYOUT>(W, quads / 4, packed, [&] { return T; });
+        return;
+    }
+    for (; g0 < quads; g0 += step) {
+        const bl_v4w w = next;
+        const int64_t gn = g0 + step + lane;
+        next = p4[gn < quads ? gn : quads - 1];
+        int n = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const bool redo = g0 + lane < quads && (w[j] & (w[j] >> 1) & 0x55555555u) != 0;
+            const uint64_t m = __ballot(redo);
+            if (redo) list[wave][n + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0))] = (uint8_t)(lane * 4 + j);
+            n += __builtin_popcountll(m);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (n > 128) {                          /* most of them: whole chunks, read without gaps */
+            for (int i = 0; i < 16; i += 4) {
+                const int64_t c0 = g0 / 4 + i, chunks = quads / 4;
+                bl_v4f f[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) f[j] = W[(c0 + j < chunks ? c0 + j : chunks - 1) * 64 + lane];
+                const uint32_t v = bl_pack_group<LAYOUT>(f, T);
+                if (c0 + (lane & 3) < chunks) packed[(c0 + (lane & 3)) * 16 + (lane >> 2)] = v;
+            }
+            continue;
+        }
+        for (int i = 0; i < n; i += 32) {
+            bl_v4f f[2];
+            int64_t word[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int at = i + 16 * h + (lane >> 2);
+                word[h] = g0 * 4 + list[wave][at < n ? at : n - 1];
+                f[h] = W[word[h] * 4 + (lane & 3)];
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                uint32_t v = 0;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) v |= bl_code(f[h][t], T) << (LAYOUT == 1 ? 8 * t + 2 * (lane & 3) : 8 * (lane & 3) + 2 * t);
+                v |= (uint32_t)bl_dpp<BL_DPP_QUAD_XOR1>((int)v);
+                v |= (uint32_t)bl_dpp<BL_DPP_QUAD_XOR2>((int)v);
+                if (i + 16 * h + (lane >> 2) < n && (lane & 3) == 0) packed[word[h]] = v;
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -367,6 +571,23 @@ __global__ void bl_zero_i32(int32_t* p, int n) {
     if (i < n) p[i] = 0;
 }
 
+/* From 12 Mi weights: the third launch costs what the shorter read saves at about 10 (1920 x 5120 17.3 us in two reads, 17.1
+ * with a guess; 2560 x 2560 14.1 and 14.6; 2560 x 6912 24.7 and 22.8).  Non-temporal loads from 128 MiB of W (4096 x 11008 50.1
+ * us without, 46.3 with them; 13824 x 2560 39.6, 37.9; 2560 x 6912 22.8, 23.3: the settling finds less of W in the caches). */
+#define PACK_GUESS_COUNT (12 << 20)
+#define PACK_NT_COUNT (32 << 20)
+template <int LAYOUT>
+static bl_status launch_pack_guess(const bl_v4f* W, int64_t count, uint8_t* packed, float* beta, double* partial, hipStream_t st) {
+    const int64_t chunks = count / 256, quads = count / 64, blocks = (quads + PACK_THREADS - 1) / PACK_THREADS;
+    bl_pack_sample* sample = (bl_pack_sample*)(partial + PACK_GUESS_BLOCKS);
+    const bl_pack_scale sc = {partial, PACK_GUESS_BLOCKS, (double)count, beta};
+    bl_abs_sum_sample<<<PACK_SAMPLE_BLOCKS, PACK_THREADS, 0, st>>>(W, count / 16, sample);
+    if (count < PACK_NT_COUNT) bl_pack_guess<LAYOUT, false><<<PACK_GUESS_BLOCKS, PACK_THREADS, 0, st>>>(W, sample, chunks, (uint32_t*)packed, partial);
+    else bl_pack_guess<LAYOUT, true><<<PACK_GUESS_BLOCKS, PACK_THREADS, 0, st>>>(W, sample, chunks, (uint32_t*)packed, partial);
+    bl_pack_settle<LAYOUT><<<(unsigned)(blocks < 1024 ? blocks : 1024), PACK_THREADS, 0, st>>>(W, sample, sc, quads, (uint32_t*)packed);
+    return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
+}
+
 extern "C" bl_status bl_pack_ternary(const void* W, int in_kind, int64_t N, int64_t K, int layout,
                                      uint8_t* packed, float* beta, void* workspace, bl_stream s) {
     if (!W || !packed || !beta) return BL_ERR_NULL;
@@ -381,6 +602,10 @@ extern "C" bl_status bl_pack_ternary(const void* W, int in_kind, int64_t N, int6
         if (!workspace) return BL_ERR_WORKSPACE;
         if (!bl_aligned(workspace, 8)) return BL_ERR_ALIGN;
         const int64_t count = N * K, n4 = count / 4;
+        if (bl_shape_unpadded(N, K) && count >= PACK_GUESS_COUNT && (layout == BL_LAYOUT_ROWMAJOR || layout == BL_LAYOUT_K16)) {
+            if (layout == BL_LAYOUT_ROWMAJOR) return launch_pack_guess<0>((const bl_v4f*)W, count, packed, beta, (double*)workspace, st);
+            return launch_pack_guess<1>((const bl_v4f*)W, count, packed, beta, (double*)workspace, st);
+        }
         sc.partial = (double*)workspace;
         sc.np = (int)(n4 < 1 ? 1 : n4 < BL_PACK_PARTIALS ? n4 : BL_PACK_PARTIALS);
         sc.count = (double)count;
