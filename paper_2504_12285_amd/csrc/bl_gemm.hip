@@ -10,6 +10,7 @@
 #include "bl_host.h"
 
 #include <atomic>
+#include <type_traits>
 
 /* ---- tile kernel ------------------------------------------------------------
  * BM x BN output tile per workgroup, k step 128, STAGES LDS stages filled by direct
@@ -383,7 +384,7 @@ __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : 
             }
         }
         /* EPI 1: the residual values of four row groups (32 rows) are requested ahead, a group's successor
-         * when it has been stored; clamped and unconditional.  The first ones travel while the row terms are
+         * when it has been stored (if there is one); clamped and unconditional.  The first ones travel while the row terms are
          * handed over.  (Fetched in front of their own stores they cost eight round trips to memory per
          * tile; all at once they spill 63 registers, this form three.  With the row maxima by DPP instead of shuffles, at M = 4096: residual
          * epilogue 82 -> 75.5 us, gate epilogue 180 -> 168 us, means of two layers.) */
@@ -490,71 +491,76 @@ __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : 
              * before quantisation) and the row maximum of |bf16(t)|: over the lane's columns, then over
              * the 32 lanes of a half wave (DPP), then one atomic max per row on the float bits
              * (non-negative floats order like integers, so the result does not depend on the order) */
-            const int NOUT = EPI == 2 ? N / 2 : N;
             constexpr int MAG0 = 0x007F0000;          /* added to a magnitude's bits: infinity is the largest int, a NaN negative */
+            /* A tile inside the matrix without an int32 output stores unconditionally, so that neither a branch nor a
+             * wait for memory stands between its stores; `cut`: every other one (and the residual in 128-row tiles, where both
+             * forms together spill 55 registers: 4096 x 2560 -> 2560 48.9 us, 40.5 with `cut` alone).  With the
+             * atomics of eight rows in one instruction (before: two rows; the epilogue waited for each), at 2560 -> 13824 with the
+             * gate: 128 tokens 61 -> 23 us, 512 54 -> 25, 2048 78 -> 69, 4096 146 -> 135. */
+            const int NOUT = EPI == 2 ? N / 2 : N, col0 = EPI == 2 ? tn * (BN / 2) + wn0 / 2 + l32 : n0 + wn0 + l32;
+            const int mlast = M - 1 - m0;
+            auto finish = [&](auto cut_t) __attribute__((always_inline)) {
+                constexpr bool cut = decltype(cut_t)::value;
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi)
+                for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-                for (int vq = 0; vq < 4; ++vq) {
-                    float rowmax[4];
+                    for (int vq = 0; vq < 4; ++vq) {
+                        const int ml = wm0 + mi * 32 + vq * 8 + h * 4;
+                        float rowmax[4];
 #pragma unroll
-                    for (int v4 = 0; v4 < 4; ++v4) {
-                        const int v = vq * 4 + v4;
-                        const int ml = wm0 + mi * 32 + vq * 8 + h * 4 + v4;
-                        const int m = m0 + ml;
-                        int mx = MAG0;
-                        if (m < M) {
-                            const int rs = rs_s[ml];
-                            const float c = cf_s[ml];
-                            if (EPI == 1) {
+                        for (int v4 = 0; v4 < 4; ++v4) {
+                            const int v = vq * 4 + v4;
+                            int mx = MAG0;
+                            if (!cut || ml + v4 <= mlast) {
+                                const int rs = rs_s[ml + v4];
+                                const float c = cf_s[ml + v4];
+                                const int64_t m = m0 + ml + v4;
 #pragma unroll
-                                for (int ni = 0; ni < NI; ++ni) {
-                                    const int n = n0 + wn0 + ni * 32 + l32;
-                                    if (n < N) {
+                                for (int ni = 0; ni < (EPI == 2 ? 1 : NI); ++ni) {
+                                    const int n = col0 + ni * 32;
+                                    if (!cut || n < NOUT) {
                                         const int val = C[mi][ni][v] - rs;
-                                        if (acc) acc[(int64_t)m * N + n] = val;
+                                        if (cut && acc) {
+                                            acc[m * N + n] = val;
+                                            if (EPI == 2) acc[m * N + NOUT + n] = C[mi][NI - 1][v] - rs;
+                                        }
                                         const float t = (float)val * c;
-                                        const float o = rres[vq][v4][ni] + t;
-                                        if (y) __builtin_nontemporal_store(o, y + (int64_t)m * N + n);
+                                        float o;
+                                        if (EPI == 1) {
+                                            o = rres[vq][v4][ni] + t;
+                                        } else {
+                                            const float u = (float)(C[mi][NI - 1][v] - rs) * c;
+                                            const float r = fmaxf(t, 0.0f);
+                                            const float r2 = r * r;
+                                            o = r2 * u;
+                                        }
+                                        if (cut ? y != nullptr : EPI == 1) __builtin_nontemporal_store(o, y + m * NOUT + n);
                                         const uint32_t bits = bl_pack2_bf16(o, o);
-                                        xb[(int64_t)m * NOUT + n] = (uint16_t)bits;
+                                        xb[m * NOUT + n] = (uint16_t)bits;
                                         mx = max(mx, (int)(((bits << 16) & 0x7FFF0000u) + (uint32_t)MAG0));
                                     }
                                 }
-                            } else {
-                                const int j = tn * (BN / 2) + wn0 / 2 + l32;     /* column of the gated output */
-                                if (j < NOUT) {
-                                    const int vg = C[mi][0][v] - rs, vu = C[mi][NI - 1][v] - rs;
-                                    if (acc) {
-                                        acc[(int64_t)m * N + j] = vg;
-                                        acc[(int64_t)m * N + NOUT + j] = vu;
-                                    }
-                                    const float g = (float)vg * c, u = (float)vu * c;
-                                    const float r = fmaxf(g, 0.0f);
-                                    const float r2 = r * r;
-                                    const float o = r2 * u;
-                                    if (y) __builtin_nontemporal_store(o, y + (int64_t)m * NOUT + j);
-                                    const uint32_t bits = bl_pack2_bf16(o, o);
-                                    xb[(int64_t)m * NOUT + j] = (uint16_t)bits;
-                                    mx = max(mx, (int)(((bits << 16) & 0x7FFF0000u) + (uint32_t)MAG0));
-                                }
                             }
+                            rowmax[v4] = __int_as_float(mx - MAG0);
                         }
-                        rowmax[v4] = __int_as_float(mx - MAG0);
-                    }
-                    if constexpr (EPI == 1) {
-                        if (mi + 1 < MI) fetch_res(mi + 1, vq);
-                    }
-#pragma unroll
-                    for (int v4 = 0; v4 < 4; ++v4) rowmax[v4] = bl_half_max(rowmax[v4]);
-                    if (l32 == 0) {
-#pragma unroll
-                        for (int v4 = 0; v4 < 4; ++v4) {
-                            const int m = m0 + wm0 + mi * 32 + vq * 8 + h * 4 + v4;
-                            if (m < M) atomicMax(absmax + m, __float_as_int(rowmax[v4]));
+                        if constexpr (EPI == 1) {
+                            if (mi + 1 < MI) fetch_res(mi + 1, vq);
                         }
+#pragma unroll
+                        for (int v4 = 0; v4 < 4; ++v4) rowmax[v4] = bl_half_max(rowmax[v4]);
+                        /* lane v4 of a half stands for row v4: one atomic instruction for eight rows */
+                        const float mine = l32 == 0 ? rowmax[0] : l32 == 1 ? rowmax[1] : l32 == 2 ? rowmax[2] : rowmax[3];
+                        if (l32 < 4 && (!cut || ml + l32 <= mlast)) atomicMax(absmax + m0 + ml + l32, __float_as_int(mine));
                     }
-                }
+            };
+            constexpr bool both = EPI == 2 || BM < 128;
+            const bool whole = mlast >= G3_BM - 1 && (EPI == 2 || n0 + BN <= N) && !acc && (y != nullptr) == (EPI == 1);
+            if constexpr (both) {
+                if (whole) finish(std::false_type{});
+                else finish(std::true_type{});
+            } else {
+                finish(std::true_type{});
+            }
         }
         if (vb2 < 0) {
             if (stamp && tid == 0) {
@@ -1159,6 +1165,19 @@ extern "C" bl_status bl_gemm_w158a8(const uint8_t* packed, const float* beta, in
     return bl_gemm_w158a8_res(packed, beta, layout, q, scale, rowsum, M, N, K, nullptr, acc, y, workspace, s);
 }
 
+/* The tile of a fused epilogue: 64 x 128 (two waves across, so that a row's maximum meets two atomics and not four) up to 352
+ * tiles of 128 x 128, where the larger one leaves compute units idle.  2560 -> 2560 with residual at 192 tokens 21.3 / 13.1 us, 512
+ * 22.6 / 14.5, 2048 (320 tiles) 28.6 / 22.5, 2560 (400) 30.8 / 30.7; 6912 -> 2560 at 512 tokens 40.2 / 27.7, 2048 51.1 / 43.9, 2560 56.7
+ * / 60.3; 2560 -> 13824 with the gate at 192 (216 tiles) 23.7 / 19.6, 384 (324) 25.8 / 23.4, 512 (432) 25.4 / 27.6.  Four stages at
+ * one workgroup per compute unit gain nothing here (512 tokens: 18.1, 38.7, 24.8). */
+template <int EPI>
+static bl_status launch_fused(const uint8_t* packed, const float* beta, const int8_t* q, const float* scale, const int32_t* rowsum, int m, int n,
+                              int k, const float* residual, int32_t* acc, float* y, const bl_epi_args ea, hipStream_t st) {
+    if ((int64_t)((m + 127) / 128) * ((n + 127) / 128) <= 352)
+        return launch_tile256_t<64, 128, 2, 2, 2, EPI>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st, ea);
+    return launch_tile256_t<128, 128, 2, 2, 2, EPI>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st, ea);
+}
+
 /* Prefill product with a fused producer epilogue (see bl_gemm_tile256, EPI = 1 and 2). */
 extern "C" bl_status bl_gemm_w158a8_fused(const uint8_t* packed, const float* beta, int layout, const int8_t* q,
                                           const float* scale, const int32_t* rowsum, int64_t M, int64_t N, int64_t K,
@@ -1176,11 +1195,8 @@ extern "C" bl_status bl_gemm_w158a8_fused(const uint8_t* packed, const float* be
         return BL_ERR_ALIGN;
     const bl_epi_args ea = {ep->x_bf16, (int*)ep->absmax};
     hipStream_t st = (hipStream_t)s;
-    if (ep->kind == BL_EPI_RESIDUAL)
-        return launch_tile256_t<128, 128, 2, 2, 2, 1>(packed, beta, q, scale, rowsum, (int)M, (int)N, (int)K,
-                                                      ep->residual, acc, ep->y, st, ea);
-    return launch_tile256_t<128, 128, 2, 2, 2, 2>(packed, beta, q, scale, rowsum, (int)M, (int)N, (int)K, nullptr, acc,
-                                                  ep->y, st, ea);
+    if (ep->kind == BL_EPI_RESIDUAL) return launch_fused<1>(packed, beta, q, scale, rowsum, (int)M, (int)N, (int)K, ep->residual, acc, ep->y, ea, st);
+    return launch_fused<2>(packed, beta, q, scale, rowsum, (int)M, (int)N, (int)K, nullptr, acc, ep->y, ea, st);
 }
 
 /* ---- entry point that allocates nothing ---------------------------------------------------
