@@ -189,7 +189,8 @@ __global__ __launch_bounds__(256) void bl_stream_prep(const bl_stream_prep_item*
  * core computes 32 times what is wanted and is busy a fifth of the time.
  * Thirty layers of 2560 / 6912 in one launch: 88.9 -> 85.4 us in the 2-bit form (six tenths of it the order of the
  * loads, below), 107.4 -> 89.4 in the form of five per byte; sixty of 640 / 1280 20.7 -> 15.4 and 39.0 -> 17.5.
- * (One layer of 2560 / 6912, five per byte: 8.7 -> 9.7; its rows of 6912 are three dependent parts.)
+ * (Slower, five per byte: one layer of 2560 / 6912 8.7 -> 9.7, its rows of 6912 are three dependent parts; three layers of
+ * 896 / 2624 6.9 -> 7.4, the staging is most of a small table.)
  *
  * A product's quantised activation row lives in LDS for the workgroup (staged once per product
  * and workgroup: quantised from bf16 right there, or taken from the int8 row), as the 6-bit pieces
