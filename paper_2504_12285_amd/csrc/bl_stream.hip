@@ -21,6 +21,7 @@
 #include "bl_gemv_common.h"
 #include "bl_host.h"
 #include "bl_producer.h"
+#include "bl_stream_index.h"
 
 /* ---- device side -------------------------------------------------------------------------- */
 
@@ -277,18 +278,18 @@ __device__ __forceinline__ void bl_lds_barrier() {
 
 /* The activations that meet one packed word, as they were loaded (nothing waits for them here): UD pairs of bf16
  * words, or, of an int8 row, UD dwords in x[.][0] (five per byte) or in the first sixteen bytes.  A row may end
- * inside a word of five: the values behind `valid` dwords are zeros. */
+ * inside a word of five or in front of one: the values behind `valid` dwords (which may be negative) are zeros. */
 template <int FORM>
 struct bl_unit {
     static constexpr int UD = FORM == BL_FORM_TRIT5 ? 5 : 4;
     bl_v2i x[UD];
     int valid;
     __device__ __forceinline__ void load(const uint16_t* xbf16, int wd, int dwords) {
-        valid = dwords - wd * UD;
+        valid = bl_word_valid<UD>(wd, dwords);
         if constexpr (FORM == BL_FORM_TRIT5) {
-            const bl_v2i BL_G* p = bl_gc<bl_v2i>(xbf16) + wd * UD;
+            const bl_v2i BL_G* p = bl_gc<bl_v2i>(xbf16) + bl_word_first<UD>(wd, dwords);
 #pragma unroll
-            for (int i = 0; i < UD; ++i) x[i] = p[i < valid ? i : 0];
+            for (int i = 0; i < UD; ++i) x[i] = p[bl_word_dword(i, valid)];
         } else {
             const bl_gv4i* p = (const bl_gv4i*)xbf16 + wd * 2;
             const bl_v4i a = p[0], b = p[1];
@@ -299,11 +300,11 @@ struct bl_unit {
         }
     }
     __device__ __forceinline__ void load_q(const int8_t* q, int wd, int dwords) {
-        valid = dwords - wd * UD;
+        valid = bl_word_valid<UD>(wd, dwords);
         if constexpr (FORM == BL_FORM_TRIT5) {
-            const int BL_G* p = bl_gc<int>(q) + wd * UD;
+            const int BL_G* p = bl_gc<int>(q) + bl_word_first<UD>(wd, dwords);
 #pragma unroll
-            for (int i = 0; i < UD; ++i) x[i] = bl_v2i{p[i < valid ? i : 0], 0};
+            for (int i = 0; i < UD; ++i) x[i] = bl_v2i{p[bl_word_dword(i, valid)], 0};
         } else {
             const bl_v4i a = ((const bl_gv4i*)q)[wd];
             x[0] = bl_v2i{a[0], a[1]};
