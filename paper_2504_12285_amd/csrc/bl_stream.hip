@@ -551,18 +551,17 @@ __device__ __forceinline__ void bl_stream_slice(const bl_stream_item& P, const i
     auto issue = [&](bl_v4i* p, float& rv) {
         const bool over = irg == first + mine;
         const int rows = N - irg * 8;                    /* rows from this row group on */
-        int off = ipart * (LP * 128);
-        const int end = max(row_end - off, 0);
-        int limit = rows >= 8 ? 0x7FFFFFFF : rows * row_bytes - 16 - off;
-        off = over ? -8 * row_bytes : limit < 0 ? 0 : off;
-        limit = over || limit < 0 ? 0 : limit;
+        const int part_at = ipart * (LP * 128);
+        const int end = max(row_end - part_at, 0);
+        const bl_part_window win = bl_part_of(rows, row_bytes, part_at, over);
+        int limit = win.limit;
         asm("" : "+s"(limit));                           /* (one scalar, not a select per lane and load) */
-        const char BL_G* const base = rg_at + off;
+        const char BL_G* const base = rg_at + win.off;
 #pragma unroll
         for (int i = 0; i < LP; ++i)
             p[i] = __builtin_nontemporal_load(
                 (const bl_gv4i*)(base + (uint32_t)min(min(lane_off[i], end), limit)));
-        const int rlim = res_g ? (over ? -1 : rows - 1) : 0;
+        const int rlim = res_g ? bl_last_residual(rows) : 0;
         rv = rv_at[min(r, rlim)];
         const bool next = !over && ++ipart == parts;
         ipart = next ? 0 : ipart;

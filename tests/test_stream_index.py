@@ -21,7 +21,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["activations"])
+@pytest.mark.parametrize("what", ["activations", "issue"])
 def test_reads_stay_inside(driver, what):
     run = subprocess.run([driver, what], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
     assert run.returncode == 0 and "walk ok" in run.stdout, run.stdout
