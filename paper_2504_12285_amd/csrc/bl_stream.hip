@@ -21,6 +21,7 @@
 #include "bl_gemv_common.h"
 #include "bl_host.h"
 #include "bl_producer.h"
+#include "bl_stream_cut.h"
 #include "bl_stream_index.h"
 
 /* ---- device side -------------------------------------------------------------------------- */
@@ -1232,6 +1233,7 @@ __global__ __launch_bounds__(256) void bl_mb_finish(const bl_mb_fin_item* __rest
 #define BL_STREAM_LDS_BYTES                                                                          \
     (layout == BL_LAYOUT_KMAJOR ? max_units * 64 + max_cols * 64 + 64                                \
                                 : (max_slots + 1) * (layout == BL_LAYOUT_TRIT5 ? BL_T5_CHUNK : BL_B2_CHUNK) + 64)
+static_assert(sizeof(bl_cut_pos) == sizeof(int2), "read as int2 by the kernels");
 #define BL_KM_MAX_N 3072      /* k-major form: at most three dword columns of 64 lanes per weight row (48 sums per lane) */
 
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -1250,60 +1252,6 @@ static bl_stream_layout stream_layout(int count, size_t q_bytes, size_t acc_byte
     L.acc_off = L.q_off + align_up(q_bytes, 256);
     L.total = L.acc_off + align_up(acc_bytes, 256);
     return L;
-}
-
-/* Cuts a table of products (units[i] row groups of unit_cost[i] each, enter_cost[i] for every
- * workgroup that enters product i) into `blocks` contiguous slices of about equal cost: walk the
- * row groups once, cutting whenever a workgroup's cost reaches the target; the last workgroup
- * takes what is left.  Returns blocks + 1 positions (product, row group). */
-static std::vector<int2> cut_slices(const std::vector<int>& units, const std::vector<int64_t>& unit_cost,
-                                    const std::vector<int64_t>& enter_cost, int blocks) {
-    const int count = (int)units.size();
-    std::vector<int2> wg((size_t)blocks + 1);
-    int64_t all = 0;
-    for (int i = 0; i < count; ++i) all += (int64_t)units[(size_t)i] * unit_cost[(size_t)i] + enter_cost[(size_t)i];
-    /* every cut inside a product adds one more entry, so the target is refined until the
-     * last workgroup (which takes what is left) is no longer than the others */
-    int64_t target = all / blocks + 1;
-    for (int iter = 0; iter < 12; ++iter) {
-        int pi = 0, unit = 0;
-        for (int b = 0; b < blocks; ++b) {
-            wg[(size_t)b] = make_int2(pi, unit);
-            int64_t c = 0;
-            bool entered = false;
-            while (pi < count && b < blocks - 1) {
-                if (!entered) { c += enter_cost[(size_t)pi]; entered = true; }
-                const int64_t uc = unit_cost[(size_t)pi];
-                const int64_t room = target - c;
-                const int64_t take = room > 0 ? (room + uc - 1) / uc : 0;
-                const int left = units[(size_t)pi] - unit;
-                if (take >= left) {
-                    c += (int64_t)left * uc;
-                    ++pi;
-                    unit = 0;
-                    entered = false;
-                    if (c >= target) break;
-                } else {
-                    unit += (int)take;
-                    break;
-                }
-            }
-        }
-        /* cost of what is left for the last workgroup */
-        int64_t last = 0;
-        {
-            int pi = wg[(size_t)blocks - 1].x, unit = wg[(size_t)blocks - 1].y;
-            for (; pi < count; ++pi, unit = 0)
-                if (units[(size_t)pi] > unit)
-                    last += enter_cost[(size_t)pi] + (int64_t)(units[(size_t)pi] - unit) * unit_cost[(size_t)pi];
-        }
-        if (last <= target + target / 64) break;
-        target += (last - target) / blocks + 1;
-    }
-    /* normalise an end position (count, 0) to (count - 1, units): the kernel never reads entry `count` */
-    for (int b = 0; b <= blocks; ++b)
-        if (b == blocks || wg[(size_t)b].x >= count) wg[(size_t)b] = make_int2(count - 1, units[(size_t)count - 1]);
-    return wg;
 }
 
 static bool desc_is_fused(const bl_decode_desc& d) { return d.X || d.prod.in0; }
@@ -1617,10 +1565,10 @@ static bl_status stack_build_batched(const bl_decode_desc* descs, int count, int
     if (blocks64 > BL_STREAM_MAX_BLOCKS) blocks64 = BL_STREAM_MAX_BLOCKS;
     if (blocks64 < 1) blocks64 = 1;
     const int blocks = (int)blocks64;
-    const std::vector<int2> wg = cut_slices(units_v, ucost_v, ecost_v, blocks);
+    const std::vector<bl_cut_pos> wg = bl_cut_slices(units_v, ucost_v, ecost_v, blocks, BL_MB_WAVES);
     std::vector<uint8_t> blob(L.ws_off, 0);
     memcpy(blob.data(), items.data(), items.size() * sizeof(bl_stream_item));
-    memcpy(blob.data() + L.wg_off, wg.data(), wg.size() * sizeof(int2));
+    memcpy(blob.data() + L.wg_off, wg.data(), wg.size() * sizeof(bl_cut_pos));
     if (!fins.empty()) memcpy(blob.data() + L.fin_off, fins.data(), fins.size() * sizeof(bl_mb_fin_item));
     /* the partial sums start at zero; every run leaves them at zero again */
     if (ws_bytes && hipMemsetAsync(dev_base + L.ws_off, 0, ws_bytes, st) != hipSuccess) return BL_ERR_HIP;
@@ -1827,10 +1775,10 @@ extern "C" bl_status bl_stack_build(const bl_decode_desc* descs, int count, int 
         ucost_v[(size_t)i] = unit_bytes[(size_t)i];
         ecost_v[(size_t)i] = items[(size_t)i].xbf16 ? (int64_t)36 << 10 : (int64_t)12 << 10;
     }
-    const std::vector<int2> wg = cut_slices(units_v, ucost_v, ecost_v, blocks);
+    const std::vector<bl_cut_pos> wg = bl_cut_slices(units_v, ucost_v, ecost_v, blocks, 4);
     std::vector<uint8_t> blob(L.rowsum_off, 0);
     memcpy(blob.data(), items.data(), items.size() * sizeof(bl_stream_item));
-    memcpy(blob.data() + L.wg_off, wg.data(), wg.size() * sizeof(int2));
+    memcpy(blob.data() + L.wg_off, wg.data(), wg.size() * sizeof(bl_cut_pos));
     if (!preps.empty()) memcpy(blob.data() + L.prep_off, preps.data(), preps.size() * sizeof(bl_stream_prep_item));
     hipStream_t st = (hipStream_t)s;
     /* the k-major form's partial sums start at zero; every run leaves them at zero again */

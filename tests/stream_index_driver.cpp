@@ -1,12 +1,15 @@
 /* Walks the index rules of the one-token stream (csrc/bl_stream_index.h) over the shapes that the library takes and
- * reports every read outside its row, matrix or vector.  argv[1]: activations | issue. */
+ * reports every read outside its row, matrix or vector; and the shares of the workgroups (csrc/bl_stream_cut.h).
+ * argv[1]: activations | issue | cut. */
 #include <stdint.h>
 #include <stdio.h>
 #include <string.h>
 
 #include <algorithm>
+#include <vector>
 
 #include "bl_host.h"
+#include "bl_stream_cut.h"
 #include "bl_stream_index.h"
 
 static long bad = 0;
@@ -60,6 +63,35 @@ static void wave(int N, int nchunks, int lp, int first, int mine) {
     }
 }
 
+/* Slices are contiguous, cover the table once, and none costs more than a fair share (a quarter more: the bisection is taken for a fifth less),
+ * a row group for each wave and two entries (its own and the one that stopped its neighbour). */
+static void cut(const std::vector<int>& units, const std::vector<int64_t>& uc, const std::vector<int64_t>& ec, int blocks, int waves) {
+    const std::vector<bl_cut_pos> wg = bl_cut_slices(units, uc, ec, blocks, waves);
+    const int count = (int)units.size();
+    int64_t all = 0, uc_max = 0, ec_max = 0;
+    for (int i = 0; i < count; ++i) {
+        all += units[i] * uc[i] + ec[i];
+        uc_max = std::max(uc_max, uc[i]);
+        ec_max = std::max(ec_max, ec[i]);
+    }
+    int pi = 0, unit = 0;
+    for (int b = 0; b < blocks; ++b) {
+        int64_t cost = 0;
+        /* as the kernels walk it */
+        for (int p = wg[b].x; p <= wg[b + 1].x; ++p) {
+            if (p == wg[b + 1].x && wg[b + 1].y == 0) break;
+            const int ub = p == wg[b].x ? wg[b].y : 0, ue = p == wg[b + 1].x ? wg[b + 1].y : units[p];
+            if (ub >= ue) continue;
+            if (unit == units[pi]) ++pi, unit = 0;
+            expect(p == pi && ub == unit, "gap (products, blocks, block, product)", count, blocks, b, p);
+            unit = ue;
+            cost += ec[p] + (ue - ub) * uc[p];
+        }
+        expect(cost <= all / blocks / 4 * 5 + uc_max * waves + 2 * ec_max + 1, "share (products, blocks, block, cost)", count, blocks, b, (long)cost);
+    }
+    expect(pi == count - 1 && unit == units[pi], "rest", count, blocks, pi, unit);
+}
+
 int main(int argc, char** argv) {
     if (argc < 2) return 2;
     if (!strcmp(argv[1], "activations")) {
@@ -80,6 +112,30 @@ int main(int argc, char** argv) {
                                 wave(N, nchunks, lp, ub + w * each + std::min(w, extra), each + (w < extra ? 1 : 0));
                             }
                 }
+    } else if (!strcmp(argv[1], "cut")) {
+        cut(std::vector<int>(12, 512), std::vector<int64_t>(12, 9472), std::vector<int64_t>(12, 36 << 10), 1024, 4);
+        cut(std::vector<int>(54, 512), std::vector<int64_t>(54, 8960), std::vector<int64_t>(54, 36 << 10), 1024, 4);
+        cut({1728}, {128}, {36 << 10}, 432, 4);
+        cut({1}, {128}, {36 << 10}, 1, 4);
+        uint32_t x = 12345;
+        auto rnd = [&x](int lo, int hi) {
+            x = x * 1664525u + 1013904223u;
+            return lo + (int)((uint64_t)(x >> 8) * (uint64_t)(hi - lo + 1) >> 24);
+        };
+        for (int k = 0; k < 400; ++k) {
+            const int count = rnd(1, k % 4 ? 40 : 1024);
+            std::vector<int> units(count);
+            std::vector<int64_t> uc(count), ec(count);
+            int64_t total = 0;
+            for (int i = 0; i < count; ++i) {
+                units[i] = rnd(1, 4000) >> rnd(0, 10);
+                units[i] += units[i] == 0;
+                uc[i] = (int64_t)rnd(1, 320) * 128;
+                ec[i] = (int64_t)rnd(0, 36) << 10;
+                total += units[i];
+            }
+            cut(units, uc, ec, (int)std::min<int64_t>(rnd(1, 4096), (total + 3) / 4), k % 2 ? 4 : 8);
+        }
     } else {
         return 2;
     }

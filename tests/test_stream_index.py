@@ -1,5 +1,5 @@
-"""The reads of the one-token stream, on the CPU: its index rules stand in a header of their own, and a host program
-walks them over the shapes that the library takes.  (On the GPU a read behind a buffer shows only where the mapping ends.)"""
+"""The reads of the one-token stream and the shares of its workgroups, on the CPU: both stand in headers of their own, and a host
+program walks them over the shapes that the library takes.  (On the GPU a read behind a buffer shows only where the mapping ends.)"""
 import os
 import shutil
 import subprocess
@@ -21,7 +21,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["activations", "issue"])
-def test_reads_stay_inside(driver, what):
+@pytest.mark.parametrize("what", ["activations", "issue", "cut"])
+def test_stream_index(driver, what):
     run = subprocess.run([driver, what], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
     assert run.returncode == 0 and "walk ok" in run.stdout, run.stdout
