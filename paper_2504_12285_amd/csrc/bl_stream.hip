@@ -44,7 +44,7 @@ struct bl_stream_item {
     float* scale_out;
     float fixed_scale;        /* xbf16 only: > 0 replaces absmax/127 in the rescale */
     int N, nchunks, lp, layout, units;
-    int shift;                /* one token: chunks that the loads of odd rows start in front of their row (0 or 4) */
+    int lq, mod, lead;        /* one token: row groups to a block (log2), what their shifts come from (bl_group_shift), the largest shift */
     int parts;                /* one token: the row is read in this many parts of wave-wide loads (128 bytes of a row each) */
     int qgroups;              /* 16-byte groups of the quantised row (its padded length / 16) */
     int m;                    /* tokens of the entry (batched form; 1 otherwise) */
@@ -364,13 +364,13 @@ __device__ __forceinline__ void bl_stream_stage(const bl_stream_item& P, const b
     int* ssum = misc + 6;
     /* zeros in front of and behind the row, see bl_stream_slice */
     {
-        const int lead = P.shift * CHUNK / 16, tail = (P.shift + P.nchunks) * CHUNK / 16,
-                  all = (P.shift + P.parts * LP * 8 + 1) * CHUNK / 16;
+        const int lead = P.lead * CHUNK / 16, tail = (P.lead + P.nchunks) * CHUNK / 16,
+                  all = (P.lead + P.parts * LP * 8 + 1) * CHUNK / 16;
 #pragma unroll 1
         for (int i = tid; i < lead + all - tail; i += 256)
             ((bl_v4i*)Qs)[i < lead ? i : i - lead + tail] = bl_v4i{0, 0, 0, 0};
     }
-    uint8_t* const img = Qs + P.shift * CHUNK;
+    uint8_t* const img = Qs + P.lead * CHUNK;
     int part = 0;
     auto place = [&](int wd, const uint32_t* a) __attribute__((always_inline)) {
         if constexpr (FORM == BL_FORM_TRIT5) bl_lds_put20(img, wd, a);
@@ -506,7 +506,7 @@ __device__ __forceinline__ void bl_t5_digits(const uint32_t w, int& d01, int& d2
     d4 = (int)__builtin_amdgcn_perm(o, e, 0x07030501u);
 }
 
-/* One product slice [ub, ue) of row groups of eight weight rows.  A row group is read in P.parts
+/* One product slice [ub, ue) of row groups of eight weight rows (eight consecutive ones, or CLASSES).  A row group is read in P.parts
  * parts of LP wave-wide loads; each of the four waves of the workgroup takes a contiguous quarter of the
  * row groups (round-robin, the workgroups read in step at one stride, which may be that of few
  * memory channels: sixty products of 13824 x 2560 100 us against 86) and
@@ -517,19 +517,20 @@ __device__ __forceinline__ void bl_t5_digits(const uint32_t w, int& d01, int& d2
  * with the row's weights: a load issued later, in the epilogue, could only be waited for
  * together with every weight load issued before it (with no residual every lane reads beta
  * instead, a valid address, and the value is not used). */
-template <int FORM, int LP>
+template <int FORM, int LP, bool CLASSES>
 __device__ __forceinline__ void bl_stream_slice(const bl_stream_item& P, const int ub, const int ue,
                                                     uint8_t* __restrict__ Qs, int* __restrict__ misc,
                                                     const bool restage) {
     constexpr int CHUNK = FORM == BL_FORM_TRIT5 ? BL_T5_CHUNK : BL_B2_CHUNK;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int N = P.N, parts = P.parts;
-    /* lanes 0..31 take the even rows of a row group, 32..63 the odd ones.  Where rows are an odd multiple of 64 bytes
-     * long (K = 6912) an odd row starts in the middle of a 128-byte line: its loads, and its k group of A, are
-     * P.shift = 4 chunks back, so that every load of a row is one line (P.shift zero chunks in front of the image). */
-    const int r = ((lane >> 2) & 6) | (lane >> 5), u = lane & 7, h = lane >> 5;
+    /* Lanes 0..31 take the rows of the even class of a row group, 32..63 those of the odd one.  The loads of a class that does not
+     * start with a 128-byte line, and its k group of A, are bl_group_shift chunks back, so that every load of a row is one line
+     * (P.lead zero chunks in front of the image): at K = 6912 odd rows by 4; with lq > 0 classes that differ from row group to
+     * row group.  Where mod is 0 and rows still lie across lines they are read as they lie. */
+    const int u = lane & 7, h = lane >> 5, lq = CLASSES ? P.lq : 0, mod = P.mod;
+    const int r = bl_group_row((lane >> 3) & 3, h, lq);
     const int row_bytes = P.nchunks * 16;
-    const int u16 = u * 16 - (h ? P.shift * 16 : 0);
     const char BL_G* const wbase = (const char BL_G*)P.packed;
     int32_t BL_G* const acc_g = (int32_t BL_G*)P.acc;
     float BL_G* const y_g = (float BL_G*)P.y;
@@ -540,35 +541,42 @@ __device__ __forceinline__ void bl_stream_slice(const bl_stream_item& P, const i
     int irg = first, ipart = 0;                          /* issue cursor */
     /* Lanes behind their row's end read its last chunk again, which meets zero activations (the next row's chunks would
      * do as well, but are fetched twice then: 60 layers of 640 / 1280 16.4 us against 15.4); a
-     * shifted load in front of an odd row reads the end of the even one.  Rows behind N are held inside the matrix
+     * shifted load in front of a row reads the end of the row before.  Rows behind N are held inside the matrix
      * and not stored.  Behind the wave's last row group every lane reads the first bytes of that row group once more: one
      * line, and the loop needs no second copy of itself without loads. */
-    const int row_end = r * row_bytes + row_bytes - 16;
-    const char BL_G* rg_at = wbase + (int64_t)irg * 8 * row_bytes;
-    const float BL_G* rv_at = res_g ? res_g + (int64_t)irg * 8 : (const float BL_G*)P.beta;
+    const int bias = P.lead * 16, row_end = r * row_bytes + row_bytes - 16 + bias;
+    int rows = N - bl_group_base(first, lq);             /* rows from this row group's first one on */
+    const char BL_G* rg_at = wbase + (int64_t)(N - rows) * row_bytes - bias;
+    const float BL_G* rv_at = res_g ? res_g + (N - rows) : (const float BL_G*)P.beta;
+    int ishift = bl_group_shift(first, h, lq, mod);
     int lane_off[LP];
 #pragma unroll
-    for (int i = 0; i < LP; ++i) lane_off[i] = r * row_bytes + u16 + i * 128;
+    for (int i = 0; i < LP; ++i) lane_off[i] = r * row_bytes + (u - ishift) * 16 + bias + i * 128;
     auto issue = [&](bl_v4i* p, float& rv) {
         const bool over = irg == first + mine;
-        const int rows = N - irg * 8;                    /* rows from this row group on */
         const int part_at = ipart * (LP * 128);
-        const int end = max(row_end - part_at, 0);
-        const bl_part_window win = bl_part_of(rows, row_bytes, part_at, over);
-        int limit = win.limit;
+        const int end = row_end - part_at;
+        int limit = over ? 0 : bl_part_limit(rows, row_bytes, part_at, bias, lq);
         asm("" : "+s"(limit));                           /* (one scalar, not a select per lane and load) */
-        const char BL_G* const base = rg_at + win.off;
+        const int back = bl_group_next(irg - 1, lq);     /* rows back to the row group in front */
+        const char BL_G* const base = rg_at + (over ? bias - back * row_bytes : part_at);
 #pragma unroll
         for (int i = 0; i < LP; ++i)
             p[i] = __builtin_nontemporal_load(
                 (const bl_gv4i*)(base + (uint32_t)min(min(lane_off[i], end), limit)));
-        const int rlim = res_g ? bl_last_residual(rows) : 0;
+        const int rlim = res_g ? (over ? -back : rows - 1) : 0;
         rv = rv_at[min(r, rlim)];
         const bool next = !over && ++ipart == parts;
+        const int skip = next ? bl_group_next(irg, lq) : 0;
         ipart = next ? 0 : ipart;
         irg += next ? 1 : 0;
-        rg_at += next ? 8 * row_bytes : 0;
-        rv_at += next && res_g ? 8 : 0;
+        rows -= skip;
+        rg_at += (int64_t)skip * row_bytes;
+        rv_at += res_g ? skip : 0;
+        const int was = ishift;
+        ishift = bl_group_shift(irg, h, lq, mod);
+#pragma unroll
+        for (int i = 0; i < LP; ++i) lane_off[i] += (was - ishift) * 16;
     };
     bl_v4i pa[LP], pb[LP];
     float ra = 0.0f, rb = 0.0f;
@@ -600,10 +608,11 @@ __device__ __forceinline__ void bl_stream_slice(const bl_stream_item& P, const i
 
     /* this lane of A: chunk u, k group (lane / 8) % 2, piece (lane / 16) % 2; zeros in the other k group */
     const bool live = ((lane >> 3) & 1) == h;
-    const int a_first = live ? (u + (h ? 0 : P.shift)) * CHUNK + ((lane >> 4) & 1) * (CHUNK / 2) : (P.shift + parts * LP * 8) * CHUNK;
-    const int a_step = live ? 8 * CHUNK : 0;
-    const int live_loads = (P.nchunks + P.shift + 7) / 8 - (parts - 1) * LP;
-    int at = a_first, ppart = 0, prg = first;            /* process cursor */
+    const int a_chunk = live ? CHUNK : 0, a_step = live ? 8 * CHUNK : 0;
+    const int a_first = live ? (u + P.lead) * CHUNK + ((lane >> 4) & 1) * (CHUNK / 2) : (P.lead + parts * LP * 8) * CHUNK;
+    const int live_loads = (P.nchunks + P.lead + 7) / 8 - (parts - 1) * LP;
+    int ppart = 0, prg = first, prow = bl_group_base(first, lq);   /* process cursor */
+    int at = a_first - bl_group_shift(prg, h, lq, mod) * a_chunk;
     const int store_row = u == 0 ? r : 1 << 30;          /* one lane of eight stores */
     bl_v16f D = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
     auto step = [&](const bl_v4i* p, const float rv) {
@@ -680,17 +689,18 @@ __device__ __forceinline__ void bl_stream_slice(const bl_stream_item& P, const i
         t += bl_dppf<BL_DPP_QUAD_XOR2>(t);
         t += bl_dppf<BL_DPP_ROW_HALF_MIRROR>(t);
         const int v = (int)(t * 16.0f);
-        if (store_row < N - prg * 8) {
+        if (store_row < N - prow) {
             const int val = FORM == BL_FORM_TRIT5 ? rs - v : v - rs;
-            if (acc_g) acc_g[(int64_t)prg * 8 + (uint32_t)store_row] = val;
+            if (acc_g) acc_g[(int64_t)prow + (uint32_t)store_row] = val;
             if (y_g) {
                 const float o = (float)val * cf;
-                y_g[(int64_t)prg * 8 + (uint32_t)store_row] = res_g ? rv + o : o;
+                y_g[(int64_t)prow + (uint32_t)store_row] = res_g ? rv + o : o;
             }
         }
         ppart = 0;
-        at = a_first;
+        prow += bl_group_next(prg, lq);
         ++prg;
+        at = a_first - bl_group_shift(prg, h, lq, mod) * a_chunk;
     };
     for (int left = mine * parts;;) {
         issue(pb, rb);
@@ -706,7 +716,7 @@ __device__ __forceinline__ void bl_stream_slice(const bl_stream_item& P, const i
  * (product, row group).  One part length per table: the host takes the one that leaves the fewest
  * load slots idle (a row whose loads do not divide by it re-reads its last chunk, a cache hit).
  * Four waves per SIMD, no scratch memory: a version that spilled lost a third of the stream rate. */
-template <int FORM, int LP>
+template <int FORM, int LP, bool CLASSES>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void bl_stream_m1(const bl_stream_item* __restrict__ items, const int2* __restrict__ wgstart, const int q_ints) {
     extern __shared__ __attribute__((aligned(16))) int lds[];   /* q_ints ints of image + 16 */
@@ -722,7 +732,7 @@ void bl_stream_m1(const bl_stream_item* __restrict__ items, const int2* __restri
         const int ub = pi == p_first ? u_first : 0;
         const int ue = pi == p_last ? u_last : P.units;
         if (ub >= ue) continue;
-        bl_stream_slice<FORM, LP>(P, ub, ue, Qs, misc, staged);
+        bl_stream_slice<FORM, LP, CLASSES>(P, ub, ue, Qs, misc, staged);
         staged = true;
     }
 }
@@ -1606,20 +1616,48 @@ extern "C" size_t bl_stack_table_bytes(const bl_decode_desc* descs, int count) {
 static int64_t row_chunks(int64_t K, int layout) {
     return layout == BL_LAYOUT_TRIT5 ? bl_kpad5(K) / 80 : bl_kpad(K) / 64;
 }
-/* Chunks that the loads of odd rows start early so that they cover whole 128-byte lines, and the wave-wide
- * loads of a row group. */
-static int row_shift(int64_t chunks) { return chunks % 8 == 4 ? 4 : 0; }
-static int row_loads(int64_t chunks) { return (int)((chunks + row_shift(chunks) + 7) / 8); }
+/* Rows that are no multiple of 64 bytes: read from the starts of their lines too, by row groups of two classes of rows
+ * (bl_stream_index.h), where they are longer than 2560 weights, in the 2-bit form.  A load whose eight pieces each lie across
+ * two lines asks for sixteen: 250 MB of K = 3200 53.6 -> 46.8 us, 8768 57.8 -> 48.8, 19904 64 -> 57; up to 2560 the loop does not wait for
+ * it (K = 2240 48.6 / 47.6, 1472 48.8 / 50.0; five per byte K = 4000 64 / 64, and 3440 62 / 71 for the extra load of some rows).
+ * A table takes the kernel for it where such products are a quarter of its bytes and 6 MiB: 10240 x 3200 5.16 / 4.93, 6144 x 3200
+ * 4.67 / 4.90, 1024 x 3200 4.54 / 4.76 (more zeros to stage). */
+static bool wants_classes(int64_t K, int layout) {
+    const int64_t chunks = row_chunks(K, layout);
+    return (layout == BL_LAYOUT_ROWMAJOR || layout == BL_LAYOUT_K16) && chunks > 40 && chunks % 4 != 0;
+}
+static bool table_classes(const bl_decode_desc* descs, int count, int layout) {
+    int64_t all = 0, such = 0;
+    for (int i = 0; i < count; ++i) {
+        const int64_t bytes = descs[i].N * row_chunks(descs[i].K, layout) * 16;
+        all += bytes;
+        if (wants_classes(descs[i].K, layout)) such += bytes;
+    }
+    return such >= (int64_t)6 << 20 && such >= all / 4;
+}
+/* How the rows of a product are read: lq, mod and lead of its bl_stream_item, and the wave-wide loads of a row group. */
+struct row_plan {
+    int lq, mod, lead, loads;
+};
+static row_plan plan_rows(int64_t K, int layout, bool classes) {
+    const int chunks = (int)row_chunks(K, layout);
+    row_plan r;
+    r.lq = classes && wants_classes(K, layout) ? bl_row_classes(chunks) : 0;
+    r.mod = r.lq || chunks % 4 == 0 ? chunks % 8 : 0;
+    r.lead = bl_row_lead(r.mod);
+    r.loads = (chunks + r.lead + 7) / 8;
+    return r;
+}
 /* Wave-wide loads of a part (3, 4 or 5) for a table of one-token products: the least cost over the table,
  * in quarters of a load that is multiplied; an idle slot of a row's last part is loaded (a cache hit) but not
  * multiplied, and a part costs about half a load besides. */
-static int part_loads(const bl_decode_desc* descs, int count, int layout) {
+static int part_loads(const bl_decode_desc* descs, int count, int layout, bool classes) {
     int best = BL_STREAM_LMAX;
     int64_t least = INT64_MAX;
     for (int lp = BL_STREAM_LMAX; lp >= BL_STREAM_LMIN; --lp) {
         int64_t cost = 0;
         for (int i = 0; i < count; ++i) {
-            const int64_t loads = row_loads(row_chunks(descs[i].K, layout)), parts = (loads + lp - 1) / lp;
+            const int64_t loads = plan_rows(descs[i].K, layout, classes).loads, parts = (loads + lp - 1) / lp;
             cost += (descs[i].N + 7) / 8 * (3 * loads + parts * lp + 2 * parts);
         }
         if (cost < least) {
@@ -1629,13 +1667,17 @@ static int part_loads(const bl_decode_desc* descs, int count, int layout) {
     }
     return best;
 }
-static const void* stream_kernel(int layout, int lp) {
+/* The kernel of a table: `form` = loads of a part, + BL_STREAM_CLASSES where row groups of classes occur. */
+#define BL_STREAM_CLASSES 8
+template <int FORM, bool CLASSES>
+static const void* stream_kernel_lp(int lp) {
+    return lp == 5 ? (const void*)bl_stream_m1<FORM, 5, CLASSES>
+         : lp == 4 ? (const void*)bl_stream_m1<FORM, 4, CLASSES> : (const void*)bl_stream_m1<FORM, 3, CLASSES>;
+}
+static const void* stream_kernel(int layout, int form) {
     if (layout == BL_LAYOUT_KMAJOR) return (const void*)bl_stream_m1_km;
-    if (layout == BL_LAYOUT_TRIT5)
-        return lp == 5 ? (const void*)bl_stream_m1<BL_FORM_TRIT5, 5>
-             : lp == 4 ? (const void*)bl_stream_m1<BL_FORM_TRIT5, 4> : (const void*)bl_stream_m1<BL_FORM_TRIT5, 3>;
-    return lp == 5 ? (const void*)bl_stream_m1<BL_FORM_BIT2, 5>
-         : lp == 4 ? (const void*)bl_stream_m1<BL_FORM_BIT2, 4> : (const void*)bl_stream_m1<BL_FORM_BIT2, 3>;
+    if (layout == BL_LAYOUT_TRIT5) return stream_kernel_lp<BL_FORM_TRIT5, false>(form);
+    return form & BL_STREAM_CLASSES ? stream_kernel_lp<BL_FORM_BIT2, true>(form & ~BL_STREAM_CLASSES) : stream_kernel_lp<BL_FORM_BIT2, false>(form);
 }
 
 extern "C" bl_status bl_stack_build(const bl_decode_desc* descs, int count, int layout, int64_t M, void* table,
@@ -1653,7 +1695,8 @@ extern "C" bl_status bl_stack_build(const bl_decode_desc* descs, int count, int 
     }
     const bl_stream_layout L = stream_layout(count, q_bytes, acc_bytes);
     uint8_t* const dev_base = (uint8_t*)table;
-    const int lp = layout == BL_LAYOUT_KMAJOR ? 0 : part_loads(descs, count, layout);
+    const bool classes = layout != BL_LAYOUT_KMAJOR && table_classes(descs, count, layout);
+    const int lp = layout == BL_LAYOUT_KMAJOR ? 0 : part_loads(descs, count, layout, classes);
     std::vector<bl_stream_item> items((size_t)count);
     std::vector<bl_stream_prep_item> preps;
     int inline_count = 0, max_slots = 0, max_units = 0, max_cols = 0;
@@ -1681,10 +1724,13 @@ extern "C" bl_status bl_stack_build(const bl_decode_desc* descs, int count, int 
         it.layout = layout;
         int R = 8;                                           /* weight rows of a unit */
         if (layout != BL_LAYOUT_KMAJOR) {
-            it.shift = row_shift(it.nchunks);
-            it.parts = (row_loads(it.nchunks) + lp - 1) / lp;
-            it.units = (it.N + R - 1) / R;
-            if (it.parts * lp * 8 + it.shift > max_slots) max_slots = it.parts * lp * 8 + it.shift;
+            const row_plan rp = plan_rows(d.K, layout, classes);
+            it.lq = rp.lq;
+            it.mod = rp.mod;
+            it.lead = rp.lead;
+            it.parts = (rp.loads + lp - 1) / lp;
+            it.units = bl_groups(it.N, it.lq);
+            if (it.parts * lp * 8 + it.lead > max_slots) max_slots = it.parts * lp * 8 + it.lead;
         }
         if (layout == BL_LAYOUT_KMAJOR) {
             /* one row per k: dword columns of 16 output features; a unit is 64 consecutive k */
@@ -1750,11 +1796,12 @@ extern "C" bl_status bl_stack_build(const bl_decode_desc* descs, int count, int 
     }
     /* persistent grid: the workgroups that are resident at once, but no more than one per four
      * row groups' worth of work (a workgroup has four waves) */
+    const int form = classes ? lp | BL_STREAM_CLASSES : lp;
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per_cu, stream_kernel(layout, lp), 256, (size_t)BL_STREAM_LDS_BYTES) != hipSuccess ||
+            &per_cu, stream_kernel(layout, form), 256, (size_t)BL_STREAM_LDS_BYTES) != hipSuccess ||
         cus < 1 || per_cu < 1)
         return BL_ERR_HIP;
     /* (four workgroups per compute unit also where a fifth would fit: 72 products of 13824 x 2048 84 us against 88) */
@@ -1795,7 +1842,7 @@ extern "C" bl_status bl_stack_build(const bl_decode_desc* descs, int count, int 
     plan->norm = any_norm ? 1 : 0;
     plan->lds_bytes = BL_STREAM_LDS_BYTES;
     plan->layout = layout;
-    plan->red_ints = layout == BL_LAYOUT_KMAJOR ? max_cols * 16 : lp;
+    plan->red_ints = layout == BL_LAYOUT_KMAJOR ? max_cols * 16 : form;
     plan->wg_offset = (int64_t)L.wg_off;
     plan->prep_offset = (int64_t)L.prep_off;
     plan->packed_bytes = packed_bytes;
@@ -1853,7 +1900,8 @@ extern "C" bl_status bl_stack_run(void* table, const bl_stack_plan* plan, bl_str
         plan->lds_bytes > 64 * 1024 || plan->lds_bytes % 16 ||
         plan->layout < 0 || plan->layout > BL_LAYOUT_KMAJOR || plan->red_ints < 0 || plan->red_ints > BL_KM_MAX_N ||
         (plan->layout == BL_LAYOUT_KMAJOR ? plan->red_ints < 64 || plan->lds_bytes < 64 + 64 + plan->red_ints * 4
-                                          : plan->red_ints < BL_STREAM_LMIN || plan->red_ints > BL_STREAM_LMAX))
+                                          : plan->red_ints & ~(BL_STREAM_CLASSES | 7) || (plan->red_ints & 7) < BL_STREAM_LMIN ||
+                                                (plan->red_ints & 7) > BL_STREAM_LMAX || (plan->layout == BL_LAYOUT_TRIT5 && plan->red_ints > 7)))
         return BL_ERR_VALUE;
     const bl_stream_layout L = stream_layout(plan->count, 0);
     if (plan->wg_offset != (int64_t)L.wg_off || plan->prep_offset != (int64_t)L.prep_off) return BL_ERR_VALUE;

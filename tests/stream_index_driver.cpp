@@ -32,35 +32,53 @@ static void activations(int64_t K) {
         }
 }
 
-/* The requests of one wave: row groups first .. first + mine - 1 of N rows of nchunks chunks, parts of lp loads, and
- * the one part more.  Cursor and lane offsets as in bl_stream_slice. */
-static void wave(int N, int nchunks, int lp, int first, int mine) {
-    const int shift = nchunks % 8 == 4 ? 4 : 0, parts = ((nchunks + shift + 7) / 8 + lp - 1) / lp, row_bytes = nchunks * 16;
-    int irg = first, ipart = 0;
+/* The requests of one wave: row groups first .. first + mine - 1 of N rows of n chunks, parts of lp loads, and the one
+ * part more.  Cursor and lane offsets as in bl_stream_slice. */
+static void wave(int N, int n, int lq, int mod, int lead, int lp, int first, int mine) {
+    const int parts = ((n + lead + 7) / 8 + lp - 1) / lp, row_bytes = n * 16, bias = lead * 16;
+    int irg = first, ipart = 0, rows = N - bl_group_base(first, lq);
     for (int k = 0; k <= mine * parts; ++k) {
         const bool over = irg == first + mine;
-        const int rows = N - irg * 8, at = ipart * lp * 128;
-        const bl_part_window win = bl_part_of(rows, row_bytes, at, over);
+        const int at = ipart * lp * 128, base_row = N - rows;
+        const int limit = over ? 0 : bl_part_limit(rows, row_bytes, at, bias, lq);
+        const int back = bl_group_next(irg - 1, lq);
+        const int64_t base = (int64_t)base_row * row_bytes - bias + (over ? bias - back * row_bytes : at);
         for (int lane = 0; lane < 64; ++lane) {
-            const int r = ((lane >> 2) & 6) | (lane >> 5), u16 = (lane & 7) * 16 - (lane >> 5 ? shift * 16 : 0);
-            const int end = std::max(r * row_bytes + row_bytes - 16 - at, 0);
+            const int h = lane >> 5, u = lane & 7, r = bl_group_row((lane >> 3) & 3, h, lq), shift = bl_group_shift(irg, h, lq, mod);
+            const int end = r * row_bytes + row_bytes - 16 + bias - at;
             for (int i = 0; i < lp; ++i) {
-                const int64_t x = (int64_t)irg * 8 * row_bytes + win.off + std::min(std::min(r * row_bytes + u16 + i * 128, end), win.limit);
-                expect(x >= 0 && x + 16 <= (int64_t)N * row_bytes, "weights (N, chunks, row group, byte)", N, nchunks, irg, (long)x);
-                /* a live lane reads its own chunk */
-                const int chunk = ipart * lp * 8 + i * 8 + (lane & 7) - (lane >> 5 ? shift : 0);
-                if (!over && irg * 8 + r < N && chunk >= 0 && chunk < nchunks)
-                    expect(x == ((int64_t)irg * 8 + r) * row_bytes + chunk * 16, "wrong chunk", N, nchunks, irg, (long)x);
+                const int off = std::min(std::min(r * row_bytes + (u - shift) * 16 + bias + i * 128, end), limit);
+                const int64_t x = base + (uint32_t)off;
+                expect(x >= 0 && x + 16 <= (int64_t)N * row_bytes, "weights (N, chunks, row group, byte)", N, n, irg, (long)x);
+                /* a live lane reads its own chunk, shifted ones whole lines */
+                const int chunk = ipart * lp * 8 + i * 8 + u - shift;
+                if (!over && base_row + r < N && chunk >= 0 && chunk < n)
+                    expect(x == ((int64_t)base_row + r) * row_bytes + chunk * 16, "wrong chunk", N, n, irg, (long)x);
+                if (lead || n % 8 == 0) expect((n * (base_row + r) + chunk) % 8 == u || over, "not a line", N, n, irg, chunk);
             }
-            const int64_t v = (int64_t)irg * 8 + std::min(r, bl_last_residual(rows));
-            expect(v >= 0 && v < N, "residual (N, chunks, row group, element)", N, nchunks, irg, (long)v);
-            if (!over && irg * 8 + r < N) expect(v == irg * 8 + r, "wrong residual", N, nchunks, irg, (long)v);
+            const int64_t v = base_row + std::min(r, over ? -back : rows - 1);
+            expect(v >= 0 && v < N, "residual (N, chunks, row group, element)", N, n, irg, (long)v);
+            if (!over && base_row + r < N) expect(v == base_row + r, "wrong residual", N, n, irg, (long)v);
         }
         if (!over && ++ipart == parts) {
+            rows -= bl_group_next(irg, lq);
             ipart = 0;
             ++irg;
         }
     }
+}
+/* Every row is in one row group. */
+static void groups(int N, int lq) {
+    std::vector<int> seen(N, 0);
+    for (int g = 0; g < bl_groups(N, lq); ++g) {
+        expect(bl_group_base(g, lq) < N, "empty row group", N, lq, g, bl_group_base(g, lq));
+        expect(bl_group_base(g + 1, lq) == bl_group_base(g, lq) + bl_group_next(g, lq), "next row group", N, lq, g, 0);
+        for (int i = 0; i < 8; ++i) {
+            const int row = bl_group_base(g, lq) + bl_group_row(i >> 1, i & 1, lq);
+            if (row < N) ++seen[row];
+        }
+    }
+    for (int r = 0; r < N; ++r) expect(seen[r] == 1, "row", N, lq, r, seen[r]);
 }
 
 /* Slices are contiguous, cover the table once, and none costs more than a fair share (a quarter more: the bisection is taken for a fifth less),
@@ -100,18 +118,23 @@ int main(int argc, char** argv) {
             activations<5>(K);
         }
     } else if (!strcmp(argv[1], "issue")) {
-        for (int nchunks : {1, 2, 3, 4, 5, 7, 8, 11, 12, 20, 23, 32, 36, 40, 44, 60, 87, 108, 132, 256, 320})
-            for (int lp = 3; lp <= 5; ++lp)
-                for (int N : {1, 2, 3, 4, 5, 7, 8, 9, 12, 15, 16, 17, 29, 37, 64, 100, 2564, 5003}) {
-                    const int units = (N + 7) / 8;
-                    /* every slice of a small product; the last ones of a large one */
-                    for (int ub = units > 9 ? units - 9 : 0; ub < units; ++ub)
-                        for (int ue = ub + 1; ue <= units; ++ue)
-                            for (int w = 0; w < 4; ++w) {
-                                const int each = (ue - ub) >> 2, extra = (ue - ub) & 3;
-                                wave(N, nchunks, lp, ub + w * each + std::min(w, extra), each + (w < extra ? 1 : 0));
-                            }
-                }
+        for (int n : {1, 2, 3, 4, 5, 7, 8, 11, 12, 20, 23, 32, 36, 40, 43, 44, 50, 60, 62, 87, 108, 113, 132, 253, 256, 317, 320})
+            for (int form = 0; form < 2; ++form) {
+                const int lq = form == 0 ? 0 : bl_row_classes(n), mod = form == 0 && n % 4 ? 0 : n % 8, lead = bl_row_lead(mod);
+                for (int lp = 3; lp <= 5; ++lp)
+                    for (int N : {1, 2, 3, 4, 5, 7, 8, 9, 12, 15, 16, 17, 29, 37, 64, 100, 2564, 5003}) {
+                        const int units = bl_groups(N, lq);
+                        /* every slice of a small product; the last ones of a large one */
+                        for (int ub = units > 9 ? units - 9 : 0; ub < units; ++ub)
+                            for (int ue = ub + 1; ue <= units; ++ue)
+                                for (int w = 0; w < 4; ++w) {
+                                    const int each = (ue - ub) >> 2, extra = (ue - ub) & 3;
+                                    wave(N, n, lq, mod, lead, lp, ub + w * each + std::min(w, extra), each + (w < extra ? 1 : 0));
+                                }
+                    }
+            }
+        for (int lq = 0; lq < 3; ++lq)
+            for (int N = 1; N < 300; ++N) groups(N, lq);
     } else if (!strcmp(argv[1], "cut")) {
         cut(std::vector<int>(12, 512), std::vector<int64_t>(12, 9472), std::vector<int64_t>(12, 36 << 10), 1024, 4);
         cut(std::vector<int>(54, 512), std::vector<int64_t>(54, 8960), std::vector<int64_t>(54, 36 << 10), 1024, 4);

@@ -45,6 +45,26 @@ def test_one_width(bl, K, layout, bf16):
         assert np.array_equal(it["acc"].cpu().numpy(), c.acc), c.N
 
 
+@pytest.mark.parametrize("K", [2624, 2688, 2752, 3200, 4032, 6976, 20416])
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("bf16", [True, False])
+def test_rows_across_lines(bl, K, layout, bf16):
+    """Rows longer than 2560 that are no multiple of 64 bytes: row groups of two classes of rows out of sixteen or thirty-two, with
+    blocks that end inside a class, a residual, and products of the plain form in the same table."""
+    cases = [Case(9500 + K + n, 1, n, K) for n in (1, 2, 3, 8, 15, 17, 31, 33, 65, 130)] + [Case(9600 + K, 1, 21, 2560), Case(9601 + K, 1, 9, 6912)]
+    rng = np.random.default_rng(K)
+    items, residuals = [_item(c, layout, bf16) for c in cases], [rng.standard_normal(c.N).astype(np.float32) for c in cases]
+    for it, c, r in zip(items, cases, residuals):
+        it.update(y=torch.empty((1, c.N), dtype=torch.float32, device=DEV), residual=to_dev(r))
+        if not bf16:
+            it["scale"] = to_dev(np.array([c.scale[0]], dtype=np.float32))
+    bl.Stack(items, layout, 1, DEV).run()
+    torch.cuda.synchronize()
+    for it, c, r in zip(items, cases, residuals):
+        assert np.array_equal(it["acc"].cpu().numpy(), c.acc), c.N
+        assert np.array_equal(it["y"].cpu().numpy()[0], r + c.y[0]), c.N
+
+
 @pytest.mark.parametrize("layout", [0, 1, 2])
 def test_mixed_widths(bl, layout):
     """Widths that favour different part lengths in one table: each is read in parts that are not its best."""
