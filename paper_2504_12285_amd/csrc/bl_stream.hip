@@ -1814,12 +1814,15 @@ extern "C" bl_status bl_stack_build(const bl_decode_desc* descs, int count, int 
 
     /* Slice boundaries: a workgroup's time is its bytes, plus a fixed cost each time it enters a
      * product (activation row, pipeline refill; larger when it quantises the row itself), expressed
-     * in bytes at a workgroup's share of the stream rate. */
+     * in bytes at a workgroup's share of the stream rate.  A row group of short rows takes a wave about as long as 2 KiB
+     * (0.65 us, a load's latency over two in flight): with their bytes alone one workgroup was given thousands of them (twelve products of
+     * 64 .. 11776 columns, 45 MB: 43.1 us, 12.3 like this; 1024 and 3072 instead of 2048: 14.7 and 11.3, but tables of 640 - 1024 columns
+     * 0 - 10 % and up to 20 % slower with 3072). */
     std::vector<int> units_v((size_t)count);
     std::vector<int64_t> ucost_v((size_t)count), ecost_v((size_t)count);
     for (int i = 0; i < count; ++i) {
         units_v[(size_t)i] = items[(size_t)i].units;
-        ucost_v[(size_t)i] = unit_bytes[(size_t)i];
+        ucost_v[(size_t)i] = layout == BL_LAYOUT_KMAJOR ? unit_bytes[(size_t)i] : std::max<int64_t>(unit_bytes[(size_t)i], 2048);
         ecost_v[(size_t)i] = items[(size_t)i].xbf16 ? (int64_t)36 << 10 : (int64_t)12 << 10;
     }
     const std::vector<bl_cut_pos> wg = bl_cut_slices(units_v, ucost_v, ecost_v, blocks, 4);
