@@ -341,8 +341,8 @@ bl_status bl_quant_from_absmax(const uint16_t* X, float* absmax, int64_t M, int6
  * walked by the prefill tile kernel instead (Section 5.1: packed tiles expanded to int8 on chip
  * for the int8 matrix cores): 64 x 128 output tiles, both operands streamed through LDS, the
  * tiles of all products balanced over the resident workgroups by their k steps, one launch,
- * weights read once; plan->red_ints then holds the tile count (one token: the wave-wide loads of
- * a part of a row, or, in the k-major form, the partial sums kept in LDS).
+ * weights read once; plan->red_ints then holds the tile count (one token: which form of the
+ * kernel walks the table, or, in the k-major form, the partial sums kept in LDS).
  * Same arithmetic, bit for bit, as bl_gemv_w158a8 on each product. */
 enum { BL_STACK_MAX_COUNT = 1024, BL_STACK_MAX_TOKENS = 64 };
 typedef struct {

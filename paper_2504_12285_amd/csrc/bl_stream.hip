@@ -44,6 +44,7 @@ struct bl_stream_item {
     float* scale_out;
     float fixed_scale;        /* xbf16 only: > 0 replaces absmax/127 in the rescale */
     int N, nchunks, lp, layout, units;
+    int lgG;                  /* one token, bl_stream_dot: log2 of the lanes per row */
     int lq, mod, lead;        /* one token: row groups to a block (log2), what their shifts come from (bl_group_shift), the largest shift */
     int parts;                /* one token: the row is read in this many parts of wave-wide loads (128 bytes of a row each) */
     int qgroups;              /* 16-byte groups of the quantised row (its padded length / 16) */
@@ -191,8 +192,7 @@ __global__ __launch_bounds__(256) void bl_stream_prep(const bl_stream_prep_item*
  * core computes 32 times what is wanted and is busy a fifth of the time.
  * Thirty layers of 2560 / 6912 in one launch: 88.9 -> 85.4 us in the 2-bit form (six tenths of it the order of the
  * loads, below), 107.4 -> 89.4 in the form of five per byte; sixty of 640 / 1280 20.7 -> 15.4 and 39.0 -> 17.5.
- * (Slower, five per byte: one layer of 2560 / 6912 8.7 -> 9.7, its rows of 6912 are three dependent parts; three layers of
- * 896 / 2624 6.9 -> 7.4, the staging is most of a small table.)
+ * (Small tables and long rows stay on the vector unit: bl_stream_dot.h.)
  *
  * A product's quantised activation row lives in LDS for the workgroup (staged once per product
  * and workgroup: quantised from bf16 right there, or taken from the int8 row), as the 6-bit pieces
@@ -737,6 +737,8 @@ void bl_stream_m1(const bl_stream_item* __restrict__ items, const int2* __restri
     }
 }
 
+#include "bl_stream_dot.h"
+
 /* ---- k-major form (BL_LAYOUT_KMAJOR): skipping the weights of zero activations -----------------
  * Section 2 of the report takes squared ReLU in the feed-forward block for the sparsity it gives
  * the activations of the down projection.  Stored k-major (one row of N codes per input feature k),
@@ -1242,7 +1244,8 @@ __global__ __launch_bounds__(256) void bl_mb_finish(const bl_mb_fin_item* __rest
 #define BL_STREAM_MAX_BLOCKS 4096
 #define BL_STREAM_LDS_BYTES                                                                          \
     (layout == BL_LAYOUT_KMAJOR ? max_units * 64 + max_cols * 64 + 64                                \
-                                : (max_slots + 1) * (layout == BL_LAYOUT_TRIT5 ? BL_T5_CHUNK : BL_B2_CHUNK) + 64)
+                                : (max_slots + 1) * (dot ? (layout == BL_LAYOUT_TRIT5 ? bl_dot_stride<BL_FORM_TRIT5>() : bl_dot_stride<BL_FORM_BIT2>()) * 4 \
+                                                        : layout == BL_LAYOUT_TRIT5 ? BL_T5_CHUNK : BL_B2_CHUNK) + 64)
 static_assert(sizeof(bl_cut_pos) == sizeof(int2), "read as int2 by the kernels");
 #define BL_KM_MAX_N 3072      /* k-major form: at most three dword columns of 64 lanes per weight row (48 sums per lane) */
 
@@ -1648,6 +1651,35 @@ static row_plan plan_rows(int64_t K, int layout, bool classes) {
     r.loads = (chunks + r.lead + 7) / 8;
     return r;
 }
+/* Lanes of a row in bl_stream_dot (log2): at most BL_STREAM_LMAX loads of a lane. */
+static int dot_lanes(int64_t chunks) {
+    int lgG = 3;
+    while (((chunks + (1 << lgG) - 1) >> lgG) > BL_STREAM_LMAX) ++lgG;   /* (K is bounded: at most 6) */
+    return lgG;
+}
+/* Tables for bl_stream_dot, by the row groups of eight of the whole table and the loads of one.  With few of them a workgroup stages
+ * its row and multiplies one or two row groups, and a long row is one wave's serial chain on the matrix cores.  Measured over
+ * 2150 tables (one product of 64 .. 50000 rows x 64 .. 20480, 1 .. 70 layers, mixed sizes), dot / matrix cores:
+ * 2-bit: rows of 6 loads (K > 2560) and more under 600 row groups .53 - .98 (1024 x 14336 5.6 / 9.2 us, 256 x 4096 3.9 / 4.5), 600 - 900
+ * 1.05 - 1.1; of 30 loads up to 1400 .89 - 1.03; shorter rows 1.02 - 1.15.
+ * Five per byte, tables of one width: rows of 3 - 5 loads under 3500 row groups .92 - 1.0, above 1.0 - 1.2; of 6 and more, under 600 or 75 per load
+ * .43 - .98 (2048 x 20480 6.5 / 13.1), above 1.05 - 1.2; shorter rows 0.95 - 1.05, larger tables up to 2.3.  Of several widths under 5000
+ * .81 - 1.03 (one layer of 2560 / 6912 9.7 / 10.3, of 4096 / 11008 15.5 / 17.9), above 1.0 - 1.35.  K > 20400: an image of which four
+ * fit no compute unit (32768 x 20480 34 / 40). */
+static bool table_dot(const bl_decode_desc* descs, int count, int layout) {
+    int64_t groups = 0, loads = 0, longest = 0;
+    for (int i = 0; i < count; ++i) {
+        const int64_t g = (descs[i].N + 7) / 8, l = plan_rows(descs[i].K, layout, false).loads;
+        groups += g;
+        loads += g * l;
+        longest = std::max(longest, l);
+    }
+    if (layout != BL_LAYOUT_TRIT5) return loads >= 6 * groups && (groups < 600 || (loads >= 30 * groups && groups < 1400));
+    if (longest * 8 > 255) return true;
+    if (loads < 3 * groups) return false;
+    if (2 * longest * groups >= 3 * loads) return groups < 5000;
+    return loads < 6 * groups ? groups < 3500 : groups < 600 || groups * groups < 75 * loads;
+}
 /* Wave-wide loads of a part (3, 4 or 5) for a table of one-token products: the least cost over the table,
  * in quarters of a load that is multiplied; an idle slot of a row's last part is loaded (a cache hit) but not
  * multiplied, and a part costs about half a load besides. */
@@ -1667,7 +1699,7 @@ static int part_loads(const bl_decode_desc* descs, int count, int layout, bool c
     }
     return best;
 }
-/* The kernel of a table: `form` = loads of a part, + BL_STREAM_CLASSES where row groups of classes occur. */
+/* The kernel of a table: `form` = 0 bl_stream_dot; otherwise loads of a part, + BL_STREAM_CLASSES where row groups of classes occur. */
 #define BL_STREAM_CLASSES 8
 template <int FORM, bool CLASSES>
 static const void* stream_kernel_lp(int lp) {
@@ -1676,6 +1708,7 @@ static const void* stream_kernel_lp(int lp) {
 }
 static const void* stream_kernel(int layout, int form) {
     if (layout == BL_LAYOUT_KMAJOR) return (const void*)bl_stream_m1_km;
+    if (form == 0) return layout == BL_LAYOUT_TRIT5 ? (const void*)bl_stream_dot<BL_FORM_TRIT5> : (const void*)bl_stream_dot<BL_FORM_BIT2>;
     if (layout == BL_LAYOUT_TRIT5) return stream_kernel_lp<BL_FORM_TRIT5, false>(form);
     return form & BL_STREAM_CLASSES ? stream_kernel_lp<BL_FORM_BIT2, true>(form & ~BL_STREAM_CLASSES) : stream_kernel_lp<BL_FORM_BIT2, false>(form);
 }
@@ -1695,8 +1728,9 @@ extern "C" bl_status bl_stack_build(const bl_decode_desc* descs, int count, int 
     }
     const bl_stream_layout L = stream_layout(count, q_bytes, acc_bytes);
     uint8_t* const dev_base = (uint8_t*)table;
-    const bool classes = layout != BL_LAYOUT_KMAJOR && table_classes(descs, count, layout);
-    const int lp = layout == BL_LAYOUT_KMAJOR ? 0 : part_loads(descs, count, layout, classes);
+    const bool dot = layout != BL_LAYOUT_KMAJOR && table_dot(descs, count, layout);
+    const bool classes = layout != BL_LAYOUT_KMAJOR && !dot && table_classes(descs, count, layout);
+    const int lp = layout == BL_LAYOUT_KMAJOR || dot ? 0 : part_loads(descs, count, layout, classes);
     std::vector<bl_stream_item> items((size_t)count);
     std::vector<bl_stream_prep_item> preps;
     int inline_count = 0, max_slots = 0, max_units = 0, max_cols = 0;
@@ -1723,7 +1757,13 @@ extern "C" bl_status bl_stack_build(const bl_decode_desc* descs, int count, int 
         it.qgroups = (int)(Kp / 16);
         it.layout = layout;
         int R = 8;                                           /* weight rows of a unit */
-        if (layout != BL_LAYOUT_KMAJOR) {
+        if (dot) {
+            it.lgG = dot_lanes(it.nchunks);
+            it.lp = (it.nchunks + (1 << it.lgG) - 1) >> it.lgG;
+            R = 64 >> it.lgG;
+            it.units = (it.N + R - 1) / R;
+            if (it.nchunks > max_slots) max_slots = it.nchunks;
+        } else if (layout != BL_LAYOUT_KMAJOR) {
             const row_plan rp = plan_rows(d.K, layout, classes);
             it.lq = rp.lq;
             it.mod = rp.mod;
@@ -1805,7 +1845,7 @@ extern "C" bl_status bl_stack_build(const bl_decode_desc* descs, int count, int 
         cus < 1 || per_cu < 1)
         return BL_ERR_HIP;
     /* (four workgroups per compute unit also where a fifth would fit: 72 products of 13824 x 2048 84 us against 88) */
-    if (layout != BL_LAYOUT_KMAJOR && per_cu > 4) per_cu = 4;
+    if (layout != BL_LAYOUT_KMAJOR && !dot && per_cu > 4) per_cu = 4;
     int64_t blocks64 = (int64_t)cus * per_cu;
     if (blocks64 > (total_units + 3) / 4) blocks64 = (total_units + 3) / 4;
     if (blocks64 > BL_STREAM_MAX_BLOCKS) blocks64 = BL_STREAM_MAX_BLOCKS;
@@ -1853,6 +1893,11 @@ extern "C" bl_status bl_stack_build(const bl_decode_desc* descs, int count, int 
     plan->tokens = 1;
     plan->entries = count;
     return BL_OK;
+}
+
+static bool stream_form_ok(int layout, int form) {
+    const int lp = form & ~BL_STREAM_CLASSES;
+    return form == 0 || (lp >= BL_STREAM_LMIN && lp <= BL_STREAM_LMAX && (lp == form || layout != BL_LAYOUT_TRIT5));
 }
 
 extern "C" bl_status bl_stack_run(void* table, const bl_stack_plan* plan, bl_stream s) {
@@ -1903,8 +1948,7 @@ extern "C" bl_status bl_stack_run(void* table, const bl_stack_plan* plan, bl_str
         plan->lds_bytes > 64 * 1024 || plan->lds_bytes % 16 ||
         plan->layout < 0 || plan->layout > BL_LAYOUT_KMAJOR || plan->red_ints < 0 || plan->red_ints > BL_KM_MAX_N ||
         (plan->layout == BL_LAYOUT_KMAJOR ? plan->red_ints < 64 || plan->lds_bytes < 64 + 64 + plan->red_ints * 4
-                                          : plan->red_ints & ~(BL_STREAM_CLASSES | 7) || (plan->red_ints & 7) < BL_STREAM_LMIN ||
-                                                (plan->red_ints & 7) > BL_STREAM_LMAX || (plan->layout == BL_LAYOUT_TRIT5 && plan->red_ints > 7)))
+                                          : !stream_form_ok(plan->layout, plan->red_ints)))
         return BL_ERR_VALUE;
     const bl_stream_layout L = stream_layout(plan->count, 0);
     if (plan->wg_offset != (int64_t)L.wg_off || plan->prep_offset != (int64_t)L.prep_off) return BL_ERR_VALUE;
