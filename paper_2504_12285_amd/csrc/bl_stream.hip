@@ -1623,8 +1623,9 @@ static int64_t row_chunks(int64_t K, int layout) {
  * (bl_stream_index.h), where they are longer than 2560 weights, in the 2-bit form.  A load whose eight pieces each lie across
  * two lines asks for sixteen: 250 MB of K = 3200 53.6 -> 46.8 us, 8768 57.8 -> 48.8, 19904 64 -> 57; up to 2560 the loop does not wait for
  * it (K = 2240 48.6 / 47.6, 1472 48.8 / 50.0; five per byte K = 4000 64 / 64, and 3440 62 / 71 for the extra load of some rows).
- * A table takes the kernel for it where such products are a quarter of its bytes and 6 MiB: 10240 x 3200 5.16 / 4.93, 6144 x 3200
- * 4.67 / 4.90, 1024 x 3200 4.54 / 4.76 (more zeros to stage). */
+ * A table takes the kernel for it where such products are an eighth of its bytes (8 layers of 4096 / 9408, where they are 24 %, 68.0
+ * us without it, 55.9 with it; the other products lose up to 1 %) and 6 MiB: 10240 x 3200 5.16 / 4.93, 6144 x 3200 4.67 / 4.90, 1024 x 3200
+ * 4.54 / 4.76 (more zeros to stage). */
 static bool wants_classes(int64_t K, int layout) {
     const int64_t chunks = row_chunks(K, layout);
     return (layout == BL_LAYOUT_ROWMAJOR || layout == BL_LAYOUT_K16) && chunks > 40 && chunks % 4 != 0;
@@ -1636,7 +1637,7 @@ static bool table_classes(const bl_decode_desc* descs, int count, int layout) {
         all += bytes;
         if (wants_classes(descs[i].K, layout)) such += bytes;
     }
-    return such >= (int64_t)6 << 20 && such >= all / 4;
+    return such >= (int64_t)6 << 20 && such >= all / 8;
 }
 /* How the rows of a product are read: lq, mod and lead of its bl_stream_item, and the wave-wide loads of a row group. */
 struct row_plan {
@@ -1663,7 +1664,7 @@ static int dot_lanes(int64_t chunks) {
  * 2-bit: rows of 6 loads (K > 2560) and more under 600 row groups .53 - .98 (1024 x 14336 5.6 / 9.2 us, 256 x 4096 3.9 / 4.5), 600 - 900
  * 1.05 - 1.1; of 30 loads up to 1400 .89 - 1.03; shorter rows 1.02 - 1.15.
  * Five per byte, tables of one width: rows of 3 - 5 loads under 3500 row groups .92 - 1.0, above 1.0 - 1.2; of 6 and more, under 600 or 75 per load
- * .43 - .98 (2048 x 20480 6.5 / 13.1), above 1.05 - 1.2; shorter rows 0.95 - 1.05, larger tables up to 2.3.  Of several widths under 5000
+ * .43 - .98 (2048 x 20480 6.5 / 13.1), above 1.05 - 1.2; shorter rows under 200 .95 - 1.01, larger tables up to 2.3.  Of several widths under 5000
  * .81 - 1.03 (one layer of 2560 / 6912 9.7 / 10.3, of 4096 / 11008 15.5 / 17.9), above 1.0 - 1.35.  K > 20400: an image of which four
  * fit no compute unit (32768 x 20480 34 / 40). */
 static bool table_dot(const bl_decode_desc* descs, int count, int layout) {
@@ -1676,7 +1677,7 @@ static bool table_dot(const bl_decode_desc* descs, int count, int layout) {
     }
     if (layout != BL_LAYOUT_TRIT5) return loads >= 6 * groups && (groups < 600 || (loads >= 30 * groups && groups < 1400));
     if (longest * 8 > 255) return true;
-    if (loads < 3 * groups) return false;
+    if (loads < 3 * groups) return groups < 200;
     if (2 * longest * groups >= 3 * loads) return groups < 5000;
     return loads < 6 * groups ? groups < 3500 : groups < 600 || groups * groups < 75 * loads;
 }
@@ -1863,6 +1864,7 @@ extern "C" bl_status bl_stack_build(const bl_decode_desc* descs, int count, int 
     for (int i = 0; i < count; ++i) {
         units_v[(size_t)i] = items[(size_t)i].units;
         ucost_v[(size_t)i] = layout == BL_LAYOUT_KMAJOR ? unit_bytes[(size_t)i] : std::max<int64_t>(unit_bytes[(size_t)i], 2048);
+        if (dot && items[(size_t)i].lp != 5) ucost_v[(size_t)i] = ucost_v[(size_t)i] * 26 / 25;   /* (four slots of a lane stream 4 % slower than five) */
         ecost_v[(size_t)i] = items[(size_t)i].xbf16 ? (int64_t)36 << 10 : (int64_t)12 << 10;
     }
     const std::vector<bl_cut_pos> wg = bl_cut_slices(units_v, ucost_v, ecost_v, blocks, 4);
