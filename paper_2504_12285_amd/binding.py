@@ -181,6 +181,8 @@ def _first_native():
     _get_torch()
     try:
         from . import _bl_torch
+        if _bl_torch.__doc__ != "built for torch %s" % _build.torch_version():
+            raise ImportError("it is " + _bl_torch.__doc__)
     except ImportError as e:
         warnings.warn("the binding's small calls run in Python (7 - 11 us each, 3 - 4 in native code): _bl_torch is not "
                       "built for this interpreter and torch (%s)" % e, RuntimeWarning, stacklevel=3)

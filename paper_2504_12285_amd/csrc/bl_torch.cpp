@@ -207,7 +207,8 @@ PyMethodDef methods[] = {{"quant", (PyCFunction)(void (*)(void))quant, METH_FAST
                          {"bind", bind, METH_VARARGS, nullptr},
                          {"current_stream", current_stream, METH_NOARGS, nullptr},
                          {nullptr, nullptr, 0, nullptr}};
-PyModuleDef module = {PyModuleDef_HEAD_INIT, "_bl_torch", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+/* (the doc string is what tells a build against another torch) */
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_bl_torch", "built for torch " BL_TORCH_VERSION, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace
 
