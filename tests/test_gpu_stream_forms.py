@@ -68,7 +68,7 @@ def test_both_forms(bl, K, layout, bf16):
     items = [_item(c, layout, bf16, r) for c, r in zip(cases, residuals)]
     for matrix in (False, True):
         form, out = _run(bl, items, layout, matrix)
-        vector = not matrix and (K > 2560 if layout != 2 else K >= 1920)
+        vector = not matrix and (K > 2560 or layout == 2)
         assert (form == 0) == vector or (layout == 2 and K > 20400), form
         for (acc, y), c, r in zip(out, cases, residuals):
             assert np.array_equal(acc, c.acc), (matrix, c.N)
