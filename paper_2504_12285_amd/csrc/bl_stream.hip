@@ -1665,8 +1665,8 @@ static int dot_lanes(int64_t chunks) {
  * 1.05 - 1.1; of 30 loads up to 1400 .89 - 1.03; shorter rows 1.02 - 1.15.
  * Five per byte, tables of one width: rows of 3 - 5 loads under 3500 row groups .92 - 1.0, above 1.0 - 1.2; of 6 and more, under 600 or 75 per load
  * .43 - .98 (2048 x 20480 6.5 / 13.1), above 1.05 - 1.2; shorter rows under 200 .95 - 1.01, larger tables up to 2.3.  Of several widths under 5000
- * .81 - 1.03 (one layer of 2560 / 6912 9.7 / 10.3, of 4096 / 11008 15.5 / 17.9), above 1.0 - 1.35.  K > 20400: an image of which four
- * fit no compute unit (32768 x 20480 34 / 40). */
+ * .81 - 1.03 (one layer of 2560 / 6912 9.7 / 10.3, of 4096 / 11008 15.5 / 17.9), above 1.0 - 1.35.  K > 19200: an image of which four
+ * fit no compute unit (32768 x 20480 34 / 40, 32768 x 19840 33 / 38, twenty of 2560 x 19840 55 / 61). */
 static bool table_dot(const bl_decode_desc* descs, int count, int layout) {
     int64_t groups = 0, loads = 0, longest = 0;
     for (int i = 0; i < count; ++i) {
@@ -1676,7 +1676,7 @@ static bool table_dot(const bl_decode_desc* descs, int count, int layout) {
         longest = std::max(longest, l);
     }
     if (layout != BL_LAYOUT_TRIT5) return loads >= 6 * groups && (groups < 600 || (loads >= 30 * groups && groups < 1400));
-    if (longest * 8 > 255) return true;
+    if (longest > 30) return true;
     if (loads < 3 * groups) return groups < 200;
     if (2 * longest * groups >= 3 * loads) return groups < 5000;
     return loads < 6 * groups ? groups < 3500 : groups < 600 || groups * groups < 75 * loads;

@@ -58,7 +58,7 @@ def _item(c, layout, bf16, residual=None, q=None):
     return it
 
 
-@pytest.mark.parametrize("K", [64, 1280, 2560, 2624, 3200, 4032, 5120, 6912, 8448, 13760, 20480])
+@pytest.mark.parametrize("K", [64, 1280, 2560, 2624, 3200, 4032, 5120, 6912, 8448, 13760, 19200, 19264, 20480])
 @pytest.mark.parametrize("layout", [0, 1, 2])
 @pytest.mark.parametrize("bf16", [True, False])
 def test_both_forms(bl, K, layout, bf16):
@@ -69,7 +69,7 @@ def test_both_forms(bl, K, layout, bf16):
     for matrix in (False, True):
         form, out = _run(bl, items, layout, matrix)
         vector = not matrix and (K > 2560 or layout == 2)
-        assert (form == 0) == vector or (layout == 2 and K > 20400), form
+        assert (form == 0) == vector or (layout == 2 and K > 19200), form
         for (acc, y), c, r in zip(out, cases, residuals):
             assert np.array_equal(acc, c.acc), (matrix, c.N)
             assert np.array_equal(y, c.y if r is None else r + c.y), (matrix, c.N)
@@ -78,9 +78,11 @@ def test_both_forms(bl, K, layout, bf16):
 @pytest.mark.parametrize("value", [-128, -1, 127])
 @pytest.mark.parametrize("layout", [0, 1, 2])
 def test_extreme_sums(bl, value, layout):
-    c = Case(8800, 1, 9, 20352, full=False)
-    c.Wt = np.tile(np.array([1, -1, 0], dtype=np.int8), 3)[:, None] * np.ones((9, 20352), dtype=np.int8)
-    q = np.full((1, 20352), value, dtype=np.int8)
+    # The longest rows of which the layout has both forms.
+    K = 19200 if layout == 2 else 20352
+    c = Case(8800, 1, 9, K, full=False)
+    c.Wt = np.tile(np.array([1, -1, 0], dtype=np.int8), 3)[:, None] * np.ones((9, K), dtype=np.int8)
+    q = np.full((1, K), value, dtype=np.int8)
     it = _item(c, layout, False, q=q)
     for matrix in (False, True):
         assert np.array_equal(_run(bl, [it], layout, matrix)[1][0][0], q.astype(np.int32) @ c.Wt.T.astype(np.int32)), matrix
