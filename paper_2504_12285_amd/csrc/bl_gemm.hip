@@ -496,7 +496,7 @@ __global__ __launch_bounds__(WM * WN * 64, (DEFER && BM * BN >= 128 * 128 ? 2 : 
              * wait for memory stands between its stores; `cut`: every other one (and the residual in 128-row tiles, where both
              * forms together spill 55 registers: 4096 x 2560 -> 2560 48.9 us, 40.5 with `cut` alone).  With the
              * atomics of eight rows in one instruction (before: two rows; the epilogue waited for each), at 2560 -> 13824 with the
-             * gate: 128 tokens 61 -> 23 us, 512 54 -> 25, 2048 78 -> 69, 4096 146 -> 135. */
+             * gate and the tiles of launch_fused: 128 tokens 60 -> 20 us, 512 53 -> 25, 2048 82 -> 73, 4096 151 -> 138. */
             const int NOUT = EPI == 2 ? N / 2 : N, col0 = EPI == 2 ? tn * (BN / 2) + wn0 / 2 + l32 : n0 + wn0 + l32;
             const int mlast = M - 1 - m0;
             auto finish = [&](auto cut_t) __attribute__((always_inline)) {
@@ -1088,7 +1088,9 @@ __global__ __launch_bounds__(256) void bl_rowsum_kernel(const int8_t* __restrict
  * flight.  A lone workgroup's k step waits for its loads (0.47 us, with four stages 0.32; the matrix cores work 0.12 of it):
  * 512 x 2560 -> 3840 15.9 / 13.5 us, 1024 x 4096 -> 2048 21.0 / 17.4, 1000 x 6912 -> 2000 30.2 / 24.3, 512 x 2304 -> 3840
  * 14.3 / 12.9, 256 x 2304 -> 8000 13.5 / 12.8, but 256 x 2176 -> 8000 12.4 / 12.5, 256 x 2048 -> 8000 11.6 / 12.1 and 400 x 1000 ->
- * 4000 9.3 / 9.6.  From two workgroups per unit on they cover each other: 777 x 2999 -> 5003 24.8 / 26.9.
+ * 4000 9.3 / 9.6.  That is with activations that come from beyond the L2, as a quantiser or another product in front leaves them;
+ * the same ones multiplied again and again wait less, and four stages take 1.00 - 1.04 of the time of two.
+ * From two workgroups per unit on they cover each other: 777 x 2999 -> 5003 24.8 / 26.9.
  * fp32 output alone: the stores of a tile travel during the workgroup's next tile (measured at M = 2048 /
  * 8192: the 13824-wide shape 77 - 80 us against 86 - 90, 297 - 308 against 317 - 327; the 64 x 128 kernel
  * with deferred stores loses: it has under one tile per workgroup on the shapes it serves).

@@ -187,8 +187,9 @@ __global__ __launch_bounds__(PACK_THREADS) void bl_pack_flat(const bl_v4f* __res
  * normally distributed weights) and adds up |W| on its way; bl_pack_settle, with beta, takes up the words that hold a 3, from
  * W.  Where beta is not between the ends (also NaN, infinite) it packs the whole matrix again.  Exact for every
  * input: the sample decides the time alone.  Bound by the one read of W, beside the write of the codes: 13824 x 2560 53.9 ->
- * 38.6 us (sample 4, guess 25, settle 9 with their launches), 28672 x 8192 352 -> 218; with |W| heavy-tailed (0.1 % of it
- * fiftyfold) 54.0 -> 41.1, every weight undecided 53.7 -> 61, beta NaN 52.8 -> 59. */
+ * 38.6 us (sample 4, guess 25, settle 9 with their launches), 28672 x 8192 352 -> 215; with |W| heavy-tailed (0.1 % of it
+ * fiftyfold) 54.0 -> 41.1, every weight undecided 53.7 -> 61, beta NaN 52.8 -> 59 (smaller matrices of such
+ * weights up to 1.3 times: 5120 x 2560). */
 typedef uint32_t bl_v4w __attribute__((ext_vector_type(4)));
 #define PACK_SAMPLE_BLOCKS 256
 #define PACK_SAMPLE_PIECES 65536                /* of 16 weights: a lane of every quad reads four */

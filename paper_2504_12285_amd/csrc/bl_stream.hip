@@ -189,7 +189,7 @@ __global__ __launch_bounds__(256) void bl_stream_prep(const bl_stream_prep_item*
  * activations (chunk u's) and the two k groups hold different rows, so A has a row for each u
  * (8), k group (2) and piece (2), 32 together, zero in the other k group; of the 32 x 32 results
  * the one with the column's own u counts, and a row's eight chunks are added at the end.  The matrix
- * core computes 32 times what is wanted and is busy a fifth of the time.
+ * core computes 32 times what is wanted and is busy 15 % of the time (five per byte: 19 %).
  * Thirty layers of 2560 / 6912 in one launch: 88.9 -> 85.4 us in the 2-bit form (six tenths of it the order of the
  * loads, below), 107.4 -> 89.4 in the form of five per byte; sixty of 640 / 1280 20.7 -> 15.4 and 39.0 -> 17.5.
  * (Small tables and long rows stay on the vector unit: bl_stream_dot.h.)
