@@ -7,6 +7,7 @@
  * rowsum[m] = sum_k q[m][k] (exact int32 identity), then rescales.
  */
 #include "bl_device.h"
+#include "bl_gemm_pipe.h"
 #include "bl_host.h"
 
 #include <atomic>
@@ -610,6 +611,28 @@ struct bl_tile256_launch {
     }
 };
 
+/* Order of the tiles (see bl_gemm_pipe).  Rows of activations per band: at most ~1.5 MB of int8 (measured, medians of six
+ * interleaved rounds at M = 2048: +7 % on the 13824-wide shape against bands of all rows, equal on the others).  A rectangle
+ * per XCD unless its size means more tiles for the busiest of an XCD's 32 compute units than an even share
+ * does: 2140 x 3840 -> 13458 (17 row tiles, bands of 3: two XCDs idle) 148 / 122 us, 1100 x 2560 -> 7000 (70
+ * tiles against 62) 36 / 27.5; 777 x 2999 -> 5003 with its quantiser (70 and 60 tiles against 65: three on
+ * the busiest unit either way) 28.1 / 30.6 (tiles of 128 x 128 and 64 x 128). */
+struct bl_tile_order {
+    int gm, band, vgrid;
+};
+static bl_tile_order tile_order(int tiles_m, int tiles_n, int BM, int K) {
+    int gm = 1;
+    while (gm < 8 && (int64_t)((tiles_m + gm - 1) / gm) * BM * K > (3 << 19)) gm *= 2;
+    int band = (tiles_m + gm - 1) / gm;
+    const int rect = band * ((tiles_n + 8 / gm - 1) / (8 / gm)), share = (tiles_m * tiles_n + 7) / 8;
+    if ((rect + 31) / 32 <= (share + 31) / 32) return {gm, band, 8 * rect};
+    int64_t most = (3 << 19) / ((int64_t)BM * K);
+    if (most < 1) most = 1;
+    const int bands = (int)((tiles_m + most - 1) / most);
+    band = (tiles_m + bands - 1) / bands;
+    return {0, band, 8 * share};
+}
+
 template <int BM, int BN, int STAGES, int WM, int WN, int EPI = 0, bool DEFER = false, bool HALF = false, int LAYOUT = 1>
 static bl_status launch_tile256_t(const uint8_t* packed, const float* beta, const int8_t* q, const float* scale,
                                   const int32_t* rowsum, int M, int N, int K, const float* residual,
@@ -621,25 +644,8 @@ static bl_status launch_tile256_t(const uint8_t* packed, const float* beta, cons
     /* the gate epilogue's tile holds 64 gate rows and the 64 matching up rows: N/2 / 64 column tiles */
     const int tiles_m = (M + G3_BM - 1) / G3_BM, tiles_n = EPI == 2 ? (N / 2 + BN / 2 - 1) / (BN / 2) : (N + BN - 1) / BN;
     if ((int64_t)tiles_m * tiles_n > ((int64_t)1 << 30)) return BL_ERR_SHAPE;   /* (outputs beyond 2^43 values) */
-    /* rows of activations per band: at most ~1.5 MB of int8 (measured, medians of six interleaved rounds at
-     * M = 2048: +7 % on the 13824-wide shape against bands of all rows, equal on the others).  A rectangle
-     * per XCD unless its size means more tiles for the busiest of an XCD's 32 compute units than an even share
-     * does: 2140 x 3840 -> 13458 (17 row tiles, bands of 3: two XCDs idle) 148 / 122 us, 1100 x 2560 -> 7000 (70
-     * tiles against 62) 36 / 27.5; 777 x 2999 -> 5003 with its quantiser (70 and 60 tiles against 65: three on
-     * the busiest unit either way) 28.1 / 30.6. */
-    int gm = 1;
-    while (gm < 8 && (int64_t)((tiles_m + gm - 1) / gm) * BM * K > (3 << 19)) gm *= 2;
-    int band = (tiles_m + gm - 1) / gm;
-    const int rect = band * ((tiles_n + 8 / gm - 1) / (8 / gm)), share = (tiles_m * tiles_n + 7) / 8;
-    int vgrid = 8 * rect;
-    if ((rect + 31) / 32 > (share + 31) / 32) {
-        int64_t most = (3 << 19) / ((int64_t)BM * K);
-        if (most < 1) most = 1;
-        const int bands = (int)((tiles_m + most - 1) / most);
-        band = (tiles_m + bands - 1) / bands;
-        gm = 0;
-        vgrid = 8 * share;
-    }
+    const bl_tile_order o = tile_order(tiles_m, tiles_n, BM, K);
+    const int gm = o.gm, band = o.band, vgrid = o.vgrid;
     if (blocks > vgrid) blocks = vgrid;
     bl_gemm_tile256<BM, BN, STAGES, WM, WN, EPI, false, DEFER, HALF, LAYOUT><<<blocks, WM * WN * 64, L::lds, st>>>(
         packed, q, rowsum, beta, scale, M, N, K, tiles_m, tiles_n, gm, band, vgrid, residual, acc, y, ep.xb, ep.absmax, (long long*)bl_clock_stamps(), nullptr, nullptr, 0, nullptr, nullptr);
@@ -691,24 +697,22 @@ bl_status bl_gemm_table_launch(const bl_tile_item* items, const int* tile0, int 
  * are fetched by four times as many workgroups, from the L2.
  * Same LDS layout, swizzles, half last step and layout-0 words as bl_gemm_tile256 (one wave: pieces of
  * eight activation rows and one of 32 weight rows).
- * Used up to KS_MAX_TILES tiles of 64 x 128; measured (us, 64 x 128 tiles / this kernel): 40 tiles
- * 128 x 6912 -> 2560 22.2 / 10.7, 80 tiles 256 x 2560 -> 2560 12.4 / 7.9, 128 tiles 1000 x 4096 -> 1000
- * 16.3 / 11.6, 140 tiles 400 x 6912 -> 2560 27.8 / 21.2, 160 tiles 512 x 2560 -> 2560 12.3 / 11.8, 216 tiles
- * 128 x 2560 -> 13824 12.9 / 14.3, 240 tiles 512 x 2560 -> 3840 12.7 / 13.9: there the tiles fill the chip. */
-#define KS_MAX_TILES 160
+ * Measured (us, 64 x 128 tiles of bl_gemm_pipe / this kernel): 40 tiles 128 x 6912 -> 2560 19.8 / 11.2, 80 tiles 256 x 2560 ->
+ * 2560 10.0 / 8.3, 104 tiles 800 x 7000 -> 1024 20.5 / 17.1, 160 tiles 512 x 2560 -> 2560 10.4 / 12.9: there the tiles fill the chip. */
 #define KS_STAGE (64 * G3_BK + 32 * G3_BK / 4)
 
 template <int LAYOUT>
 __global__ __launch_bounds__(256, 2) void bl_gemm_ksplit(const uint8_t* __restrict__ packed, const int8_t* __restrict__ q,
                                                          const int32_t* __restrict__ rowsum, const float* __restrict__ beta,
                                                          const float* __restrict__ scale, int M, int N, int K, int tiles_m,
-                                                         int tiles, const float* __restrict__ residual,
+                                                         int tiles, int across, const float* __restrict__ residual,
                                                          int32_t* __restrict__ acc, float* __restrict__ y,
                                                          long long* __restrict__ stamps) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];      /* [wave][stage] */
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int l32 = lane & 31, h = lane >> 5;
-    /* workgroup L runs on XCD L % 8: each XCD takes one eighth of the tiles, row tiles fastest */
+    /* workgroup L runs on XCD L % 8: each XCD takes one eighth of the tiles, row tiles fastest or (across: the tiles across N)
+     * column tiles fastest, whichever makes an XCD read less */
     const int share = (tiles + 7) >> 3, at = ((int)blockIdx.x & 7) * share + ((int)blockIdx.x >> 3);
     if (((int)blockIdx.x >> 3) >= share || at >= tiles) return;         /* the whole workgroup (never workgroup 0) */
     const bool stamp = stamps != nullptr && blockIdx.x == 0;            /* measurement hook, as in bl_gemm_tile256 */
@@ -717,7 +721,8 @@ __global__ __launch_bounds__(256, 2) void bl_gemm_ksplit(const uint8_t* __restri
         c_start = clock64();
         w_start = wall_clock64();
     }
-    const int tn = at / tiles_m, tm = at - tn * tiles_m, m0 = tm * 64, n0 = tn * 32;
+    const int along = across ? across : tiles_m, major = at / along, minor = at - major * along;
+    const int m0 = (across ? major : minor) * 64, n0 = (across ? minor : major) * 32;
     const int steps = (K + G3_BK - 1) / G3_BK;
     const bool half = (K & 64) != 0;
 
@@ -824,6 +829,25 @@ __global__ __launch_bounds__(256, 2) void bl_gemm_ksplit(const uint8_t* __restri
     }
 }
 
+/* The order of the tiles and what an XCD reads: bytes per k of its share, 64 to a row tile, 8 to a column tile; a share in
+ * one order is whole lines in the other.  3931 x 4480 -> 256 (62 row tiles and 8 column tiles; row tiles fastest, every XCD reads
+ * all activations) 24.5 us, columns fastest 13.1; 2528 x 1877 -> 320 10.7 / 7.7. */
+struct bl_ksplit_order {
+    bool across;
+    int64_t bytes;
+};
+static bl_ksplit_order ksplit_order(int m, int n) {
+    const int64_t tm = (m + 63) / 64, tn = (n + 31) / 32, share = (tm * tn + 7) / 8;
+    const int64_t down = (share < tm ? share : tm) * 64 + (share + tm - 1) / tm * 8, over = (share < tn ? share : tn) * 8 + (share + tn - 1) / tn * 64;
+    return {over < down, over < down ? over : down};
+}
+/* Its time (us), for the tile choice below: rounds of 512 workgroups, and what an XCD reads. */
+static float ksplit_us(int m, int n, int k) {
+    const int64_t tiles = (int64_t)((m + 63) / 64) * ((n + 31) / 32);
+    const float rounds = (float)((tiles + 511) / 512), steps = (float)((k + G3_BK - 1) / G3_BK);
+    return 1.40f + rounds * (steps * .0875f + 2.21f) + 2.33e-6f * (float)ksplit_order(m, n).bytes * (float)k + 1.13e-6f * (float)m * (float)n;
+}
+
 template <int LAYOUT>
 static bl_status launch_ksplit(const uint8_t* packed, const float* beta, const int8_t* q, const float* scale,
                                const int32_t* rowsum, int m, int n, int k, const float* residual, int32_t* acc, float* y,
@@ -835,225 +859,43 @@ static bl_status launch_ksplit(const uint8_t* packed, const float* beta, const i
         if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) return BL_ERR_HIP;
         attr_set.store(true, std::memory_order_release);
     }
-    const int tiles_m = (m + 63) / 64, tiles = tiles_m * ((n + 31) / 32);
-    kern<<<(tiles + 7) / 8 * 8, 256, lds, st>>>(packed, q, rowsum, beta, scale, m, n, k, tiles_m, tiles, residual, acc, y,
+    const int tiles_m = (m + 63) / 64, tiles_n = (n + 31) / 32, tiles = tiles_m * tiles_n, share = (tiles + 7) / 8;
+    /* bytes per k that an XCD reads: 64 to a row tile, 8 to a column tile; a share of one order is whole lines of the other */
+    const int64_t down = (int64_t)(share < tiles_m ? share : tiles_m) * 64 + (int64_t)((share + tiles_m - 1) / tiles_m) * 8;
+    const int64_t over = (int64_t)(share < tiles_n ? share : tiles_n) * 8 + (int64_t)((share + tiles_n - 1) / tiles_n) * 64;
+    kern<<<share * 8, 256, lds, st>>>(packed, q, rowsum, beta, scale, m, n, k, tiles_m, tiles, over < down ? tiles_n : 0, residual, acc, y,
                                                  (long long*)bl_clock_stamps());
     return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
 }
 
-#define GEMM_THREADS 256
-#define GEMM_PAD 16   /* bytes of padding per activation row in LDS (bank spread) */
-
-/* ---- register-staged kernel: launches bound by their output --------------------------------
- * One workgroup per tile and plain stores: where the k loop is short against the output, or rows of the
- * output do not start on whole cache lines, it writes faster than the tile kernels above (which are
- * faster everywhere else; the rule is staged_is_faster below).
- * Block tile BM x BN, k step BK (64 or 128), four waves arranged WGM x WGN.
- * LDS is double buffered: while the matrix cores work on buffer b, the next
- * k step travels global -> registers -> buffer 1-b; one barrier per k step.
- *   A buffer: BM rows x (BK + pad) int8 activations.
- *   W buffer: BN rows x (BK/16 + 1) packed words (16 weights each).
- * Operand mapping of v_mfma_i32_32x32x32_i8: lane l supplies 16 consecutive k
- * (offset 16*(l/32)) of row l%32 for both operands; a packed word expands to
- * exactly those 16 int8 (layout 1), so one ds_read_b32 feeds one B operand. */
-template <int BM, int BN, int BK, int WGM, int LAYOUT>
-__global__ __launch_bounds__(GEMM_THREADS) void bl_gemm_mfma(const uint8_t* __restrict__ packed,
-                                                              const int8_t* __restrict__ q,
-                                                              const int32_t* __restrict__ rowsum,
-                                                              const float* __restrict__ beta,
-                                                              const float* __restrict__ scale, int M, int N, int K,
-                                                              int32_t* __restrict__ acc, float* __restrict__ y,
-                                                              long long* __restrict__ stamps) {
-    constexpr int WGN = 4 / WGM;
-    constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NI = WN / 32;
-    constexpr int KS = BK / 32;                       /* MFMA k sub-steps per k step  */
-    constexpr int A_STRIDE = BK + GEMM_PAD;           /* bytes                        */
-    constexpr int W_WORDS = BK / 16;                  /* packed words per row, k step */
-    constexpr int W_STRIDE = W_WORDS + 1;             /* dwords                       */
-    constexpr int A_UPR = BK / 16;                    /* 16-byte units per A row      */
-    constexpr int A_UNITS = BM * A_UPR / GEMM_THREADS;
-    constexpr int W_UPR = BK / 64;                    /* 16-byte units per W row      */
-    constexpr int W_UNITS = (BN * W_UPR + GEMM_THREADS - 1) / GEMM_THREADS;
-    static_assert(BM * A_UPR % GEMM_THREADS == 0, "A tile must split evenly");
-    static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile must be a multiple of 32");
-
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    constexpr int A_BYTES = BM * A_STRIDE;
-    constexpr int W_BYTES = BN * W_STRIDE * 4;
-    auto As = [&](int b) { return smem + b * A_BYTES; };
-    auto Ws = [&](int b) { return (uint32_t*)(smem + 2 * A_BYTES + b * W_BYTES); };
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;
-    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-    const int l32 = lane & 31, h = lane >> 5;
-    const int kb = K / 4;
-    const bool stamp = stamps != nullptr && blockIdx.x == 0 && blockIdx.y == 0;   /* measurement hook, as in bl_gemm_tile256 */
-    long long c_start = 0, w_start = 0;
-    if (stamp) {
-        c_start = clock64();
-        w_start = wall_clock64();
+/* Launch of bl_gemm_pipe: a persistent grid of the workgroups that are resident at once. */
+template <int MI, int NI, int WM, int WN, int S, int OCC, int EPI, int LAYOUT>
+static bl_status launch_pipe(const uint8_t* packed, const float* beta, const int8_t* q, const float* scale, const int32_t* rowsum,
+                             int M, int N, int K, const float* residual, int32_t* acc, float* y, hipStream_t st,
+                             bl_epi_args ep = bl_epi_args{nullptr, nullptr}) {
+    using G = bl_pipe_geom<MI, NI, WM, WN, S>;
+    const auto kern = bl_gemm_pipe<MI, NI, WM, WN, S, OCC, EPI, LAYOUT>;
+    static std::atomic<int> cached{0};
+    int blocks = cached.load(std::memory_order_acquire);
+    if (blocks == 0) {
+        int dev = 0, cus = 0, per_cu = 0;
+        if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS) != hipSuccess ||
+            hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kern, G::THREADS, G::LDS) != hipSuccess ||
+            cus < 1 || per_cu < 1)
+            return BL_ERR_HIP;
+        blocks = cus * per_cu < 8 ? 8 : cus * per_cu / 8 * 8;      /* (a multiple of 8 keeps a workgroup on its XCD's share) */
+        cached.store(blocks, std::memory_order_release);
     }
-
-    bl_v16i C[MI][NI];
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) C[mi][ni][v] = 0;
-
-    uint4 areg[A_UNITS];
-    uint4 wreg[W_UNITS];
-    const uint8_t* aptr[A_UNITS];
-    const uint8_t* wptr[W_UNITS];
-#pragma unroll
-    for (int i = 0; i < A_UNITS; ++i) {
-        const int u = tid + i * GEMM_THREADS, row = u / A_UPR, c = u % A_UPR;
-        int m = m0 + row;
-        if (m >= M) m = M - 1;
-        aptr[i] = (const uint8_t*)q + (int64_t)m * K + c * 16;
-    }
-#pragma unroll
-    for (int i = 0; i < W_UNITS; ++i) {
-        const int u = tid + i * GEMM_THREADS, row = u / W_UPR, c = u % W_UPR;
-        int n = n0 + row;
-        if (n >= N) n = N - 1;
-        wptr[i] = packed + (int64_t)n * kb + c * 16;
-    }
-
-    auto load_tiles = [&](int kk) {
-#pragma unroll
-        for (int i = 0; i < A_UNITS; ++i) areg[i] = *(const uint4*)(aptr[i] + (int64_t)kk * BK);
-#pragma unroll
-        for (int i = 0; i < W_UNITS; ++i)
-            if (tid + i * GEMM_THREADS < BN * W_UPR) wreg[i] = *(const uint4*)(wptr[i] + (int64_t)kk * (BK / 4));
-    };
-    auto store_tiles = [&](int b) {
-#pragma unroll
-        for (int i = 0; i < A_UNITS; ++i) {
-            const int u = tid + i * GEMM_THREADS, row = u / A_UPR, c = u % A_UPR;
-            uint32_t a0 = areg[i].x, a1 = areg[i].y, a2 = areg[i].z, a3 = areg[i].w;
-            if (LAYOUT == 0) bl_transpose4x4(a0, a1, a2, a3);
-            *(uint4*)(As(b) + row * A_STRIDE + c * 16) = make_uint4(a0, a1, a2, a3);
-        }
-#pragma unroll
-        for (int i = 0; i < W_UNITS; ++i) {
-            const int u = tid + i * GEMM_THREADS, row = u / W_UPR, c = u % W_UPR;
-            if (u < BN * W_UPR) {
-                uint32_t* d = Ws(b) + row * W_STRIDE + c * 4;
-                d[0] = wreg[i].x; d[1] = wreg[i].y; d[2] = wreg[i].z; d[3] = wreg[i].w;
-            }
-        }
-    };
-
-    const int steps = K / BK;
-    load_tiles(0);
-    store_tiles(0);
-    __syncthreads();
-    for (int kk = 0; kk < steps; ++kk) {
-        const int b = kk & 1;
-        if (kk + 1 < steps) load_tiles(kk + 1);
-        const uint8_t* Ab = As(b) + (wm0 + l32) * A_STRIDE + h * 16;
-        const uint32_t* Wb = Ws(b) + (wn0 + l32) * W_STRIDE + h;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            bl_v4i a[MI];
-#pragma unroll
-            for (int mi = 0; mi < MI; ++mi) a[mi] = *(const bl_v4i*)(Ab + mi * 32 * A_STRIDE + ks * 32);
-#pragma unroll
-            for (int ni = 0; ni < NI; ++ni) {
-                const uint32_t p = Wb[ni * 32 * W_STRIDE + ks * 2];
-                bl_v4i bop;
-                bop[0] = (int)(p & 0x03030303u);
-                bop[1] = (int)((p >> 2) & 0x03030303u);
-                bop[2] = (int)((p >> 4) & 0x03030303u);
-                bop[3] = (int)((p >> 6) & 0x03030303u);
-#pragma unroll
-                for (int mi = 0; mi < MI; ++mi)
-                    C[mi][ni] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[mi], bop, C[mi][ni], 0, 0, 0);
-            }
-        }
-        if (kk + 1 < steps) store_tiles(b ^ 1);
-        __syncthreads();
-    }
-
-    /* Epilogue: per-row terms through LDS once (see bl_gemm_tile256). */
-    bl_mfma_fence();
-    __syncthreads();
-    int* rs_s = (int*)smem;
-    float* cf_s = (float*)(smem + BM * 4);
-    for (int i = tid; i < BM; i += GEMM_THREADS) {
-        const int m = m0 + i;
-        rs_s[i] = m < M ? rowsum[m] : 0;
-        cf_s[i] = (y && m < M) ? *beta * scale[m] : 0.0f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int ml = wm0 + mi * 32 + (v >> 2) * 8 + h * 4 + (v & 3);
-            const int m = m0 + ml;
-            if (m < M) {
-                const int rs = rs_s[ml];
-                const float c = cf_s[ml];
-#pragma unroll
-                for (int ni = 0; ni < NI; ++ni) {
-                    const int n = n0 + wn0 + ni * 32 + l32;
-                    if (n < N) {
-                        const int val = C[mi][ni][v] - rs;
-                        if (acc) acc[(int64_t)m * N + n] = val;
-                        if (y) {
-                            const float t = (float)val * c;
-                            y[(int64_t)m * N + n] = t;
-                        }
-                    }
-                }
-            }
-        }
-    if (stamp && tid == 0) {
-        stamps[0] = clock64() - c_start;
-        stamps[1] = wall_clock64() - w_start;
-    }
-}
-
-template <int BK, int LAYOUT>
-static bl_status launch_staged(const uint8_t* packed, const float* beta, const int8_t* q, const float* scale,
-                               const int32_t* rowsum, int M, int N, int K, int32_t* acc, float* y, hipStream_t st) {
-    constexpr size_t lds = 2 * (size_t)(128 * (BK + GEMM_PAD) + 128 * (BK / 16 + 1) * 4);
-    static_assert(lds <= 64 * 1024, "no attribute needed");
-    const dim3 grid((unsigned)((N + 127) / 128), (unsigned)((M + 127) / 128));
-    bl_gemm_mfma<128, 128, BK, 2, LAYOUT><<<grid, GEMM_THREADS, lds, st>>>(packed, q, rowsum, beta, scale, M, N, K, acc, y,
-                                                                           (long long*)bl_clock_stamps());
+    const int tiles_m = (M + G::BM - 1) / G::BM, out = EPI == 2 ? N / 2 : N, cover = EPI == 2 ? G::BN / 2 : G::BN;
+    const int tiles_n = (out + cover - 1) / cover;
+    if ((int64_t)tiles_m * tiles_n > ((int64_t)1 << 28)) return BL_ERR_SHAPE;
+    const bl_tile_order o = tile_order(tiles_m, tiles_n, G::BM, K);
+    if (blocks > o.vgrid) blocks = o.vgrid;
+    kern<<<blocks, G::THREADS, G::LDS, st>>>(packed, q, rowsum, beta, scale, M, N, K, tiles_m, tiles_n, o.gm, o.band, o.vgrid, blocks,
+                                             residual, acc, y, ep.xb, ep.absmax, (long long*)bl_clock_stamps());
     return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
-}
-
-/* Whether a product in layout 0, or with a half last k step (layout 1 with K % 128 == 0 was never measured
- * here), is faster on the register-staged kernel.  Measured over 32 shapes x 20 lengths, both layouts; time of the
- * tile kernels over its time, in the ranges that it takes / just outside:
- *   residual given: 0.16 - 0.93, never.  At most 160 tiles of 64 x 128 (split k loop): 0.18 - 0.6, never.
- *   int32 and fp32 outputs, up to 400 tiles of 128 x 128: K <= 256 0.98 - 1.12 / 0.93 - 1.04;  to 768 tiles: half
- *   steps to K = 3072 0.93 - 1.39 / 0.9 - 1.05, whole ones at every K 1.02 - 1.36;  beyond: half steps to K = 1024
- *   (1152 where N % 16 != 0) 0.84 - 1.46 / 0.8 - 1.09, whole ones to 3072 0.92 - 1.4 / 0.94 - 1.06.
- *   int32 output alone, 401 .. 768 tiles: K <= 512 (640 where N % 16 != 0) 1.0 - 1.19 / 0.95 - 1.08.
- *   fp32 output alone, more than 400 tiles: K <= 64 (128 beyond 768 tiles) 0.83 - 1.11 / 0.9 - 1.08; where the
- *   output's rows do not start on 64 bytes (N % 16 != 0) the non-temporal stores of the tile kernels write lines in
- *   parts: K <= 640 (1152 where N % 4 != 0) 0.79 - 1.66, and for 513 .. 768 tiles, a second round of the deferred
- *   stores, K <= 3072 0.96 - 1.37 / 0.98 - 1.05; rows on 64 but not on 128 bytes, beyond 768 tiles: K <= 256 1.0 - 1.12. */
-static bool staged_is_faster(int m, int n, int k, bool acc, bool y, bool residual) {
-    if (residual || m > 65535 * 128 || (int64_t)((m + 63) / 64) * ((n + 127) / 128) <= KS_MAX_TILES) return false;
-    const int64_t tiles = (int64_t)((m + 127) / 128) * ((n + 127) / 128);
-    const bool half = k % G3_BK != 0, many = tiles > 768, parts = n % 16 != 0;
-    if (acc && y) {
-        if (tiles <= 400) return k <= 256;
-        if (many) return k <= (!half ? 3072 : parts ? 1152 : 1024);
-        return !half || k <= 3072;
-    }
-    if (tiles <= 400) return false;
-    if (acc) return !many && k <= (parts ? 640 : 512);
-    if (parts) return k <= (tiles > 512 && !many ? 3072 : n % 4 != 0 ? 1152 : 640);
-    return k <= (!many ? 64 : n % 32 != 0 ? 256 : 128);
 }
 
 /* rowsum[m] = sum_k q[m][k]; one wave per row. */
@@ -1075,55 +917,45 @@ __global__ __launch_bounds__(256) void bl_rowsum_kernel(const int8_t* __restrict
     if (lane == 0) rowsum[m] = s;
 }
 
-/* Tile choice of a plain product.  Measured on MI355X at M = 2048 on the four 2B-layer shapes: 128x128
- * tiles, k step 128, two LDS stages filled by direct global->LDS loads, XCD-aware tile order, three
- * workgroups per CU: about 1450 TOPS over the layer against 1310 for a register-staged 128x128 kernel.
- * Also measured and dropped (no longer in the library): 256x256 tiles with 2x2 / 2x4 / 4x2 waves and
- * 256x128 (0.9 - 1.1 POP/s), a three-stage 128x128 and 4- or 6-stage pipelines (what hides the load
- * latency is the number of workgroups per CU, not the depth), 64x256 (equal within noise).  When the
- * problem has at most ~1.5 tiles of 128x128 per CU, 64x128 tiles balance better: +17..21 % on the
- * N = 2560 shapes at M = 2048, +22..27 % on every small shape at M = 1024, equal at 480 tiles and slower
- * on the wide shape.
- * At most 256 tiles of 64x128 (one workgroup to a compute unit) and long rows: four LDS stages, three k steps of loads in
- * flight.  A lone workgroup's k step waits for its loads (0.47 us, with four stages 0.32; the matrix cores work 0.12 of it):
- * 512 x 2560 -> 3840 15.9 / 13.5 us, 1024 x 4096 -> 2048 21.0 / 17.4, 1000 x 6912 -> 2000 30.2 / 24.3, 512 x 2304 -> 3840
- * 14.3 / 12.9, 256 x 2304 -> 8000 13.5 / 12.8, but 256 x 2176 -> 8000 12.4 / 12.5, 256 x 2048 -> 8000 11.6 / 12.1 and 400 x 1000 ->
- * 4000 9.3 / 9.6.  That is with activations that come from beyond the L2, as a quantiser or another product in front leaves them;
- * the same ones multiplied again and again wait less, and four stages take 1.00 - 1.04 of the time of two.
- * From two workgroups per unit on they cover each other: 777 x 2999 -> 5003 24.8 / 26.9.
- * fp32 output alone: the stores of a tile travel during the workgroup's next tile (measured at M = 2048 /
- * 8192: the 13824-wide shape 77 - 80 us against 86 - 90, 297 - 308 against 317 - 327; the 64 x 128 kernel
- * with deferred stores loses: it has under one tile per workgroup on the shapes it serves).
- * Deferred stores mean two workgroups per CU instead of three: between 512 and 768 tiles (what is resident) that is a second
- * round, which long rows do not win back (4096 x 6912 -> 2560 83.3 us against 78.6 in one round, 4096 x 6976
- * 93.4 / 83.6, 3000 x 4096 -> 3200 51.8 / 49.9) and short ones do (4096 x 2560 -> 2560 37.4 / 37.4, 3500 x 2048 ->
- * 3400 34.6 / 39.7, 2816 x 1024 -> 3840 19.4 / 21.9); over eight shapes of 546 to 756 tiles, one round against two:
- * K = 2048 0.96 - 1.14 times the time, 2560 0.93 - 1.12, 3072 0.92 - 1.09, 3584 0.91 - 1.04, 4096 0.91 - 1.02, 4608 0.90 - 1.01.
- * Layout 0, whose words are turned in the k loop, loses
- * with two workgroups for every long row: 4096 x 6912 -> 13824 422 us deferred, 390 at once, 4096 x 4096 ->
- * 13824 263 / 245, 2048 x 4096 -> 7000 equal. */
-template <bool HALF, int LAYOUT>
+/* Tile choice of a plain product: the kernel with the least time by this estimate (us),
+ *     fixed + busiest * (steps * (step + lone) + tile) + 2^-20 outputs,
+ * busiest = tiles of the busiest of 256 compute units, lone (to `step`) only where no unit has more than one.  Fitted to 190 shapes in
+ * both layouts (65 .. 4096 x 300 .. 14000, K 256 .. 7000): the choice takes 1.004 times the time of the best of the five, and
+ * .88 of that of the kernels before them (128 x 128 with deferred stores, 64 x 128 with two or four stages, a
+ * register-staged 128 x 128; worst 1.045).  Where each is the best:
+ *   128 x 256, two workgroups to a unit: many tiles (4096 x 2560 -> 13824 118 us; 128 x 192 124, 64 x 128 158; before 148);
+ *   128 x 192, two workgroups: where it fills the units better (2048 x 2560 -> 13824 66 / 69 / 80; before 74);
+ *   128 x 192, one workgroup with four stages: at most one tile to a unit (2048 x 6912 -> 2560 38.1; 128 x 256 45, 64 x 128 43;
+ *     before 43.7);
+ *   64 x 128, four stages, three workgroups: few tokens (1000 x 2560 -> 3840 14.3; 128 x 192 16.7; before 17.5);
+ *   the k loop split over the waves (bl_gemm_ksplit): fewer tiles than units (512 tiles of 64 x 32 in a round; 128 x 6912 -> 2560
+ *     11.2, 64 x 128 19.8). */
+struct bl_tile_cost {
+    int bm, bn;
+    float fixed, step, lone, tile, out;
+    float us(int m, int n, int k) const {
+        const int64_t tiles = (int64_t)((m + bm - 1) / bm) * ((n + bn - 1) / bn), busiest = (tiles + 255) / 256;
+        const float steps = (float)((k + G3_BK - 1) / G3_BK);
+        return fixed + (float)busiest * (steps * (step + (busiest == 1 ? lone : 0.0f)) + tile) + out * 1e-6f * (float)m * (float)n;
+    }
+};
+static constexpr bl_tile_cost cost_256 = {128, 256, 4.99f, .667f, .058f, 0.0f, .573f};
+static constexpr bl_tile_cost cost_192 = {128, 192, 4.40f, .557f, .070f, .254f, .518f};
+static constexpr bl_tile_cost cost_192_lone = {128, 192, 3.19f, .588f, 0.0f, 1.85f, .494f};
+static constexpr bl_tile_cost cost_128 = {64, 128, 3.80f, .246f, .082f, 0.0f, .573f};
+
+template <int LAYOUT>
 static bl_status launch_plain(const uint8_t* packed, const float* beta, const int8_t* q, const float* scale,
                               const int32_t* rowsum, int m, int n, int k, const float* residual, int32_t* acc, float* y,
                               hipStream_t st) {
-    if constexpr (HALF || LAYOUT == 0) {
-        if (staged_is_faster(m, n, k, acc != nullptr, y != nullptr, residual != nullptr))
-            return launch_staged<HALF ? 64 : 128, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, acc, y, st);
-    }
-    if ((int64_t)((m + 63) / 64) * ((n + 127) / 128) <= KS_MAX_TILES)
+    const float t256 = cost_256.us(m, n, k), t192 = cost_192.us(m, n, k), t192l = cost_192_lone.us(m, n, k), t128 = cost_128.us(m, n, k);
+    const float best = fminf(fminf(t256, t192), fminf(t192l, t128));
+    if (ksplit_us(m, n, k) < best)
         return launch_ksplit<LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
-    if (k >= 2304 && (int64_t)((m + 63) / 64) * ((n + 127) / 128) <= 256)
-        return launch_tile256_t<64, 128, 4, 1, 4, 0, false, HALF, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
-    if ((int64_t)((m + 127) / 128) * ((n + 127) / 128) <= 400)
-        return launch_tile256_t<64, 128, 2, 1, 4, 0, false, HALF, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
-    const int64_t tiles = (int64_t)((m + 127) / 128) * ((n + 127) / 128);
-    const int two_rounds = bl_tile256_launch<128, 128, 2, 2, 2, 0, true, HALF, LAYOUT>::resident();
-    const int one = bl_tile256_launch<128, 128, 2, 2, 2, 0, false, HALF, LAYOUT>::resident();
-    if (two_rounds == 0 || one == 0) return BL_ERR_HIP;
-    const bool one_round = tiles > two_rounds && tiles <= one && k >= 4096;
-    if (!one_round && !(LAYOUT == 0 && k >= 4096) && !acc && !residual && (int64_t)m * n < ((int64_t)1 << 30))
-        return launch_tile256_t<128, 128, 2, 2, 2, 0, true, HALF, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
-    return launch_tile256_t<128, 128, 2, 2, 2, 0, false, HALF, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
+    if (best == t128) return launch_pipe<2, 1, 1, 4, 4, 3, 0, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
+    if (best == t192l) return launch_pipe<2, 3, 2, 2, 4, 1, 0, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
+    if (best == t192) return launch_pipe<2, 3, 2, 2, 3, 2, 0, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
+    return launch_pipe<2, 4, 2, 2, 3, 2, 0, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
 }
 
 /* Arguments already validated by the public entry points. */
@@ -1138,11 +970,8 @@ bl_status bl_gemm_dispatch(const uint8_t* packed, const float* beta, int layout,
         rowsum = rs;
     }
     const int m = (int)M, n = (int)N, k = (int)K;              /* k: a multiple of 64 */
-    if (layout == 1 && k % G3_BK == 0)
-        return launch_plain<false, 1>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
-    if (layout == 1) return launch_plain<true, 1>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
-    if (k % G3_BK == 0) return launch_plain<false, 0>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
-    return launch_plain<true, 0>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
+    if (layout == 1) return launch_plain<1>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
+    return launch_plain<0>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
 }
 
 extern "C" bl_status bl_gemm_w158a8_res(const uint8_t* packed, const float* beta, int layout, const int8_t* q,
