@@ -839,13 +839,14 @@ struct bl_ksplit_order {
 static bl_ksplit_order ksplit_order(int m, int n) {
     const int64_t tm = (m + 63) / 64, tn = (n + 31) / 32, share = (tm * tn + 7) / 8;
     const int64_t down = (share < tm ? share : tm) * 64 + (share + tm - 1) / tm * 8, over = (share < tn ? share : tn) * 8 + (share + tn - 1) / tn * 64;
-    return {over < down, over < down ? over : down};
+    const bool across = over * 2 < down;                       /* (rows first otherwise: 395 x 2176 -> 1600 8.0 us, 8.7 across) */
+    return {across, across ? over : down};
 }
 /* Its time (us), for the tile choice below: rounds of 512 workgroups, and what an XCD reads. */
 static float ksplit_us(int m, int n, int k) {
     const int64_t tiles = (int64_t)((m + 63) / 64) * ((n + 31) / 32);
     const float rounds = (float)((tiles + 511) / 512), steps = (float)((k + G3_BK - 1) / G3_BK);
-    return 1.40f + rounds * (steps * .0875f + 2.21f) + 2.33e-6f * (float)ksplit_order(m, n).bytes * (float)k + 1.13e-6f * (float)m * (float)n;
+    return 1.81f + rounds * (steps * .091f + 1.83f) + 2.18e-6f * (float)ksplit_order(m, n).bytes * (float)k + 1.31e-6f * (float)m * (float)n;
 }
 
 template <int LAYOUT>
@@ -893,7 +894,7 @@ static bl_status launch_pipe(const uint8_t* packed, const float* beta, const int
     if ((int64_t)tiles_m * tiles_n > ((int64_t)1 << 28)) return BL_ERR_SHAPE;
     const bl_tile_order o = tile_order(tiles_m, tiles_n, G::BM, K);
     if (blocks > o.vgrid) blocks = o.vgrid;
-    kern<<<blocks, G::THREADS, G::LDS, st>>>(packed, q, rowsum, beta, scale, M, N, K, tiles_m, tiles_n, o.gm, o.band, o.vgrid, blocks,
+    kern<<<blocks, G::THREADS, G::LDS, st>>>(packed, q, rowsum, beta, scale, M, N, K, tiles_m, tiles_n, o.gm ? 3 - __builtin_ctz(o.gm) : -1, o.band, o.vgrid, blocks,
                                              residual, acc, y, ep.xb, ep.absmax, (long long*)bl_clock_stamps());
     return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
 }
@@ -919,17 +920,18 @@ __global__ __launch_bounds__(256) void bl_rowsum_kernel(const int8_t* __restrict
 
 /* Tile choice of a plain product: the kernel with the least time by this estimate (us),
  *     fixed + busiest * (steps * (step + lone) + tile) + 2^-20 outputs,
- * busiest = tiles of the busiest of 256 compute units, lone (to `step`) only where no unit has more than one.  Fitted to 190 shapes in
- * both layouts (65 .. 4096 x 300 .. 14000, K 256 .. 7000): the choice takes 1.004 times the time of the best of the five, and
- * .88 of that of the kernels before them (128 x 128 with deferred stores, 64 x 128 with two or four stages, a
- * register-staged 128 x 128; worst 1.045).  Where each is the best:
- *   128 x 256, two workgroups to a unit: many tiles (4096 x 2560 -> 13824 118 us; 128 x 192 124, 64 x 128 158; before 148);
- *   128 x 192, two workgroups: where it fills the units better (2048 x 2560 -> 13824 66 / 69 / 80; before 74);
- *   128 x 192, one workgroup with four stages: at most one tile to a unit (2048 x 6912 -> 2560 38.1; 128 x 256 45, 64 x 128 43;
- *     before 43.7);
- *   64 x 128, four stages, three workgroups: few tokens (1000 x 2560 -> 3840 14.3; 128 x 192 16.7; before 17.5);
- *   the k loop split over the waves (bl_gemm_ksplit): fewer tiles than units (512 tiles of 64 x 32 in a round; 128 x 6912 -> 2560
- *     11.2, 64 x 128 19.8). */
+ * busiest = tiles of the busiest of 256 compute units, lone (to `step`) only where no unit has more than one.  Fitted to 200 shapes in
+ * both layouts (65 .. 4096 x 300 .. 14000, K 256 .. 7000): the choice takes 1.005 times the time of the best of the six, and
+ * .86 of that of the kernels before them (128 x 128 with deferred stores, 64 x 128 with two or four stages, a
+ * register-staged 128 x 128; worst 1.12, 4072 x 640 -> 1915).  Where each is the best (us; in brackets the kernels before):
+ *   128 x 256, two workgroups to a unit: many tiles (4096 x 2560 -> 13824 117; 128 x 192 122, 128 x 128 129, 64 x 128 151 [149]);
+ *   128 x 192, two workgroups: where it fills the units better (2048 x 2560 -> 13824 63.6; 128 x 256 68, 64 x 128 79 [72]);
+ *   128 x 192, one workgroup with four stages: at most one tile to a unit (2048 x 6912 -> 2560 37.2; 128 x 256 44.5, 128 x 128 40.6,
+ *     64 x 128 42.2 [43.2]);
+ *   128 x 128, two workgroups: two tiles to a unit (2048 x 2560 -> 3840 22.3; 128 x 256 25.4, 64 x 128 25.7 [25.2]);
+ *   64 x 128, four workgroups: few tokens (512 x 2560 -> 3840 10.4; 128 x 128 12.5 [14.1]);
+ *   the k loop split over the waves (bl_gemm_ksplit): fewer tiles than units (512 tiles of 64 x 32 in a round; 128 x 2560 -> 3840
+ *     6.6, 64 x 128 8.7). */
 struct bl_tile_cost {
     int bm, bn;
     float fixed, step, lone, tile, out;
@@ -939,23 +941,42 @@ struct bl_tile_cost {
         return fixed + (float)busiest * (steps * (step + (busiest == 1 ? lone : 0.0f)) + tile) + out * 1e-6f * (float)m * (float)n;
     }
 };
-static constexpr bl_tile_cost cost_256 = {128, 256, 4.99f, .667f, .058f, 0.0f, .573f};
-static constexpr bl_tile_cost cost_192 = {128, 192, 4.40f, .557f, .070f, .254f, .518f};
-static constexpr bl_tile_cost cost_192_lone = {128, 192, 3.19f, .588f, 0.0f, 1.85f, .494f};
-static constexpr bl_tile_cost cost_128 = {64, 128, 3.80f, .246f, .082f, 0.0f, .573f};
+/* the kernel of the least cost: its place in the list */
+template <int COUNT>
+static int least(const bl_tile_cost (&cost)[COUNT], int m, int n, int k, float* us = nullptr) {
+    int best = 0;
+    float t = cost[0].us(m, n, k);
+    for (int i = 1; i < COUNT; ++i) {
+        const float ti = cost[i].us(m, n, k);
+        if (ti < t) {
+            t = ti;
+            best = i;
+        }
+    }
+    if (us) *us = t;
+    return best;
+}
+static constexpr bl_tile_cost plain_cost[5] = {{128, 256, 4.55f, .616f, .093f, .252f, .515f}, {128, 192, 4.05f, .508f, .110f, .317f, .505f},
+                                               {128, 192, 2.96f, .564f, 0.0f, 2.01f, .465f}, {128, 128, 4.16f, .351f, .066f, 0.0f, .553f},
+                                               {64, 128, 3.70f, .225f, .068f, 0.0f, .492f}};
 
 template <int LAYOUT>
 static bl_status launch_plain(const uint8_t* packed, const float* beta, const int8_t* q, const float* scale,
                               const int32_t* rowsum, int m, int n, int k, const float* residual, int32_t* acc, float* y,
                               hipStream_t st) {
-    const float t256 = cost_256.us(m, n, k), t192 = cost_192.us(m, n, k), t192l = cost_192_lone.us(m, n, k), t128 = cost_128.us(m, n, k);
-    const float best = fminf(fminf(t256, t192), fminf(t192l, t128));
-    if (ksplit_us(m, n, k) < best)
-        return launch_ksplit<LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
-    if (best == t128) return launch_pipe<2, 1, 1, 4, 4, 3, 0, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
-    if (best == t192l) return launch_pipe<2, 3, 2, 2, 4, 1, 0, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
-    if (best == t192) return launch_pipe<2, 3, 2, 2, 3, 2, 0, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
-    return launch_pipe<2, 4, 2, 2, 3, 2, 0, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
+    float us;
+    const int kernel = least(plain_cost, m, n, k, &us);
+    /* (fitted with fp32 output alone; the split k loop has the residual at hand when its sums are ready, and writes two outputs at
+     * once: 663 x 781 -> 1088 5.9 us with residual, 64 x 128 tiles 8.0; 436 x 576 -> 2330 with both 6.2 / 6.9) */
+    us += residual ? 2.0f : acc && y ? 0.8f : 0.0f;
+    if (ksplit_us(m, n, k) < us) return launch_ksplit<LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
+    switch (kernel) {
+        case 0: return launch_pipe<2, 4, 2, 2, 3, 2, 0, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
+        case 1: return launch_pipe<2, 3, 2, 2, 3, 2, 0, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
+        case 2: return launch_pipe<2, 3, 2, 2, 4, 1, 0, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
+        case 3: return launch_pipe<2, 2, 2, 2, 3, 2, 0, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
+        default: return launch_pipe<2, 1, 1, 4, 3, 4, 0, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
+    }
 }
 
 /* Arguments already validated by the public entry points. */
@@ -996,20 +1017,16 @@ extern "C" bl_status bl_gemm_w158a8(const uint8_t* packed, const float* beta, in
     return bl_gemm_w158a8_res(packed, beta, layout, q, scale, rowsum, M, N, K, nullptr, acc, y, workspace, s);
 }
 
-/* The tile of a fused epilogue: 64 x 128 (two waves across, so that a row's maximum meets two atomics and not four) up to 352
- * tiles of 128 x 128, where the larger one leaves compute units idle.  2560 -> 2560 with residual at 192 tokens 21.3 / 13.1 us, 512
- * 22.6 / 14.5, 2048 (320 tiles) 28.6 / 22.5, 2560 (400) 30.8 / 30.7; 6912 -> 2560 at 512 tokens 40.2 / 27.7, 2048 51.1 / 43.9, 2560 56.7
- * / 60.3; 2560 -> 13824 with the gate at 192 (216 tiles) 23.7 / 19.6, 384 (324) 25.8 / 23.4, 512 (432) 25.4 / 27.6.  Four stages at
- * one workgroup per compute unit gain nothing here (512 tokens: 18.1, 38.7, 24.8). */
-template <int EPI>
-static bl_status launch_fused(const uint8_t* packed, const float* beta, const int8_t* q, const float* scale, const int32_t* rowsum, int m, int n,
-                              int k, const float* residual, int32_t* acc, float* y, const bl_epi_args ea, hipStream_t st) {
-    if ((int64_t)((m + 127) / 128) * ((n + 127) / 128) <= 352)
-        return launch_tile256_t<64, 128, 2, 2, 2, EPI>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st, ea);
-    return launch_tile256_t<128, 128, 2, 2, 2, EPI>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st, ea);
-}
+/* The tile of a fused epilogue, by the same estimate (gate: tiles of outputs), fitted to 140 shapes; the choice takes 1.003 times
+ * the time of the best, .80 (residual) and .88 (gate) of that of the 128 x 128 and 64 x 128 tiles before it.  us [before]:
+ *   residual 4096 x 2560 -> 2560 40 [45], 4096 x 6912 -> 2560 88 [93], 1000 x 2560 -> 2560 15.7 [20.1], 128 x 6912 -> 2560 21.2 [26.7];
+ *   gate 2560 -> 13824 at 4096 tokens 120 [142], 2048 70 [72.6], 1000 38.5 [48.5], 128 18.2 [19.5].
+ * Slower than before: gates of short rows with few tiles (834 x 256 -> 3328 6.7 [6.0], 94 x 1024 -> 6400 9.9 [9.5]). */
+static constexpr bl_tile_cost residual_cost[3] = {{128, 256, 0.0f, .450f, .207f, 8.97f, .929f}, {128, 128, 3.26f, .266f, .103f, 3.68f, .988f},
+                                                  {64, 128, 3.84f, .193f, .112f, .966f, 1.17f}};
+static constexpr bl_tile_cost gate_cost[2] = {{128, 128, 6.24f, .614f, .072f, 0.0f, .756f}, {64, 64, 4.52f, .230f, .056f, 0.0f, .872f}};
 
-/* Prefill product with a fused producer epilogue (see bl_gemm_tile256, EPI = 1 and 2). */
+/* Prefill product with a fused producer epilogue (see bl_gemm_pipe, EPI = 1 and 2). */
 extern "C" bl_status bl_gemm_w158a8_fused(const uint8_t* packed, const float* beta, int layout, const int8_t* q,
                                           const float* scale, const int32_t* rowsum, int64_t M, int64_t N, int64_t K,
                                           const bl_gemm_epilogue* ep, int32_t* acc, bl_stream s) {
@@ -1026,8 +1043,17 @@ extern "C" bl_status bl_gemm_w158a8_fused(const uint8_t* packed, const float* be
         return BL_ERR_ALIGN;
     const bl_epi_args ea = {ep->x_bf16, (int*)ep->absmax};
     hipStream_t st = (hipStream_t)s;
-    if (ep->kind == BL_EPI_RESIDUAL) return launch_fused<1>(packed, beta, q, scale, rowsum, (int)M, (int)N, (int)K, ep->residual, acc, ep->y, ea, st);
-    return launch_fused<2>(packed, beta, q, scale, rowsum, (int)M, (int)N, (int)K, nullptr, acc, ep->y, ea, st);
+    const int m = (int)M, n = (int)N, k = (int)K;
+    if (ep->kind == BL_EPI_RESIDUAL) {
+        switch (least(residual_cost, m, n, k)) {
+            case 0: return launch_pipe<2, 4, 2, 2, 3, 2, 1, 1>(packed, beta, q, scale, rowsum, m, n, k, ep->residual, acc, ep->y, st, ea);
+            case 1: return launch_pipe<2, 2, 2, 2, 3, 2, 1, 1>(packed, beta, q, scale, rowsum, m, n, k, ep->residual, acc, ep->y, st, ea);
+            default: return launch_pipe<1, 2, 2, 2, 3, 4, 1, 1>(packed, beta, q, scale, rowsum, m, n, k, ep->residual, acc, ep->y, st, ea);
+        }
+    }
+    if (least(gate_cost, m, n / 2, k) == 0)
+        return launch_pipe<2, 4, 2, 2, 3, 2, 2, 1>(packed, beta, q, scale, rowsum, m, n, k, nullptr, acc, ep->y, st, ea);
+    return launch_pipe<1, 2, 2, 2, 3, 4, 2, 1>(packed, beta, q, scale, rowsum, m, n, k, nullptr, acc, ep->y, st, ea);
 }
 
 /* ---- entry point that allocates nothing ---------------------------------------------------

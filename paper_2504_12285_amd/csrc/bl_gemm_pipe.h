@@ -43,34 +43,34 @@
 
 #define GP_BK 128
 
-/* sets of row terms: the tile in its epilogue and those that the loads may have reached */
 template <int MI, int NI, int WM, int WN, int S>
 struct bl_pipe_geom {
     static constexpr int BM = WM * MI * 32, BN = WN * NI * 32, THREADS = WM * WN * 64;
     static constexpr int A_BYTES = BM * GP_BK, W_BYTES = BN * GP_BK / 4, STAGE = A_BYTES + W_BYTES;
-    static constexpr int LDS = S * STAGE + S * BM * 8 + S * WM * WN * 8;
+    static constexpr int SETS = S + 1;                      /* of row terms: the tile in its epilogue and those that the loads may have reached */
+    static constexpr int LDS = S * STAGE + SETS * (BM + WM * WN) * 8;
 };
 
 template <int MI, int NI, int WM, int WN, int S, int OCC, int EPI, int LAYOUT>
 __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t* __restrict__ packed, const int8_t* __restrict__ q,
                                                                   const int32_t* __restrict__ rowsum, const float* __restrict__ beta,
                                                                   const float* __restrict__ scale, int M, int N, int K, int tiles_m,
-                                                                  int tiles_n, int gm, int band, int vgrid, int grid,
+                                                                  int tiles_n, int gs, int band, int vgrid, int grid,
                                                                   const float* __restrict__ residual, int32_t* __restrict__ acc,
                                                                   float* __restrict__ y, uint16_t* __restrict__ xb,
                                                                   int* __restrict__ absmax, long long* __restrict__ stamps) {
 #if defined(__HIP_DEVICE_COMPILE__)   /* (the host has no type for a buffer descriptor) */
     using G = bl_pipe_geom<MI, NI, WM, WN, S>;
-    constexpr int NW = WM * WN, BM = G::BM, BN = G::BN, STAGE = G::STAGE, AB = G::A_BYTES;
+    constexpr int SETS = G::SETS, NW = WM * WN, BM = G::BM, BN = G::BN, STAGE = G::STAGE, AB = G::A_BYTES;
     constexpr int AL = AB / 1024 / NW, WP = G::W_BYTES / 1024, WL = (WP + NW - 1) / NW, LOADS = AL + WL;
     constexpr int SL = MI * NI;                              /* MFMAs of a sub-step */
-    static_assert(AB % (1024 * NW) == 0 && S >= 3 && (S - 2) * LOADS < 64, "whole loads per wave; vmcnt is a 6-bit count");
+    static_assert(AB % (1024 * NW) == 0 && S >= 3 && (S - 1) * LOADS < 64, "whole loads per wave; vmcnt is a 6-bit count");
     static_assert(EPI != 2 || NI % 2 == 0, "gate and up blocks in pairs");
     constexpr bool TURN_A = LAYOUT == 0 && NI > 1, TURN_W = LAYOUT == 0 && NI == 1;
     typedef __attribute__((address_space(3))) void* lds_p;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    int* const terms = (int*)(smem + S * STAGE);             /* S sets of BM row sums and BM scales */
-    int* const ahead = terms + S * 2 * BM;                   /* each wave's tiles that the loads have reached: S of (tm, tn) */
+    int* const terms = (int*)(smem + S * STAGE);             /* SETS sets of BM row sums and BM scales */
+    int* const ahead = terms + SETS * 2 * BM;                /* each wave's tiles that the loads have reached: SETS of (tm, tn) */
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, h = lane >> 5;
     const int wm0 = (wave / WN) * (MI * 32), wn0 = (wave % WN) * (NI * 32);
@@ -81,18 +81,18 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
 
     /* XCD-aware tile order: workgroup L runs on XCD L%8.  The row tiles are cut into bands so narrow that
      * a band's activation panel stays in an XCD's 4 MB L2 while its weight tiles stream through, row tiles
-     * fastest.  Either a rectangle per XCD (gm bands x 8 / gm column blocks), or (gm = 0) the tiles are
+     * fastest.  Either a rectangle per XCD (8 >> gs bands x 1 << gs column blocks), or (gs < 0) the tiles are
      * numbered band by band and each XCD takes one eighth of the sequence; the host chooses.  The grid is persistent:
      * a workgroup takes virtual blocks vb = blockIdx.x, + grid, .. (grid is a multiple of 8). */
-    const int tiles = tiles_m * tiles_n, share = (tiles + 7) >> 3, band_tiles = band * tiles_n;
-    const int gn = gm ? 8 / gm : 1, cols = (tiles_n + gn - 1) / gn;
     auto tile_of = [&](int vb, int& tm, int& tn) {
         const int xcd = vb & 7, idx = vb >> 3;
-        if (gm) {
-            tm = (xcd / gn) * band + idx % band;
-            tn = (xcd % gn) * cols + idx / band;
-            return idx < band * cols && tm < tiles_m && tn < tiles_n;
+        if (gs >= 0) {
+            const int cols = (tiles_n + (1 << gs) - 1) >> gs, col = idx / band;
+            tm = (xcd >> gs) * band + (idx - col * band);
+            tn = (xcd & ((1 << gs) - 1)) * cols + col;
+            return col < cols && tm < tiles_m && tn < tiles_n;
         }
+        const int tiles = tiles_m * tiles_n, share = (tiles + 7) >> 3, band_tiles = band * tiles_n;
         const int at = xcd * share + idx;
         if (idx >= share || at >= tiles) return false;
         const int b = at / band_tiles, in = at - b * band_tiles;
@@ -143,6 +143,9 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
             if (n > N - 32) n = max(min(n, N - 1) & ~31, 0);          /* blocks past the end: the last one again */
             rw[j] = rsrc(packed + (int64_t)n * kb, (uint32_t)min(32, N - n) * (uint32_t)kb);
         }
+    };
+    auto setup_terms = [&]() __attribute__((always_inline)) {
+        const int m0 = ltm * BM, rows = min(BM, M - m0);
 #pragma unroll
         for (int j = 0; j < (2 * BM + NW * 64 - 1) / (NW * 64); ++j) {
             const int g = (j * NW + wave) * 64;
@@ -162,16 +165,17 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
                 lkk = 0;
                 if (lvb >= 0) {
                     lvb = next_tile(lvb + grid, ltm, ltn);
-                    lset = lset + 1 == S ? 0 : lset + 1;
+                    lset = lset + 1 == SETS ? 0 : lset + 1;
                     if (lvb >= 0) {
                         setup();
+                        setup_terms();
                     } else {
                         ra = rsrc(q, 0);
 #pragma unroll
                         for (int j = 0; j < WL; ++j) rw[j] = rsrc(packed, 0);
                         ltm = -1;
                     }
-                    int* const slot = ahead + (wave * S + lset) * 2;
+                    int* const slot = ahead + (wave * SETS + lset) * 2;
                     slot[0] = ltm;
                     slot[1] = ltn;
                 }
@@ -190,9 +194,13 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
      * are spread over the MFMAs up to the next barrier: 2048 x 2560 -> 2560 in 128 x 192 tiles, four stages 16.8 / 17.8 us, and
      * in 128 x 256 tiles with three 23.3 / 20.6. */
     constexpr bool SPREAD = S > 3;
-    constexpr int FIRST = SPREAD ? (LOADS + 3) / 4 : LOADS;                     /* in the sub-step behind the barrier */
+    /* DEEP: with few MFMAs to a sub-step they don't cover an LDS read, so a wave reads a whole step's operands one step ahead;
+     * the step's barrier then stands in front of it, and the buffer of the step itself is free for loads (stage t + S). */
+    constexpr bool DEEP = SL <= 4;
+    constexpr int FIRST = SPREAD && !DEEP ? (LOADS + 3) / 4 : LOADS;            /* in the sub-step behind the barrier */
     constexpr int GAP = LOADS > FIRST ? 3 * SL / (LOADS - FIRST) : 1;           /* MFMAs between the others */
-    static_assert(FIRST <= SL || !SPREAD, "one load per MFMA");
+    static_assert(FIRST <= SL || !SPREAD || DEEP, "one load per MFMA");
+    constexpr int INIT = DEEP ? S : S - 1;                                      /* stages on their way in front of the first step */
 
     /* per-lane LDS read offsets inside a stage */
     const int a_off = (wm0 + l32) * GP_BK, a_swz = (l32 >> 1) & 7;
@@ -214,29 +222,44 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
     tm = ltm;
     tn = ltn;
     setup();
+    if (steps >= INIT) {
+#pragma unroll
+        for (int s = 0; s < INIT; ++s) {
+            lst = smem + s * STAGE;
+            lko = min(s * GP_BK, max(K - GP_BK, 0));
+#pragma unroll
+            for (int j = 0; j < (s < INIT - 1 ? LOADS : FIRST); ++j) load(j);
+            if (s == 0) setup_terms();                       /* (behind the loads that are waited for first) */
+        }
+        lkk = lbuf = INIT - 1;
+    } else {                                                 /* rows of few k steps: the first stages are of several tiles */
+        setup_terms();
 #pragma nounroll
-    for (int s = 0; s < S - 1; ++s) {
-        advance(s == 0);
+        for (int s = 0; s < INIT; ++s) {
+            advance(s == 0);
 #pragma unroll
-        for (int j = 0; j < FIRST; ++j) load(j);
-        if (s < S - 2) {
+            for (int j = 0; j < FIRST; ++j) load(j);
+            if (s < INIT - 1) {
 #pragma unroll
-            for (int j = FIRST; j < LOADS; ++j) load(j);
+                for (int j = FIRST; j < LOADS; ++j) load(j);
+            }
         }
     }
-    int buf = 0, set = 0;
-    BL_WAIT_VM((S - 3) * LOADS + FIRST);
+    int stage_at = 0, set = 0;
+    BL_WAIT_VM((INIT - 2) * LOADS + FIRST);
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    bl_v4i wq[NI], a[2][MI];
+    bl_v4i wq[DEEP ? 2 : 1][NI], a[DEEP ? 8 : 2][MI];
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni) wq[ni] = *(const bl_v4i*)(smem + w_off + ni * 1024);
+    for (int ni = 0; ni < NI; ++ni) wq[0][ni] = *(const bl_v4i*)(smem + w_off + ni * 1024);
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi) a[0][mi] = *(const bl_v4i*)(smem + au[0] + mi * 32 * GP_BK);
+    for (int ks = 0; ks < (DEEP ? 4 : 1); ++ks)
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) a[ks][mi] = *(const bl_v4i*)(smem + au[ks] + mi * 32 * GP_BK);
     if (K < GP_BK && h == 1) {
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni) wq[ni] = bl_v4i{0, 0, 0, 0};
+        for (int ni = 0; ni < NI; ++ni) wq[0][ni] = bl_v4i{0, 0, 0, 0};
     }
     /* LAYOUT 0: half (0, 1) of the 4 x 4 byte transpose of sixteen activations */
     auto turn = [&](bl_v4i& v, const int half) __attribute__((always_inline)) {
@@ -278,7 +301,7 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
             turn(a[0][mi], 1);
         }
     }
-    bl_v4i bop = bl_unpack16(TURN_W ? bl_word_to_k16((uint32_t)wq[0][0]) : (uint32_t)wq[0][0]);
+    bl_v4i bop = bl_unpack16(TURN_W ? bl_word_to_k16((uint32_t)wq[0][0][0]) : (uint32_t)wq[0][0][0]);
 
     while (true) {
         const int m0 = tm * BM, n0 = tn * BN;
@@ -291,16 +314,16 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
                 for (int v = 0; v < 16; ++v) C[mi][ni][v] = 0;
 
         /* MI MFMAs of one block of 32 weight rows; behind each: `extra`, and a part of the next block's codes opened
-         * (w, or with `last` the first word of the next stage) */
-        auto chunk = [&](const int ab, const int ni, const uint32_t w, const bool last, auto&& extra) __attribute__((always_inline)) {
+         * (w, or with last >= 0 the first word of the next stage, from wq[last]) */
+        auto chunk = [&](const int ab, const int ni, const uint32_t w, const int last, auto&& extra) __attribute__((always_inline)) {
             bl_v4i nx;
             uint32_t x = w;
 #pragma unroll
             for (int mi = 0; mi < MI; ++mi) {
                 C[mi][ni] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[ab][mi], bop, C[mi][ni], 0, 0, 0);
                 extra(ni * MI + mi);
-                if (last) x = (uint32_t)wq[0][0];
-                if (TURN_W && (mi == 0 || last)) x = bl_word_to_k16(x);
+                if (last >= 0) x = (uint32_t)wq[last >= 0 ? last : 0][0][0];
+                if (TURN_W && (mi == 0 || last >= 0)) x = bl_word_to_k16(x);
 #pragma unroll
                 for (int j = mi * 4 / MI; j < (mi + 1) * 4 / MI; ++j) {
                     int t = (int)((x >> 2 * j) & 0x03030303u);
@@ -311,13 +334,77 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
             }
             bop = nx;
         };
+        auto clear = [&](bl_v4i (&w)[NI]) __attribute__((always_inline)) {
+            const bool z = h == dead;
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) w[ni][i] = z ? 0 : w[ni][i];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) bop[i] = z ? 0 : bop[i];
+        };
+        if constexpr (DEEP) {
+            /* one step: multiplies set P of the operands and reads the next step's into set 1 - P */
+            auto step = [&](auto p, const int kk) __attribute__((always_inline)) {
+                constexpr int P = decltype(p)::value, Q = 1 - P;
+                const int ahead_at = stage_at + STAGE == S * STAGE ? 0 : stage_at + STAGE;
+                /* this step's operands are in registers; the next stage has landed, the S - 2 behind it may stay in flight */
+                BL_WAIT_LGKM0();
+                BL_WAIT_VM((S - 2) * LOADS);
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                const uint8_t* sn = smem + ahead_at;
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                    for (int ni = 0; ni < NI; ++ni)
+                        chunk(P * 4 + ks, ni, (uint32_t)(ni + 1 < NI ? wq[P][ni + 1 < NI ? ni + 1 : 0][ks] : ks < 3 ? wq[P][0][ks < 3 ? ks + 1 : 0] : 0),
+                              ks == 3 && ni + 1 == NI ? Q : -1, [&](const int sl) __attribute__((always_inline)) {
+                                  constexpr int SLOTS = 4 * SL - 1, READS = NI + 4 * MI, RPER = (READS + SLOTS - 2) / (SLOTS - 1);
+                                  const int at = ks * SL + sl;
+                                  /* reads from the first MFMA on, so that they have the step to arrive */
+#pragma unroll
+                                  for (int r0 = 0; r0 < RPER; ++r0) {
+                                      const int r = at * RPER + r0;
+                                      if (r < NI) wq[Q][r < NI ? r : 0] = *(const bl_v4i*)(sn + w_off + r * 1024);
+                                      else if (r < READS) a[Q * 4 + (r - NI) / MI % 4][(r - NI) % MI >= 0 ? (r - NI) % MI : 0] = *(const bl_v4i*)(sn + au[(r - NI) / MI % 4] + (r - NI) % MI * 32 * GP_BK);
+                                  }
+                                  if (at == 0) advance(false);
+                                  if (at > 0) {
+#pragma unroll
+                                      for (int j = 0; j < LOADS; ++j)
+                                          if (at == 1 + j * SLOTS / LOADS) load(j);
+                                  }
+                                  turn_at(ks < 3 ? a[P * 4 + (ks < 3 ? ks + 1 : 0)] : a[Q * 4], sl);
+                              });
+                stage_at = ahead_at;
+                if (kk == zstep) clear(wq[Q]);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            int kk = 0;
+            for (; kk + 1 < steps; kk += 2) {
+                step(std::integral_constant<int, 0>{}, kk);
+                step(std::integral_constant<int, 1>{}, kk + 1);
+            }
+            if (kk < steps) {                                /* an odd step, and every tile starts with set 0 */
+                step(std::integral_constant<int, 0>{}, kk);
+#pragma unroll
+                for (int ni = 0; ni < NI; ++ni) wq[0][ni] = wq[DEEP ? 1 : 0][ni];
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                    for (int mi = 0; mi < MI; ++mi) a[ks][mi] = a[DEEP ? 4 + ks : 0][mi];
+            }
+        } else {
         for (int kk = 0; kk < steps; ++kk) {
-            const uint8_t* st = smem + buf * STAGE;
+            const uint8_t* st = smem + stage_at;
+            const int ahead_at = stage_at + STAGE == S * STAGE ? 0 : stage_at + STAGE;
 #pragma unroll
             for (int ks = 0; ks < 3; ++ks)
 #pragma unroll
                 for (int ni = 0; ni < NI; ++ni)
-                    chunk(ks & 1, ni, (uint32_t)(ni + 1 < NI ? wq[ni + 1 < NI ? ni + 1 : 0][ks] : wq[0][ks + 1]), false,
+                    chunk(ks & 1, ni, (uint32_t)(ni + 1 < NI ? wq[0][ni + 1 < NI ? ni + 1 : 0][ks] : wq[0][0][ks + 1]), -1,
                           [&](const int sl) __attribute__((always_inline)) {
                               const int at = ks * SL + sl;
                               if (LOADS > FIRST && at % GAP == 0 && FIRST + at / GAP < LOADS) load(FIRST + at / GAP);
@@ -330,24 +417,24 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
             asm volatile("" ::: "memory");
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
-            advance(false);
-            __builtin_amdgcn_sched_barrier(0);
-            buf = buf + 1 == S ? 0 : buf + 1;
-            const uint8_t* sn = smem + buf * STAGE;          /* (behind the last step of all: zeros or an old stage, unused) */
+            const uint8_t* sn = smem + ahead_at;             /* (behind the last step of all: zeros or an old stage, unused) */
             uint32_t w3[NI];
 #pragma unroll
-            for (int ni = 0; ni < NI; ++ni) w3[ni] = (uint32_t)wq[ni][3];
+            for (int ni = 0; ni < NI; ++ni) w3[ni] = (uint32_t)wq[0][ni][3];
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni)
-                chunk(1, ni, ni + 1 < NI ? w3[ni + 1 < NI ? ni + 1 : 0] : 0u, ni + 1 == NI, [&](const int sl) __attribute__((always_inline)) {
+                chunk(1, ni, ni + 1 < NI ? w3[ni + 1 < NI ? ni + 1 : 0] : 0u, ni + 1 == NI ? 0 : -1, [&](const int sl) __attribute__((always_inline)) {
+                    /* (scalar work between the barrier and the first MFMA would hold up both) */
+                    if (sl == 0) advance(false);
                     if constexpr (!SPREAD) {
-                        if (sl == 0) {
+                        if (sl == 1) {
 #pragma unroll
                             for (int j = 0; j < LOADS; ++j) load(j);
                         }
                     } else {
                         constexpr int E = SL / FIRST;
                         if (sl % E == E - 1 && sl / E < FIRST) load(sl / E);
+                        static_assert(E > 1, "behind advance");
                     }
                     /* first code word, activations, the other words */
                     constexpr int PER = (NI + MI + SL - 1) / SL;
@@ -358,17 +445,15 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
                             a[0][r >= 1 && r <= MI ? r - 1 : 0] = *(const bl_v4i*)(sn + au[0] + (r - 1) * 32 * GP_BK);
                         } else if (r < NI + MI) {
                             const int wi = r == 0 ? 0 : r - MI;
-                            wq[wi < NI ? wi : 0] = *(const bl_v4i*)(sn + w_off + wi * 1024);
+                            wq[0][wi < NI ? wi : 0] = *(const bl_v4i*)(sn + w_off + wi * 1024);
                         }
                     }
                     turn_at(a[0], sl);
                 });
-            if (kk == zstep && h == dead) {
-#pragma unroll
-                for (int ni = 0; ni < NI; ++ni) wq[ni] = bl_v4i{0, 0, 0, 0};
-                bop = bl_v4i{0, 0, 0, 0};
-            }
+            stage_at = ahead_at;
+            if (kk == zstep) clear(wq[0]);
             __builtin_amdgcn_sched_barrier(0);
+        }
         }
 
         /* Epilogue: the loads of the next tile's first stages travel meanwhile. */
@@ -381,6 +466,7 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
          * 1000 x 2560 -> 3840 in 128 x 128 tiles 20.5 / 14.7 us). */
         constexpr uint32_t NOWHERE = 0x80000000u;
         constexpr int NT = 2;                                 /* non-temporal */
+        constexpr int AHEAD = SL > 4 ? 2 : MI == 1 ? 3 : 4;   /* groups of residual values on their way (more spill) */
         /* A descriptor of the eight rows of group g of the wave (rows of `bytes` bytes), none past M. */
         auto span = [&](const void* p, const uint32_t bytes, const int g) __attribute__((always_inline)) {
             const int m = m0 + wm0 + g * 8, left = __builtin_amdgcn_readfirstlane(max(min(8, M - m), 0));
@@ -391,14 +477,14 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
 #pragma unroll
             for (int g = 0; g < 4 * MI; ++g) {
                 int ml = wm0 + g * 8 + h * 4;
-                asm volatile("" : "+v"(ml));
+                if (SL > 4) asm volatile("" : "+v"(ml));     /* (large tiles: keeps the groups apart, or registers spill) */
                 before(g);
                 const bl_v4i rs = *(const bl_v4i*)(rs_s + ml);
                 const bl_v4f sc = *(const bl_v4f*)(sc_s + ml);
 #pragma unroll
                 for (int v4 = 0; v4 < 4; ++v4) row(g, g / 4, (g % 4) * 4 + v4, v4, rs[v4], bt * sc[v4]);
                 after(g, ml);
-                __builtin_amdgcn_sched_barrier(0);
+                if (SL > 4) __builtin_amdgcn_sched_barrier(0);
             }
         };
         auto nothing = [](auto...) __attribute__((always_inline)) {};
@@ -436,102 +522,149 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
             if (y && !residual) {
                 /* A non-temporal store of part of a line goes to memory as part of a line once the output outgrows the L2
                  * (3812 x 677 -> 6613 51.1 us, plain stores 35.0; 2048 x 2560 -> 13826 77.2 / 73.0; whole and half lines or
-                 * outputs that fit gain by it: 2048 x 2560 -> 13840 66.7 / 69.3, 1000 x 2560 -> 3850 15.1 / 15.9). */
-                if (N % 16 == 0 || (int64_t)M * N <= (8 << 20)) plain(std::integral_constant<int, NT>{});
+                 * outputs that fit gain by it: 2048 x 2560 -> 13840 66.7 / 69.3, 1000 x 2560 -> 3850 15.1 / 15.9; not beside an
+                 * int32 output). */
+                if (N % 16 == 0 || (!acc && (int64_t)M * N <= (8 << 20))) plain(std::integral_constant<int, NT>{});
                 else plain(std::integral_constant<int, 0>{});
             } else if (y) {
-                /* the residual values of four rows first, then their stores back to back: a load
-                 * between two stores would make each store wait for the one before it */
-                float res[4][NI];
-                rows([&](const int g) __attribute__((always_inline)) {
-                    ro = span(y, wide, g);
+                /* the residual values are requested ahead of their rows */
+                constexpr int RING = AHEAD;
+                float res[RING][4][NI];
+                auto fetch = [&](const int g) __attribute__((always_inline)) {
                     rr = span(residual, wide, g);
 #pragma unroll
                     for (int v4 = 0; v4 < 4; ++v4)
 #pragma unroll
                         for (int ni = 0; ni < NI; ++ni)
-                            res[v4][ni] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rr, col[ni] + (uint32_t)v4 * wide, 0, 0));
-                }, [&](const int, const int mi, const int v, const int v4, const int rs, const float c) __attribute__((always_inline)) {
+                            res[g % RING][v4][ni] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rr, col[ni] + (uint32_t)v4 * wide, 0, 0));
+                };
+#pragma unroll
+                for (int g = 0; g < RING; ++g) fetch(g);
+                rows([&](const int g) __attribute__((always_inline)) { ro = span(y, wide, g); },
+                     [&](const int g, const int mi, const int v, const int v4, const int rs, const float c) __attribute__((always_inline)) {
 #pragma unroll
                     for (int ni = 0; ni < NI; ++ni)
-                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(res[v4][ni] + (float)(C[mi][ni][v] - rs) * c), ro, col[ni] + (uint32_t)v4 * wide, 0, NT);
-                }, nothing);
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(res[g % RING][v4][ni] + (float)(C[mi][ni][v] - rs) * c), ro, col[ni] + (uint32_t)v4 * wide, 0, NT);
+                }, [&](const int g, const int) __attribute__((always_inline)) {
+                    if (g + RING < 4 * MI) fetch(g + RING);
+                });
             }
         } else {
             /* fused producer epilogue: glue value t, its bf16 narrowing (the next BitLinear's input before quantisation) and the
              * row maximum of |bf16(t)|: over the lane's columns, then over the 32 lanes of a half wave (DPP), then one atomic
              * max for the eight rows of a group on the float bits (non-negative floats order like integers, so the result does
-             * not depend on the order). */
-            constexpr int MAG0 = 0x007F0000;          /* added to a magnitude's bits: infinity is the largest int, a NaN negative */
+             * not depend on the order).  Two rows at a time: a lane narrows its column of both in one instruction, trades with
+             * its neighbour and stores two columns of one row, and the maxima are taken on 16-bit patterns, both rows at once. */
+            typedef short v2s __attribute__((ext_vector_type(2)));
+            constexpr int MAG = 0x007F007F;           /* added to magnitudes: infinity is the largest int16, a NaN negative */
             constexpr int NO = EPI == 2 ? NI / 2 : NI;
             const int NOUT = EPI == 2 ? N / 2 : N;
             const uint32_t narrow = (uint32_t)NOUT * 2;
-            uint32_t colb[NO];
-            bool in[NO];
+            uint32_t colx[NO], coly[NO];
+            int in[NO];
 #pragma unroll
             for (int ni = 0; ni < NO; ++ni) {
                 const int n = (EPI == 2 ? tn * (BN / 2) + wn0 / 2 : n0 + wn0) + ni * 32 + l32;
-                in[ni] = n < NOUT;
-                colb[ni] = (in[ni] ? (uint32_t)n * 2 : NOWHERE / 2) + (uint32_t)(h * 4) * narrow;
+                in[ni] = n < NOUT ? 0x7FFF7FFF : 0;
+                coly[ni] = (n < NOUT ? (uint32_t)n * 4 : NOWHERE) + (uint32_t)(h * 4) * narrow * 2;
+                colx[ni] = (n < NOUT ? (uint32_t)(n & ~1) * 2 : NOWHERE) + (uint32_t)(h * 4 + (lane & 1)) * narrow;
             }
+            const uint32_t pick = lane & 1 ? 0x03020706u : 0x05040100u;
             decltype(rsrc(nullptr, 0)) rx;
-            /* EPI 1: the residual values of two groups are requested ahead */
-            float res[2][4][EPI == 1 ? NI : 1];
+            /* EPI 1: the residual values are requested ahead */
+            constexpr int RING = AHEAD;
+            float res[RING][4][EPI == 1 ? NI : 1];
             auto fetch = [&](const int g) __attribute__((always_inline)) {
                 rr = span(residual, narrow * 2, g);
 #pragma unroll
                 for (int v4 = 0; v4 < 4; ++v4)
 #pragma unroll
                     for (int ni = 0; ni < NO; ++ni)
-                        res[g & 1][v4][EPI == 1 ? ni : 0] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rr, (colb[ni] + (uint32_t)v4 * narrow) * 2, 0, 0));
+                        res[g % RING][v4][EPI == 1 ? ni : 0] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rr, coly[ni] + (uint32_t)v4 * narrow * 2, 0, 0));
             };
             if constexpr (EPI == 1) {
-                fetch(0);
-                fetch(1);
+#pragma unroll
+                for (int g = 0; g < RING; ++g) fetch(g);
             }
-            float rowmax[4];
+            float first[NO];
+            int most[2], maxes[4 * MI];
+            auto gated = [&](const int mi, const int ni, const int v, const int rs, const float c) __attribute__((always_inline)) {
+                const float t = (float)(C[mi][ni][v] - rs) * c, u = (float)(C[mi][ni + (EPI == 2 ? NO : 0)][v] - rs) * c;
+                const float r = fmaxf(t, 0.0f);
+                const float r2 = r * r;
+                return r2 * u;
+            };
+            if (EPI == 2 && y) {
+                rows([&](const int g) __attribute__((always_inline)) { ro = span(y, narrow * 2, g); },
+                     [&](const int, const int mi, const int v, const int v4, const int rs, const float c) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int ni = 0; ni < NO; ++ni)
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(gated(mi, ni, v, rs, c)), ro, coly[ni] + (uint32_t)v4 * narrow * 2, 0, NT);
+                }, nothing);
+            }
             rows([&](const int g) __attribute__((always_inline)) {
                 rx = span(xb, narrow, g);
-                ro = span(y, y ? narrow * 2 : 0, g);          /* (no fp32 output: nothing in range) */
+                if (EPI == 1) ro = span(y, y ? narrow * 2 : 0, g);      /* (no fp32 output: nothing in range) */
             }, [&](const int g, const int mi, const int v, const int v4, const int rs, const float c) __attribute__((always_inline)) {
-                int mx = MAG0;
+                v2s mx = __builtin_bit_cast(v2s, MAG);
 #pragma unroll
                 for (int ni = 0; ni < NO; ++ni) {
-                    const float t = (float)(C[mi][ni][v] - rs) * c;
-                    float o;
-                    if (EPI == 1) {
-                        o = res[g & 1][v4][EPI == 1 ? ni : 0] + t;
+                    const float o = EPI == 1 ? res[g % RING][v4][EPI == 1 ? ni : 0] + (float)(C[mi][ni][v] - rs) * c : gated(mi, ni, v, rs, c);
+                    if (EPI == 1) __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(o), ro, coly[ni] + (uint32_t)v4 * narrow * 2, 0, NT);
+                    if (v4 % 2 == 0) {
+                        first[ni] = o;
                     } else {
-                        const float u = (float)(C[mi][ni + (EPI == 2 ? NO : 0)][v] - rs) * c;
-                        const float r = fmaxf(t, 0.0f);
-                        const float r2 = r * r;
-                        o = r2 * u;
+                        const uint32_t two = bl_pack2_bf16(first[ni], o);
+                        const uint32_t other = (uint32_t)bl_dpp<BL_DPP_QUAD_XOR1>((int)two);
+                        __builtin_amdgcn_raw_buffer_store_b32((int)__builtin_amdgcn_perm(other, two, pick), rx, colx[ni] + (uint32_t)(v4 - 1) * narrow, 0, 0);
+                        const v2s mag = __builtin_bit_cast(v2s, (int)two & in[ni]) + __builtin_bit_cast(v2s, MAG);
+                        mx = __builtin_elementwise_max(mx, mag);
                     }
-                    if (EPI == 1 || y) __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(o), ro, (colb[ni] + (uint32_t)v4 * narrow) * 2, 0, NT);
-                    const uint32_t bits = bl_pack2_bf16(o, o);
-                    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)bits, rx, colb[ni] + (uint32_t)v4 * narrow, 0, 0);
-                    const int mag = (int)(((bits << 16) & 0x7FFF0000u) + (uint32_t)MAG0);
-                    mx = max(mx, in[ni] ? mag : MAG0);
                 }
-                rowmax[v4] = __int_as_float(mx - MAG0);
+                if (v4 % 2 == 1) most[v4 / 2] = __builtin_bit_cast(int, mx);
             }, [&](const int g, const int ml) __attribute__((always_inline)) {
                 if constexpr (EPI == 1) {
-                    if (g + 2 < 4 * MI) fetch(g + 2);
+                    if (g + RING < 4 * MI) fetch(g + RING);
                 }
+                auto larger = [](const int a, const int b) __attribute__((always_inline)) {
+                    return __builtin_bit_cast(int, __builtin_elementwise_max(__builtin_bit_cast(v2s, a), __builtin_bit_cast(v2s, b)));
+                };
 #pragma unroll
-                for (int v4 = 0; v4 < 4; ++v4) rowmax[v4] = bl_half_max(rowmax[v4]);
+                for (int i = 0; i < 2; ++i) {
+                    int m = most[i];
+                    m = larger(m, bl_dpp<BL_DPP_QUAD_XOR1>(m));
+                    m = larger(m, bl_dpp<BL_DPP_QUAD_XOR2>(m));
+                    m = larger(m, bl_dpp<BL_DPP_ROW_HALF_MIRROR>(m));
+                    m = larger(m, bl_dpp<BL_DPP_ROW_MIRROR>(m));
+                    const auto t = __builtin_amdgcn_permlane16_swap((uint32_t)m, (uint32_t)m, false, false);
+                    most[i] = __builtin_bit_cast(int, __builtin_bit_cast(v2s, larger((int)t[0], (int)t[1])) - __builtin_bit_cast(v2s, MAG));
+                }
                 /* lane v4 of a half stands for row v4: one atomic instruction for eight rows */
-                const float mine = l32 == 0 ? rowmax[0] : l32 == 1 ? rowmax[1] : l32 == 2 ? rowmax[2] : rowmax[3];
-                if (l32 < 4 && m0 + ml + l32 < M) atomicMax(absmax + m0 + ml + l32, __float_as_int(mine));
+                const int pair = l32 < 2 ? most[0] : most[1];
+                const int mine = l32 & 1 ? pair & (int)0xFFFF0000 : pair << 16;
+                maxes[g] = mine;
             });
+            if (l32 < 4) {
+                const int m = m0 + wm0 + h * 4 + l32;
+#pragma unroll
+                for (int g = 0; g < 4 * MI; ++g)
+                    if (m + g * 8 < M) atomicMax(absmax + m + g * 8, maxes[g]);
+            }
         }
-        set = set + 1 == S ? 0 : set + 1;
-        const int* const slot = ahead + (wave * S + set) * 2;
-        tm = __builtin_amdgcn_readfirstlane(slot[0]);
+        set = set + 1 == SETS ? 0 : set + 1;
+        const int* const slot = ahead + (wave * SETS + set) * 2;
+        const int ntm = __builtin_amdgcn_readfirstlane(slot[0]);
+        if (ntm < 0) {
+            /* No load may write to LDS once the workgroup has gone: those behind the last tile are older than the tile's
+             * outputs, of which there are at least OUT (a wait for those would be half a microsecond). */
+            constexpr int OUT = EPI == 0 ? 16 * MI * NI : EPI == 1 ? 24 * MI * NI : 4 * MI * NI, MAXES = EPI == 0 ? 0 : 4 * MI;
+            if (m0 + BM <= M) BL_WAIT_VM(OUT + MAXES < 63 ? OUT + MAXES : 63);
+            else BL_WAIT_VM(OUT < 63 ? OUT : 63);
+            break;
+        }
+        tm = ntm;
         tn = __builtin_amdgcn_readfirstlane(slot[1]);
-        if (tm < 0) break;
     }
-    BL_WAIT_VM(0);
     if (stamp && tid == 0) {
         stamps[0] = clock64() - c_start;
         stamps[1] = wall_clock64() - w_start;

@@ -56,3 +56,34 @@ def test_nothing_beside_the_outputs(bl, M, N, K):
     for t, w in ((y, y_want), (acc, want)):
         assert torch.equal(t[pad:pad + M * N].view(M, N), w)
         assert (t[:pad] == 7).all() and (t[pad + M * N:] == 7).all()
+
+
+@pytest.mark.parametrize("M,N,K", [(3969, 4100, 128), (2049, 13824, 384), (1000, 2560, 640), (129, 644, 128), (64, 384, 1280), (65, 13824, 256), (300, 1664, 512)])
+def test_fused_epilogues(bl, M, N, K):
+    """Residual, and the gate where N allows it: the fp32 value, its bf16 narrowing, the row maxima and the int32 output, in memory
+    with something behind it."""
+    import ctypes
+    packed, beta, q, scale, rowsum, want, y_want = _product(bl, 1, M, N, K)
+    residual = torch.randn((M, N), generator=torch.Generator(device=DEV).manual_seed(4), device=DEV)
+    for kind in (bl.BL_EPI_RESIDUAL, bl.BL_EPI_RELU2_GATE):
+        if kind == bl.BL_EPI_RELU2_GATE and N % 128:
+            continue
+        gate, NO = kind == bl.BL_EPI_RELU2_GATE, N // 2 if kind == bl.BL_EPI_RELU2_GATE else N
+        r = torch.relu(y_want[:, :NO])
+        t = (r * r) * y_want[:, NO:] if gate else residual + y_want
+        for with_y, with_acc in ((True, False), (False, True)):
+            y, xb = torch.full((M * NO + 500,), 7.0, device=DEV), torch.full((M * NO + 500,), 7.0, dtype=torch.bfloat16, device=DEV)
+            acc, top = torch.full((M * N + 500,), 7, dtype=torch.int32, device=DEV), torch.zeros(M + 8, device=DEV)
+            ep = bl.GemmEpilogue()
+            ep.kind, ep.residual, ep.x_bf16, ep.absmax = kind, None if gate else residual.data_ptr(), xb.data_ptr(), top.data_ptr()
+            ep.y = y.data_ptr() if with_y else None
+            bl._check(bl.load().bl_gemm_w158a8_fused(packed.data_ptr(), beta.data_ptr(), 1, q.data_ptr(), scale.data_ptr(), rowsum.data_ptr(), M, N, K,
+                                                     ctypes.byref(ep), acc.data_ptr() if with_acc else None, torch.cuda.current_stream().cuda_stream),
+                      "bl_gemm_w158a8_fused")
+            torch.cuda.synchronize()
+            b = t.to(torch.bfloat16)
+            assert torch.equal(xb[:M * NO].view(M, NO), b) and torch.equal(top[:M], b.abs().amax(1).float())
+            assert (xb[M * NO:] == 7).all() and (top[M:] == 0).all()
+            assert not with_y or torch.equal(y[:M * NO].view(M, NO), t)
+            assert not with_acc or torch.equal(acc[:M * N].view(M, N), want)
+            assert (y[M * NO if with_y else 0:] == 7).all() and (acc[M * N if with_acc else 0:] == 7).all()
