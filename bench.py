@@ -563,8 +563,8 @@ def main():
                                             "us_per_layer_at_that_rate": round(out_bytes / write_roof / 1e3, 1)},
                           "roofline": {"bound": "mfma", "achieved": round(tops, 2), "peak": INT8_PEAK_TOPS,
                                        "unit": "TOP/s", "frac": round(tops / INT8_PEAK_TOPS, 4),
-                                       "traffic": profiled_traffic("bl_gemm_tile256:layer_m2048") if Mp == 2048 else None,
-                                       "kernel": "bl_gemm_tile256", "achievable": round(mfma_roof, 1),
+                                       "traffic": profiled_traffic("bl_gemm_pipe:layer_m2048") if Mp == 2048 else None,
+                                       "kernel": "bl_gemm_pipe", "achievable": round(mfma_roof, 1),
                                        "frac_of_achievable": round(tops / mfma_roof, 4),
                                        "achievable_random_operands": round(mfma_roof_rnd, 1),
                                        "achievable_random_operands_clock_mhz": mfma_rnd_mhz,

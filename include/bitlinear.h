@@ -337,12 +337,12 @@ bl_status bl_quant_from_absmax(const uint16_t* X, float* absmax, int64_t M, int6
  * partial sums meet in scratch inside `table` through integer atomics (exact, order-free) and
  * are finished (row sum, rescale, residual) by a second small launch of the same run, which
  * also clears the scratch.  plan->entries tells how many entries the table holds.
- * With more than 48 tokens, and every row length a multiple of 128 after padding, the table is
+ * With more than 48 tokens (33 to 48 in tables of 128 tiles and more), and every row length a multiple of 128 after padding, the table is
  * walked by the prefill tile kernel instead (Section 5.1: packed tiles expanded to int8 on chip
- * for the int8 matrix cores): 64 x 128 output tiles, both operands streamed through LDS, the
- * tiles of all products balanced over the resident workgroups by their k steps, one launch,
- * weights read once; plan->red_ints then holds the tile count (one token: which form of the
- * kernel walks the table, or, in the k-major form, the partial sums kept in LDS).
+ * for the int8 matrix cores): tiles of all tokens x 256 weight rows, both operands streamed
+ * through LDS, the tiles of all products balanced over the resident workgroups by their k steps, one
+ * launch, weights read once; plan->red_ints then holds the table's blocks of 128 weight rows (one token:
+ * which form of the kernel walks the table, or, in the k-major form, the partial sums kept in LDS).
  * Same arithmetic, bit for bit, as bl_gemv_w158a8 on each product. */
 enum { BL_STACK_MAX_COUNT = 1024, BL_STACK_MAX_TOKENS = 64 };
 typedef struct {
@@ -390,7 +390,7 @@ bl_status bl_debug_force_path(int path);
  *                         tiles, dword stores of 32 consecutive floats per row, non-temporal) and
  *                         does nothing else: the rate at which the outputs of a prefill launch can be
  *                         written when every workgroup stores at once.  workgroups_per_cu 1..8
- *                         (0 = 3, the occupancy of the tile kernel).
+ *                         (0 = 3).
  *   bl_probe_mfma_i8      one launch of `iters` x 4 back-to-back v_mfma_i32_32x32x32_i8 per
  *                         wave, operands in registers; *ops (HOST, optional) receives the
  *                         integer operations of the launch (2 per multiply-accumulate).

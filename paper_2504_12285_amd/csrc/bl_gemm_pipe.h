@@ -35,9 +35,15 @@
  *
  * EPI: 0 = int32 and/or fp32 outputs, optional residual; 1 = "residual": t = residual + product as fp32 (y, optional) and
  * bf16 (xb), the row maximum of |bf16(t)| folded into absmax; 2 = "squared-ReLU gate": a wave's NI blocks of 32 weight
- * rows are NI/2 blocks of gate rows and the NI/2 matching blocks of up rows (n and N/2 + n), t = (relu(g)*relu(g))*u. */
+ * rows are NI/2 blocks of gate rows and the NI/2 matching blocks of up rows (n and N/2 + n), t = (relu(g)*relu(g))*u.
+ *
+ * TABLE: the tiles of a whole table of products of at most BM tokens (device arrays: items; workgroup b takes tile_list[wg_start[b] ..
+ * wg_start[b+1]), an entry = product << BL_TILE_BITS | block of BN weight rows): the batched decode of a stack of BitLinears
+ * in one launch whose weights are read once.  K, N and the pointers are then those of the product in hand; rows are whole
+ * k steps, layout 1, plain epilogue. */
 #pragma once
 #include "bl_device.h"
+#include "bl_host.h"
 
 #include <type_traits>
 
@@ -48,17 +54,19 @@ struct bl_pipe_geom {
     static constexpr int BM = WM * MI * 32, BN = WN * NI * 32, THREADS = WM * WN * 64;
     static constexpr int A_BYTES = BM * GP_BK, W_BYTES = BN * GP_BK / 4, STAGE = A_BYTES + W_BYTES;
     static constexpr int SETS = S + 1;                      /* of row terms: the tile in its epilogue and those that the loads may have reached */
-    static constexpr int LDS = S * STAGE + SETS * (BM + WM * WN) * 8;
+    static constexpr int LDS = S * STAGE + SETS * (BM * 8 + WM * WN * 16);
 };
 
-template <int MI, int NI, int WM, int WN, int S, int OCC, int EPI, int LAYOUT>
+template <int MI, int NI, int WM, int WN, int S, int OCC, int EPI, int LAYOUT, bool TABLE = false>
 __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t* __restrict__ packed, const int8_t* __restrict__ q,
                                                                   const int32_t* __restrict__ rowsum, const float* __restrict__ beta,
                                                                   const float* __restrict__ scale, int M, int N, int K, int tiles_m,
                                                                   int tiles_n, int gs, int band, int vgrid, int grid,
                                                                   const float* __restrict__ residual, int32_t* __restrict__ acc,
                                                                   float* __restrict__ y, uint16_t* __restrict__ xb,
-                                                                  int* __restrict__ absmax, long long* __restrict__ stamps) {
+                                                                  int* __restrict__ absmax, long long* __restrict__ stamps,
+                                                                  const bl_tile_item* __restrict__ items, const int* __restrict__ wg_start,
+                                                                  const int* __restrict__ tile_list) {
 #if defined(__HIP_DEVICE_COMPILE__)   /* (the host has no type for a buffer descriptor) */
     using G = bl_pipe_geom<MI, NI, WM, WN, S>;
     constexpr int SETS = G::SETS, NW = WM * WN, BM = G::BM, BN = G::BN, STAGE = G::STAGE, AB = G::A_BYTES;
@@ -70,14 +78,21 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
     typedef __attribute__((address_space(3))) void* lds_p;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     int* const terms = (int*)(smem + S * STAGE);             /* SETS sets of BM row sums and BM scales */
-    int* const ahead = terms + SETS * 2 * BM;                /* each wave's tiles that the loads have reached: SETS of (tm, tn) */
+    int* const ahead = terms + SETS * 2 * BM;                /* each wave's tiles that the loads have reached: SETS of four ints (tm, tn; TABLE: steps) */
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, h = lane >> 5;
     const int wm0 = (wave / WN) * (MI * 32), wn0 = (wave % WN) * (NI * 32);
-    const int kb = K / 4, steps = (K + GP_BK - 1) / GP_BK;
+    static_assert(!TABLE || (EPI == 0 && LAYOUT == 1 && WM == 1), "one block of rows, plain epilogue");
+    /* of the product whose tile the loads have reached (one product: of all) */
+    int lN = N, lK = K;
+    const uint8_t* lpacked = packed;
+    const int8_t* lq = q;
+    const int32_t* lrowsum = rowsum;
+    const float* lscale = scale;
+    int steps = (K + GP_BK - 1) / GP_BK, lsteps = steps;
     /* at the end of step `zstep` of a tile the codes at hand are those of a half step */
-    const int zstep = K % GP_BK == 0 ? -1 : max(steps - 2, 0), dead = K < GP_BK ? 1 : 0;
-    const float bt = (EPI != 0 || y != nullptr) ? *beta : 0.0f;
+    const int zstep = TABLE || K % GP_BK == 0 ? -1 : max(steps - 2, 0), dead = !TABLE && K < GP_BK ? 1 : 0;
+    float bt = !TABLE && (EPI != 0 || y != nullptr) ? *beta : 0.0f;
 
     /* XCD-aware tile order: workgroup L runs on XCD L%8.  The row tiles are cut into bands so narrow that
      * a band's activation panel stays in an XCD's 4 MB L2 while its weight tiles stream through, row tiles
@@ -101,7 +116,16 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
         tm = b * band + (in - tn * rows);
         return true;
     };
+    int vend = vgrid;
+    if constexpr (TABLE) vend = wg_start[blockIdx.x + 1];
     auto next_tile = [&](int vb, int& tm, int& tn) {
+        if constexpr (TABLE) {                               /* vb: position in the list; tm: the product */
+            if (vb >= vend) return -1;
+            const int e = tile_list[vb];
+            tm = e >> BL_TILE_BITS;
+            tn = e & ((1 << BL_TILE_BITS) - 1);
+            return vb;
+        }
         for (; vb < vgrid; vb += grid)
             if (tile_of(vb, tm, tn)) return vb;
         return -1;
@@ -117,21 +141,35 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
         return (j + 1) * NW <= WP ? j * NW + wave : j * NW + wave % (WP - j * NW > 0 ? WP - j * NW : 1);
     };
     uint32_t ao[AL], wo[WL];
+    auto offsets = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < AL; ++j) {
-        const int row = (j * NW + wave) * 8 + (lane >> 3);
-        ao[j] = (uint32_t)row * (uint32_t)K + (uint32_t)(((lane & 7) ^ ((row >> 1) & 7)) * 16);
-    }
+        for (int j = 0; j < AL; ++j) {
+            const int row = (j * NW + wave) * 8 + (lane >> 3);
+            ao[j] = (uint32_t)row * (uint32_t)lK + (uint32_t)(((lane & 7) ^ ((row >> 1) & 7)) * 16);
+        }
 #pragma unroll
-    for (int j = 0; j < WL; ++j)                             /* (inside the piece) */
-        wo[j] = (uint32_t)(lane >> 1) * (uint32_t)kb + (uint32_t)(((lane & 1) ^ ((lane >> 4) & 1)) * 16);
+        for (int j = 0; j < WL; ++j)                         /* (inside the piece) */
+            wo[j] = (uint32_t)(lane >> 1) * (uint32_t)(lK / 4) + (uint32_t)(((lane & 1) ^ ((lane >> 4) & 1)) * 16);
+    };
+    if constexpr (!TABLE) offsets();
 
     /* the load cursor: tile, k step, buffer, set of row terms */
     int lvb, ltm = 0, ltn = 0, lkk = 0, lbuf = 0, lset = 0;
     decltype(rsrc(nullptr, 0)) ra, rw[WL];
     auto setup = [&]() {
-        const int m0 = ltm * BM, rows = min(BM, M - m0);
-        ra = rsrc(q + (int64_t)m0 * K, (uint32_t)rows * (uint32_t)K);
+        if constexpr (TABLE) {
+            const bl_tile_item it = items[ltm];
+            lpacked = it.packed;
+            lq = it.q;
+            lrowsum = it.rowsum;
+            lscale = it.scale;
+            lN = it.N;
+            lK = it.K;
+            lsteps = lK / GP_BK;
+            offsets();
+        }
+        const int m0 = TABLE ? 0 : ltm * BM, rows = min(BM, M - m0), kb = lK / 4;
+        ra = rsrc(lq + (int64_t)m0 * lK, (uint32_t)rows * (uint32_t)lK);
 #pragma unroll
         for (int j = 0; j < WL; ++j) {
             const int p = wpiece(j);
@@ -140,19 +178,19 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
                 n = (p % NI >= NI / 2 ? N / 2 : 0) + ltn * (BN / 2) + (p / NI) * (NI * 16) + (p % (NI / 2 > 0 ? NI / 2 : 1)) * 32;
             else
                 n = ltn * BN + p * 32;
-            if (n > N - 32) n = max(min(n, N - 1) & ~31, 0);          /* blocks past the end: the last one again */
-            rw[j] = rsrc(packed + (int64_t)n * kb, (uint32_t)min(32, N - n) * (uint32_t)kb);
+            if (n > lN - 32) n = max(min(n, lN - 1) & ~31, 0);          /* blocks past the end: the last one again */
+            rw[j] = rsrc(lpacked + (int64_t)n * kb, (uint32_t)min(32, lN - n) * (uint32_t)kb);
         }
     };
     auto setup_terms = [&]() __attribute__((always_inline)) {
-        const int m0 = ltm * BM, rows = min(BM, M - m0);
+        const int m0 = TABLE ? 0 : ltm * BM, rows = min(BM, M - m0);
 #pragma unroll
         for (int j = 0; j < (2 * BM + NW * 64 - 1) / (NW * 64); ++j) {
             const int g = (j * NW + wave) * 64;
             if (g >= 2 * BM) break;
             const bool s = g >= BM;
-            const void* src = s ? (const void*)(scale + m0) : (const void*)(rowsum + m0);
-            const auto rt = rsrc(src, s && !scale ? 0 : rows * 4);
+            const void* src = s ? (const void*)(lscale + m0) : (const void*)(lrowsum + m0);
+            const auto rt = rsrc(src, s && !lscale ? 0 : rows * 4);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rt, (lds_p)(terms + lset * 2 * BM + g), 4, ((s ? g - BM : g) + lane) * 4, 0, 0, 0);
         }
     };
@@ -161,28 +199,29 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
     auto advance = [&](const bool first) __attribute__((always_inline)) {
         if (!first) {
             lbuf = lbuf + 1 == S ? 0 : lbuf + 1;
-            if (++lkk == steps) {
+            if (++lkk == lsteps) {
                 lkk = 0;
                 if (lvb >= 0) {
-                    lvb = next_tile(lvb + grid, ltm, ltn);
+                    lvb = next_tile(lvb + (TABLE ? 1 : grid), ltm, ltn);
                     lset = lset + 1 == SETS ? 0 : lset + 1;
                     if (lvb >= 0) {
                         setup();
                         setup_terms();
                     } else {
-                        ra = rsrc(q, 0);
+                        ra = rsrc(lq, 0);
 #pragma unroll
-                        for (int j = 0; j < WL; ++j) rw[j] = rsrc(packed, 0);
+                        for (int j = 0; j < WL; ++j) rw[j] = rsrc(lpacked, 0);
                         ltm = -1;
                     }
-                    int* const slot = ahead + (wave * SETS + lset) * 2;
+                    int* const slot = ahead + (wave * SETS + lset) * 4;
                     slot[0] = ltm;
                     slot[1] = ltn;
+                    if constexpr (TABLE) slot[2] = lsteps;
                 }
             }
         }
         lst = smem + lbuf * STAGE;
-        lko = lvb < 0 ? 0 : max(min(lkk * GP_BK, K - GP_BK), 0);
+        lko = lvb < 0 ? 0 : max(min(lkk * GP_BK, lK - GP_BK), 0);
     };
     auto load = [&](const int j) __attribute__((always_inline)) {
         if (j < AL)
@@ -210,7 +249,7 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
     for (int ks = 0; ks < 4; ++ks) au[ks] = a_off + ((4 * h + ks) ^ a_swz) * 16;
 
     int tm, tn;
-    lvb = next_tile((int)blockIdx.x, ltm, ltn);
+    lvb = next_tile(TABLE ? wg_start[blockIdx.x] : (int)blockIdx.x, ltm, ltn);
     if (lvb < 0) return;
     /* measurement hook: workgroup 0 counts shader clocks and wall-clock ticks over its lifetime */
     const bool stamp = stamps != nullptr && blockIdx.x == 0;
@@ -222,11 +261,12 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
     tm = ltm;
     tn = ltn;
     setup();
+    if constexpr (TABLE) steps = lsteps;
     if (steps >= INIT) {
 #pragma unroll
         for (int s = 0; s < INIT; ++s) {
             lst = smem + s * STAGE;
-            lko = min(s * GP_BK, max(K - GP_BK, 0));
+            lko = min(s * GP_BK, max(lK - GP_BK, 0));
 #pragma unroll
             for (int j = 0; j < (s < INIT - 1 ? LOADS : FIRST); ++j) load(j);
             if (s == 0) setup_terms();                       /* (behind the loads that are waited for first) */
@@ -257,7 +297,7 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
     for (int ks = 0; ks < (DEEP ? 4 : 1); ++ks)
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) a[ks][mi] = *(const bl_v4i*)(smem + au[ks] + mi * 32 * GP_BK);
-    if (K < GP_BK && h == 1) {
+    if (!TABLE && K < GP_BK && h == 1) {
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni) wq[0][ni] = bl_v4i{0, 0, 0, 0};
     }
@@ -304,7 +344,15 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
     bl_v4i bop = bl_unpack16(TURN_W ? bl_word_to_k16((uint32_t)wq[0][0][0]) : (uint32_t)wq[0][0][0]);
 
     while (true) {
-        const int m0 = tm * BM, n0 = tn * BN;
+        const int m0 = TABLE ? 0 : tm * BM, n0 = tn * BN;
+        if constexpr (TABLE) {                               /* what the epilogue stores to arrives under the k loop */
+            const bl_tile_item it = items[tm];
+            N = it.N;
+            acc = it.acc;
+            y = it.y;
+            residual = it.residual;
+            bt = y ? *bl_gc<float>(it.beta) : 0.0f;
+        }
         bl_v16i C[MI][NI];
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
@@ -652,7 +700,7 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
             }
         }
         set = set + 1 == SETS ? 0 : set + 1;
-        const int* const slot = ahead + (wave * SETS + set) * 2;
+        const int* const slot = ahead + (wave * SETS + set) * 4;
         const int ntm = __builtin_amdgcn_readfirstlane(slot[0]);
         if (ntm < 0) {
             /* No load may write to LDS once the workgroup has gone: those behind the last tile are older than the tile's
@@ -664,6 +712,7 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
         }
         tm = ntm;
         tn = __builtin_amdgcn_readfirstlane(slot[1]);
+        if constexpr (TABLE) steps = __builtin_amdgcn_readfirstlane(slot[2]);
     }
     if (stamp && tid == 0) {
         stamps[0] = clock64() - c_start;

@@ -27,7 +27,10 @@ int bl_forced_decode_path(void);
  * tile kernel, or NULL (the default).  Process-wide, atomic. */
 int64_t* bl_clock_stamps(void);
 
-/* One product of a table walked by the TABLE form of bl_gemm_tile256 (device memory). */
+/* One product of a table walked by the TABLE form of bl_gemm_pipe (device memory).  An entry of the tile list: product <<
+ * BL_TILE_BITS | block of BL_TILE_ROWS weight rows (at most 1024 products of 2^24 rows). */
+#define BL_TILE_BITS 17
+#define BL_TILE_ROWS 256
 struct bl_tile_item {
     const uint8_t* packed;
     const int8_t* q;
@@ -42,5 +45,4 @@ struct bl_tile_item {
 
 /* Launch of that table walk (bl_gemm.hip) for the batched streamed decode (bl_stream.hip). */
 int bl_gemm_table_blocks(void);
-bl_status bl_gemm_table_launch(const bl_tile_item* items, const int* tile0, int nitems, int total_tiles, int M,
-                               int blocks, const int* wg_start, const int* tile_list, bl_stream s);
+bl_status bl_gemm_table_launch(const bl_tile_item* items, int M, int blocks, const int* wg_start, const int* tile_list, bl_stream s);

@@ -1375,31 +1375,33 @@ extern "C" size_t bl_stack_table_bytes_batched(const bl_decode_desc* descs, int 
     return total;
 }
 
-/* More than 48 tokens per product: the token rows of most products no longer fit LDS whole, the
- * work is a dense contraction, and the table is walked by the prefill tile kernel instead
- * (64 x 128 tiles, both operands streamed through LDS per k step, weights read once; measured on
- * the 30-layer table at M = 64: 6.3 us per layer against 9.3 with two token groups of 32; at
- * M = 48 the two are equal, below the LDS-resident form wins).  Needs rows padded to 128. */
-#define BL_MB_TILE_ROUTE_MIN 49
+/* More than 32 tokens per product: the token rows of most products no longer fit LDS whole and go in two groups, which read the
+ * weights twice; the work is a dense contraction, and the table is walked by the prefill tile kernel instead (tiles of 64 x 256,
+ * both operands streamed through LDS per k step, weights read once).  Needs rows padded to 128; up to 48 tokens, 128 tiles
+ * (a single layer stays: two groups of 2560 / 6912 at 36, 40, 44, 48 tokens 21.7, 24.6, 20.3, 25.6 us, tiles 22.7).  us, LDS-resident
+ * form / tiles: thirty layers of 2560 / 6912 at 32 tokens 146 / 156, 36 182 / 158, 48 196 / 167; twenty of 1024 / 2816 at 32
+ * 26.2 / 24.0, 36 36.2 / 24.3, 48 40.5 / 26.2; four of 4096 / 11008 at 36 93.4 / 51.8, 48 94.8 / 54.0. */
+#define BL_MB_TILE_ROUTE_MIN 33
 static bool mb_tile_route(const bl_decode_desc* descs, int count, int64_t M) {
     if (M < BL_MB_TILE_ROUTE_MIN) return false;
-    int64_t tiles = 0;
+    int64_t tiles = 0, entries = 0;
     for (int i = 0; i < count; ++i) {
         if (bl_kpad(descs[i].K) % 128 != 0) return false;
         tiles += (descs[i].N + 127) / 128;
+        entries += (descs[i].N + BL_TILE_ROWS - 1) / BL_TILE_ROWS;
     }
+    if (M <= 48 && entries < 128) return false;
     return tiles <= ((int64_t)1 << 22);       /* beyond ~4 M tiles (a 16 MB tile list) the table stays on bl_stream_mb */
 }
 
 /* Device buffer of the tile route: [products][first tile of each product][first list position of
  * each workgroup][tile list]. */
 struct tile_layout_t {
-    size_t t0_off, wg_off, list_off, total;
+    size_t wg_off, list_off, total;
 };
 static tile_layout_t tile_layout(int count, int64_t tiles) {
     tile_layout_t L;
-    L.t0_off = align_up((size_t)count * sizeof(bl_tile_item), 256);
-    L.wg_off = L.t0_off + align_up((size_t)count * sizeof(int), 256);
+    L.wg_off = align_up((size_t)count * sizeof(bl_tile_item), 256);
     L.list_off = L.wg_off + align_up((size_t)(BL_STREAM_MAX_BLOCKS + 1) * sizeof(int), 256);
     L.total = L.list_off + align_up((size_t)tiles * sizeof(int), 256);
     return L;
@@ -1420,14 +1422,15 @@ static bl_status stack_build_tiles(const bl_decode_desc* descs, int count, int l
     if (resident < 1) return BL_ERR_HIP;
     const int64_t tiles = tile_route_tiles(descs, count);
     const tile_layout_t L = tile_layout(count, tiles);
-    int blocks = (int)(tiles < resident ? tiles : resident);
+    int64_t entries = 0;                                  /* of the list: blocks of BL_TILE_ROWS rows, no more than `tiles` */
+    for (int i = 0; i < count; ++i) entries += (descs[i].N + BL_TILE_ROWS - 1) / BL_TILE_ROWS;
+    int blocks = (int)(entries < resident ? entries : resident);
     if (blocks > BL_STREAM_MAX_BLOCKS) blocks = BL_STREAM_MAX_BLOCKS;
     std::vector<uint8_t> blob(L.total, 0);
     bl_tile_item* items = (bl_tile_item*)blob.data();
-    int* tile0 = (int*)(blob.data() + L.t0_off);
     int* wg_start = (int*)(blob.data() + L.wg_off);
     int* tile_list = (int*)(blob.data() + L.list_off);
-    int64_t packed_bytes = 0, t = 0;
+    int64_t packed_bytes = 0;
     /* (cost, first tile, tiles) of each product; cost of a tile = its k steps + a fixed part for
      * set-up and stores */
     std::vector<std::pair<int, int>> by_cost;             /* (-cost, product) */
@@ -1436,8 +1439,6 @@ static bl_status stack_build_tiles(const bl_decode_desc* descs, int count, int l
         const int64_t Kp = bl_kpad(d.K);
         items[i] = bl_tile_item{d.packed, d.q, d.rowsum, d.beta, d.y ? d.scale : nullptr, d.residual, d.acc, d.y,
                                 (int)d.N, (int)Kp};
-        tile0[i] = (int)t;
-        t += (d.N + 127) / 128;
         packed_bytes += d.N * (Kp / 4);
         by_cost.push_back({-(int)(Kp / 128 + 4), i});
     }
@@ -1447,11 +1448,11 @@ static bl_status stack_build_tiles(const bl_decode_desc* descs, int count, int l
     std::priority_queue<std::pair<int64_t, int>, std::vector<std::pair<int64_t, int>>, std::greater<std::pair<int64_t, int>>> load;
     for (int b = 0; b < blocks; ++b) load.push({0, b});
     for (const auto& pc : by_cost) {
-        const int i = pc.second, n_tiles = (int)((descs[i].N + 127) / 128);
+        const int i = pc.second, n_tiles = (int)((descs[i].N + BL_TILE_ROWS - 1) / BL_TILE_ROWS);
         for (int j = 0; j < n_tiles; ++j) {
             auto top = load.top();
             load.pop();
-            lists[(size_t)top.second].push_back(tile0[i] + j);
+            lists[(size_t)top.second].push_back(i << BL_TILE_BITS | j);
             top.first += -pc.first;
             load.push(top);
         }
@@ -1474,7 +1475,7 @@ static bl_status stack_build_tiles(const bl_decode_desc* descs, int count, int l
     plan->table_bytes = (int64_t)bl_stack_table_bytes_batched(descs, count, M);
     plan->tokens = M;
     plan->entries = count;
-    plan->red_ints = (int32_t)tiles;                      /* tiles of the whole table */
+    plan->red_ints = (int32_t)tiles;                      /* blocks of 128 rows of the whole table: room for the list */
     plan->norm = 3;                                       /* the tile route */
     return BL_OK;
 }
@@ -1914,8 +1915,7 @@ extern "C" bl_status bl_stack_run(void* table, const bl_stack_plan* plan, bl_str
         if (plan->wg_offset != (int64_t)Lt.wg_off || plan->prep_offset != (int64_t)Lt.list_off) return BL_ERR_VALUE;
         if (!bl_aligned(table, 256)) return BL_ERR_ALIGN;
         const uint8_t* tb = (const uint8_t*)table;
-        return bl_gemm_table_launch((const bl_tile_item*)tb, (const int*)(tb + Lt.t0_off), plan->count, plan->red_ints,
-                                    plan->tokens, plan->blocks, (const int*)(tb + Lt.wg_off),
+        return bl_gemm_table_launch((const bl_tile_item*)tb, plan->tokens, plan->blocks, (const int*)(tb + Lt.wg_off),
                                     (const int*)(tb + Lt.list_off), s);
     }
     if (plan->tokens > 1) {
