@@ -15,7 +15,9 @@ TORCH_EXT_PATH = os.path.join(PKG_DIR, "_bl_torch" + sysconfig.get_config_var("E
 TORCH_EXT_SOURCE = os.path.join(CSRC, "bl_torch.cpp")
 SOURCES = ["bl_api.cpp", "bl_pack.hip", "bl_quant.hip", "bl_gemv.hip", "bl_gemv_one.hip", "bl_gemv_panel.hip", "bl_gemm.hip", "bl_stream.hip", "bl_probe.hip"]
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-ffp-contract=off",
-               "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+               "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+               # the first 14 scalar registers of a kernel's arguments are in place when its waves start
+               "-mllvm", "-amdgpu-kernarg-preload-count=14"]
 
 
 def sources():

@@ -83,81 +83,95 @@ __device__ __forceinline__ float bl_norm_factor(double ss, double inv_k, int K, 
     return r;
 }
 
-/* What the kernel needs to know, fetched from the arguments in one go. */
-struct bl_one_args {
-    const void* packed;
-    const void* in0;                 /* bf16, fp32 or int8 row */
-    const float* in1;                /* second fp32 row: the other summand, or the up half */
+/* What the kernel needs to know late, fetched from the arguments in one go ... */
+struct bl_one_rest {
     float* aux_out;
-    const float* gain;
     const float* beta;
     const float* scale;              /* int8 input */
-    const float* residual;
     int32_t* acc;
     float* y;
     int8_t* q_out;
     float* scale_out;
-    int N, K, rows, layout;          /* rows of a workgroup */
-    int kind, voff, hd;
-    uint32_t mul_hd, mul_group;      /* ceil(2^32 / .): quotients by a multiply (mul_group = 0: group 1) */
-    float eps, fixed_scale;
     double inv_k;
+    int layout;
+    float eps, fixed_scale;
 };
-enum { BL_ONE_BF16, BL_ONE_F32, BL_ONE_PAIR, BL_ONE_INT8 };   /* plain / V gather, residual or gate, quantised */
+/* ... and what its first loads need (bl_gemv_one). */
+struct bl_one_args : bl_one_rest {
+    const void* packed;
+    const void* in0;                 /* bf16, fp32 or int8 row */
+    const float* in1;                /* second fp32 row: the other summand, or the up half */
+    const float* gain;
+    const float* residual;
+    int N, K, rows;                  /* rows of a workgroup */
+    int kind, voff, hd;
+    uint32_t mul_hd, mul_group;      /* V gather: ceil(2^32 / .): quotients by a multiply (mul_group = 0: group 1) */
+};
+typedef uint32_t bl_v4u __attribute__((ext_vector_type(4)));
+enum { BL_ONE_BF16, BL_ONE_F32, BL_ONE_PAIR, BL_ONE_INT8, BL_ONE_V };   /* plain, residual or gate, quantised, V gather */
 
 /* G lanes share a weight row (64 / G rows at a time, RW times); NL: 16-byte weight loads per lane and
  * row (K <= 64 * G * NL); UN: units of four elements of the activation row per thread (K <= 4 * UN *
  * threads).  SRC and NORM fix which loads there are, so that all of them go out without a wait. */
 template <int SRC, int G, int RW, int NL, int UN, bool NORM>
-__global__ __launch_bounds__(BL_ONE_WAVES * 64) void bl_gemv_one(const bl_one_args Pin) {
+/* What the row's and the weights' loads need comes first, 14 registers of it (`where`: weights, row; `beside`: second row or the two
+ * multipliers of the V gather, gains; `size`: residual, N, K; `how`: rows of a workgroup | kind << 8 | head size << 16, offset of V):
+ * the hardware has them in place when a wave starts (the build asks for that), the structure behind them is fetched while the loads
+ * travel.  One token through thirty layers 547 -> 527 us, fifteen without normalisation 241 -> 229 (the same fetched by the
+ * kernel: 537, 234).  Four vectors and not nine scalars, which cost the host .2 us more a launch. */
+__global__ __launch_bounds__(BL_ONE_WAVES * 64) void bl_gemv_one(const bl_v4u where, const bl_v4u beside, const bl_v4u size, const bl_v2u how,
+                                                                 const bl_one_rest Pin) {
     constexpr int R = 64 / G, NW = BL_ONE_WAVES, nthreads = NW * 64;
     __shared__ __attribute__((aligned(16))) uint8_t Qs[SRC == BL_ONE_INT8 ? 16 : (G * NL + 1) * BL_ONE_QSTRIDE];
     __shared__ float fs[NW];
     __shared__ double sd[NW];
     __shared__ int qsum[NW];
-    bl_one_args P = Pin;
-    /* one pin for all: the fields arrive together and stay in scalar registers */
-    asm volatile("" : "+s"(P.packed), "+s"(P.in0), "+s"(P.in1), "+s"(P.aux_out), "+s"(P.gain), "+s"(P.beta), "+s"(P.scale),
-                      "+s"(P.residual), "+s"(P.acc), "+s"(P.y), "+s"(P.q_out), "+s"(P.scale_out), "+s"(P.N), "+s"(P.K),
-                      "+s"(P.rows), "+s"(P.layout), "+s"(P.kind), "+s"(P.voff), "+s"(P.hd), "+s"(P.mul_hd),
-                      "+s"(P.mul_group), "+s"(P.eps), "+s"(P.fixed_scale), "+s"(P.inv_k));
-    const int N = P.N, K = P.K, nchunks = K >> 6;
+    const auto wide = [](uint32_t lo, uint32_t hi) { return (uint64_t)hi << 32 | lo; };
+    const void *const packed = (const void*)wide(where[0], where[1]), *const in0 = (const void*)wide(where[2], where[3]);
+    const uint64_t second = wide(beside[0], beside[1]);
+    const float *const in1 = (const float*)second, *const gain = (const float*)wide(beside[2], beside[3]);
+    const float* const residual = (const float*)wide(size[0], size[1]);
+    const int N = (int)size[2], K = (int)size[3], voff = (int)how[1];
+    const uint32_t rows_kind = how[0];
+    const int rows = rows_kind & 0xFF, kind = (rows_kind >> 8) & 0xFF;
+    const int nchunks = K >> 6;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int units = K >> 2;
     const bool first_block = blockIdx.x == 0;
     const bool norm = NORM;
     const int r = lane / G, g = lane % G;
-    const int n0 = (int)blockIdx.x * P.rows + w * RW * R;  /* first row of this wave; row j * R + r is lane (r, g)'s */
-    const int nend = min(N, ((int)blockIdx.x + 1) * P.rows);
+    const int n0 = (int)blockIdx.x * rows + w * RW * R;  /* first row of this wave; row j * R + r is lane (r, g)'s */
+    const int nend = min(N, ((int)blockIdx.x + 1) * rows);
 
     /* 1. every load of the row, then every load of the weights.  All but the residual's are
      * unconditional (out of range: a valid address, and a zero chunk of activations or no store), so
      * the waits count exactly and the row is not waited for together with the weights. */
     float res = 0.0f;
-    if (P.residual && g < RW && n0 + g * R + r < nend) res = bl_gc<float>(P.residual)[n0 + g * R + r];
+    if (residual && g < RW && n0 + g * R + r < nend) res = bl_gc<float>(residual)[n0 + g * R + r];
     bl_v4i aq[NL][4];                                      /* this lane's activations: dword s of packed word d */
     bl_v2u xb[UN];
     bl_v4f ra[UN], rb[UN], rg[UN];
-    const bool has_gain = NORM && P.gain != nullptr;
+    const bool has_gain = NORM && gain != nullptr;
     if (SRC != BL_ONE_INT8) {
 #pragma unroll
         for (int j = 0; j < UN; ++j) {
             int u = tid + j * nthreads;
             u = u < units ? u : units - 1;
             if (SRC == BL_ONE_BF16) {
-                xb[j] = bl_gc<bl_v2u>(P.in0)[u];
+                xb[j] = bl_gc<bl_v2u>(in0)[u];
             } else {
                 int off = u * 4;
-                if (SRC == BL_ONE_F32 && P.kind == BL_PROD_ATTN_V) {
-                    const int head = (int)__umulhi((uint32_t)off, P.mul_hd);
-                    const int kv = P.mul_group ? (int)__umulhi((uint32_t)head, P.mul_group) : head;
-                    off = P.voff + kv * P.hd + (off - head * P.hd);
+                if (SRC == BL_ONE_V) {
+                    const int hd = rows_kind >> 16, head = (int)__umulhi((uint32_t)off, (uint32_t)second);
+                    const uint32_t mul_group = (uint32_t)(second >> 32);
+                    const int kv = mul_group ? (int)__umulhi((uint32_t)head, mul_group) : head;
+                    off = voff + kv * hd + (off - head * hd);
                 }
-                ra[j] = *bl_gc<bl_v4f>((const float*)P.in0 + off);
-                if (SRC == BL_ONE_PAIR) rb[j] = *bl_gc<bl_v4f>(P.in1 + off);
+                ra[j] = *bl_gc<bl_v4f>((const float*)in0 + off);
+                if (SRC == BL_ONE_PAIR) rb[j] = *bl_gc<bl_v4f>(in1 + off);
             }
-            if (NORM && has_gain) rg[j] = *bl_gc<bl_v4f>(P.gain + u * 4);
+            if (NORM && has_gain) rg[j] = *bl_gc<bl_v4f>(gain + u * 4);
         }
     } else {
 #pragma unroll
@@ -166,7 +180,7 @@ __global__ __launch_bounds__(BL_ONE_WAVES * 64) void bl_gemv_one(const bl_one_ar
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
                 aq[i][d] = bl_v4i{0, 0, 0, 0};
-                if (chunk < nchunks) aq[i][d] = bl_gc<bl_v4i>(P.in0)[chunk * 4 + d];
+                if (chunk < nchunks) aq[i][d] = bl_gc<bl_v4i>(in0)[chunk * 4 + d];
             }
         }
     }
@@ -175,13 +189,18 @@ __global__ __launch_bounds__(BL_ONE_WAVES * 64) void bl_gemv_one(const bl_one_ar
 #pragma unroll
     for (int j = 0; j < RW; ++j) {
         const int n = n0 + j * R + r;
-        const bl_v4i BL_G* wrow = bl_gc<bl_v4i>(P.packed) + (int64_t)(n < nend ? n : nend - 1) * nchunks;
+        const bl_v4i BL_G* wrow = bl_gc<bl_v4i>(packed) + (int64_t)(n < nend ? n : nend - 1) * nchunks;
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
             const int chunk = g + G * i;
             p[j][i] = __builtin_nontemporal_load(wrow + (chunk < nchunks ? chunk : nchunks - 1));
         }
     }
+    __builtin_amdgcn_sched_barrier(0);
+    bl_one_rest P = Pin;
+    /* one pin for all: the fields arrive together and stay in scalar registers */
+    asm volatile("" : "+s"(P.aux_out), "+s"(P.beta), "+s"(P.scale), "+s"(P.acc), "+s"(P.y), "+s"(P.q_out), "+s"(P.scale_out),
+                      "+s"(P.layout), "+s"(P.eps), "+s"(P.fixed_scale), "+s"(P.inv_k));
     const float bt = *bl_gc<float>(P.beta);
     float cf = 0.0f;
     int nq = 0;                                            /* sum_k q */
@@ -205,7 +224,7 @@ __global__ __launch_bounds__(BL_ONE_WAVES * 64) void bl_gemv_one(const bl_one_ar
                     v[j][1] = __uint_as_float(xb[j].x & 0xFFFF0000u);
                     v[j][2] = __uint_as_float(xb[j].y << 16);
                     v[j][3] = __uint_as_float(xb[j].y & 0xFFFF0000u);
-                } else if (SRC == BL_ONE_PAIR && P.kind == BL_PROD_RELU2_GATE) {
+                } else if (SRC == BL_ONE_PAIR && kind == BL_PROD_RELU2_GATE) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const float rl = fmaxf(a[e], 0.0f);
@@ -375,7 +394,7 @@ __global__ __launch_bounds__(BL_ONE_WAVES * 64) void bl_gemv_one(const bl_one_ar
         if (P.acc) bl_g(P.acc)[n] = mine;
         if (P.y) {
             const float t = (float)mine * cf;
-            bl_g(P.y)[n] = P.residual ? res + t : t;
+            bl_g(P.y)[n] = residual ? res + t : t;
         }
     }
 }
@@ -383,20 +402,31 @@ __global__ __launch_bounds__(BL_ONE_WAVES * 64) void bl_gemv_one(const bl_one_ar
 template <int G, int RW, int NL, int UN>
 static void launch_one(const bl_one_args& A, int src, bool norm, hipStream_t st) {
     const int blocks = (A.N + A.rows - 1) / A.rows, threads = BL_ONE_WAVES * 64;
+    const auto lo = [](uint64_t v) { return (uint32_t)v; };
+    const auto hi = [](uint64_t v) { return (uint32_t)(v >> 32); };
+    const uint64_t w = (uint64_t)A.packed, x = (uint64_t)A.in0, g = (uint64_t)A.gain, r = (uint64_t)A.residual;
+    const uint64_t s = src == BL_ONE_V ? (uint64_t)A.mul_group << 32 | A.mul_hd : (uint64_t)A.in1;
+    const bl_v4u where = {lo(w), hi(w), lo(x), hi(x)}, beside = {lo(s), hi(s), lo(g), hi(g)};
+    const bl_v4u size = {lo(r), hi(r), (uint32_t)A.N, (uint32_t)A.K};
+    const bl_v2u how = {(uint32_t)A.rows | (uint32_t)A.kind << 8 | (uint32_t)A.hd << 16, (uint32_t)A.voff};
     switch (src) {
         case BL_ONE_BF16:
-            if (norm) bl_gemv_one<BL_ONE_BF16, G, RW, NL, UN, true><<<blocks, threads, 0, st>>>(A);
-            else bl_gemv_one<BL_ONE_BF16, G, RW, NL, UN, false><<<blocks, threads, 0, st>>>(A);
+            if (norm) bl_gemv_one<BL_ONE_BF16, G, RW, NL, UN, true><<<blocks, threads, 0, st>>>(where, beside, size, how, A);
+            else bl_gemv_one<BL_ONE_BF16, G, RW, NL, UN, false><<<blocks, threads, 0, st>>>(where, beside, size, how, A);
             break;
         case BL_ONE_F32:
-            if (norm) bl_gemv_one<BL_ONE_F32, G, RW, NL, UN, true><<<blocks, threads, 0, st>>>(A);
-            else bl_gemv_one<BL_ONE_F32, G, RW, NL, UN, false><<<blocks, threads, 0, st>>>(A);
+            if (norm) bl_gemv_one<BL_ONE_F32, G, RW, NL, UN, true><<<blocks, threads, 0, st>>>(where, beside, size, how, A);
+            else bl_gemv_one<BL_ONE_F32, G, RW, NL, UN, false><<<blocks, threads, 0, st>>>(where, beside, size, how, A);
+            break;
+        case BL_ONE_V:
+            if (norm) bl_gemv_one<BL_ONE_V, G, RW, NL, UN, true><<<blocks, threads, 0, st>>>(where, beside, size, how, A);
+            else bl_gemv_one<BL_ONE_V, G, RW, NL, UN, false><<<blocks, threads, 0, st>>>(where, beside, size, how, A);
             break;
         case BL_ONE_PAIR:
-            if (norm) bl_gemv_one<BL_ONE_PAIR, G, RW, NL, UN, true><<<blocks, threads, 0, st>>>(A);
-            else bl_gemv_one<BL_ONE_PAIR, G, RW, NL, UN, false><<<blocks, threads, 0, st>>>(A);
+            if (norm) bl_gemv_one<BL_ONE_PAIR, G, RW, NL, UN, true><<<blocks, threads, 0, st>>>(where, beside, size, how, A);
+            else bl_gemv_one<BL_ONE_PAIR, G, RW, NL, UN, false><<<blocks, threads, 0, st>>>(where, beside, size, how, A);
             break;
-        default: bl_gemv_one<BL_ONE_INT8, G, RW, NL, UN, false><<<blocks, threads, 0, st>>>(A);
+        default: bl_gemv_one<BL_ONE_INT8, G, RW, NL, UN, false><<<blocks, threads, 0, st>>>(where, beside, size, how, A);
     }
 }
 
@@ -435,7 +465,8 @@ bool bl_gemv_one_launch(const bl_gemv_prob& P, hipStream_t st, bl_status* status
     if (P.fused) {
         A.in0 = d.in0; A.aux_out = d.kind == BL_PROD_RESIDUAL ? d.aux_out : nullptr; A.kind = d.kind;
         A.q_out = P.q_out; A.scale_out = P.scale_out; A.fixed_scale = P.fixed_scale;
-        src = d.kind == BL_PROD_BF16 ? BL_ONE_BF16 : d.kind == BL_PROD_RESIDUAL || d.kind == BL_PROD_RELU2_GATE ? BL_ONE_PAIR : BL_ONE_F32;
+        src = d.kind == BL_PROD_BF16 ? BL_ONE_BF16 : d.kind == BL_PROD_RESIDUAL || d.kind == BL_PROD_RELU2_GATE ? BL_ONE_PAIR :
+              d.kind == BL_PROD_ATTN_V ? BL_ONE_V : BL_ONE_F32;
         A.in1 = d.kind == BL_PROD_RESIDUAL ? d.in1 : (const float*)d.in0 + P.K;
         if (d.kind == BL_PROD_ATTN_V) {
             A.voff = d.voff; A.hd = d.hd;
@@ -453,7 +484,7 @@ bool bl_gemv_one_launch(const bl_gemv_prob& P, hipStream_t st, bl_status* status
     int rows = P.N > 8 * 256 ? (P.N + 255) / 256 : 8;
     const int most = P.K <= 4096 ? 64 : 32;
     if (rows > most) rows = most;
-    A.rows = rows;
+    A.rows = rows;                                         /* (8 bits, like the kind; a head has at most K = 8192 values) */
     if (rows <= 16) {
         if (P.K <= 3072) launch_one<16, 1, 3, 3>(A, src, norm, st);
         else if (P.K <= 4096) launch_one<16, 1, 4, 4>(A, src, norm, st);
