@@ -14,12 +14,13 @@
  * Loads go through buffer descriptors: a lane's offset inside a tile never changes, a tile is a scalar base, a k step a
  * scalar offset, and rows past the end of a matrix are out of range (zeros) without a clamp.
  *
- * What bounds it: the LDS serves arriving direct loads at about 48 B/clk and reads at about 138 B/clk, one after the other,
- * and the matrix cores of a CU take 32 clocks for four 32x32x32.  A 128 x 256 tile in 2 x 2 waves of 64 x 128 needs 500 + 348
- * clocks of LDS for 1024 of MFMA, 128 x 128 in waves of 64 x 64 417 + 290 for 512: the wide tile is what lets the matrix
+ * What bounds it: a compute unit takes 59 B/clk of direct loads (24 KB in 416 clocks, LDS reads beside them for nothing) and its
+ * matrix cores 32 clocks for four 32x32x32.  A 128 x 256 tile in 2 x 2 waves of 64 x 128 needs 24 KB of loads and 48 KB of LDS reads
+ * for 1024 clocks of MFMA, 128 x 128 in waves of 64 x 64 20 KB and 40 KB for 512: the wide tile is what lets the matrix
  * cores run, and the fixed order is what lets two waves per SIMD (its registers) be enough.  Without output stores it reaches
- * 2.9 POP/s (8192 x 4096 -> 8192; 1.74 GHz under power management, where the bare MFMA loop reaches 3.4 - 3.6), the
- * kernel of 128 x 128 tiles before it 2.3.
+ * 2.9 POP/s (8192 x 4096 -> 8192 at 1.73 GHz: the power management; the bare MFMA loop reaches 3.4 - 3.6), the
+ * kernel of 128 x 128 tiles before it 2.3.  One wave per SIMD issues an MFMA every 41 clocks (two: 35), which is all that a lone
+ * 128 x 192 tile loses in its loop (0.51 us a step, without loads, reads and unpacking 0.50); eight waves on the same tile gain nothing.
  *
  * LDS stage = A part (BM rows x 128 int8, 16-byte units XOR-swizzled by (row/2)%8) + W part (BN rows x 32 packed bytes =
  * two units, swapped by row/8%2): sixteen consecutive lanes of a ds_read_b128 fall on sixteen different 16-byte bank
