@@ -93,13 +93,6 @@ __device__ __forceinline__ float bl_wave_max(float v) {
     return bl_max_pos(bl_max_pos(bl_lane_f(v, 0), bl_lane_f(v, 16)), bl_max_pos(bl_lane_f(v, 32), bl_lane_f(v, 48)));
 }
 
-/* Maximum over the 32 lanes of a half wave (non-negative floats), in every one of them. */
-__device__ __forceinline__ float bl_half_max(float v) {
-    v = bl_row_max(v);
-    const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(t[0] > t[1] ? t[0] : t[1]);
-}
-
 /* 4x4 byte transpose of four dwords: out[s].byte[b] = in[b].byte[s]. */
 __device__ __forceinline__ void bl_transpose4x4(uint32_t& a0, uint32_t& a1, uint32_t& a2, uint32_t& a3) {
     const uint32_t t0 = __builtin_amdgcn_perm(a1, a0, 0x05010400u);

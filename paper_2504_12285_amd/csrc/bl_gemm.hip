@@ -11,7 +11,6 @@
 #include "bl_host.h"
 
 #include <atomic>
-#include <type_traits>
 
 /* Outputs of the fused producer epilogues (device pointers; see bl_gemm_pipe). */
 struct bl_epi_args {
