@@ -7,6 +7,7 @@
  * rowsum[m] = sum_k q[m][k] (exact int32 identity), then rescales.
  */
 #include "bl_device.h"
+#include "bl_gemm_choice.h"
 #include "bl_gemm_pipe.h"
 #include "bl_host.h"
 
@@ -17,28 +18,6 @@ struct bl_epi_args {
     uint16_t* xb;
     int* absmax;
 };
-
-/* Order of the tiles (see bl_gemm_pipe).  Rows of activations per band: at most ~1.5 MB of int8 (measured, medians of six
- * interleaved rounds at M = 2048: +7 % on the 13824-wide shape against bands of all rows, equal on the others).  A rectangle
- * per XCD unless its size means more tiles for the busiest of an XCD's 32 compute units than an even share
- * does: 2140 x 3840 -> 13458 (17 row tiles, bands of 3: two XCDs idle) 148 / 122 us, 1100 x 2560 -> 7000 (70
- * tiles against 62) 36 / 27.5; 777 x 2999 -> 5003 with its quantiser (70 and 60 tiles against 65: three on
- * the busiest unit either way) 28.1 / 30.6 (tiles of 128 x 128 and 64 x 128). */
-struct bl_tile_order {
-    int gm, band, vgrid;
-};
-static bl_tile_order tile_order(int tiles_m, int tiles_n, int BM, int K) {
-    int gm = 1;
-    while (gm < 8 && (int64_t)((tiles_m + gm - 1) / gm) * BM * K > (3 << 19)) gm *= 2;
-    int band = (tiles_m + gm - 1) / gm;
-    const int rect = band * ((tiles_n + 8 / gm - 1) / (8 / gm)), share = (tiles_m * tiles_n + 7) / 8;
-    if ((rect + 31) / 32 <= (share + 31) / 32) return {gm, band, 8 * rect};
-    int64_t most = (3 << 19) / ((int64_t)BM * K);
-    if (most < 1) most = 1;
-    const int bands = (int)((tiles_m + most - 1) / most);
-    band = (tiles_m + bands - 1) / bands;
-    return {0, band, 8 * share};
-}
 
 /* ---- few tiles: the k loop split over the waves of a workgroup -------------------------------
  * With few tokens (65 .. a few hundred) a product has fewer 64 x 128 tiles than the chip has compute
@@ -182,26 +161,6 @@ __global__ __launch_bounds__(256, 2) void bl_gemm_ksplit(const uint8_t* __restri
     }
 }
 
-/* The order of the tiles and what an XCD reads: bytes per k of its share, 64 to a row tile, 8 to a column tile; a share in
- * one order is whole lines in the other.  3931 x 4480 -> 256 (62 row tiles and 8 column tiles; row tiles fastest, every XCD reads
- * all activations) 24.5 us, columns fastest 13.1; 2528 x 1877 -> 320 10.7 / 7.7. */
-struct bl_ksplit_order {
-    bool across;
-    int64_t bytes;
-};
-static bl_ksplit_order ksplit_order(int m, int n) {
-    const int64_t tm = (m + 63) / 64, tn = (n + 31) / 32, share = (tm * tn + 7) / 8;
-    const int64_t down = (share < tm ? share : tm) * 64 + (share + tm - 1) / tm * 8, over = (share < tn ? share : tn) * 8 + (share + tn - 1) / tn * 64;
-    const bool across = over * 2 < down;                       /* (rows first otherwise: 395 x 2176 -> 1600 8.0 us, 8.7 across) */
-    return {across, across ? over : down};
-}
-/* Its time (us), for the tile choice below: rounds of 512 workgroups, and what an XCD reads. */
-static float ksplit_us(int m, int n, int k) {
-    const int64_t tiles = (int64_t)((m + 63) / 64) * ((n + 31) / 32);
-    const float rounds = (float)((tiles + 511) / 512), steps = (float)((k + GP_BK - 1) / GP_BK);
-    return 1.81f + rounds * (steps * .091f + 1.83f) + 2.18e-6f * (float)ksplit_order(m, n).bytes * (float)k + 1.31e-6f * (float)m * (float)n;
-}
-
 template <int LAYOUT>
 static bl_status launch_ksplit(const uint8_t* packed, const float* beta, const int8_t* q, const float* scale,
                                const int32_t* rowsum, int m, int n, int k, const float* residual, int32_t* acc, float* y,
@@ -214,10 +173,7 @@ static bl_status launch_ksplit(const uint8_t* packed, const float* beta, const i
         attr_set.store(true, std::memory_order_release);
     }
     const int tiles_m = (m + 63) / 64, tiles_n = (n + 31) / 32, tiles = tiles_m * tiles_n, share = (tiles + 7) / 8;
-    /* bytes per k that an XCD reads: 64 to a row tile, 8 to a column tile; a share of one order is whole lines of the other */
-    const int64_t down = (int64_t)(share < tiles_m ? share : tiles_m) * 64 + (int64_t)((share + tiles_m - 1) / tiles_m) * 8;
-    const int64_t over = (int64_t)(share < tiles_n ? share : tiles_n) * 8 + (int64_t)((share + tiles_n - 1) / tiles_n) * 64;
-    kern<<<share * 8, 256, lds, st>>>(packed, q, rowsum, beta, scale, m, n, k, tiles_m, tiles, over < down ? tiles_n : 0, residual, acc, y,
+    kern<<<share * 8, 256, lds, st>>>(packed, q, rowsum, beta, scale, m, n, k, tiles_m, tiles, bl_ksplit_order_of(m, n).across ? tiles_n : 0, residual, acc, y,
                                                  (long long*)bl_clock_stamps());
     return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
 }
@@ -245,7 +201,7 @@ static bl_status launch_pipe(const uint8_t* packed, const float* beta, const int
     const int tiles_m = (M + G::BM - 1) / G::BM, out = EPI == 2 ? N / 2 : N, cover = EPI == 2 ? G::BN / 2 : G::BN;
     const int tiles_n = (out + cover - 1) / cover;
     if ((int64_t)tiles_m * tiles_n > ((int64_t)1 << 28)) return BL_ERR_SHAPE;
-    const bl_tile_order o = tile_order(tiles_m, tiles_n, G::BM, K);
+    const bl_tile_order o = bl_tile_order_of(tiles_m, tiles_n, G::BM, K);
     if (blocks > o.vgrid) blocks = o.vgrid;
     kern<<<blocks, G::THREADS, G::LDS, st>>>(packed, q, rowsum, beta, scale, M, N, K, tiles_m, tiles_n, o.gm ? 3 - __builtin_ctz(o.gm) : -1, o.band, o.vgrid, blocks,
                                              residual, acc, y, ep.xb, ep.absmax, (long long*)bl_clock_stamps(), nullptr, nullptr, nullptr);
@@ -305,64 +261,17 @@ __global__ __launch_bounds__(256) void bl_rowsum_kernel(const int8_t* __restrict
     if (lane == 0) rowsum[m] = s;
 }
 
-/* Tile choice of a plain product: the kernel with the least time by this estimate (us),
- *     fixed + busiest * (steps * (step + lone) + tile) + 2^-20 outputs,
- * busiest = tiles of the busiest of 256 compute units, lone (to `step`) only where no unit has more than one.  Fitted to 200 shapes in
- * both layouts (65 .. 4096 x 300 .. 14000, K 256 .. 7000): the choice takes 1.005 times the time of the best of the six, and
- * .86 of that of the kernels before them (128 x 128 with deferred stores, 64 x 128 with two or four stages, a
- * register-staged 128 x 128; worst 1.12, 4072 x 640 -> 1915).  Where each is the best (us; in brackets the kernels before):
- *   128 x 256, two workgroups to a unit: many tiles (4096 x 2560 -> 13824 117; 128 x 192 122, 128 x 128 129, 64 x 128 151 [149]);
- *   128 x 192, two workgroups: where it fills the units better (2048 x 2560 -> 13824 63.6; 128 x 256 68, 64 x 128 79 [72]);
- *   128 x 192, one workgroup with four stages: at most one tile to a unit (2048 x 6912 -> 2560 37.2; 128 x 256 44.5, 128 x 128 40.6,
- *     64 x 128 42.2 [43.2]);
- *   128 x 128, two workgroups: two tiles to a unit (2048 x 2560 -> 3840 22.3; 128 x 256 25.4, 64 x 128 25.7 [25.2]);
- *   64 x 128, four workgroups: few tokens (512 x 2560 -> 3840 10.4; 128 x 128 12.5 [14.1]);
- *   the k loop split over the waves (bl_gemm_ksplit): fewer tiles than units (512 tiles of 64 x 32 in a round; 128 x 2560 -> 3840
- *     6.6, 64 x 128 8.7). */
-struct bl_tile_cost {
-    int bm, bn;
-    float fixed, step, lone, tile, out;
-    float us(int m, int n, int k) const {
-        const int64_t tiles = (int64_t)((m + bm - 1) / bm) * ((n + bn - 1) / bn), busiest = (tiles + 255) / 256;
-        const float steps = (float)((k + GP_BK - 1) / GP_BK);
-        return fixed + (float)busiest * (steps * (step + (busiest == 1 ? lone : 0.0f)) + tile) + out * 1e-6f * (float)m * (float)n;
-    }
-};
-/* the kernel of the least cost: its place in the list */
-template <int COUNT>
-static int least(const bl_tile_cost (&cost)[COUNT], int m, int n, int k, float* us = nullptr) {
-    int best = 0;
-    float t = cost[0].us(m, n, k);
-    for (int i = 1; i < COUNT; ++i) {
-        const float ti = cost[i].us(m, n, k);
-        if (ti < t) {
-            t = ti;
-            best = i;
-        }
-    }
-    if (us) *us = t;
-    return best;
-}
-static constexpr bl_tile_cost plain_cost[5] = {{128, 256, 4.55f, .616f, .093f, .252f, .515f}, {128, 192, 4.05f, .508f, .110f, .317f, .505f},
-                                               {128, 192, 2.96f, .564f, 0.0f, 2.01f, .465f}, {128, 128, 4.16f, .351f, .066f, 0.0f, .553f},
-                                               {64, 128, 3.70f, .225f, .068f, 0.0f, .492f}};
-
 template <int LAYOUT>
 static bl_status launch_plain(const uint8_t* packed, const float* beta, const int8_t* q, const float* scale,
                               const int32_t* rowsum, int m, int n, int k, const float* residual, int32_t* acc, float* y,
                               hipStream_t st) {
-    float us;
-    const int kernel = least(plain_cost, m, n, k, &us);
-    /* (fitted with fp32 output alone; the split k loop has the residual at hand when its sums are ready, and writes two outputs at
-     * once: 663 x 781 -> 1088 5.9 us with residual, 64 x 128 tiles 8.0; 436 x 576 -> 2330 with both 6.2 / 6.9) */
-    us += residual ? 2.0f : acc && y ? 0.8f : 0.0f;
-    if (ksplit_us(m, n, k) < us) return launch_ksplit<LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
-    switch (kernel) {
+    switch (bl_plain_kernel(m, n, k, residual != nullptr, acc && y)) {
         case 0: return launch_pipe<2, 4, 2, 2, 3, 2, 0, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
         case 1: return launch_pipe<2, 3, 2, 2, 3, 2, 0, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
         case 2: return launch_pipe<2, 3, 2, 2, 4, 1, 0, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
         case 3: return launch_pipe<2, 2, 2, 2, 3, 2, 0, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
-        default: return launch_pipe<2, 1, 1, 4, 3, 4, 0, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
+        case 4: return launch_pipe<2, 1, 1, 4, 3, 4, 0, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
+        default: return launch_ksplit<LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
     }
 }
 
@@ -404,15 +313,6 @@ extern "C" bl_status bl_gemm_w158a8(const uint8_t* packed, const float* beta, in
     return bl_gemm_w158a8_res(packed, beta, layout, q, scale, rowsum, M, N, K, nullptr, acc, y, workspace, s);
 }
 
-/* The tile of a fused epilogue, by the same estimate (gate: tiles of outputs), fitted to 140 shapes; the choice takes 1.003 times
- * the time of the best, .80 (residual) and .88 (gate) of that of the 128 x 128 and 64 x 128 tiles before it.  us [before]:
- *   residual 4096 x 2560 -> 2560 40 [45], 4096 x 6912 -> 2560 88 [93], 1000 x 2560 -> 2560 15.7 [20.1], 128 x 6912 -> 2560 21.2 [26.7];
- *   gate 2560 -> 13824 at 4096 tokens 120 [142], 2048 70 [72.6], 1000 38.5 [48.5], 128 18.2 [19.5].
- * Slower than before: gates of short rows with few tiles (834 x 256 -> 3328 6.7 [6.0], 94 x 1024 -> 6400 9.9 [9.5]). */
-static constexpr bl_tile_cost residual_cost[3] = {{128, 256, 0.0f, .450f, .207f, 8.97f, .929f}, {128, 128, 3.26f, .266f, .103f, 3.68f, .988f},
-                                                  {64, 128, 3.84f, .193f, .112f, .966f, 1.17f}};
-static constexpr bl_tile_cost gate_cost[2] = {{128, 128, 6.24f, .614f, .072f, 0.0f, .756f}, {64, 64, 4.52f, .230f, .056f, 0.0f, .872f}};
-
 /* Prefill product with a fused producer epilogue (see bl_gemm_pipe, EPI = 1 and 2). */
 extern "C" bl_status bl_gemm_w158a8_fused(const uint8_t* packed, const float* beta, int layout, const int8_t* q,
                                           const float* scale, const int32_t* rowsum, int64_t M, int64_t N, int64_t K,
@@ -432,13 +332,13 @@ extern "C" bl_status bl_gemm_w158a8_fused(const uint8_t* packed, const float* be
     hipStream_t st = (hipStream_t)s;
     const int m = (int)M, n = (int)N, k = (int)K;
     if (ep->kind == BL_EPI_RESIDUAL) {
-        switch (least(residual_cost, m, n, k)) {
+        switch (bl_residual_kernel(m, n, k)) {
             case 0: return launch_pipe<2, 4, 2, 2, 3, 2, 1, 1>(packed, beta, q, scale, rowsum, m, n, k, ep->residual, acc, ep->y, st, ea);
             case 1: return launch_pipe<2, 2, 2, 2, 3, 2, 1, 1>(packed, beta, q, scale, rowsum, m, n, k, ep->residual, acc, ep->y, st, ea);
             default: return launch_pipe<1, 2, 2, 2, 3, 4, 1, 1>(packed, beta, q, scale, rowsum, m, n, k, ep->residual, acc, ep->y, st, ea);
         }
     }
-    if (least(gate_cost, m, n / 2, k) == 0)
+    if (bl_gate_kernel(m, n, k) == 0)
         return launch_pipe<2, 4, 2, 2, 3, 2, 2, 1>(packed, beta, q, scale, rowsum, m, n, k, nullptr, acc, ep->y, st, ea);
     return launch_pipe<1, 2, 2, 2, 3, 4, 2, 1>(packed, beta, q, scale, rowsum, m, n, k, nullptr, acc, ep->y, st, ea);
 }

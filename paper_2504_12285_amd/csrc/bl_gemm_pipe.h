@@ -44,11 +44,10 @@
  * k steps, layout 1, plain epilogue. */
 #pragma once
 #include "bl_device.h"
+#include "bl_gemm_choice.h"
 #include "bl_host.h"
 
 #include <type_traits>
-
-#define GP_BK 128
 
 template <int MI, int NI, int WM, int WN, int S>
 struct bl_pipe_geom {

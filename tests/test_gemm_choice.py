@@ -1,0 +1,63 @@
+"""Which kernel a prefill product takes and in which order, on the CPU: the rules stand in a header of their own, which the launcher
+includes, and a host program answers for it."""
+import os
+import random
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("g++ not available")
+    exe = str(tmp_path_factory.mktemp("gemm_choice") / "driver")
+    cmd = ["g++", "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover=all",
+           "-I", os.path.join(ROOT, "paper_2504_12285_amd", "csrc"), os.path.join(ROOT, "tests", "gemm_choice_driver.cpp"), "-o", exe]
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert res.returncode == 0, res.stdout
+
+    def answers(questions):
+        run = subprocess.run([exe], input="\n".join(questions), stdout=subprocess.PIPE, text=True, timeout=120)
+        lines = run.stdout.splitlines()
+        assert run.returncode == 0 and len(lines) == len(questions)
+        return [tuple(int(v) for v in line.split()) for line in lines]
+    return answers
+
+
+def _bytes(along, total, per_line, per_item):
+    """Bytes per k of the XCD that reads most, when each takes an eighth of `total` tiles in lines of `along`."""
+    share, most = -(-total // 8), 0
+    for first in range(0, total, share):
+        last = min(total, first + share) - 1
+        most = max(most, (last // along - first // along + 1) * per_line + min(along, last - first + 1) * per_item)
+    return most
+
+
+def test_split_k_order(ask):
+    """The order is the one that reads less by a quarter, and what the estimate reckons with is that order's bytes."""
+    measured = {(3931, 256): 1, (2528, 320): 1, (512, 1024): 1, (408, 925): 1, (452, 891): 1,        # faster across
+                (395, 1600): 0, (444, 1600): 0, (329, 1438): 0, (384, 1407): 0, (392, 1280): 0}      # slower across
+    for (M, N), (across, _) in zip(measured, ask(["order %d %d" % s for s in measured])):
+        assert across == measured[M, N], (M, N)
+    rng = random.Random(1)
+    shapes = [(rng.randint(1, 4096), rng.randint(1, 14000)) for _ in range(2000)] + [(1, 1), (64, 32), (65, 33), (1 << 24, 1), (1, 1 << 24), (1 << 24, 1 << 24)]
+    for (M, N), (across, got) in zip(shapes, ask(["order %d %d" % s for s in shapes])):
+        tm, tn = -(-M // 64), -(-N // 32)
+        down, over = _bytes(tm, tm * tn, 8, 64), _bytes(tn, tm * tn, 64, 8)
+        want, line = (over, 64) if across else (down, 8)
+        assert want <= got <= want + line, (M, N)                  # (a share that starts inside a line may be reckoned to touch one more)
+        assert not across or 4 * over <= 3 * (down + 8)
+        assert across or 4 * (over + 64) > 3 * down
+
+
+def test_split_k_shapes(ask):
+    """The shapes of the GPU test go to the split k loop, in the order that they stand for."""
+    import test_gpu_gemm_split_k as t
+    for shapes, want in ((t.ACROSS, 1), (t.DOWN, 0)):
+        assert [a for a, _ in ask(["order %d %d" % s[:2] for s in shapes])] == [want] * len(shapes)
+        for both in (0, 1):
+            assert ask(["plain %d %d %d 0 %d" % (M, N, -(-K // 64) * 64, both) for M, N, K in shapes]) == [(5,)] * len(shapes)
