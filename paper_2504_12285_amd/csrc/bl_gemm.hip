@@ -265,7 +265,7 @@ template <int LAYOUT>
 static bl_status launch_plain(const uint8_t* packed, const float* beta, const int8_t* q, const float* scale,
                               const int32_t* rowsum, int m, int n, int k, const float* residual, int32_t* acc, float* y,
                               hipStream_t st) {
-    switch (bl_plain_kernel(m, n, k, residual != nullptr, acc && y)) {
+    switch (bl_plain_kernel(m, n, k, residual != nullptr, acc != nullptr, y != nullptr)) {
         case 0: return launch_pipe<2, 4, 2, 2, 3, 2, 0, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
         case 1: return launch_pipe<2, 3, 2, 2, 3, 2, 0, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);
         case 2: return launch_pipe<2, 3, 2, 2, 4, 1, 0, LAYOUT>(packed, beta, q, scale, rowsum, m, n, k, residual, acc, y, st);

@@ -77,14 +77,17 @@ static inline int bl_least(const bl_tile_cost (&cost)[COUNT], int m, int n, int 
 /* Tile choice of a plain product: the kernel with the least time by this estimate (us),
  *     fixed + busiest * (steps * (step + lone) + tile) + 2^-20 outputs,
  * busiest = tiles of the busiest of 256 compute units, lone (to `step`) only where no unit has more than one.  Fitted to 200 shapes in
- * both layouts (65 .. 4096 x 300 .. 14000, K 256 .. 7000): the choice takes 1.005 times the time of the best of the six, and
- * .86 of that of the kernels before them (128 x 128 with deferred stores, 64 x 128 with two or four stages, a
- * register-staged 128 x 128; worst 1.12, 4072 x 640 -> 1915).  Where each is the best (us; in brackets the kernels before):
+ * both layouts (65 .. 4096 x 300 .. 14000, K 256 .. 7000).  Over 380 products of other shapes, K 64 .. 7000, the choice (with the split k
+ * loop) takes 1.010 times the time of the best of the six, and .87 of that of the kernels before them (128 x 128 with deferred stores, 64 x
+ * 128 with two or four stages, a register-staged 128 x 128); up to 1.05 where K <= 256 makes a launch one of stores (2067 x 256 ->
+ * 12928 27.0 / 28.5).  Where each is the best (us; in brackets the kernels before):
  *   128 x 256, two workgroups to a unit: many tiles (4096 x 2560 -> 13824 117; 128 x 192 122, 128 x 128 129, 64 x 128 151 [149]);
- *   128 x 192, two workgroups: where it fills the units better (2048 x 2560 -> 13824 63.6; 128 x 256 68, 64 x 128 79 [72]);
+ *   128 x 192, two workgroups: where it fills the units better (1616 x 4800 -> 5154 48.9; 128 x 256 58.0, 128 x 128 54.2, 64 x 128
+ *     59.0 [62.8]);
  *   128 x 192, one workgroup with four stages: at most one tile to a unit (2048 x 6912 -> 2560 37.2; 128 x 256 44.5, 128 x 128 40.6,
  *     64 x 128 42.2 [43.2]);
- *   128 x 128, two workgroups: two tiles to a unit (2048 x 2560 -> 3840 22.3; 128 x 256 25.4, 64 x 128 25.7 [25.2]);
+ *   128 x 128, two workgroups: two tiles to a unit (2048 x 2560 -> 3840 22.3; 128 x 256 25.4, 64 x 128 25.7 [25.2]), and where it ends
+ *     evenly (2048 x 2560 -> 13824 70.2; 128 x 192 69.0, 128 x 256 74.8, 64 x 128 86.8 [79.0]);
  *   64 x 128, four workgroups: few tokens (512 x 2560 -> 3840 10.4; 128 x 128 12.5 [14.1]);
  *   the k loop split over the waves (bl_gemm_ksplit): fewer tiles than units (512 tiles of 64 x 32 in a round; 128 x 2560 -> 3840
  *     6.6, 64 x 128 8.7). */
@@ -99,13 +102,15 @@ static inline float bl_ksplit_us(int m, int n, int k) {
     return 1.97f + rounds * (steps * (tiles > 256 ? .174f : .105f) + 1.83f) + .50e-6f * (float)bl_ksplit_order_of(m, n).bytes * (float)k +
            .94e-6f * (float)m * (float)n;
 }
-/* The kernel of a plain product: its place in the list of costs, or 5, the split k loop. */
-static inline int bl_plain_kernel(int m, int n, int k, bool residual, bool both) {
+/* The kernel of a plain product: its place in the list of costs, or 5, the split k loop.  The lists are fitted with fp32 output alone;
+ * against the split k loop the tiles take longer with a residual (it has that at hand when its sums are ready: 663 x 781 -> 1088
+ * 5.9 us, 64 x 128 tiles 8.0), with both outputs (which it writes at once: 436 x 576 -> 2330 6.2 / 6.9), and where rows of fp32 start inside
+ * a line, which the few tiles of such a launch write past the caches in parts and it does not (909 x 256 -> 460 4.4 / 5.0, 293 x 448 ->
+ * 3082 5.2 / 5.7, 357 x 256 -> 1001 4.4 / 4.9; but 242 x 256 -> 4032 5.0 / 4.7). */
+static inline int bl_plain_kernel(int m, int n, int k, bool residual, bool acc, bool y) {
     float us;
     const int kernel = bl_least(bl_plain_cost, m, n, k, &us);
-    /* (fitted with fp32 output alone; the split k loop has the residual at hand when its sums are ready, and writes two outputs at
-     * once: 663 x 781 -> 1088 5.9 us with residual, 64 x 128 tiles 8.0; 436 x 576 -> 2330 with both 6.2 / 6.9) */
-    us += residual ? 2.0f : both ? 0.8f : 0.0f;
+    us += residual ? 2.0f : acc && y ? 0.8f : y && n % 16 != 0 ? 0.5f : 0.0f;
     return bl_ksplit_us(m, n, k) < us ? 5 : kernel;
 }
 

@@ -1,5 +1,5 @@
 /* Answers what csrc/bl_gemm_choice.h chooses: one question a line on stdin, one answer a line on stdout.
- *   plain M N K residual both   place of the kernel (5: the split k loop)
+ *   plain M N K residual acc y  place of the kernel (5: the split k loop)
  *   residual M N K | gate M N K   place of the tile
  *   order M N                   the split k loop's order: across, bytes per k that an XCD reads
  *   tiles tiles_m tiles_n BM K  the tile kernels' order: gm, band, vgrid */
@@ -11,9 +11,9 @@
 int main() {
     char what[16];
     while (scanf("%15s", what) == 1) {
-        int a, b, c, d, e;
-        if (!strcmp(what, "plain") && scanf("%d %d %d %d %d", &a, &b, &c, &d, &e) == 5) {
-            printf("%d\n", bl_plain_kernel(a, b, c, d != 0, e != 0));
+        int a, b, c, d, e, f;
+        if (!strcmp(what, "plain") && scanf("%d %d %d %d %d %d", &a, &b, &c, &d, &e, &f) == 6) {
+            printf("%d\n", bl_plain_kernel(a, b, c, d != 0, e != 0, f != 0));
         } else if (!strcmp(what, "residual") && scanf("%d %d %d", &a, &b, &c) == 3) {
             printf("%d\n", bl_residual_kernel(a, b, c));
         } else if (!strcmp(what, "gate") && scanf("%d %d %d", &a, &b, &c) == 3) {

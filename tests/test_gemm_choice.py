@@ -59,5 +59,15 @@ def test_split_k_shapes(ask):
     import test_gpu_gemm_split_k as t
     for shapes, want in ((t.ACROSS, 1), (t.DOWN, 0)):
         assert [a for a, _ in ask(["order %d %d" % s[:2] for s in shapes])] == [want] * len(shapes)
-        for both in (0, 1):
-            assert ask(["plain %d %d %d 0 %d" % (M, N, -(-K // 64) * 64, both) for M, N, K in shapes]) == [(5,)] * len(shapes)
+        for acc in (0, 1):
+            assert ask(["plain %d %d %d 0 %d 1" % (M, N, -(-K // 64) * 64, acc) for M, N, K in shapes]) == [(5,)] * len(shapes)
+
+
+def test_broken_lines_of_few_tokens(ask):
+    """fp32 rows that start inside a line: where the split k loop measured 7 - 14 % faster than tiles of 64 x 128.  Whole lines, and int32
+    output alone, the other way round."""
+    shapes = [(909, 460, 256), (492, 831, 256), (357, 1001, 256), (293, 3082, 448), (772, 975, 448), (1654, 308, 64), (670, 382, 128)]
+    assert ask(["plain %d %d %d 0 0 1" % s for s in shapes]) == [(5,)] * len(shapes)
+    shapes = [(512, 3840, 2560), (1000, 3840, 2560), (1161, 1914, 64), (242, 4032, 256), (403, 1536, 64), (237, 1856, 64)]
+    assert ask(["plain %d %d %d 0 0 1" % s for s in shapes]) == [(4,)] * len(shapes)
+    assert ask(["plain 370 2033 256 0 1 0", "plain 242 4032 256 0 1 0"]) == [(4,), (4,)]
