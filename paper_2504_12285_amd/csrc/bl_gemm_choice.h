@@ -114,6 +114,13 @@ static inline int bl_plain_kernel(int m, int n, int k, bool residual, bool acc, 
     return bl_ksplit_us(m, n, k) < us ? 5 : kernel;
 }
 
+/* Whether the tile kernels store fp32 output past the caches (non-temporal).  Whole and half lines gain by it (2048 x 2560 -> 13840 66.7 us,
+ * plain stores 69.3).  Rows that start inside a line write lines in parts: such a store goes to memory as a part once the output
+ * outgrows the L2s, from about 5 M values (2106 x 256 -> 3705 15.9 / 10.4, 4072 x 640 -> 1915 17.2 / 13.3, 2242 x 192 -> 2986 12.4 / 10.4, 3812 x 677 ->
+ * 6613 51.1 / 35.0), and up to there gains where the k loop is long (422 x 1280 -> 4751 8.3 / 8.9, 387 x 2560 -> 7778 14.2 / 14.9) and loses
+ * less where it is short (734 x 256 -> 2034 5.7 / 5.3).  Not beside an int32 output. */
+static constexpr bool bl_past_caches(int m, int n, bool acc) { return n % 16 == 0 || (!acc && (int64_t)m * n <= (4 << 20)); }
+
 /* The tile of a fused epilogue, by the same estimate (gate: tiles of outputs), fitted to 140 shapes; the choice takes 1.003 times
  * the time of the best, .80 (residual) and .88 (gate) of that of the 128 x 128 and 64 x 128 tiles before it.  us [before]:
  *   residual 4096 x 2560 -> 2560 40 [45], 4096 x 6912 -> 2560 88 [93], 1000 x 2560 -> 2560 15.7 [20.1], 128 x 6912 -> 2560 21.2 [26.7];

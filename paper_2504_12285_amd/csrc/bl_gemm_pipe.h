@@ -568,11 +568,7 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
                 }, nothing);
             };
             if (y && !residual) {
-                /* A non-temporal store of part of a line goes to memory as part of a line once the output outgrows the L2
-                 * (3812 x 677 -> 6613 51.1 us, plain stores 35.0; 2048 x 2560 -> 13826 77.2 / 73.0; whole and half lines or
-                 * outputs that fit gain by it: 2048 x 2560 -> 13840 66.7 / 69.3, 1000 x 2560 -> 3850 15.1 / 15.9; not beside an
-                 * int32 output). */
-                if (N % 16 == 0 || (!acc && (int64_t)M * N <= (8 << 20))) plain(std::integral_constant<int, NT>{});
+                if (bl_past_caches(M, N, acc != nullptr)) plain(std::integral_constant<int, NT>{});
                 else plain(std::integral_constant<int, 0>{});
             } else if (y) {
                 /* the residual values are requested ahead of their rows */

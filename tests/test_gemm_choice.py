@@ -71,3 +71,12 @@ def test_broken_lines_of_few_tokens(ask):
     shapes = [(512, 3840, 2560), (1000, 3840, 2560), (1161, 1914, 64), (242, 4032, 256), (403, 1536, 64), (237, 1856, 64)]
     assert ask(["plain %d %d %d 0 0 1" % s for s in shapes]) == [(4,)] * len(shapes)
     assert ask(["plain 370 2033 256 0 1 0", "plain 242 4032 256 0 1 0"]) == [(4,), (4,)]
+
+
+def test_stores_of_broken_lines(ask):
+    """Outputs of 5 million values and more whose rows start inside a line: plain stores measured 0.66 - 0.90 of the time."""
+    shapes = [(4072, 1915), (842, 8443), (713, 10148), (1328, 4641), (585, 10937), (2242, 2986), (2106, 3705), (2443, 3038), (3812, 6613), (4096, 13823)]
+    assert ask(["stores %d %d 0" % s for s in shapes]) == [(0,)] * len(shapes)
+    shapes = [(422, 4751), (387, 7778), (2077, 1335), (4096, 13824), (2048, 13840)]
+    assert ask(["stores %d %d 0" % s for s in shapes]) == [(1,)] * len(shapes)
+    assert ask(["stores 422 4751 1", "stores 4096 13824 1"]) == [(0,), (1,)]
