@@ -121,11 +121,11 @@ static inline int bl_plain_kernel(int m, int n, int k, bool residual, bool acc, 
  * less where it is short (734 x 256 -> 2034 5.7 / 5.3).  Not beside an int32 output. */
 static constexpr bool bl_past_caches(int m, int n, bool acc) { return n % 16 == 0 || (!acc && (int64_t)m * n <= (4 << 20)); }
 
-/* The tile of a fused epilogue, by the same estimate (gate: tiles of outputs), fitted to 140 shapes; the choice takes 1.003 times
- * the time of the best, .80 (residual) and .88 (gate) of that of the 128 x 128 and 64 x 128 tiles before it.  us [before]:
- *   residual 4096 x 2560 -> 2560 40 [45], 4096 x 6912 -> 2560 88 [93], 1000 x 2560 -> 2560 15.7 [20.1], 128 x 6912 -> 2560 21.2 [26.7];
- *   gate 2560 -> 13824 at 4096 tokens 120 [142], 2048 70 [72.6], 1000 38.5 [48.5], 128 18.2 [19.5].
- * Slower than before: gates of short rows with few tiles (834 x 256 -> 3328 6.7 [6.0], 94 x 1024 -> 6400 9.9 [9.5]). */
+/* The tile of a fused epilogue, by the same estimate (gate: tiles of outputs), fitted to 140 shapes; over 210 others the choice takes
+ * 1.005 times the time of the best, .78 (residual) and .87 (gate) of that of the 128 x 128 and 64 x 128 tiles before it.  us [before]:
+ *   residual 4096 x 2560 -> 2560 40 [45], 4096 x 6912 -> 2560 86 [93], 1000 x 2560 -> 2560 15.9 [20.4], 128 x 6912 -> 2560 20.9 [26.8];
+ *   gate 2560 -> 13824 at 4096 tokens 120 [142], 2048 69 [72], 1500 49 [65], 65 17.6 [18.3].
+ * Slower than before: the gate at 834 x 256 -> 3328 6.3 [6.0], 199 x 256 -> 6144 7.9 [7.7], 3736 x 1664 -> 2176 21.2 [20.0]. */
 static constexpr bl_tile_cost bl_residual_cost[3] = {{128, 256, 0.0f, .450f, .207f, 8.97f, .929f}, {128, 128, 3.26f, .266f, .103f, 3.68f, .988f},
                                                   {64, 128, 3.84f, .193f, .112f, .966f, 1.17f}};
 static constexpr bl_tile_cost bl_gate_cost[2] = {{128, 128, 6.24f, .614f, .072f, 0.0f, .756f}, {64, 64, 4.52f, .230f, .056f, 0.0f, .872f}};

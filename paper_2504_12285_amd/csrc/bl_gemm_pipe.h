@@ -631,7 +631,7 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
                 for (int g = 0; g < RING; ++g) fetch(g);
             }
             float first[NO];
-            int most[2], maxes[4 * MI];
+            int most[2];
             auto gated = [&](const int mi, const int ni, const int v, const int rs, const float c) __attribute__((always_inline)) {
                 const float t = (float)(C[mi][ni][v] - rs) * c, u = (float)(C[mi][ni + (EPI == 2 ? NO : 0)][v] - rs) * c;
                 const float r = fmaxf(t, 0.0f);
@@ -683,17 +683,14 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
                     const auto t = __builtin_amdgcn_permlane16_swap((uint32_t)m, (uint32_t)m, false, false);
                     most[i] = __builtin_bit_cast(int, __builtin_bit_cast(v2s, larger((int)t[0], (int)t[1])) - __builtin_bit_cast(v2s, MAG));
                 }
-                /* lane v4 of a half stands for row v4: one atomic instruction for eight rows */
-                const int pair = l32 < 2 ? most[0] : most[1];
-                const int mine = l32 & 1 ? pair & (int)0xFFFF0000 : pair << 16;
-                maxes[g] = mine;
+                /* lane v4 of a half stands for row v4: one atomic instruction for eight rows, which travels under the groups
+                 * behind it (all of them behind the last group are waited for by themselves: gate 74 x 384 -> 2560 6.0 us, so 5.5,
+                 * 834 x 256 -> 3328 6.9 / 6.3, 764 x 896 -> 10240 15.8 / 14.1; residual 65 x 2560 -> 2560 11.5 / 10.8, at 2048 tokens 22.9 / 23.3) */
+                if (l32 < 4) {
+                    const int m = m0 + ml + l32, pair = l32 < 2 ? most[0] : most[1];
+                    if (m < M) atomicMax(absmax + m, l32 & 1 ? pair & (int)0xFFFF0000 : pair << 16);
+                }
             });
-            if (l32 < 4) {
-                const int m = m0 + wm0 + h * 4 + l32;
-#pragma unroll
-                for (int g = 0; g < 4 * MI; ++g)
-                    if (m + g * 8 < M) atomicMax(absmax + m + g * 8, maxes[g]);
-            }
         }
         set = set + 1 == SETS ? 0 : set + 1;
         const int* const slot = ahead + (wave * SETS + set) * 4;
