@@ -278,7 +278,7 @@ bl_status bl_gemm_w158a8_res(const uint8_t* packed, const float* beta, int layou
  *                      g = acc_g*(beta*scale[m]), u = acc_u*(..), t = (max(g,0)*max(g,0))*u;
  *                      N_out = N/2; needs N % 128 == 0
  *   y       device out fp32 [M][N_out] or NULL: t itself (wanted when t is a later residual)
- *   x_bf16  device out bf16 [M][N_out]: bf16(t)
+ *   x_bf16  device out bf16 [M][N_out]: bf16(t); 2-byte aligned (4-byte aligned is faster)
  *   absmax  device in/out fp32 [M]: must hold 0 (or an earlier partial maximum of the same rows)
  *           before the launch; receives max_n |bf16(t)|.  bl_quant_from_absmax clears it again.
  *   acc     device out int32 [M][N] or NULL (the raw accumulators, natural column order).

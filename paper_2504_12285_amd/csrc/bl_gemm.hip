@@ -179,12 +179,12 @@ static bl_status launch_ksplit(const uint8_t* packed, const float* beta, const i
 }
 
 /* Launch of bl_gemm_pipe: a persistent grid of the workgroups that are resident at once. */
-template <int MI, int NI, int WM, int WN, int S, int OCC, int EPI, int LAYOUT>
+template <int MI, int NI, int WM, int WN, int S, int OCC, int EPI, int LAYOUT, bool ODD = false>
 static bl_status launch_pipe(const uint8_t* packed, const float* beta, const int8_t* q, const float* scale, const int32_t* rowsum,
                              int M, int N, int K, const float* residual, int32_t* acc, float* y, hipStream_t st,
                              bl_epi_args ep = bl_epi_args{nullptr, nullptr}) {
     using G = bl_pipe_geom<MI, NI, WM, WN, S>;
-    const auto kern = bl_gemm_pipe<MI, NI, WM, WN, S, OCC, EPI, LAYOUT>;
+    const auto kern = bl_gemm_pipe<MI, NI, WM, WN, S, OCC, EPI, LAYOUT, false, ODD>;
     static std::atomic<int> cached{0};
     int blocks = cached.load(std::memory_order_acquire);
     if (blocks == 0) {
@@ -331,6 +331,11 @@ extern "C" bl_status bl_gemm_w158a8_fused(const uint8_t* packed, const float* be
     const bl_epi_args ea = {ep->x_bf16, (int*)ep->absmax};
     hipStream_t st = (hipStream_t)s;
     const int m = (int)M, n = (int)N, k = (int)K;
+    if (!bl_aligned(ep->x_bf16, 4)) {                          /* (rare: one tile, the smallest, for every size) */
+        if (ep->kind == BL_EPI_RESIDUAL)
+            return launch_pipe<1, 2, 2, 2, 3, 4, 1, 1, true>(packed, beta, q, scale, rowsum, m, n, k, ep->residual, acc, ep->y, st, ea);
+        return launch_pipe<1, 2, 2, 2, 3, 4, 2, 1, true>(packed, beta, q, scale, rowsum, m, n, k, nullptr, acc, ep->y, st, ea);
+    }
     if (ep->kind == BL_EPI_RESIDUAL) {
         switch (bl_residual_kernel(m, n, k)) {
             case 0: return launch_pipe<2, 4, 2, 2, 3, 2, 1, 1>(packed, beta, q, scale, rowsum, m, n, k, ep->residual, acc, ep->y, st, ea);

@@ -37,6 +37,7 @@
  * EPI: 0 = int32 and/or fp32 outputs, optional residual; 1 = "residual": t = residual + product as fp32 (y, optional) and
  * bf16 (xb), the row maximum of |bf16(t)| folded into absmax; 2 = "squared-ReLU gate": a wave's NI blocks of 32 weight
  * rows are NI/2 blocks of gate rows and the NI/2 matching blocks of up rows (n and N/2 + n), t = (relu(g)*relu(g))*u.
+ * ODD: an xb that starts at an odd multiple of two bytes, stored value by value (a dword store has to be aligned).
  *
  * TABLE: the tiles of a whole table of products of at most BM tokens (device arrays: items; workgroup b takes tile_list[wg_start[b] ..
  * wg_start[b+1]), an entry = product << BL_TILE_BITS | block of BN weight rows): the batched decode of a stack of BitLinears
@@ -57,7 +58,7 @@ struct bl_pipe_geom {
     static constexpr int LDS = S * STAGE + SETS * (BM * 8 + WM * WN * 16);
 };
 
-template <int MI, int NI, int WM, int WN, int S, int OCC, int EPI, int LAYOUT, bool TABLE = false>
+template <int MI, int NI, int WM, int WN, int S, int OCC, int EPI, int LAYOUT, bool TABLE = false, bool ODD = false>
 __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t* __restrict__ packed, const int8_t* __restrict__ q,
                                                                   const int32_t* __restrict__ rowsum, const float* __restrict__ beta,
                                                                   const float* __restrict__ scale, int M, int N, int K, int tiles_m,
@@ -611,7 +612,7 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
                 const int n = (EPI == 2 ? tn * (BN / 2) + wn0 / 2 : n0 + wn0) + ni * 32 + l32;
                 in[ni] = n < NOUT ? 0x7FFF7FFF : 0;
                 coly[ni] = (n < NOUT ? (uint32_t)n * 4 : NOWHERE) + (uint32_t)(h * 4) * narrow * 2;
-                colx[ni] = (n < NOUT ? (uint32_t)(n & ~1) * 2 : NOWHERE) + (uint32_t)(h * 4 + (lane & 1)) * narrow;
+                colx[ni] = (n < NOUT ? (uint32_t)(ODD ? n : n & ~1) * 2 : NOWHERE) + (uint32_t)(h * 4 + (ODD ? 0 : lane & 1)) * narrow;
             }
             const uint32_t pick = lane & 1 ? 0x03020706u : 0x05040100u;
             decltype(rsrc(nullptr, 0)) rx;
@@ -659,8 +660,13 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void bl_gemm_pipe(const uint8_t*
                         first[ni] = o;
                     } else {
                         const uint32_t two = bl_pack2_bf16(first[ni], o);
-                        const uint32_t other = (uint32_t)bl_dpp<BL_DPP_QUAD_XOR1>((int)two);
-                        __builtin_amdgcn_raw_buffer_store_b32((int)__builtin_amdgcn_perm(other, two, pick), rx, colx[ni] + (uint32_t)(v4 - 1) * narrow, 0, 0);
+                        if constexpr (ODD) {
+                            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)two, rx, colx[ni] + (uint32_t)(v4 - 1) * narrow, 0, 0);
+                            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(two >> 16), rx, colx[ni] + (uint32_t)v4 * narrow, 0, 0);
+                        } else {
+                            const uint32_t other = (uint32_t)bl_dpp<BL_DPP_QUAD_XOR1>((int)two);
+                            __builtin_amdgcn_raw_buffer_store_b32((int)__builtin_amdgcn_perm(other, two, pick), rx, colx[ni] + (uint32_t)(v4 - 1) * narrow, 0, 0);
+                        }
                         const v2s mag = __builtin_bit_cast(v2s, (int)two & in[ni]) + __builtin_bit_cast(v2s, MAG);
                         mx = __builtin_elementwise_max(mx, mag);
                     }

@@ -72,3 +72,22 @@ def test_gate(bl, M, F, with_acc, with_y):
         assert np.array_equal(y.cpu().numpy(), want_f32)
     if with_acc:
         assert np.array_equal(acc.cpu().numpy(), acc_o)
+
+
+@pytest.mark.parametrize("M,N", [(1, 128), (65, 384), (300, 2560), (2433, 2560)])
+@pytest.mark.parametrize("kind", ["residual", "gate"])
+def test_bf16_output_at_every_second_byte(bl, kind, M, N):
+    """x_bf16 one value into an aligned buffer: the values are in place, and nothing beside them changes."""
+    rng, _, prod, dev = _inputs(M, N, 128)
+    res = (rng.standard_normal((M, N)) * 5).astype(np.float32) if kind == "residual" else None
+    NO = N if kind == "residual" else N // 2
+    want = oracle.f32_to_bf16(oracle.chain_residual(res, prod)) if kind == "residual" else oracle.chain_relu2_gate(prod)
+    buf = torch.full((M * NO + 64,), 7.0, dtype=torch.bfloat16, device=DEV)
+    xb, absmax = buf[33:33 + M * NO].view(M, NO), torch.zeros(M, device=DEV)
+    assert xb.data_ptr() % 4 == 2
+    bl.bl_gemm_w158a8_fused(*dev, N, bl.BL_EPI_RESIDUAL if kind == "residual" else bl.BL_EPI_RELU2_GATE, xb, absmax,
+                            residual=None if res is None else to_dev(res))
+    torch.cuda.synchronize()
+    assert np.array_equal(xb.view(torch.int16).cpu().numpy().view(np.uint16), want)
+    assert np.array_equal(absmax.cpu().numpy(), np.abs(synth.bf16_bits_to_f32(want)).max(axis=1))
+    assert (buf[:33] == 7).all() and (buf[33 + M * NO:] == 7).all()
