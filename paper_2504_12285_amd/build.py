@@ -53,11 +53,12 @@ def _older(path, deps):
 
 
 def _headers():
-    return [os.path.join(INCLUDE, "bitlinear.h")] + [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".h")]
+    """The headers, and this file, which holds the flags."""
+    return [os.path.abspath(__file__), os.path.join(INCLUDE, "bitlinear.h")] + [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".h")]
 
 
 def torch_ext_is_stale():
-    if _older(TORCH_EXT_PATH, [TORCH_EXT_SOURCE, os.path.join(INCLUDE, "bitlinear.h")]):
+    if _older(TORCH_EXT_PATH, [TORCH_EXT_SOURCE, os.path.join(INCLUDE, "bitlinear.h"), os.path.abspath(__file__)]):
         return True
     with open(TORCH_EXT_PATH, "rb") as f:
         return _torch_mark() not in f.read()

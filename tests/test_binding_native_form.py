@@ -102,3 +102,20 @@ def test_the_library_is_built_without_the_tools_of_the_extension(tree, monkeypat
     with pytest.warns(RuntimeWarning, match="no g"):
         hip_build.build()
     assert (tree / "lib.so").read_text() == "" and not (tree / "_bl_torch.x.so").exists()
+
+
+def test_other_build_flags_make_the_build_stale(tree, monkeypatch):
+    """The flags stand in build.py itself."""
+    (tree / "build.py").write_text("")
+    os.utime(str(tree / "build.py"), (1000, 1000))
+    monkeypatch.setattr(hip_build, "__file__", str(tree / "build.py"))
+    monkeypatch.setattr(hip_build, "torch_ext_missing", lambda: None)
+    assert not hip_build.is_stale()
+    os.utime(str(tree / "build.py"), (1e10, 1e10))
+    assert hip_build.is_stale()
+    os.utime(str(tree / "_bl_torch.x.so"), (2e10, 2e10))
+    assert hip_build.is_stale()                                      # the library
+    os.utime(str(tree / "lib.so"), (2e10, 2e10))
+    assert not hip_build.is_stale()
+    os.utime(str(tree / "_bl_torch.x.so"), (1000, 1000))
+    assert hip_build.is_stale()                                      # the extension
