@@ -131,3 +131,15 @@ static constexpr bl_tile_cost bl_residual_cost[3] = {{128, 256, 0.0f, .450f, .20
 static constexpr bl_tile_cost bl_gate_cost[2] = {{128, 128, 6.24f, .614f, .072f, 0.0f, .756f}, {64, 64, 4.52f, .230f, .056f, 0.0f, .872f}};
 static inline int bl_residual_kernel(int m, int n, int k) { return bl_least(bl_residual_cost, m, n, k); }
 static inline int bl_gate_kernel(int m, int n, int k) { return bl_least(bl_gate_cost, m, n / 2, k); }
+
+/* Whether a table of 33 to 48 tokens is walked by the tile kernel: entries = its tiles of 64 x 256, steps = the k steps of all of them,
+ * chain = of the longest.  Not below 128 entries.  us: the tiles take a lone tile's chain, slower where units share two, or their even
+ * share; the form with the tokens in LDS (two groups of them) a row's staging and its share.  LDS form / tiles over 33, 36, .. 48 tokens:
+ * three layers of 2560 / 6912 27 - 35 / 33 - 35 (267 entries), four 34 - 42 / 34 - 36, eight 60 - 70 / 50; one of 4096 / 11008 29 - 31 / 36, two 48 -
+ * 51 / 48 - 51, three 70 - 76 / 52; four of 2048 / 5632 25 - 31 / 28 - 29, eight 43 - 48 / 32; four of 896 / 2560 20 - 28 / 12.  Even within 10 %
+ * either way: two layers of 2560 / 6912 (23 - 29 / 25), three of 2048 / 5632 (23 - 26 / 23 - 24). */
+static inline bool bl_table_in_tiles(int64_t entries, int64_t steps, int64_t chain) {
+    const float share = (float)steps / 256.0f, alone = (float)chain * (entries > 256 ? .58f : .39f);
+    const float tiles = 2.0f + (alone > .72f * share ? alone : .72f * share), few = 18.0f + .35f * share, many = 4.0f + 1.05f * share;
+    return entries >= 128 && tiles <= (few > many ? few : many);
+}

@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "bl_device.h"
+#include "bl_gemm_choice.h"
 #include "bl_gemv_common.h"
 #include "bl_host.h"
 #include "bl_producer.h"
@@ -1377,25 +1378,26 @@ extern "C" size_t bl_stack_table_bytes_batched(const bl_decode_desc* descs, int 
 
 /* More than 32 tokens per product: the token rows of most products no longer fit LDS whole and go in two groups, which read the
  * weights twice; the work is a dense contraction, and the table is walked by the prefill tile kernel instead (tiles of 64 x 256,
- * both operands streamed through LDS per k step, weights read once).  Needs rows padded to 128; up to 48 tokens, 128 tiles
- * (a single layer stays: two groups of 2560 / 6912 at 36, 40, 44, 48 tokens 21.7, 24.6, 20.3, 25.6 us, tiles 22.7).  us, LDS-resident
- * form / tiles: thirty layers of 2560 / 6912 at 32 tokens 146 / 156, 36 182 / 158, 48 196 / 167; twenty of 1024 / 2816 at 32
- * 26.2 / 24.0, 36 36.2 / 24.3, 48 40.5 / 26.2; four of 4096 / 11008 at 36 93.4 / 51.8, 48 94.8 / 54.0. */
+ * both operands streamed through LDS per k step, weights read once).  Needs rows padded to 128; up to 48 tokens where it pays
+ * (bl_table_in_tiles).  At 32 tokens, one group, it is the form with the tokens in LDS: thirty layers of 2560 / 6912 150 us, tiles 164,
+ * three 23 / 34 (though twenty of 1024 / 2816 take 27.7 there and 25.2 in tiles, twelve of 4096 / 11008 186 and 158). */
 #define BL_MB_TILE_ROUTE_MIN 33
 static bool mb_tile_route(const bl_decode_desc* descs, int count, int64_t M) {
     if (M < BL_MB_TILE_ROUTE_MIN) return false;
-    int64_t tiles = 0, entries = 0;
+    int64_t tiles = 0, entries = 0, steps = 0, chain = 0;
     for (int i = 0; i < count; ++i) {
-        if (bl_kpad(descs[i].K) % 128 != 0) return false;
+        const int64_t Kp = bl_kpad(descs[i].K), blocks = (descs[i].N + BL_TILE_ROWS - 1) / BL_TILE_ROWS;
+        if (Kp % 128 != 0) return false;
         tiles += (descs[i].N + 127) / 128;
-        entries += (descs[i].N + BL_TILE_ROWS - 1) / BL_TILE_ROWS;
+        entries += blocks;
+        steps += blocks * (Kp / 128);
+        chain = std::max(chain, Kp / 128);
     }
-    if (M <= 48 && entries < 128) return false;
+    if (M <= 48 && !bl_table_in_tiles(entries, steps, chain)) return false;
     return tiles <= ((int64_t)1 << 22);       /* beyond ~4 M tiles (a 16 MB tile list) the table stays on bl_stream_mb */
 }
 
-/* Device buffer of the tile route: [products][first tile of each product][first list position of
- * each workgroup][tile list]. */
+/* Device buffer of the tile route: [products][first list position of each workgroup][tile list]. */
 struct tile_layout_t {
     size_t wg_off, list_off, total;
 };

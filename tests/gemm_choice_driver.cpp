@@ -3,6 +3,7 @@
  *   residual M N K | gate M N K   place of the tile
  *   stores M N acc              whether fp32 output is stored past the caches
  *   order M N                   the split k loop's order: across, bytes per k that an XCD reads
+ *   table entries steps chain   whether a table of 33 to 48 tokens goes to the tile kernel
  *   tiles tiles_m tiles_n BM K  the tile kernels' order: gm, band, vgrid */
 #include "bl_gemm_choice.h"
 
@@ -21,6 +22,8 @@ int main() {
             printf("%d\n", bl_gate_kernel(a, b, c));
         } else if (!strcmp(what, "stores") && scanf("%d %d %d", &a, &b, &c) == 3) {
             printf("%d\n", (int)bl_past_caches(a, b, c != 0));
+        } else if (!strcmp(what, "table") && scanf("%d %d %d", &a, &b, &c) == 3) {
+            printf("%d\n", (int)bl_table_in_tiles(a, b, c));
         } else if (!strcmp(what, "order") && scanf("%d %d", &a, &b) == 2) {
             const bl_ksplit_order o = bl_ksplit_order_of(a, b);
             printf("%d %lld\n", (int)o.across, (long long)o.bytes);

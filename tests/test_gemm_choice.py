@@ -80,3 +80,15 @@ def test_stores_of_broken_lines(ask):
     shapes = [(422, 4751), (387, 7778), (2077, 1335), (4096, 13824), (2048, 13840)]
     assert ask(["stores %d %d 0" % s for s in shapes]) == [(1,)] * len(shapes)
     assert ask(["stores 422 4751 1", "stores 4096 13824 1"]) == [(0,), (1,)]
+
+
+def test_tables_of_33_to_48_tokens(ask):
+    """Layers (hidden, ffn, count) whose tables measured faster in tiles, and with the tokens in LDS."""
+    def layers(hidden, ffn, count):
+        shapes = [(hidden + 2 * (hidden // 4), hidden), (hidden, hidden), (2 * ffn, hidden), (hidden, ffn)]
+        blocks = [(-(-N // 256), -(-K // 128)) for N, K in shapes]
+        return "table %d %d %d" % (count * sum(n for n, _ in blocks), count * sum(n * k for n, k in blocks), max(k for _, k in blocks))
+    tiles = [(2560, 6912, 4), (2560, 6912, 30), (4096, 11008, 3), (4096, 8192, 2), (2304, 5760, 3), (1536, 4608, 6), (1024, 2816, 5), (896, 2560, 4)]
+    lds = [(2560, 6912, 1), (2560, 6912, 3), (4096, 11008, 1), (2048, 5632, 4), (4096, 8192, 1), (3584, 9472, 1)]
+    assert ask([layers(*s) for s in tiles]) == [(1,)] * len(tiles)
+    assert ask([layers(*s) for s in lds]) == [(0,)] * len(lds)

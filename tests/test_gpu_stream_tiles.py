@@ -55,3 +55,21 @@ def test_tables_of_tiles(bl, M, shapes):
     for it, (acc, y) in zip(items, wants):
         assert "y" not in it or torch.equal(it["y"], y)
         assert "acc" not in it or torch.equal(it["acc"], acc)
+
+
+LAYER = [(3840, 2560), (2560, 2560), (13824, 2560), (2560, 6912)]
+
+
+@pytest.mark.parametrize("M", [33, 48, 49])
+@pytest.mark.parametrize("layers,in_tiles", [(3, False), (4, True)])
+def test_few_layers_of_long_rows(bl, M, layers, in_tiles):
+    """Up to 48 tokens three layers stay with the tokens in LDS, four go to the tiles."""
+    items, wants = _table(bl, M, LAYER * layers)
+    st = bl.Stack(items, 1, M, DEV)
+    assert (st.plan.norm == 3) == (in_tiles or M > 48)
+    for _ in range(2):
+        st.run()
+    torch.cuda.synchronize()
+    for it, (acc, y) in zip(items, wants):
+        assert "y" not in it or torch.equal(it["y"], y)
+        assert "acc" not in it or torch.equal(it["acc"], acc)
