@@ -337,8 +337,8 @@ bl_status bl_quant_from_absmax(const uint16_t* X, float* absmax, int64_t M, int6
  * partial sums meet in scratch inside `table` through integer atomics (exact, order-free) and
  * are finished (row sum, rescale, residual) by a second small launch of the same run, which
  * also clears the scratch.  plan->entries tells how many entries the table holds.
- * With more than 48 tokens (33 to 48 in tables of 128 tiles and more), and every row length a multiple of 128 after padding, the table is
- * walked by the prefill tile kernel instead (Section 5.1: packed tiles expanded to int8 on chip
+ * With more than 48 tokens (33 to 48: tables that are large against their longest row), and every row length a multiple of 128
+ * after padding, the table is walked by the prefill tile kernel instead (Section 5.1: packed tiles expanded to int8 on chip
  * for the int8 matrix cores): tiles of all tokens x 256 weight rows, both operands streamed
  * through LDS, the tiles of all products balanced over the resident workgroups by their k steps, one
  * launch, weights read once; plan->red_ints then holds the table's blocks of 128 weight rows (one token:

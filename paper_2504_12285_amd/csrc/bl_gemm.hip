@@ -208,7 +208,7 @@ static bl_status launch_pipe(const uint8_t* packed, const float* beta, const int
     return hipGetLastError() == hipSuccess ? BL_OK : BL_ERR_HIP;
 }
 
-/* Table walk (batched decode of a stack, more than 48 tokens): one launch over every tile of 64 x BL_TILE_ROWS of every product
+/* Table walk (batched decode of a stack, more than 32 tokens, see mb_tile_route): one launch over every tile of 64 x BL_TILE_ROWS of every product
  * (see bl_gemm_pipe); M <= 64 tokens, the same for every product; the host balances the k steps over the workgroups.  Thirty
  * 2560 / 6912 layers at 64 tokens 182 us (64 x 128 tiles with two stages, four workgroups to a unit: 220; this kernel with tiles of
  * 64 x 128 206, x 384 189, x 512 235; weights not kept in the caches 323: a line holds four k steps of a row).

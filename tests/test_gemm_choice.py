@@ -92,3 +92,26 @@ def test_tables_of_33_to_48_tokens(ask):
     lds = [(2560, 6912, 1), (2560, 6912, 3), (4096, 11008, 1), (2048, 5632, 4), (4096, 8192, 1), (3584, 9472, 1)]
     assert ask([layers(*s) for s in tiles]) == [(1,)] * len(tiles)
     assert ask([layers(*s) for s in lds]) == [(0,)] * len(lds)
+
+
+def test_gpu_shapes_reach_the_kernels_that_they_stand_for(ask):
+    import test_gpu_gemm_pipe as pipe
+    import test_gpu_tile_order as order
+    for lists in (pipe.TILES, pipe.GUARDED):
+        assert sorted(lists) == list(range(6))
+        for place, shapes in lists.items():
+            assert ask(["plain %d %d %d 0 0 1" % (M, N, -(-K // 64) * 64) for M, N, K in shapes]) == [(place,)] * len(shapes), place
+    for what, lists, count in (("residual", pipe.RESIDUAL, 3), ("gate", pipe.GATE, 2)):
+        assert sorted(lists) == list(range(count))
+        for place, shapes in lists.items():
+            assert ask(["%s %d %d %d" % ((what,) + s) for s in shapes]) == [(place,)] * len(shapes), (what, place)
+    for what, shapes, count in (("plain", order.PLAIN, 5), ("residual", order.RESIDUAL, 3), ("gate", order.GATE, 2)):
+        assert ask(["%s %d %d %d" % ((what,) + s[:3]) + (" 0 0 1" if what == "plain" else "") for s in shapes]) == [(s[3],) for s in shapes]
+        assert {s[3] for s in shapes} == set(range(count))
+
+
+def test_the_order_that_the_gpu_test_reckons_with_is_the_launchers(ask):
+    import test_gpu_tile_order as order
+    rng = random.Random(2)
+    shapes = [(rng.randint(1, 300), rng.randint(1, 300), rng.choice([64, 128]), rng.randint(1, 110) * 64) for _ in range(2000)]
+    assert [(gm, band) for gm, band, _ in ask(["tiles %d %d %d %d" % s for s in shapes])] == [order._order(*s) for s in shapes]

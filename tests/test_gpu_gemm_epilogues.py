@@ -1,5 +1,5 @@
-"""The fused epilogues of the prefill product at the edges of their tiles: 64 x 128 and 128 x 128 tiles (the latter from 353 of
-them), whole and cut by the last row or column, with and without the int32 and the fp32 output, a residual that is also the
+"""The fused epilogues of the prefill product at the edges of their tiles (64 x 128, one product 128 x 256; every tile is in
+test_gpu_gemm_pipe.py), whole and cut by the last row or column, with and without the int32 and the fp32 output, a residual that is also the
 output.  Bit for bit against the oracle's separate steps."""
 import numpy as np
 import pytest

@@ -1,8 +1,6 @@
 """The prefill kernels on rows whose last k step is half (K padded to an odd multiple of 64) and on the plain bit order: the k
-loop split over waves (up to 160 tiles of 64 x 128), 64 x 128 tiles, 128 x 128 tiles with at most one tile per workgroup
-(every store at once: launches that defer stores are in test_gpu_gemm_routes.py) or 513 to 768 tiles of long rows, with
-int32 output and residual, and the register-staged kernel.  Bit for bit against an exact integer product, with the last
-row and column ends that the loads of the half step must stay inside."""
+loop split over waves, 64 x 128 and 128 x 128 tiles, 128 x 192 tiles of long rows, with int32 output and residual.  Bit for bit against
+an exact integer product, with the last row and column ends that the loads of the half step must stay inside."""
 import numpy as np
 import pytest
 

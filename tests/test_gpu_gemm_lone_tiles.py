@@ -1,5 +1,5 @@
-"""Prefill products of 161 to 256 tiles of 64 x 128 with long rows: the tile kernel with four LDS stages, on both sides of
-its limits, with ragged edges, half last k steps, both layouts and every set of outputs, bit for bit."""
+"""Prefill products of 161 to 264 tiles of 64 x 128, one to a unit or a few more, whose rows are long (64 x 128 tiles, one product 128 x
+128): ragged edges, half last k steps, both layouts and every set of outputs, bit for bit."""
 import pytest
 
 from test_gpu_gemm_routes import _product
@@ -18,7 +18,7 @@ def bl():
 @pytest.mark.parametrize("layout", [0, 1])
 @pytest.mark.parametrize("M,N,K", [(512, 2688, 2304), (512, 2561, 2240), (512, 4096, 2303), (1000, 1999, 2368), (129, 9999, 2560), (64, 32700, 4097),
                                    (512, 4097, 2560)])
-def test_four_stages(bl, layout, M, N, K):
+def test_long_rows(bl, layout, M, N, K):
     packed, beta, q, scale, rowsum, want, y_want = _product(bl, layout, M, N, K)
     for _ in range(2):
         _, y = bl.bl_gemm_w158a8(packed, beta, layout, q, scale, rowsum, N, want_acc=False, K=K)

@@ -1,7 +1,8 @@
-"""The tiles that a prefill product can take (128 x 256, 128 x 192 with one or two workgroups to a unit, 64 x 128, the k loop
+"""The tiles that a prefill product can take (128 x 256, 128 x 192 with one or two workgroups to a unit, 128 x 128, 64 x 128, the k loop
 split over the waves): rows of one to five k steps, where the loads run ahead over one or more tile borders, with several tiles
 to a workgroup; last tiles of one row, of one column and of all but one; half last steps; both layouts and every set of outputs,
-in rows that start on whole, half and broken lines.  Bit for bit against an exact integer product."""
+in rows that start on whole, half and broken lines.  Bit for bit against an exact integer product.  The lists are by the kernel that
+fp32 output alone goes to (its place in the choice's list; test_gemm_choice.py asks the choice)."""
 import pytest
 
 from test_gpu_gemm_routes import _product
@@ -18,11 +19,24 @@ def bl():
     return binding
 
 
-SHAPES = [(3969, 8961, k) for k in (64, 128, 192, 320, 640)] + [          # 128 x 256, three tiles and more to a unit
-          (2048, 13824, 64), (2049, 13823, 448), (2047, 13825, 2496),     # 128 x 192, two workgroups
-          (2048, 2560, 2560), (2047, 2497, 1984), (1921, 2689, 2112),     # 128 x 192, one
-          (3000, 1600, 640), (1537, 897, 64), (1600, 1153, 192), (1599, 1151, 4032), (300, 14000, 448),   # 64 x 128
-          (1, 1, 64), (65, 33, 128), (64, 32, 6912), (2528, 320, 1877), (63, 4097, 576), (3931, 256, 300)]  # split k loop
+TILES = {
+    0: [(3071, 8191, 320), (3072, 8192, 448), (1793, 8449, 448), (1921, 7937, 640), (1407, 8959, 1984)],        # 128 x 256
+    1: [(2815, 4415, 448), (2817, 5761, 640), (2816, 4416, 1088), (2689, 4415, 1984)],                          # 128 x 192, two workgroups
+    2: [(2048, 2560, 2560), (2047, 2497, 1984), (1921, 2689, 2112), (513, 7297, 1984)],                         # 128 x 192, one
+    3: [(2049, 8833, 448), (2177, 8321, 640), (3073, 7681, 1088), (2047, 13825, 2496)],                         # 128 x 128
+    4: [(3969, 8961, 64), (3969, 8961, 128), (3969, 8961, 192), (2048, 13824, 64), (3000, 1600, 640), (1537, 897, 64),
+        (1600, 1153, 192), (1599, 1151, 4032), (300, 14000, 448), (3931, 256, 300)],                            # 64 x 128
+    5: [(1, 1, 64), (65, 33, 128), (64, 32, 6912), (2528, 320, 1877), (63, 4097, 576)]}                         # split k loop
+BETWEEN = [(3969, 8961, 320), (3969, 8961, 640), (2049, 13823, 448)]              # where two kernels are estimated the same
+SHAPES = [s for shapes in TILES.values() for s in shapes] + BETWEEN
+GUARDED = {0: [(1793, 8449, 448)], 1: [(2817, 5761, 640)], 2: [(2047, 2497, 1984)], 3: [(2177, 8321, 640)],
+           4: [(2100, 13700, 192), (1000, 3840, 320), (2048, 2560, 640)], 5: [(395, 1601, 640)]}
+# fused epilogues by their tiles: residual 128 x 256, 128 x 128, 64 x 128; gate 128 x 128, 64 x 64 (of outputs)
+RESIDUAL = {0: [(2047, 4060, 256), (3073, 2536, 384), (1153, 12060, 1280)], 1: [(895, 9340, 1280), (3201, 2424, 1280)],
+            2: [(129, 644, 128), (64, 384, 1280), (65, 13824, 256), (300, 1664, 512), (1000, 2560, 640)]}
+GATE = {0: [(2049, 13824, 384), (1919, 12032, 1280), (3201, 12544, 128)],
+        1: [(64, 384, 1280), (65, 13824, 256), (300, 1664, 512), (1000, 2560, 640)]}
+FUSED = sorted({s for shapes in (*RESIDUAL.values(), *GATE.values()) for s in shapes} | {(3969, 4100, 128)})
 
 
 @pytest.mark.parametrize("layout", [0, 1])
@@ -42,7 +56,7 @@ def test_tiles(bl, layout, M, N, K):
         assert torch.equal(y, residual + y_want)
 
 
-@pytest.mark.parametrize("M,N,K", [(2100, 13700, 192), (1000, 3840, 320), (2048, 2560, 640)])
+@pytest.mark.parametrize("M,N,K", [s for shapes in GUARDED.values() for s in shapes])
 def test_nothing_beside_the_outputs(bl, M, N, K):
     """Rows past M and what lies behind the last column of the last row stay as they were, in memory around the outputs."""
     packed, beta, q, scale, rowsum, want, y_want = _product(bl, 1, M, N, K)
@@ -58,7 +72,7 @@ def test_nothing_beside_the_outputs(bl, M, N, K):
         assert (t[:pad] == 7).all() and (t[pad + M * N:] == 7).all()
 
 
-@pytest.mark.parametrize("M,N,K", [(3969, 4100, 128), (2049, 13824, 384), (1000, 2560, 640), (129, 644, 128), (64, 384, 1280), (65, 13824, 256), (300, 1664, 512)])
+@pytest.mark.parametrize("M,N,K", FUSED)
 def test_fused_epilogues(bl, M, N, K):
     """Residual, and the gate where N allows it: the fp32 value, its bf16 narrowing, the row maxima and the int32 output, in memory
     with something behind it."""

@@ -1,7 +1,6 @@
-"""The routes of a prefill product in layout 0 or with a half last k step, at the sizes where they change, bit for bit
-against an exact integer product: the register-staged kernel (short rows, many tiles), and the 128 x 128 tile kernel
-whose stores travel during the workgroup's next tile, which only happens with more tiles than resident workgroups (two
-per compute unit): with fewer k steps than store groups (8) and with more, with edges in M and N, and beyond 768 tiles."""
+"""Prefill products of short and long rows with many tiles, bit for bit against an exact integer product: several tiles to a workgroup
+(fp32 output alone, its stores before the next tile's k loop), and launches that are mostly output, with every set of outputs, rows that
+start on whole and broken lines, half last k steps and both layouts."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -30,8 +29,8 @@ def _product(bl, layout, M, N, K):
 @pytest.mark.parametrize("layout", [0, 1])
 @pytest.mark.parametrize("M,N,K", [(2600, 3328, 192), (2600, 3328, 1088), (1100, 8200, 3136), (2600, 3300, 3100), (2600, 3328, 256), (2600, 3328, 1280),
                                    (2048, 7008, 192), (1100, 11200, 4160), (1100, 11200, 1100)])
-def test_deferred_stores(bl, layout, M, N, K):
-    """fp32 output alone (no case takes the register-staged kernel)."""
+def test_many_tiles(bl, layout, M, N, K):
+    """fp32 output alone."""
     tiles = -(-M // 128) * -(-N // 128)
     assert tiles > 2 * torch.cuda.get_device_properties(0).multi_processor_count
     packed, beta, q, scale, rowsum, _, y_want = _product(bl, layout, M, N, K)
@@ -46,7 +45,7 @@ def test_deferred_stores(bl, layout, M, N, K):
                                    (2048, 7000, 640), (2048, 7000, 641), (2048, 6999, 1152), (2048, 6999, 1153),
                                    (2048, 7040, 1024), (2048, 7040, 3072), (2048, 7040, 3073)])
 def test_short_rows(bl, layout, M, N, K):
-    """Every set of outputs on both sides of the register-staged kernel's limits."""
+    """Every set of outputs."""
     packed, beta, q, scale, rowsum, want, y_want = _product(bl, layout, M, N, K)
     _, y = bl.bl_gemm_w158a8(packed, beta, layout, q, scale, rowsum, N, want_acc=False, K=K)
     assert torch.equal(y, y_want)

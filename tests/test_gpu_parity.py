@@ -212,7 +212,7 @@ def test_decode_single_outputs(bl, M):
 @pytest.mark.parametrize("M", [1, 3, 40])
 def test_long_rows_beyond_the_decode_kernels(bl, M):
     """K above 8192: the decode entry point hands over to the prefill kernel; the int32 sums
-    reach 16,384 terms.  Both layouts (layout 0 takes the register-staged kernel)."""
+    reach 16,384 terms.  Both layouts."""
     c = Case(36, M, 68, 16384)
     for layout in (0, 1):
         for fn in (bl.bl_gemv_w158a8, bl.bl_gemm_w158a8):
@@ -475,12 +475,10 @@ def test_fused_fixed_scale(bl):
 
 
 @pytest.mark.parametrize("M,N,K", [(2048, 13824, 2560), (2100, 4200, 640), (1024, 8320, 128), (1100, 8200, 1152)])
-def test_gemm_prefill_fp32_output_alone_defers_its_stores(bl, M, N, K):
-    """With only the fp32 output asked for, the 128x128 prefill kernel keeps a tile's results in
-    registers and stores them during the workgroup's next tile.  More tiles than resident
-    workgroups (so tiles are deferred), edges in M and N (stored at once), fewer k steps than
-    store groups (flushed behind the k loop), one k step: bit-identical to the call that also
-    returns the accumulators, and within 1e-6 of the oracle on sampled rows."""
+def test_gemm_prefill_fp32_output_alone(bl, M, N, K):
+    """fp32 output alone, written past the caches, of more tiles than compute units, with
+    edges in M and N, of nine k steps and of one: bit-identical to the call that also returns the accumulators, and
+    within 1e-6 of the oracle on sampled rows."""
     rng = np.random.default_rng(M + N + K)
     Wt = rng.integers(-1, 2, size=(N, K), dtype=np.int8)
     q = rng.integers(-127, 128, size=(M, K), dtype=np.int8)

@@ -97,7 +97,7 @@ def test_batched_stream_token_counts(bl, M):
 
 @pytest.mark.parametrize("M", [49, 56, 64])
 def test_batched_stream_tile_route(bl, M):
-    """More than 48 tokens with every row padded to a multiple of 128: the table is walked by the
+    """More than 48 tokens (fewer: test_gpu_stream_tiles.py) with every row padded to a multiple of 128: the table is walked by the
     matrix-core tile kernel (plan.norm == 3).  Ragged N (a part-filled last tile, a single
     part-filled tile), K = 128 (one k step) to K = 6912, residuals, y alone, acc alone; two runs."""
     shapes = [(100, 2560), (259, 6912), (2563, 1000), (129, 128), (33, 4608), (1280, 1152)]

@@ -1,5 +1,5 @@
-"""Tables of more than 32 tokens on the prefill tile kernel, on both sides of the rule that takes them there (33 to 48 tokens: 128
-tiles of 256 rows), with many tiles to a workgroup, products of different row lengths next to each other (the loads run ahead
+"""Tables of more than 32 tokens on the prefill tile kernel, on both sides of the rules that take them there (33 to 48 tokens: 128
+tiles of 256 rows, and a table that is not small against its longest row), with many tiles to a workgroup, products of different row lengths next to each other (the loads run ahead
 into products of other sizes), one-step rows, last tiles of one row, and outputs of every kind.  Bit for bit."""
 import pytest
 

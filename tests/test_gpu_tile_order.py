@@ -1,7 +1,7 @@
 """The two tile orders of a prefill launch: a rectangle of tiles per XCD, or (where that loads the busiest compute
 unit more) one banded sequence of which each XCD takes an eighth.  Shapes of the second kind whose last band is part
-filled, for the 64 x 128 and 128 x 128 tiles, with deferred stores and both fused epilogues; every output against an exact
-integer product."""
+filled, for every tile of a plain product and of both fused epilogues (test_gemm_choice.py asks the choice whether these are the tiles that
+they go to); every output against an exact integer product."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -40,11 +40,24 @@ def _inputs(bl, layout, M, N, K):
     return packed, beta, q, scale, q.to(torch.int32).sum(1, dtype=torch.int32), want, want.float() * (beta * scale)[:, None], g
 
 
+# M, N, K of fp32 output alone, place of the kernel, its tile
+PLAIN = [(2100, 1664, 1024, 4, 64, 128), (2140, 3712, 1024, 3, 128, 128), (2140, 3712, 1088, 3, 128, 128), (2140, 4992, 2048, 1, 128, 192),
+         (2700, 4224, 3328, 1, 128, 192), (3458, 1728, 1024, 2, 128, 192), (2634, 5184, 1024, 0, 128, 256)]
+# M, N, K, place of the tile, the tile (of outputs)
+RESIDUAL = [(2140, 3712, 1024, 0, 128, 256), (2573, 2432, 1024, 0, 128, 256), (2140, 4992, 2048, 1, 128, 128), (2700, 4224, 3328, 1, 128, 128),
+            (2073, 640, 1024, 2, 64, 128)]
+GATE = [(2140, 3712, 1024, 0, 128, 128), (2573, 2432, 1024, 0, 128, 128), (2073, 640, 1024, 1, 64, 64)]
+
+
+def even_share_with_a_part_filled_last_band(M, outputs, K, bm, bn):
+    gm, band = _order(-(-M // bm), -(-outputs // bn), bm, K)
+    return gm == 0 and band < -(-M // bm) and -(-M // bm) % band != 0
+
+
 @pytest.mark.parametrize("layout", [0, 1])
-@pytest.mark.parametrize("M,N,K,bm", [(2100, 1664, 1024, 64), (2140, 3712, 1024, 128), (2140, 3712, 1088, 128), (2140, 4992, 2048, 128), (2700, 4224, 3328, 128)])
-def test_even_shares_with_a_part_filled_last_band(bl, layout, M, N, K, bm):
-    gm, band = _order(-(-M // bm), -(-N // 128), bm, K)
-    assert gm == 0 and band < -(-M // bm) and -(-M // bm) % band
+@pytest.mark.parametrize("M,N,K,place,bm,bn", PLAIN)
+def test_even_shares_with_a_part_filled_last_band(bl, layout, M, N, K, place, bm, bn):
+    assert even_share_with_a_part_filled_last_band(M, N, K, bm, bn)
     packed, beta, q, scale, rowsum, want, y_want, g = _inputs(bl, layout, M, N, K)
     _, y = bl.bl_gemm_w158a8(packed, beta, layout, q, scale, rowsum, N, want_acc=False)
     assert torch.equal(y, y_want)
@@ -55,11 +68,9 @@ def test_even_shares_with_a_part_filled_last_band(bl, layout, M, N, K, bm):
     assert torch.equal(y, res + y_want)
 
 
-@pytest.mark.parametrize("kind", ["residual", "gate"])
-@pytest.mark.parametrize("M,N,K", [(2140, 3712, 1024), (2140, 4992, 2048), (2700, 4224, 3328)])
-def test_fused_epilogues_in_even_shares(bl, kind, M, N, K):
-    gm, band = _order(-(-M // 128), N // 128, 128, K)
-    assert gm == 0 and -(-M // 128) % band
+@pytest.mark.parametrize("kind,M,N,K,place,bm,bn", [("residual",) + s for s in RESIDUAL] + [("gate",) + s for s in GATE])
+def test_fused_epilogues_in_even_shares(bl, kind, M, N, K, place, bm, bn):
+    assert even_share_with_a_part_filled_last_band(M, N // 2 if kind == "gate" else N, K, bm, bn)
     packed, beta, q, scale, rowsum, want, y_want, g = _inputs(bl, 1, M, N, K)
     if kind == "residual":
         res = torch.randn((M, N), generator=g, device=DEV)
