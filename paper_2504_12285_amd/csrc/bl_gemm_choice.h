@@ -118,7 +118,7 @@ static inline int bl_plain_kernel(int m, int n, int k, bool residual, bool acc, 
  * plain stores 69.3).  Rows that start inside a line write lines in parts: such a store goes to memory as a part once the output
  * outgrows the L2s, from about 5 M values (2106 x 256 -> 3705 15.9 / 10.4, 4072 x 640 -> 1915 17.2 / 13.3, 2242 x 192 -> 2986 12.4 / 10.4, 3812 x 677 ->
  * 6613 51.1 / 35.0), and up to there gains where the k loop is long (422 x 1280 -> 4751 8.3 / 8.9, 387 x 2560 -> 7778 14.2 / 14.9) and loses
- * less where it is short (734 x 256 -> 2034 5.7 / 5.3).  Not beside an int32 output. */
+ * less where it is short (734 x 256 -> 2034 5.7 / 5.3).  Beside an int32 output only whole and half lines. */
 static constexpr bool bl_past_caches(int m, int n, bool acc) { return n % 16 == 0 || (!acc && (int64_t)m * n <= (4 << 20)); }
 
 /* The tile of a fused epilogue, by the same estimate (gate: tiles of outputs), fitted to 140 shapes; over 210 others the choice takes

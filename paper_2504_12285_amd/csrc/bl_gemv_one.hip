@@ -117,8 +117,8 @@ template <int SRC, int G, int RW, int NL, int UN, bool NORM>
 /* What the row's and the weights' loads need comes first, 14 registers of it (`where`: weights, row; `beside`: second row or the two
  * multipliers of the V gather, gains; `size`: residual, N, K; `how`: rows of a workgroup | kind << 8 | head size << 16, offset of V):
  * the hardware has them in place when a wave starts (the build asks for that), the structure behind them is fetched while the loads
- * travel.  One token through thirty layers 547 -> 527 us, fifteen without normalisation 241 -> 229 (the same fetched by the
- * kernel: 537, 234).  Four vectors and not nine scalars, which cost the host .2 us more a launch. */
+ * travel.  One token through thirty layers 545 - 558 -> 528 - 545 us (1.03), fifteen without normalisation 240 -> 231 (the same
+ * fetched by the kernel: half of that); an eager call gains nothing, the host bounds it.  Four vectors and not nine scalars, which cost the host .2 us more a launch. */
 __global__ __launch_bounds__(BL_ONE_WAVES * 64) void bl_gemv_one(const bl_v4u where, const bl_v4u beside, const bl_v4u size, const bl_v2u how,
                                                                  const bl_one_rest Pin) {
     constexpr int R = 64 / G, NW = BL_ONE_WAVES, nthreads = NW * 64;
